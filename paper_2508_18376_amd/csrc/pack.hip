@@ -69,26 +69,32 @@ __global__ void pack_generic_kernel(Layout L, const T* w1, const T* w3, const T*
   }
 }
 
-// largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out
+// largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out.  One read of W2,
+// bound by HBM: four 16-byte loads in flight per thread.
 __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int64_t n, uint32_t* out) {
   uint32_t m = 0;
-  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8; i < n; i += (int64_t)gridDim.x * 256 * 8) {
-    if (i + 8 <= n && (((uintptr_t)(w + i)) & 15) == 0) {
-      const uint4 v = *(const uint4*)(w + i);
-      const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+  auto one = [&](uint32_t a) { m = a < 0x7f80u && a > m ? a : m; };
+  const bool vec = (((uintptr_t)w) & 15) == 0;
+  const int64_t step = (int64_t)gridDim.x * 256 * 8;
+  int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (vec) {
+    for (; i + 3 * step + 8 <= n; i += 4 * step) {
+      uint4 v[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t a = u[k] & 0x7fffu, b = (u[k] >> 16) & 0x7fffu;
-        if (a < 0x7f80u && a > m) m = a;
-        if (b < 0x7f80u && b > m) m = b;
-      }
-    } else {
-      for (int64_t k = i; k < n && k < i + 8; ++k) {
-        const uint32_t a = w[k] & 0x7fffu;
-        if (a < 0x7f80u && a > m) m = a;
+      for (int u = 0; u < 4; ++u) v[u] = *(const uint4*)(w + i + u * step);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t d[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          one(d[k] & 0x7fffu);
+          one((d[k] >> 16) & 0x7fffu);
+        }
       }
     }
   }
+  for (; i < n; i += step)
+    for (int64_t k = i; k < n && k < i + 8; ++k) one(w[k] & 0x7fffu);
   for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
   if ((threadIdx.x & 63) == 0 && m) atomicMax(out, m);
 }
@@ -114,148 +120,144 @@ __device__ __forceinline__ uint16_t bf16_to_scaled_half(uint16_t b, float scale)
   return __builtin_bit_cast(uint16_t, h);
 }
 
-// One thread per 16-byte chunk of the packed MFMA buffers.
-__global__ void pack_mfma_kernel(Layout L, const uint16_t* w1, const uint16_t* w3, const uint16_t* w2,
-                                 const uint16_t* sw1, const uint16_t* sw3, const uint16_t* sw2, const int32_t* perm,
-                                 char* packed, int n_shared, int F_sh, int skip_routed_w13) {
-  const int KS1 = L.D / kBK;
-  const int64_t chunks_per_stage = kStageBytes / 16;  // 2048
-  const int64_t st13 = (int64_t)L.E_res * L.P * L.NT1 * KS1;
-  const int64_t st2 = (int64_t)L.E_res * L.ND2 * (L.F / kBK);
-  const int64_t sts13 = (int64_t)(n_shared > 0 ? L.NT1_sh * KS1 : 0);
-  const int64_t sts2 = (int64_t)(n_shared > 0 ? L.ND2 * (L.F_shT / kBK) : 0);
-  const int64_t total = (st13 + st2 + sts13 + sts2) * chunks_per_stage;
-  const int64_t first = skip_routed_w13 ? st13 * chunks_per_stage : 0;  // those stages are written by pack_w13_columns_kernel
-  for (int64_t q = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < total; q += (int64_t)gridDim.x * blockDim.x) {
-    int64_t stage = q / chunks_per_stage;
-    int c = (int)(q % chunks_per_stage);
-    const int row = c / kChunksPerRow, pc = c % kChunksPerRow;
-    const int lc = swz_chunk(row, pc);  // XOR rotation is its own inverse
-    uint16_t v[8];
-    char* dst;
-    if (stage < st13 + sts13) {
-      const bool sh = stage >= st13;
-      if (sh) stage -= st13;
-      // order of the work: expert, K stage, (partition, neuron tile).  The threads at work at one time
-      // then read the same few rows d of W1 / W3 (one 2-byte element per 32-byte sector, in permuted
-      // column order), which stay in L2; the destination index below does not depend on this order.
-      const int nt1 = sh ? L.NT1_sh : L.NT1;
-      const int tiles = (sh ? 1 : L.P) * nt1;
-      const int tile = (int)(stage % tiles);
-      int64_t r = stage / tiles;
-      const int ks = (int)(r % KS1);
-      const int e = sh ? 0 : (int)(r / KS1);
-      const int jt = tile % nt1;
-      const int p = sh ? 0 : tile / nt1;
-      const int q = row >> 6, gu = (row >> 5) & 1, j = row & 31;
-      const int Fp = sh ? L.F_shT : L.Fp;
-      const int nin = jt * kMfmaNeur + q * 32 + j;  // neuron inside the partition
-      const int d0 = ks * kBK + lc * 8;
-      if (nin < Fp) {
-        if (!sh) {
-          const int pos = p * Fp + nin;
-          const int src = perm ? perm[(size_t)e * L.F + pos] : pos;
-          const uint16_t* w = gu ? w3 : w1;
-          for (int i = 0; i < 8; ++i) v[i] = bf16_shift(w[((size_t)e * L.D + d0 + i) * L.F + src], gu ? L.h_shift : 0);
-        } else {
-          const int s = nin / F_sh, n = nin % F_sh;
-          const uint16_t* w = gu ? sw3 : sw1;
-          for (int i = 0; i < 8; ++i) v[i] = bf16_shift(w[((size_t)s * L.D + d0 + i) * F_sh + n], gu ? L.h_shift : 0);
-        }
-      } else {
-        for (int i = 0; i < 8; ++i) v[i] = 0;
-      }
-      const int64_t sidx = sh ? ((int64_t)jt * KS1 + ks) : ((((int64_t)e * L.P + p) * L.NT1 + jt) * KS1 + ks);
-      dst = packed + (sh ? L.p_sw13 : L.p_w13) + sidx * kStageBytes + (int64_t)c * 16;
-    } else {
-      stage -= st13 + sts13;
-      const bool sh = stage >= st2;
-      if (sh) stage -= st2;
-      const int KT = (sh ? L.F_shT : L.F) / kBK;
-      const int kt = (int)(stage % KT);
-      int64_t r = stage / KT;
-      const int jd = (int)(r % L.ND2);
-      const int e = sh ? 0 : (int)(r / L.ND2);
-      const int d = jd * kMfmaBN2 + row;
-      const int pos0 = kt * kBK + lc * 8;
-      const float w2_scale = ((const float*)(packed + L.p_scale))[1];
-      if (d < L.D) {
-        for (int i = 0; i < 8; ++i) {
-          const int pos = pos0 + i;
-          if (!sh) {
-            const int src = perm ? perm[(size_t)e * L.F + pos] : pos;
-            v[i] = bf16_to_scaled_half(w2[((size_t)e * L.F + src) * L.D + d], w2_scale);
-          } else {
-            const int s = pos / F_sh, n = pos % F_sh;
-            v[i] = bf16_to_scaled_half(sw2[((size_t)s * F_sh + n) * L.D + d], w2_scale);
-          }
-        }
-      } else {
-        for (int i = 0; i < 8; ++i) v[i] = 0;
-      }
-      const int64_t sidx = sh ? ((int64_t)jd * KT + kt) : (((int64_t)e * L.ND2 + jd) * KT + kt);
-      dst = packed + (sh ? L.p_sw2 : L.p_w2) + sidx * kStageBytes + (int64_t)c * 16;
-    }
-    uint4 o;
-    o.x = v[0] | ((uint32_t)v[1] << 16);
-    o.y = v[2] | ((uint32_t)v[3] << 16);
-    o.z = v[4] | ((uint32_t)v[5] << 16);
-    o.w = v[6] | ((uint32_t)v[7] << 16);
-    *(uint4*)dst = o;
+// The MFMA stage images are made by transposing tiles of 32 source rows x 512 bytes through LDS: rows come in
+// as whole 512-byte segments (16 bytes per lane), image rows leave as 64-byte runs (four 16-byte chunks of
+// neighbouring lanes), so both directions move a tensor once and in wide pieces; bound by HBM.  Weights of 8
+// experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 850 us = 4.4 TB/s, W2 (1.88 GB) 390 us
+// = 4.8 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took
+// 1295 and 1181 us: 2.9 and 1.6 TB/s.)
+constexpr int kTileCols = 256;             // columns of a tile (bf16)
+constexpr int kTileStride = 128 + 2;       // dwords between tile rows in LDS: eight rows lie 16 banks apart, so the
+                                           // 4 chunks x 16 column pairs that a wavefront reads at once touch 64 banks
+struct PackTile {
+  uint32_t at[kBK * kTileStride];
+  // this thread's four 16-byte pieces of the tile: rows (tid / 32) + 8 u, columns (tid % 32) * 8 ..
+  static __device__ __forceinline__ uint4 load(const uint16_t* row, int col, int ncols, bool vec) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row == nullptr || col >= ncols) return v;
+    if (vec) return *(const uint4*)(row + col);
+    uint32_t u[4] = {0, 0, 0, 0};
+    for (int i = 0; i < 8 && col + i < ncols; ++i) u[i >> 1] |= (uint32_t)row[col + i] << (16 * (i & 1));
+    return make_uint4(u[0], u[1], u[2], u[3]);
   }
+  __device__ __forceinline__ void put(int r, int lane32, uint4 v) {
+    uint2* d = (uint2*)&at[r * kTileStride + lane32 * 4];
+    d[0] = make_uint2(v.x, v.y);
+    d[1] = make_uint2(v.z, v.w);
+  }
+  // rows lc * 8 .. lc * 8 + 7 (one 16-byte chunk of K values) of columns 2 cp and 2 cp + 1
+  __device__ __forceinline__ void get(int lc, int cp, uint4& even, uint4& odd) const {
+    uint32_t u[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = at[(lc * 8 + i) * kTileStride + cp];
+    even = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x05040100), __builtin_amdgcn_perm(u[3], u[2], 0x05040100),
+                      __builtin_amdgcn_perm(u[5], u[4], 0x05040100), __builtin_amdgcn_perm(u[7], u[6], 0x05040100));
+    odd = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302),
+                     __builtin_amdgcn_perm(u[5], u[4], 0x07060302), __builtin_amdgcn_perm(u[7], u[6], 0x07060302));
+  }
+};
+
+template <class Op>
+__device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
+  uint32_t* u = (uint32_t*)&v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) u[i] = op((uint16_t)u[i]) | ((uint32_t)op((uint16_t)(u[i] >> 16)) << 16);
+  return v;
 }
 
-// The routed W1 / W3 stages, walked in SOURCE order: a thread takes one original neuron (column
-// src of W1 and W3) and one K stage, reads its 32 values of d from 32 rows (neighbouring threads read
-// neighbouring columns: whole cache lines, where a walk in destination order fetches a line per
-// 2-byte element of a permuted column) and writes the neuron's two 64-byte image rows at the place
-// the inverse permutation names.  inv == nullptr: identity order.
-__global__ __launch_bounds__(256) void pack_w13_columns_kernel(Layout L, const uint16_t* w1, const uint16_t* w3, const int32_t* inv,
-                                                              char* packed) {
-  const int src = blockIdx.x * 256 + threadIdx.x, ks = blockIdx.y, e = blockIdx.z;
-  if (src >= L.F) return;
-  const int pos = inv ? inv[(size_t)e * L.F + src] : src;
-  const int p = pos / L.Fp, nin = pos % L.Fp;
-  const int jt = nin / kMfmaNeur, q = (nin % kMfmaNeur) >> 5, j = nin & 31;
-  const int KS1 = L.D / kBK;
-  char* stage = packed + L.p_w13 + ((((int64_t)e * L.P + p) * L.NT1 + jt) * KS1 + ks) * kStageBytes;
+// W1 / W3 -> W13 images.  A workgroup takes kTileCols original neurons (columns) of one expert and one K stage (32
+// rows d) of both matrices and writes each neuron's gate and up image rows at the place the inverse permutation
+// names (inv == nullptr: identity order).  w1, w3: [experts][D][Fs]; column c of expert e is neuron pos0 * e + c of
+// image expert e * per_expert (the shared experts are consecutive neurons of one image expert: per_expert 0).
+// What is left to the 5.3 TB/s of a large copy are the 64-byte runs that a random order scatters.
+__global__ __launch_bounds__(256) void pack_w13_kernel(const uint16_t* w1, const uint16_t* w3, const int32_t* inv, char* out, int D,
+                                                       int Fs, int Fp, int P, int NT1, int pos0, int per_expert, int h_shift, int vec) {
+  __shared__ PackTile t1, t3;
+  const int nc = (Fs + kTileCols - 1) / kTileCols;
+  const int c0 = (int)(blockIdx.x % nc) * kTileCols, ks = blockIdx.x / nc, e = blockIdx.y, tid = threadIdx.x;
+  const int KS1 = D / kBK;
+  uint4 a[4], b[4];
 #pragma unroll
-  for (int gu = 0; gu < 2; ++gu) {
-    const uint16_t* w = (gu ? w3 : w1) + ((size_t)e * L.D + (size_t)ks * kBK) * L.F + src;
-    uint16_t v[kBK];
+  for (int u = 0; u < 4; ++u) {
+    const size_t row = ((size_t)e * D + (size_t)ks * kBK + u * 8 + (tid >> 5)) * Fs;
+    a[u] = PackTile::load(w1 + row, c0 + (tid & 31) * 8, Fs, vec);
+    b[u] = PackTile::load(w3 + row, c0 + (tid & 31) * 8, Fs, vec);
+  }
 #pragma unroll
-    for (int i = 0; i < kBK; ++i) v[i] = bf16_shift(w[(size_t)i * L.F], gu ? L.h_shift : 0);
-    const int row = q * 64 + gu * 32 + j;
+  for (int u = 0; u < 4; ++u) {
+    t1.put(u * 8 + (tid >> 5), tid & 31, a[u]);
+    if (h_shift) b[u] = map_halves(b[u], [&](uint16_t v) { return (uint32_t)bf16_shift(v, h_shift); });
+    t3.put(u * 8 + (tid >> 5), tid & 31, b[u]);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int lc = 0; lc < kChunksPerRow; ++lc) {
-      uint4 o;
-      o.x = v[8 * lc + 0] | ((uint32_t)v[8 * lc + 1] << 16);
-      o.y = v[8 * lc + 2] | ((uint32_t)v[8 * lc + 3] << 16);
-      o.z = v[8 * lc + 4] | ((uint32_t)v[8 * lc + 5] << 16);
-      o.w = v[8 * lc + 6] | ((uint32_t)v[8 * lc + 7] << 16);
-      *(uint4*)(stage + row * (kBK * 2) + swz_chunk(row, lc) * 16) = o;
+  for (int pass = 0; pass < 2; ++pass) {
+    const int lc = tid & 3, cp = pass * 64 + (tid >> 2);
+    uint4 g[2], u[2];
+    t1.get(lc, cp, g[0], g[1]);
+    t3.get(lc, cp, u[0], u[1]);
+#pragma unroll
+    for (int odd = 0; odd < 2; ++odd) {
+      const int c = c0 + cp * 2 + odd;
+      if (c >= Fs) continue;
+      const int pos = inv ? inv[(size_t)e * Fs + c] : pos0 * e + c;
+      const int p = pos / Fp, nin = pos - p * Fp;
+      const int jt = nin / kMfmaNeur, row = ((nin % kMfmaNeur) >> 5) * 64 + (nin & 31);  // gate row; the up row is 32 further down
+      char* stage = out + ((((int64_t)e * per_expert * P + p) * NT1 + jt) * KS1 + ks) * kStageBytes;
+      *(uint4*)(stage + row * (kBK * 2) + swz_chunk(row, lc) * 16) = g[odd];
+      *(uint4*)(stage + (row + 32) * (kBK * 2) + swz_chunk(row + 32, lc) * 16) = u[odd];
     }
   }
 }
 
-// image rows of the neurons past the end of a partition (its last neuron tile is not full): zeros
-__global__ __launch_bounds__(256) void pack_w13_padding_kernel(Layout L, char* packed) {
-  const int pad = L.NT1 * kMfmaNeur - L.Fp;  // neurons per (expert, partition) that do not exist
-  const int KS1 = L.D / kBK;
-  const int64_t total = (int64_t)L.E_res * L.P * KS1 * pad * 2 * kChunksPerRow;
+// W2 -> W2 images (half precision times the layer's power of two).  A workgroup makes one 16 KiB stage: 32 neuron
+// positions (source rows, in permuted order) x 256 output columns.  w2: [experts][F][D].
+__global__ __launch_bounds__(256) void pack_w2_kernel(const uint16_t* w2, const int32_t* perm, char* out, const float* rec, int D, int F,
+                                                      int vec) {
+  __shared__ PackTile t;
+  const int nd = (D + kMfmaBN2 - 1) / kMfmaBN2;
+  const int jd = blockIdx.x % nd, kt = blockIdx.x / nd, e = blockIdx.y, tid = threadIdx.x;
+  const float scale = rec[1];
+  uint4 a[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int pos = kt * kBK + u * 8 + (tid >> 5);
+    const int src = perm ? perm[(size_t)e * F + pos] : pos;
+    a[u] = PackTile::load(w2 + ((size_t)e * F + src) * D, jd * kMfmaBN2 + (tid & 31) * 8, D, vec);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    t.put(u * 8 + (tid >> 5), tid & 31, map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); }));
+  __syncthreads();
+  char* stage = out + (((int64_t)e * nd + jd) * (F / kBK) + kt) * kStageBytes;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int lc = tid & 3, row = (pass * 64 + (tid >> 2)) * 2;
+    uint4 even, odd;
+    t.get(lc, row >> 1, even, odd);
+    *(uint4*)(stage + row * (kBK * 2) + swz_chunk(row, lc) * 16) = even;
+    *(uint4*)(stage + (row + 1) * (kBK * 2) + swz_chunk(row + 1, lc) * 16) = odd;
+  }
+}
+
+// image rows of the neurons past the end of a partition (its last neuron tile is not full): zeros.
+// groups: (expert, partition) pairs of the images at `out`
+__global__ __launch_bounds__(256) void pack_w13_padding_kernel(char* out, int groups, int Fp, int NT1, int KS1) {
+  const int pad = NT1 * kMfmaNeur - Fp;  // neurons per group that do not exist
+  const int64_t total = (int64_t)groups * KS1 * pad * 2 * kChunksPerRow;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= total) return;
   const int pc = (int)(t % kChunksPerRow);
   int64_t r = t / kChunksPerRow;
   const int gu = (int)(r % 2);
   r /= 2;
-  const int nin = L.Fp + (int)(r % pad);
+  const int nin = Fp + (int)(r % pad);
   r /= pad;
   const int ks = (int)(r % KS1);
   const int64_t ep = r / KS1;  // e * P + p
   const int jt = nin / kMfmaNeur, q = (nin % kMfmaNeur) >> 5, j = nin & 31;
   const int row = q * 64 + gu * 32 + j;
-  char* stage = packed + L.p_w13 + ((ep * L.NT1 + jt) * KS1 + ks) * kStageBytes;
+  char* stage = out + ((ep * NT1 + jt) * KS1 + ks) * kStageBytes;
   *(uint4*)(stage + row * (kBK * 2) + pc * 16) = make_uint4(0, 0, 0, 0);
 }
 
@@ -279,28 +281,36 @@ hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const vo
     absmax_bf16_kernel<<<dim3(2048), dim3(256), 0, s>>>((const uint16_t*)w2, (int64_t)L.E_res * L.F * L.D, rec);
     if (n_shared > 0) absmax_bf16_kernel<<<dim3(512), dim3(256), 0, s>>>((const uint16_t*)sw2, (int64_t)L.F_shT * L.D, rec);
     w2_scale_kernel<<<dim3(1), dim3(1), 0, s>>>(rec, L.h_shift);
-    // The routed W1 / W3 stages are written in source order (see pack_w13_columns_kernel), which
-    // needs the inverse permutation: it is parked in the W2 region of the packed buffer, which
-    // the last kernel overwrites.  (That region has E_res * F * D * 2 bytes, the table E_res * F * 4.)
-    const bool columns = L.D >= 2 && (int64_t)L.D / kBK <= 65535 && L.E_res <= 65535;
-    if (columns) {
-      int32_t* inv = nullptr;
-      if (perm) {
-        inv = (int32_t*)(packed + L.p_w2);
-        const int64_t n = (int64_t)L.E_res * L.F;
-        invert_perm_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(perm, inv, L.F, n);
-      }
-      pack_w13_columns_kernel<<<dim3((L.F + 255) / 256, L.D / kBK, L.E_res), dim3(256), 0, s>>>(
-          L, (const uint16_t*)w1, (const uint16_t*)w3, inv, packed);
-      const int pad = L.NT1 * kMfmaNeur - L.Fp;
-      if (pad > 0) {
-        const int64_t total = (int64_t)L.E_res * L.P * (L.D / kBK) * pad * 2 * kChunksPerRow;
-        pack_w13_padding_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s>>>(L, packed);
-      }
+    // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
+    // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
+    // (That region has E_res * F * D * 2 bytes, the table E_res * F * 4.)
+    int32_t* inv = nullptr;
+    if (perm) {
+      inv = (int32_t*)(packed + L.p_w2);
+      const int64_t n = (int64_t)L.E_res * L.F;
+      invert_perm_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(perm, inv, L.F, n);
     }
-    pack_mfma_kernel<<<grid, block, 0, s>>>(L, (const uint16_t*)w1, (const uint16_t*)w3, (const uint16_t*)w2,
-                                            (const uint16_t*)sw1, (const uint16_t*)sw3, (const uint16_t*)sw2, perm, packed,
-                                            n_shared, F_sh > 0 ? F_sh : 1, columns ? 1 : 0);
+    auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
+    auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
+      const int vec = Fs % 8 == 0 && aligned(a, b);
+      pack_w13_kernel<<<dim3((unsigned)(((Fs + kTileCols - 1) / kTileCols) * (L.D / kBK)), experts), block, 0, s>>>(
+          (const uint16_t*)a, (const uint16_t*)b, order, out, L.D, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
+      const int pad = NT1 * kMfmaNeur - Fp, groups = (per_expert ? experts : 1) * P;
+      if (pad > 0) {
+        const int64_t total = (int64_t)groups * (L.D / kBK) * pad * 2 * kChunksPerRow;
+        pack_w13_padding_kernel<<<dim3((unsigned)((total + 255) / 256)), block, 0, s>>>(out, groups, Fp, NT1, L.D / kBK);
+      }
+    };
+    auto w2_images = [&](const void* w, const int32_t* order, char* out, int experts, int F) {
+      pack_w2_kernel<<<dim3((unsigned)(L.ND2 * (F / kBK)), experts), block, 0, s>>>((const uint16_t*)w, order, out, (const float*)rec, L.D, F,
+                                                                     L.D % 8 == 0 && aligned(w, w));
+    };
+    w13(w1, w3, inv, packed + L.p_w13, L.E_res, L.F, L.Fp, L.P, L.NT1, 1);
+    w2_images(w2, perm, packed + L.p_w2, L.E_res, L.F);
+    if (n_shared > 0) {
+      w13(sw1, sw3, nullptr, packed + L.p_sw13, n_shared, F_sh, L.F_shT, 1, L.NT1_sh, 0);
+      w2_images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT);
+    }
   } else if (L.dtype == DSMOE_F32) {
     pack_generic_kernel<float><<<grid, block, 0, s>>>(L, (const float*)w1, (const float*)w3, (const float*)w2,
                                                       (const float*)sw1, (const float*)sw3, (const float*)sw2, perm, packed,
