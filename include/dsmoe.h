@@ -98,8 +98,8 @@ size_t dsmoe_workspace_bytes(const dsmoe_ctx* ctx);
 const char* dsmoe_strerror(int status);
 /* hipError_t value of the last failed HIP call on this context (0 if none). */
 int dsmoe_last_hip_error(const dsmoe_ctx* ctx);
-/* 1 if this context runs the bf16 MFMA kernels, 0 if it runs the generic fp32-accumulate kernels
- * (fp32 layers, bf16 layers whose D, F/P or shared width is not a multiple of 32, or contexts whose
+/* 1 if this context runs the bf16 MFMA kernels, 0 if it runs the full-precision kernels, which keep the
+ * intermediate activation and the partial outputs in fp32 (fp32 layers, bf16 layers whose D, F/P or shared width is not a multiple of 32, or contexts whose
  * max_tokens * D * 2 bytes of activations reach 2 GiB: split such batches). */
 int dsmoe_uses_mfma(const dsmoe_ctx* ctx);
 
@@ -145,8 +145,8 @@ int moe_route_and_mask(dsmoe_ctx* ctx, const float* logits, int32_t T, const flo
  * intermediate activation Swish(x W1) * (x W3) is stored in IEEE half precision (values beyond
  * +-65504 saturate) and multiplied with W2 held as half precision times a per-layer power of two,
  * which represents every bf16 weight within 2^-29 of the largest exactly, and the per-pair partial
- * outputs are stored in half precision unless cfg.partial_fp32 is set; bf16 layers on the generic path
- * (see dsmoe_uses_mfma) keep both in fp32.
+ * outputs are stored in half precision unless cfg.partial_fp32 is set; bf16 layers on the full-precision
+ * path (see dsmoe_uses_mfma) keep both in fp32.
  */
 int moe_dualsparse_forward(dsmoe_ctx* ctx, const void* packed, const void* x, const float* logits, const float* tau,
                            int32_t T, void* y, void* workspace, void* stream);
@@ -287,7 +287,7 @@ int moe_thresholds_for_drop_rate(dsmoe_ctx* ctx, const float* logits, int32_t T,
  *  13 work list of the second grouped GEMM, counters[1] records of 8 int32: first row, rows, expert, output column
  *     tile, bit mask of the partitions it sums over, first K stage and number of K stages inside every such
  *     partition, 0 or 1 + the partial-output tile it writes instead of the rows of the per-pair output
- * (fields 12 and 13 describe the lists of the matrix-core path and of the generic path alike)
+ * (fields 12 and 13 describe the lists of the matrix-core path and of the full-precision path alike)
  */
 #define DSMOE_PLAN_FIELDS 14
 int dsmoe_plan_layout(const dsmoe_ctx* ctx, int64_t* out);

@@ -14,7 +14,8 @@ namespace {
 inline int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-bool build_layout(const dsmoe_config& c, Layout& L) {
+// full_pool = false: no partial-output tiles on the full-precision path (GEMM-2 does not split K then)
+bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
   memset(&L, 0, sizeof(L));
   if (c.d_model < 1 || c.d_ff < 1) return false;
   if (c.n_experts < 1 || c.n_experts > kMaxExperts) return false;
@@ -53,22 +54,29 @@ bool build_layout(const dsmoe_config& c, Layout& L) {
                ? 1
                : 0;
   L.yp_half = (L.mfma && !c.partial_fp32) ? 1 : 0;
-  L.h_shift = L.mfma ? c.h_scale_log2 : 0;  // the generic path keeps the activation in fp32: nothing to scale
+  L.h_shift = L.mfma ? c.h_scale_log2 : 0;  // the full-precision path keeps the activation in fp32: nothing to scale
   const int64_t elem = c.dtype == DSMOE_F32 ? 4 : 2;
-  L.BM = L.mfma ? kMfmaBM : kGenBM;
-  const int neur = L.mfma ? kMfmaNeur : kGenBN;
-  const int bn2 = L.mfma ? kMfmaBN2 : kGenBN;
+  L.BM = L.mfma ? kMfmaBM : kFullBM;
+  const int neur = L.mfma ? kMfmaNeur : kFullNeur;
+  L.BN2 = L.mfma ? kMfmaBN2 : kFullBN2;
+  L.Dk = (int)align_up(L.D, kBK);
+  L.Fpk = (int)align_up(L.Fp, kBK);
+  L.Fh = L.P * L.Fpk;
+  L.Fsk = (int)align_up(L.F_shT, kBK);
   L.NT1 = cdiv(L.Fp, neur);
   L.NT1_sh = L.n_shared > 0 ? cdiv(L.F_shT, neur) : 0;
-  L.ND2 = cdiv(L.D, bn2);
-  L.split_items = L.mfma ? kSplitItems : 0;
+  L.ND2 = cdiv(L.D, L.BN2);
+  L.split_items = L.mfma ? kSplitItems : kFullSplitItems;
   // GEMM-2 item order.  Long contractions (a 256-column tile of W2 of 1 MiB or more) do not stay in an
   // XCD's L2 from one row tile to the next: the row tiles that share a column tile are then made
   // adjacent so they stream it together (measured: -9 % on d_ff 14336, +7 % on d_ff 1024..1408).
-  L.g2_rows_inner = (int64_t)L.F * kMfmaBN2 * 2 >= (1 << 20) ? 1 : 0;
+  // (Full-precision path: tiles of 64 rows, many to an expert, always share a column tile that way.)
+  L.g2_rows_inner = !L.mfma || (int64_t)L.F * kMfmaBN2 * 2 >= (1 << 20) ? 1 : 0;
   // tall items need whole neuron tiles (the variant for a half-full last neuron tile has no tall form)
   auto whole_tiles = [](int n) { const int m = n % kMfmaNeur; return m == 0 || m > kMfmaNeur / 2; };
-  L.tall_tiles = L.mfma && c.tall_items >= 0 && whole_tiles(L.Fp) && (L.n_shared == 0 || whole_tiles(L.F_shT)) ? 1 + c.tall_items : 0;
+  // (full-precision path: an item's time follows its rows and each one saved is a weight tile not fetched again: always)
+  L.tall_tiles = !L.mfma ? 2
+                 : c.tall_items >= 0 && whole_tiles(L.Fp) && (L.n_shared == 0 || whole_tiles(L.F_shT)) ? 1 + c.tall_items : 0;
   const int nsub_bits = L.P < kSubBits ? L.P : kSubBits;
   L.nsub = 1 << nsub_bits;
   L.nbins = L.E_res * L.nsub;
@@ -77,10 +85,16 @@ bool build_layout(const dsmoe_config& c, Layout& L) {
   const int rt = routed_tiles_bound(L, Tm);
   L.row_cap = L.sh_rows + rt * L.BM;
   L.max_tiles = rt + shared_tiles(L, Tm);
-  L.max_items1 = items1_whole_bound(L, Tm) + L.split_items / 2;  // a smaller batch may cut its last items in two
+  L.max_items1 = items1_whole_bound(L, Tm) + (L.mfma ? L.split_items / 2 : 0);  // a smaller batch may cut its last items in two
   // partial-output tiles the K splits of GEMM-2 can need: contexts whose largest batch has so few row
   // tiles that every item is split (decode sizes) stay within one extra tile per compute unit
-  L.pool_tiles = L.split_items == 0 ? 0 : ((int64_t)L.max_tiles * L.ND2 * 2 <= L.split_items ? kSplitItems : kPoolTiles);
+  L.pool_tiles = (int64_t)L.max_tiles * L.ND2 * 2 <= L.split_items ? kSplitItems : kPoolTiles;
+  L.pool_rows = kPoolRows;
+  if (!L.mfma) {  // at most kMaxSplit - 1 extra tiles per item, and fewer than split_items in all
+    const int64_t most = (int64_t)L.max_tiles * L.ND2 * (kMaxSplit - 1);
+    L.pool_tiles = !full_pool ? 0 : most < L.split_items ? (int)most : L.split_items;
+    L.pool_rows = align_up(Tm, 32) < kFullRows ? (int)align_up(Tm, 32) : kFullRows;
+  }
   L.max_items2 = L.max_tiles * L.ND2 + L.pool_tiles;
 
   int64_t o = 0;
@@ -112,16 +126,19 @@ bool build_layout(const dsmoe_config& c, Layout& L) {
     o = align_up(o, 2 << 20);
     return take(bytes);
   };
-  const int64_t helem = L.mfma ? 2 : 4;  // H: half precision on the MFMA path, fp32 on the generic path
-  L.o_H = take_big((int64_t)(L.row_cap - L.sh_rows) * L.F * helem);
-  L.o_Hs = take_big((int64_t)L.sh_rows * L.F_shT * helem);
-  L.o_Yp = take_big((int64_t)L.row_cap * L.D * (L.yp_half ? 2 : 4));
+  const int64_t helem = L.mfma ? 2 : 4;  // H: half precision on the MFMA path, fp32 on the full-precision path
+  L.o_H = take_big((int64_t)(L.row_cap - L.sh_rows) * L.Fh * helem);
+  L.o_Hs = take_big((int64_t)L.sh_rows * L.Fsk * helem);
+  {  // (the full-precision path may keep a padded copy of x here until GEMM-2)
+    const int64_t yp = (int64_t)L.row_cap * L.D * (L.yp_half ? 2 : 4), xpad = L.mfma ? 0 : (int64_t)Tm * L.Dk * elem;
+    L.o_Yp = take_big(yp > xpad ? yp : xpad);
+  }
   L.o_tau0 = take((int64_t)L.E * L.P * 4);
   L.o_sel = take((int64_t)(L.E + 1) * (kSelBins + 2) * 4);  // directly behind tau0: one fill clears both; row E: resident pairs
   L.o_logits = take((int64_t)Tm * L.E * 4);
   L.o_perm_check = take(((int64_t)L.E_res * L.F + 1) * 4);
-  L.o_pool = take_big((int64_t)L.pool_tiles * kPoolRows * kMfmaBN2 * (L.yp_half ? 2 : 4));  // partial outputs of split K ranges
-  L.o_split_of = take(L.split_items > 0 ? (int64_t)L.max_tiles * L.ND2 * 4 : 0);          // (row tile, column tile) -> first pool tile, or -1
+  L.o_pool = take_big((int64_t)L.pool_tiles * L.pool_rows * L.BN2 * (L.yp_half ? 2 : 4));  // partial outputs of split K ranges
+  L.o_split_of = take((int64_t)L.max_tiles * L.ND2 * 4);  // (row tile, column tile) -> first pool tile, or -1
   L.ws_bytes = o;
 
   // packed weights
@@ -141,12 +158,12 @@ bool build_layout(const dsmoe_config& c, Layout& L) {
     L.p_sw2 = takep(L.n_shared > 0 ? (int64_t)L.ND2 * (L.F_shT / kBK) * kStageBytes : 0);
     L.p_scale = takep(16);
   } else {
-    L.w13_expert_bytes = (int64_t)L.D * L.F * elem;
-    L.w2_expert_bytes = (int64_t)L.F * L.D * elem;
-    L.p_w13 = takep(2 * L.w13_expert_bytes * L.E_res);
+    L.w13_expert_bytes = (int64_t)L.P * L.NT1 * (2 * kFullNeur) * L.Dk * elem;
+    L.w2_expert_bytes = (int64_t)L.ND2 * kFullBN2 * L.Fh * elem;
+    L.p_w13 = takep(L.w13_expert_bytes * L.E_res);
     L.p_w2 = takep(L.w2_expert_bytes * L.E_res);
-    L.p_sw13 = takep(2 * (int64_t)L.D * L.F_shT * elem);
-    L.p_sw2 = takep((int64_t)L.F_shT * L.D * elem);
+    L.p_sw13 = takep((int64_t)L.NT1_sh * (2 * kFullNeur) * L.Dk * elem);
+    L.p_sw2 = takep((int64_t)L.ND2 * kFullBN2 * L.Fsk * elem);
   }
   // the permutation check borrows the start of the packed buffer for its counters
   const int64_t need_check = ((int64_t)L.E_res * L.F + 1) * 4;
@@ -314,8 +331,8 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
   DSMOE_STEP(2, launch_plan(L, T, ws, s));
   DSMOE_STEP(3, launch_scatter(L, T, ws, s));
   DSMOE_STEP(4, L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 0, s)
-                       : launch_gemm1_generic(L, T, (const char*)packed, x, ws, 0, s));
-  DSMOE_STEP(5, L.mfma ? launch_gemm2_mfma(L, T, (const char*)packed, ws, s) : launch_gemm2_generic(L, T, (const char*)packed, ws, s));
+                       : launch_gemm1_full(L, T, (const char*)packed, x, ws, 0, s));
+  DSMOE_STEP(5, L.mfma ? launch_gemm2_mfma(L, T, (const char*)packed, ws, s) : launch_gemm2_full(L, T, (const char*)packed, ws, s));
   DSMOE_STEP(6, launch_combine(L, T, (const char*)packed, ws, y, s));
   mark(kNumKernels);
 #undef DSMOE_STEP
@@ -349,6 +366,8 @@ int moe_dualsparse_forward_static(dsmoe_ctx* ctx_, const void* packed, const voi
   if (!build_layout(c, L)) return DSMOE_EINVAL;
   // the packed weights were laid out for the context's own layout: the two must agree on the kernels
   if (L.mfma != ctx->L.mfma || L.packed_bytes != ctx->L.packed_bytes) return DSMOE_EINVAL;
+  // (a batch that only fits without room for K splits runs without them)
+  if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES && !build_layout(c, L, false)) return DSMOE_EINVAL;
   if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES) return DSMOE_ENOSPC;
   void* ws = nullptr;
   hipError_t e = static_scratch(&ws);
@@ -363,6 +382,7 @@ size_t dsmoe_static_workspace_need(const dsmoe_ctx* ctx_, int32_t T) {
   c.max_tokens = T > 0 ? T : 1;
   Layout L;
   if (!build_layout(c, L)) return 0;
+  if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES && !build_layout(c, L, false)) return 0;
   return (size_t)L.ws_bytes;
 }
 
@@ -508,7 +528,7 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
   if (err == hipSuccess) err = launch_scatter(L, T, ws, s);
   if (err == hipSuccess)
     err = L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 1 + metric, s)
-                 : launch_gemm1_generic(L, T, (const char*)packed, x, ws, 1 + metric, s);
+                 : launch_gemm1_full(L, T, (const char*)packed, x, ws, 1 + metric, s);
   if (err == hipSuccess) err = launch_colsum(L, ws, metric, importance, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   return DSMOE_OK;

@@ -43,9 +43,13 @@ constexpr int kBK = 32;                     // K values per pipeline stage
 constexpr int kChunksPerRow = kBK / 8;      // 16-byte chunks in one tile row
 constexpr int kStageBytes = 256 * kBK * 2;  // one operand tile of one stage (bf16): 16 KiB
 
-// generic path tile shape
-constexpr int kGenBM = 64;
-constexpr int kGenBN = 64;
+// full-precision path (gemm_full.hip): 64 rows (up to 128 with the expert's short last tile) x 64 neurons (gate+up = 128
+// weight rows) for GEMM-1, x 128 output columns for GEMM-2, K stage 32
+constexpr int kFullBM = 64;
+constexpr int kFullNeur = 64;
+constexpr int kFullBN2 = 128;
+constexpr int kFullRows = kFullBM + kTallExtra;
+constexpr int kFullSplitItems = 512;  // two GEMM-2 workgroups per compute unit
 
 struct Item1 {  // one tile of GEMM-1: rows [row0, row0+nrows) x neurons tile jt of partition p
   int32_t row0, nrows, e, p, jt;
@@ -72,7 +76,10 @@ struct Layout {
   int32_t g2_rows_inner;  // GEMM-2 item order: 1 = (expert, column tile, row tile), 0 = (expert, row tile, column tile)
   int32_t tall_tiles;     // MFMA path: a GEMM item of a full row tile may also take the expert's last row tile if that has at most
                           // kTallExtra rows: 0 never, 1 where the plan's estimate says it pays (GEMM-1; always in GEMM-2), 2 wherever possible
-  int32_t split_items;  // kSplitItems if GEMM-2 may split K (MFMA path), else 0
+  int32_t split_items;  // GEMM-2 items that fill the chip: the granularity K splits aim at
+  // full-precision path: K dimensions padded to whole stages (equal to the unpadded ones on the matrix-core path)
+  int32_t Dk, Fpk, Fh, Fsk;  // D; F/P; row length of H (P * Fpk); F_shT
+  int32_t pool_rows, BN2;    // rows of a partial-output tile of the pool; output columns of a GEMM-2 tile
   int32_t max_tokens;
   // plan geometry
   int32_t BM;                 // row tile height
@@ -139,7 +146,7 @@ inline int items1_whole_bound(const Layout& L, int T) {
 // A last round of items may be cut into halves only in the weight-streaming regime: at most half a
 // tile of rows per expert on average.
 __host__ __device__ inline bool may_halve_items1(const Layout& L, int T) {
-  return L.split_items > 0 && (int64_t)T * L.K <= (int64_t)L.E_res * (L.BM / 2);
+  return L.mfma && (int64_t)T * L.K <= (int64_t)L.E_res * (L.BM / 2);
 }
 inline int items1_bound(const Layout& L, int T) {
   return items1_whole_bound(L, T) + (may_halve_items1(L, T) ? L.split_items / 2 : 0);
@@ -158,8 +165,8 @@ hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s);
 hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, void* y, hipStream_t s);
 // epi: what GEMM-1 stores per (row, neuron): 0 = Swish(gate)*up (the layer), 1..4 = the profiling
 // metrics Swish(gate), |Swish(gate)|, Swish(gate)*up, |Swish(gate)*up|
-hipError_t launch_gemm1_generic(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
-hipError_t launch_gemm2_generic(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
+hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
+hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
 hipError_t launch_select_thresholds(const Layout& L, int T, const float* tau_max, int group_size, int row_cap, char* ws,
                                     float* tau, int32_t* pair_count, hipStream_t s);
@@ -227,5 +234,10 @@ __device__ __forceinline__ float row_sum(float v) {  // every step adds two part
 // operand read (consecutive rows, same logical chunk) touches every LDS bank once per 16 lanes.
 // XOR is its own inverse: the same function maps physical to logical positions.
 __device__ __host__ __forceinline__ int swz_chunk(int row, int chunk) { return chunk ^ ((row >> 2) & 3); }
+// the same for the full-precision path's tiles, whose rows have CH = 4 (bf16) or 8 (fp32) chunks
+template <int CH>
+__device__ __host__ __forceinline__ int swz_full(int row, int chunk) {
+  return CH == 4 ? swz_chunk(row, chunk) : chunk ^ (row & 7);
+}
 
 }  // namespace dsmoe

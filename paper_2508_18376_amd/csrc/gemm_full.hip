@@ -1,0 +1,382 @@
+// Full-precision grouped GEMMs on the matrix cores: fp32 layers, and bf16 layers that the half-precision path of
+// gemm_mfma.hip does not take (widths that are no multiple of 32, batches of 2 GiB and more).  The intermediate
+// activation H and the per-pair partial outputs are fp32 here whatever the layer's type:
+//   GEMM-1  H[row][p*Fpk + j] = Swish(x_row . W1[:, j]) * (x_row . W3[:, j])      (Eq. 4, gate/up)
+//   GEMM-2  Yp[row][d] = sum over kept partitions p, neurons j of H[row][p*Fpk + j] * W2[p*Fpk + j][d]
+// Same work lists and row lists as the other path, with tiles of 64 rows (up to 128 where an item takes the expert's
+// short last tile along) x 64 neurons, resp. x 128 output columns.
+//
+// Matrix instructions: fp32 layers multiply with v_mfma_f32_32x32x2_f32 (the precision of an fmaf chain, 256 flop
+// per clock and compute unit, the chip's fp32 peak of ~155 TFLOP/s; without packed fp32 the vector units reach
+// half of that).  bf16 layers multiply x with W1 / W3 by v_mfma_f32_32x32x16_bf16 (exact products); for GEMM-2 the fp32
+// activation is cut into three bf16 values h = hi + mid + lo (8 + 8 + 8 significant bits: exact) and multiplied with
+// the bf16 weights in three such instructions, which keeps all 24 bits of H at 5 x the rate of the fp32 instruction.
+//
+// A workgroup is 4 wavefronts; wavefront w owns the weight rows 32 w .. 32 w + 31 of the tile's 128 and multiplies them
+// with all pair rows, so a tile of r rows costs ceil(r/32) blocks.  The 32 weight rows of a GEMM-1 wavefront are the gate
+// and the up projection of the same 16 neurons, which meet in one lane.  64 rows against 128 weight rows are 2048 matrix
+// cycles for 24 KiB of operands in fp32 (12 bytes per clock: well below what L2 and HBM deliver), so for fp32 the
+// tile does not have to be larger; with few rows the kernels stream weights.  Operands travel HBM/L2 -> LDS by 16-byte
+// direct-to-LDS loads through a ring of 80 KiB (2 to 6 stages of 32 K values, by the height of the tile): two workgroups
+// per compute unit, so that one streams while the other starts or ends an item.
+//
+// Measured, before (vector FMAs on 64 x 64 tiles with guarded loads) -> now:
+//   fp32, 64 experts of 2048 x 1024, 512 tokens top-8, 25 % dropped: GEMM-1 1250 -> 370 us (2.9 TB/s of weights), GEMM-2 545 -> 194 us
+//   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 207 us (4 TB/s), GEMM-2 1041 -> 215 us
+//   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 7 us, GEMM-2 33 -> 5 us (K split over several workgroups)
+#include "common.h"
+
+namespace dsmoe {
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+constexpr int kFullLds = 80 * 1024;  // two workgroups per compute unit
+
+// 16 bytes per lane from a 64-bit address into LDS at (lds_addr + lane * 16), lds_addr wave-uniform
+__device__ __forceinline__ void dma16g(const char* src, uint32_t lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds_addr), "v"(src)
+      : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_byte(const char* p) {
+  return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const char*)p);
+}
+
+__device__ __forceinline__ int xcd_run(int b) {  // runs of 32 consecutive items per XCD (see gemm_mfma.hip)
+  const int chunk = b >> 8, within = b & 255;
+  return (chunk << 8) + ((within & 7) << 5) + (within >> 3);
+}
+
+// One tile product: 128 weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
+template <int WE, int XE, int NJ>
+struct FullTile {
+  static constexpr int WR = kBK * WE, XR = kBK * XE;           // bytes of a tile row
+  static constexpr int WCH = WR / 16, XCH = XR / 16;           // 16-byte chunks of a row
+  static constexpr int NW = 128 * WR / 4096;                   // 4 KiB loads of the weight tile per stage
+  static constexpr int XROWS = XE == 2 ? (NJ + 1) / 2 * 64 : NJ * 32;
+  static constexpr int NX = XROWS * XR / 4096;
+  static constexpr int NL = NW + NX;
+  static constexpr int SB = NL * 4096;                         // bytes of a stage
+  static constexpr int NS = kFullLds / SB < 6 ? kFullLds / SB : 6;
+  static constexpr int XROWS_LOAD = 256 / XCH;                 // rows per load
+  static_assert(NS >= 2 && (NS - 2) * NL < 64, "ring");
+
+  f32x16 acc[NJ];
+
+  // rowp[i]: where this thread's chunk of its i-th row starts (K position 0); wsrc: this thread's chunk of the first weight
+  // stage; next(st): byte offset of stage st in a pair row and in the weight stages, called once per stage in order
+  template <class Next>
+  __device__ __forceinline__ void run(int n, const char* const (&rowp)[NX], const char* wsrc, Next&& next, const char* lds, int w, int lane) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    const uint32_t base = lds_byte(lds) + (uint32_t)w * 1024;
+    auto issue = [&](int st) {
+      int64_t xo, wo;
+      next(xo, wo);
+      const uint32_t slot = base + (uint32_t)(st % NS) * SB;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) dma16g(wsrc + wo + q * 4096, slot + q * 4096);
+#pragma unroll
+      for (int q = 0; q < NX; ++q) dma16g(rowp[q] + xo, slot + (NW + q) * 4096);
+    };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s)
+      if (s < n) issue(s);
+    int st = 0;
+    for (; st + NS - 1 < n; ++st) {
+      wait_loads<(NS - 2) * NL>();  // stage st has landed (for this wavefront; the barrier makes it so for all)
+      asm volatile("s_barrier" ::: "memory");
+      issue(st + NS - 1);           // into the slot of stage st - 1, which every wavefront has finished reading
+      multiply(lds + (st % NS) * SB, w, lane);
+    }
+    for (; st < n; ++st) {
+      const int left = n - 1 - st;  // later stages still in flight
+      if (NS > 2 && left >= NS - 2) wait_loads<(NS - 2) * NL>();
+      else if (NS > 3 && left == NS - 3) wait_loads<(NS > 3 ? NS - 3 : 0) * NL>();
+      else if (NS > 4 && left == NS - 4) wait_loads<(NS > 4 ? NS - 4 : 0) * NL>();
+      else if (NS > 5 && left == NS - 5) wait_loads<(NS > 5 ? NS - 5 : 0) * NL>();
+      else wait_loads<0>();
+      asm volatile("s_barrier" ::: "memory");
+      multiply(lds + (st % NS) * SB, w, lane);
+    }
+  }
+
+  __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
+    const int r32 = lane & 31, h = lane >> 5;
+    const char* wrow = stage + (w * 32 + r32) * WR;
+    const char* xrow = stage + NW * 4096 + r32 * XR;
+    if constexpr (WE == 4) {  // fp32 x fp32: chunk 2s + h of a row holds K values 8s + 4h .. 8s + 4h + 3
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const f32x4 a = *(const f32x4*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
+        f32x4 b[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) b[j] = *(const f32x4*)(xrow + j * 32 * XR + swz_full<XCH>(r32, 2 * s + h) * 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j][i], acc[j], 0, 0, 0);
+      }
+    } else if constexpr (XE == 2) {  // bf16 x bf16: K values 16s + 8h .. 16s + 8h + 7
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const bf16x8 a = *(const bf16x8*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const bf16x8 b = *(const bf16x8*)(xrow + j * 32 * XR + swz_full<XCH>(r32, 2 * s + h) * 16);
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+        }
+      }
+    } else {  // bf16 weights x fp32 activations
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const bf16x8 a = *(const bf16x8*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const char* x = xrow + j * 32 * XR;
+          const f32x4 v0 = *(const f32x4*)(x + swz_full<XCH>(r32, 4 * s + 2 * h) * 16);
+          const f32x4 v1 = *(const f32x4*)(x + swz_full<XCH>(r32, 4 * s + 2 * h + 1) * 16);
+          u32x4 part[3];
+          split3(v0, v1, part);
+#pragma unroll
+          for (int k = 2; k >= 0; --k)  // the small parts first
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, part[k]), acc[j], 0, 0, 0);
+        }
+      }
+    }
+  }
+
+  // eight fp32 values as sums of three bf16 values each: the top 16 bits, the top 16 bits of the (exact) rest, the rest
+  static __device__ __forceinline__ void split3(const f32x4& v0, const f32x4& v1, u32x4 (&part)[3]) {
+    float r[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        part[k][i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302);
+      if (k < 2) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          r[i] -= __uint_as_float(__float_as_uint(r[i]) & 0xffff0000u);
+          // an infinite value leaves NaN here: clamped (no finite value has a rest beyond 2^120), so that the first part decides
+          if (k == 0) r[i] = __builtin_amdgcn_fmed3f(r[i], -1.4e36f, 1.4e36f);
+        }
+      }
+    }
+  }
+};
+
+// ------------------------------------------------------------------------------------- GEMM-1
+template <typename T, int NJ>
+__device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it, const char* packed, const char* x, int64_t x_row, char* ws, int epi,
+                                                char* lds, int w, int lane) {
+  constexpr int E = sizeof(T);
+  using Tile = FullTile<E, E, NJ>;
+  const int tid = w * 64 + lane;
+  const bool sh = it.e == L.E_res;
+  const int Fpk = sh ? L.Fsk : L.Fpk, ld = sh ? L.Fsk : L.Fh, NT1 = sh ? L.NT1_sh : L.NT1;
+  const int KS = L.Dk / kBK;
+  const int32_t* row_token = (const int32_t*)(ws + L.o_row_token) + it.row0;
+  const uint8_t* row_bits = (const uint8_t*)(ws + L.o_row_bits) + it.row0;
+  const char* wsrc = packed + (sh ? L.p_sw13 : L.p_w13) + (((int64_t)(sh ? 0 : it.e * L.P + it.p) * NT1 + it.jt) * KS) * (128 * Tile::WR) + tid * 16;
+  const char* rowp[Tile::NX];
+#pragma unroll
+  for (int i = 0; i < Tile::NX; ++i) {
+    const int r = i * Tile::XROWS_LOAD + tid / Tile::XCH;
+    const int rr = r < it.nrows ? r : it.nrows - 1;  // rows past the end re-read the last one
+    rowp[i] = x + (int64_t)row_token[rr] * x_row + swz_full<Tile::XCH>(r, tid % Tile::XCH) * 16;
+  }
+  Tile t;
+  int64_t k = 0;
+  t.run(KS, rowp, wsrc, [&](int64_t& xo, int64_t& wo) {
+    xo = k * Tile::XR;
+    wo = k * (128 * Tile::WR);
+    ++k;
+  }, lds, w, lane);
+  // acc[j][v]: weight row 8*(v/4) + 4*h + v%4 of the wavefront's 32 (16 gate rows, then the 16 up rows of the same
+  // neurons), pair row j*32 + lane%32
+  float* H = (float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld + (size_t)it.p * Fpk;
+  const int n0 = it.jt * kFullNeur + w * 16 + (lane >> 5) * 4;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int r = j * 32 + (lane & 31);
+    if (r >= it.nfill) continue;
+    const bool kept = r < it.nrows && ((row_bits[r] >> it.p) & 1);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      f32x4 o;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[c] = kept ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
+      if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = o;
+    }
+  }
+  for (int r = NJ * 32 + (lane & 31); r < it.nfill; r += 32) {  // rows that keep nothing of this partition, beyond the blocks multiplied: zeros
+    for (int g = 0; g < 2; ++g)
+      if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void gemm1_full_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int id = xcd_run(blockIdx.x);
+  if (id >= ((const int32_t*)(ws + L.o_counters))[0]) return;
+  const Item1 it = ((const Item1*)(ws + L.o_items1))[id];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  switch ((it.nrows + 31) >> 5) {
+    case 1: gemm1_full_tile<T, 1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 2: gemm1_full_tile<T, 2>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 3: gemm1_full_tile<T, 3>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+    default: gemm1_full_tile<T, 4>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+  }
+}
+
+// ------------------------------------------------------------------------------------- GEMM-2
+template <typename T, int NJ>
+__device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it, const char* packed, char* ws, char* lds, int w, int lane) {
+  constexpr int E = sizeof(T);
+  using Tile = FullTile<E, 4, NJ>;
+  const int tid = w * 64 + lane;
+  const bool sh = it.e == L.E_res;
+  const int ld = sh ? L.Fsk : L.Fh;
+  const int KSp = (sh ? L.Fsk : L.Fpk) / kBK, np = sh ? 1 : L.P;  // stages of one partition, partitions
+  const float* H = (const float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld;
+  const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.ND2 + it.jd) * (np * KSp) * (128 * Tile::WR) + tid * 16;
+  const char* rowp[Tile::NX];
+#pragma unroll
+  for (int i = 0; i < Tile::NX; ++i) {
+    const int r = i * Tile::XROWS_LOAD + tid / Tile::XCH;
+    const int rr = r < it.nrows ? r : it.nrows - 1;
+    rowp[i] = (const char*)(H + (size_t)rr * ld) + swz_full<Tile::XCH>(r, tid % Tile::XCH) * 16;
+  }
+  // stages run over the partitions that some row of the tile keeps (Sec. 4: dropped units cost nothing)
+  int n = 0;
+  for (int p = 0; p < np; ++p) n += ((it.kmask >> p) & 1) ? it.ks_n : 0;
+  int p_cur = 0, k_in = 0;
+  while (p_cur < np && !((it.kmask >> p_cur) & 1)) ++p_cur;
+  Tile t;
+  t.run(n, rowp, wsrc, [&](int64_t& xo, int64_t& wo) {
+    const int64_t kt = p_cur * KSp + it.ks_lo + k_in;
+    if (++k_in == it.ks_n) {
+      k_in = 0;
+      ++p_cur;
+      while (p_cur < np && !((it.kmask >> p_cur) & 1)) ++p_cur;
+    }
+    xo = kt * Tile::XR;
+    wo = kt * (128 * Tile::WR);
+  }, lds, w, lane);
+  // acc[j][v]: output column w*32 + 8*(v/4) + 4*h + v%4 of the tile, pair row j*32 + lane%32
+  float* Y;
+  int ldy;
+  if (it.split == 0) {  // the item's rows of Yp
+    Y = (float*)(ws + L.o_Yp) + (size_t)it.row0 * L.D + it.jd * kFullBN2;
+    ldy = L.D;
+  } else {              // an extra K range of a split item: a partial-output tile of the pool
+    Y = (float*)(ws + L.o_pool) + (size_t)(it.split - 1) * L.pool_rows * kFullBN2;
+    ldy = kFullBN2;
+  }
+  const int c0 = w * 32 + (lane >> 5) * 4, d0 = it.jd * kFullBN2 + c0;
+  const bool vec = (L.D & 3) == 0;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int r = j * 32 + (lane & 31);
+    if (r >= it.nrows) continue;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      float* at = Y + (size_t)r * ldy + c0 + g * 8;
+      if (vec) {
+        if (d0 + g * 8 < L.D) *(f32x4*)at = f32x4{t.acc[j][g * 4], t.acc[j][g * 4 + 1], t.acc[j][g * 4 + 2], t.acc[j][g * 4 + 3]};
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (d0 + g * 8 + c < L.D) at[c] = t.acc[j][g * 4 + c];
+      }
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char* packed, char* ws) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int id = xcd_run(blockIdx.x);
+  if (id >= ((const int32_t*)(ws + L.o_counters))[1]) return;
+  const Item2 it = ((const Item2*)(ws + L.o_items2))[id];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  switch ((it.nrows + 31) >> 5) {
+    case 1: gemm2_full_tile<T, 1>(L, it, packed, ws, lds, w, lane); break;
+    case 2: gemm2_full_tile<T, 2>(L, it, packed, ws, lds, w, lane); break;
+    case 3: gemm2_full_tile<T, 3>(L, it, packed, ws, lds, w, lane); break;
+    default: gemm2_full_tile<T, 4>(L, it, packed, ws, lds, w, lane); break;
+  }
+}
+
+// x with every row at the start of a 16-byte group and zeros up to a multiple of 32 values: made where the layer's width or
+// the caller's pointer does not give that (one small pass; kept where GEMM-2 later writes Yp)
+template <typename T>
+__global__ __launch_bounds__(256) void pad_rows_kernel(const T* x, T* out, int D, int Dk, int64_t n) {
+  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (q >= n) return;
+  const int64_t t = q / Dk;
+  const int d = (int)(q - t * Dk);
+  out[q] = d < D ? x[t * D + d] : (T)0;
+}
+
+static hipError_t set_lds_attr() {
+  static PerDeviceOnce once;
+  return once.run([] {
+    for (const void* fn : {(const void*)gemm1_full_kernel<float>, (const void*)gemm1_full_kernel<uint16_t>, (const void*)gemm2_full_kernel<float>,
+                           (const void*)gemm2_full_kernel<uint16_t>}) {
+      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFullLds);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  });
+}
+
+hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
+  if (T <= 0) return hipSuccess;
+  hipError_t e = set_lds_attr();
+  if (e != hipSuccess) return e;
+  const int64_t elem = L.dtype == DSMOE_F32 ? 4 : 2;
+  const char* xs = (const char*)x;
+  int64_t x_row = L.D * elem;
+  if (L.D != L.Dk || ((uintptr_t)x & 15) != 0) {
+    const int64_t n = (int64_t)T * L.Dk;
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (elem == 4) pad_rows_kernel<float><<<grid, block, 0, s>>>((const float*)x, (float*)(ws + L.o_Yp), L.D, L.Dk, n);
+    else pad_rows_kernel<uint16_t><<<grid, block, 0, s>>>((const uint16_t*)x, (uint16_t*)(ws + L.o_Yp), L.D, L.Dk, n);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    xs = ws + L.o_Yp;
+    x_row = L.Dk * elem;
+  }
+  const dim3 block(256), grid((items1_bound(L, T) + 255) & ~255);  // whole chunks of 256: the XCD order is a bijection on them
+  if (elem == 4) gemm1_full_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
+  else gemm1_full_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* ws, hipStream_t s) {
+  if (T <= 0) return hipSuccess;
+  hipError_t e = set_lds_attr();
+  if (e != hipSuccess) return e;
+  const dim3 block(256), grid((items2_bound(L, T) + 255) & ~255);
+  if (L.dtype == DSMOE_F32) gemm2_full_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, ws);
+  else gemm2_full_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, ws);
+  return hipGetLastError();
+}
+
+}  // namespace dsmoe

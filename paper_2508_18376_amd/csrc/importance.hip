@@ -2,7 +2,7 @@
 //
 // GEMM-1 is run over the calibration tokens with every routed pair kept.  On the matrix-core path
 // its epilogue sums the chosen metric over the rows of each tile and this file adds the tiles of an
-// expert; on the generic path GEMM-1 stores the metric per (row, neuron) in fp32 and the rows of each
+// expert; on the full-precision path GEMM-1 stores the metric per (row, neuron) in fp32 and the rows of each
 // expert are summed here (one thread per neuron, rows in order).  Both are deterministic.  An
 // importance vector is turned into the permutation "neurons by descending importance, equal values
 // by ascending id".
@@ -10,24 +10,16 @@
 
 namespace dsmoe {
 
-template <typename T>
-__device__ __forceinline__ float ld_h(const T* p, size_t i);
-template <>
-__device__ __forceinline__ float ld_h<float>(const float* p, size_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float ld_h<uint16_t>(const uint16_t* p, size_t i) { return bf16_to_f32(p[i]); }
-
-// importance[e][q] = sum over the rows of expert e of H[row][q] (the packed weights must have been
-// made with the identity permutation, so column q of H is original neuron q)
+// importance[e][q] = sum over the rows of expert e of its column of H (the packed weights must have been
+// made with the identity permutation, so neuron j of partition p is original neuron p * F/P + j)
 // unscale: 2^-h_shift for the metrics that contain the up projection (the packed W3 carries 2^h_shift), else 1
-template <typename T>
 __global__ __launch_bounds__(256) void colsum_kernel(Layout L, const char* ws, float* importance, float unscale) {
   const int e = blockIdx.y;
   const int q = blockIdx.x * 256 + threadIdx.x;
   if (q >= L.F) return;
   const int32_t* exp_nrows = (const int32_t*)(ws + L.o_exp_nrows);
   const int32_t* exp_row0 = (const int32_t*)(ws + L.o_exp_row0);
-  const T* H = (const T*)(ws + L.o_H);
+  const float* H = (const float*)(ws + L.o_H) + q / L.Fp * L.Fpk + q % L.Fp;
   const int n = exp_nrows[e];
   const size_t r0 = (size_t)(exp_row0[e] - L.sh_rows);
   // rows are added in order (deterministic); eight loads are in flight at a time
@@ -36,11 +28,11 @@ __global__ __launch_bounds__(256) void colsum_kernel(Layout L, const char* ws, f
   for (; r + 8 <= n; r += 8) {
     float v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = ld_h<T>(H, (r0 + r + u) * L.F + q);
+    for (int u = 0; u < 8; ++u) v[u] = H[(r0 + r + u) * L.Fh];
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc += v[u];
   }
-  for (; r < n; ++r) acc += ld_h<T>(H, (r0 + r) * L.F + q);
+  for (; r < n; ++r) acc += H[(r0 + r) * L.Fh];
   importance[(size_t)e * L.F + q] = acc * unscale;
 }
 
@@ -63,7 +55,7 @@ __global__ __launch_bounds__(256) void colsum_tiles_kernel(Layout L, const char*
 hipError_t launch_colsum(const Layout& L, const char* ws, int metric, float* importance, hipStream_t s) {
   dim3 grid((L.F + 255) / 256, L.E_res), block(256);
   const float unscale = metric >= 2 ? ldexpf(1.f, -L.h_shift) : 1.f;
-  if (!L.mfma) colsum_kernel<float><<<grid, block, 0, s>>>(L, ws, importance, unscale);  // the generic path keeps H in fp32
+  if (!L.mfma) colsum_kernel<<<grid, block, 0, s>>>(L, ws, importance, unscale);  // the full-precision path keeps H
   else colsum_tiles_kernel<<<grid, block, 0, s>>>(L, ws, importance, unscale);
   return hipGetLastError();
 }

@@ -1,9 +1,11 @@
 // moe_partition_weights kernels: neuron reorder through perm (Sec. 4.2 b), even split into P
 // sub-experts with no W2 scaling (Sec. 3.2), written in the layout the GEMM kernels read.
 //
-// Generic layout (element type = layer dtype):
-//   W1g, W3g [E_res][D][F], W2g [E_res][F][D] with neuron axis in permuted order;
-//   shared experts concatenated along the neuron axis: SW1g, SW3g [D][F_shT], SW2g [F_shT][D].
+// Full-precision layout (element type = layer dtype): the same idea with tiles of 128 weight rows x 32 K values:
+//   W13  stage ((e*P + p)*NT1 + jt)*(Dk/32) + ks : weight row q*32 + gu*16 + j is neuron p*Fp + jt*64 + q*16 + j of W1
+//        (gu=0) or W3 (gu=1)
+//   W2   stage (e*ND2 + jd)*(P*Fpk/32) + kt : 128 output columns x 32 neurons; every partition is padded with zeros to
+//        whole stages (Fpk), as is D (Dk)
 // MFMA layout (bf16): 16 KiB "stage images", each the exact LDS contents of one operand tile of
 //   one pipeline stage, rows of kBK = 32 K-values with the 16-byte chunks XOR-rotated (swz_chunk):
 //   W13  stage ((e*P + p)*NT1 + jt)*(D/32) + ks : 256 weight rows x 32 values of d; weight row
@@ -22,52 +24,6 @@
 #include "common.h"
 
 namespace dsmoe {
-
-template <typename T>
-__global__ void pack_generic_kernel(Layout L, const T* w1, const T* w3, const T* w2, const T* sw1, const T* sw3,
-                                    const T* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh) {
-  const int64_t nW = (int64_t)L.E_res * L.D * L.F;
-  const int64_t nS = (int64_t)L.D * L.F_shT;
-  const int64_t total = 3 * nW + 3 * nS;
-  T* W1g = (T*)(packed + L.p_w13);
-  T* W3g = W1g + nW;
-  T* W2g = (T*)(packed + L.p_w2);
-  T* S1g = (T*)(packed + L.p_sw13);
-  T* S3g = S1g + nS;
-  T* S2g = (T*)(packed + L.p_sw2);
-  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < total; q += (int64_t)gridDim.x * blockDim.x) {
-    if (q < 2 * nW) {
-      const bool up = q >= nW;
-      int64_t r = up ? q - nW : q;
-      int j = (int)(r % L.F);
-      int64_t ed = r / L.F;  // e*D + d
-      int e = (int)(ed / L.D);
-      int src = perm ? perm[(size_t)e * L.F + j] : j;
-      (up ? W3g : W1g)[r] = (up ? w3 : w1)[ed * L.F + src];
-    } else if (q < 3 * nW) {
-      int64_t r = q - 2 * nW;
-      int d = (int)(r % L.D);
-      int64_t ej = r / L.D;  // e*F + j
-      int e = (int)(ej / L.F), j = (int)(ej % L.F);
-      int src = perm ? perm[(size_t)e * L.F + j] : j;
-      W2g[r] = w2[((size_t)e * L.F + src) * L.D + d];
-    } else if (q < 3 * nW + 2 * nS) {
-      int64_t r = q - 3 * nW;
-      const bool up = r >= nS;
-      if (up) r -= nS;
-      int c = (int)(r % L.F_shT);
-      int d = (int)(r / L.F_shT);
-      int s = c / F_sh, n = c % F_sh;
-      (up ? S3g : S1g)[r] = (up ? sw3 : sw1)[((size_t)s * L.D + d) * F_sh + n];
-    } else {
-      int64_t r = q - 3 * nW - 2 * nS;
-      int d = (int)(r % L.D);
-      int c = (int)(r / L.D);
-      int s = c / F_sh, n = c % F_sh;
-      S2g[r] = sw2[((size_t)s * F_sh + n) * L.D + d];
-    }
-  }
-}
 
 // largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out.  One read of W2,
 // bound by HBM: four 16-byte loads in flight per thread.
@@ -126,18 +82,28 @@ __device__ __forceinline__ uint16_t bf16_to_scaled_half(uint16_t b, float scale)
 // experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 850 us = 4.4 TB/s, W2 (1.88 GB) 390 us
 // = 4.8 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took
 // 1295 and 1181 us: 2.9 and 1.6 TB/s.)
-constexpr int kTileCols = 256;             // columns of a tile (bf16)
-constexpr int kTileStride = 128 + 2;       // dwords between tile rows in LDS: eight rows lie 16 banks apart, so the
-                                           // 4 chunks x 16 column pairs that a wavefront reads at once touch 64 banks
+constexpr int kTileStride = 128 + 2;  // dwords between tile rows in LDS: a wavefront reads 4 chunks x 16 column pairs (bf16) or
+                                      // 8 chunks x 8 columns (fp32) at once, whose rows then lie on 64 different banks
+template <typename T>
 struct PackTile {
+  static constexpr int V = 16 / sizeof(T);         // values of a 16-byte chunk
+  static constexpr int COLS = 512 / sizeof(T);     // columns of a tile
+  static constexpr int CH = kBK / V;               // chunks of an image row
+  static constexpr int COLS_GET = sizeof(T) == 2 ? 2 : 1;  // columns that get() returns
+  static constexpr int PASSES = COLS * CH / COLS_GET / 256;
   uint32_t at[kBK * kTileStride];
-  // this thread's four 16-byte pieces of the tile: rows (tid / 32) + 8 u, columns (tid % 32) * 8 ..
-  static __device__ __forceinline__ uint4 load(const uint16_t* row, int col, int ncols, bool vec) {
+  // sixteen bytes of a source row from column col on (zeros past the end; nullptr: a row of zeros)
+  static __device__ __forceinline__ uint4 load(const T* row, int col, int ncols, bool vec) {
     uint4 v = make_uint4(0, 0, 0, 0);
     if (row == nullptr || col >= ncols) return v;
     if (vec) return *(const uint4*)(row + col);
     uint32_t u[4] = {0, 0, 0, 0};
-    for (int i = 0; i < 8 && col + i < ncols; ++i) u[i >> 1] |= (uint32_t)row[col + i] << (16 * (i & 1));
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (col + i < ncols) {
+        if constexpr (sizeof(T) == 2) u[i >> 1] |= (uint32_t)row[col + i] << (16 * (i & 1));
+        else u[i] = __float_as_uint(row[col + i]);
+      }
     return make_uint4(u[0], u[1], u[2], u[3]);
   }
   __device__ __forceinline__ void put(int r, int lane32, uint4 v) {
@@ -145,15 +111,19 @@ struct PackTile {
     d[0] = make_uint2(v.x, v.y);
     d[1] = make_uint2(v.z, v.w);
   }
-  // rows lc * 8 .. lc * 8 + 7 (one 16-byte chunk of K values) of columns 2 cp and 2 cp + 1
-  __device__ __forceinline__ void get(int lc, int cp, uint4& even, uint4& odd) const {
-    uint32_t u[8];
+  // chunk lc (V K values: tile rows lc * V ..) of columns c * COLS_GET ..
+  __device__ __forceinline__ void get(int lc, int c, uint4 (&o)[COLS_GET]) const {
+    uint32_t u[V];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) u[i] = at[(lc * 8 + i) * kTileStride + cp];
-    even = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x05040100), __builtin_amdgcn_perm(u[3], u[2], 0x05040100),
-                      __builtin_amdgcn_perm(u[5], u[4], 0x05040100), __builtin_amdgcn_perm(u[7], u[6], 0x05040100));
-    odd = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302),
-                     __builtin_amdgcn_perm(u[5], u[4], 0x07060302), __builtin_amdgcn_perm(u[7], u[6], 0x07060302));
+    for (int i = 0; i < V; ++i) u[i] = at[(lc * V + i) * kTileStride + c];
+    if constexpr (sizeof(T) == 2) {
+      o[0] = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x05040100), __builtin_amdgcn_perm(u[3], u[2], 0x05040100),
+                        __builtin_amdgcn_perm(u[5], u[4], 0x05040100), __builtin_amdgcn_perm(u[7], u[6], 0x05040100));
+      o[1] = make_uint4(__builtin_amdgcn_perm(u[1], u[0], 0x07060302), __builtin_amdgcn_perm(u[3], u[2], 0x07060302),
+                        __builtin_amdgcn_perm(u[5], u[4], 0x07060302), __builtin_amdgcn_perm(u[7], u[6], 0x07060302));
+    } else {
+      o[0] = make_uint4(u[0], u[1], u[2], u[3]);
+    }
   }
 };
 
@@ -165,100 +135,125 @@ __device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
   return v;
 }
 
-// W1 / W3 -> W13 images.  A workgroup takes kTileCols original neurons (columns) of one expert and one K stage (32
+// Where neuron nin of a partition sits in its W13 images: neuron tile, image row of its gate projection; the up row is UP
+// rows further down.  FULL: the full-precision layout.
+template <typename T, bool FULL>
+struct W13Image {
+  static constexpr int NEUR = FULL ? kFullNeur : kMfmaNeur, UP = FULL ? 16 : 32, RB = kBK * sizeof(T);
+  static constexpr int64_t STAGE = 2 * NEUR * RB;
+  static __device__ __forceinline__ int row(int nin) { return nin % NEUR / UP * (2 * UP) + nin % UP; }
+  static __device__ __forceinline__ int at(int row, int lc) { return row * RB + swz_full<RB / 16>(row, lc) * 16; }
+};
+
+// W1 / W3 -> W13 images.  A workgroup takes the COLS original neurons (columns) of one expert and one K stage (32
 // rows d) of both matrices and writes each neuron's gate and up image rows at the place the inverse permutation
 // names (inv == nullptr: identity order).  w1, w3: [experts][D][Fs]; column c of expert e is neuron pos0 * e + c of
 // image expert e * per_expert (the shared experts are consecutive neurons of one image expert: per_expert 0).
 // What is left to the 5.3 TB/s of a large copy are the 64-byte runs that a random order scatters.
-__global__ __launch_bounds__(256) void pack_w13_kernel(const uint16_t* w1, const uint16_t* w3, const int32_t* inv, char* out, int D,
+template <typename T, bool FULL>
+__global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3, const int32_t* inv, char* out, int D, int KS1,
                                                        int Fs, int Fp, int P, int NT1, int pos0, int per_expert, int h_shift, int vec) {
-  __shared__ PackTile t1, t3;
-  const int nc = (Fs + kTileCols - 1) / kTileCols;
-  const int c0 = (int)(blockIdx.x % nc) * kTileCols, ks = blockIdx.x / nc, e = blockIdx.y, tid = threadIdx.x;
-  const int KS1 = D / kBK;
+  using PT = PackTile<T>;
+  using Im = W13Image<T, FULL>;
+  __shared__ PT t1, t3;
+  const int nc = (Fs + PT::COLS - 1) / PT::COLS;
+  const int c0 = (int)(blockIdx.x % nc) * PT::COLS, ks = blockIdx.x / nc, e = blockIdx.y, tid = threadIdx.x;
   uint4 a[4], b[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const size_t row = ((size_t)e * D + (size_t)ks * kBK + u * 8 + (tid >> 5)) * Fs;
-    a[u] = PackTile::load(w1 + row, c0 + (tid & 31) * 8, Fs, vec);
-    b[u] = PackTile::load(w3 + row, c0 + (tid & 31) * 8, Fs, vec);
+    const int d = ks * kBK + u * 8 + (tid >> 5);
+    const size_t row = ((size_t)e * D + d) * Fs;
+    a[u] = PT::load(d < D ? w1 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
+    b[u] = PT::load(d < D ? w3 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     t1.put(u * 8 + (tid >> 5), tid & 31, a[u]);
-    if (h_shift) b[u] = map_halves(b[u], [&](uint16_t v) { return (uint32_t)bf16_shift(v, h_shift); });
+    if (!FULL && h_shift) b[u] = map_halves(b[u], [&](uint16_t v) { return (uint32_t)bf16_shift(v, h_shift); });
     t3.put(u * 8 + (tid >> 5), tid & 31, b[u]);
   }
   __syncthreads();
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int lc = tid & 3, cp = pass * 64 + (tid >> 2);
-    uint4 g[2], u[2];
-    t1.get(lc, cp, g[0], g[1]);
-    t3.get(lc, cp, u[0], u[1]);
+  for (int pass = 0; pass < PT::PASSES; ++pass) {
+    const int lc = tid % PT::CH, cg = (pass * 256 + tid) / PT::CH;
+    uint4 g[PT::COLS_GET], u[PT::COLS_GET];
+    t1.get(lc, cg, g);
+    t3.get(lc, cg, u);
 #pragma unroll
-    for (int odd = 0; odd < 2; ++odd) {
-      const int c = c0 + cp * 2 + odd;
+    for (int i = 0; i < PT::COLS_GET; ++i) {
+      const int c = c0 + cg * PT::COLS_GET + i;
       if (c >= Fs) continue;
       const int pos = inv ? inv[(size_t)e * Fs + c] : pos0 * e + c;
       const int p = pos / Fp, nin = pos - p * Fp;
-      const int jt = nin / kMfmaNeur, row = ((nin % kMfmaNeur) >> 5) * 64 + (nin & 31);  // gate row; the up row is 32 further down
-      char* stage = out + ((((int64_t)e * per_expert * P + p) * NT1 + jt) * KS1 + ks) * kStageBytes;
-      *(uint4*)(stage + row * (kBK * 2) + swz_chunk(row, lc) * 16) = g[odd];
-      *(uint4*)(stage + (row + 32) * (kBK * 2) + swz_chunk(row + 32, lc) * 16) = u[odd];
+      const int row = Im::row(nin);
+      char* stage = out + ((((int64_t)e * per_expert * P + p) * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
+      *(uint4*)(stage + Im::at(row, lc)) = g[i];
+      *(uint4*)(stage + Im::at(row + Im::UP, lc)) = u[i];
     }
   }
 }
 
-// W2 -> W2 images (half precision times the layer's power of two).  A workgroup makes one 16 KiB stage: 32 neuron
-// positions (source rows, in permuted order) x 256 output columns.  w2: [experts][F][D].
-__global__ __launch_bounds__(256) void pack_w2_kernel(const uint16_t* w2, const int32_t* perm, char* out, const float* rec, int D, int F,
-                                                      int vec) {
-  __shared__ PackTile t;
-  const int nd = (D + kMfmaBN2 - 1) / kMfmaBN2;
-  const int jd = blockIdx.x % nd, kt = blockIdx.x / nd, e = blockIdx.y, tid = threadIdx.x;
-  const float scale = rec[1];
+// W2 -> W2 images (matrix-core path: half precision times the layer's power of two).  A workgroup takes 32 neuron positions
+// (source rows, in permuted order; zeros past the end of a partition) x COLS output columns: one stage image, or two
+// of 128 columns.  w2: [experts][P * Fp][D]; KSp: stages of a partition, KT: of the expert, nd: column tiles of the images.
+template <typename T, bool FULL>
+__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, const float* rec, int D, int F, int Fp,
+                                                      int KSp, int KT, int nd, int vec) {
+  using PT = PackTile<T>;
+  constexpr int BN = FULL ? kFullBN2 : kMfmaBN2, RB = kBK * sizeof(T);
+  __shared__ PT t;
+  const int nb = (D + PT::COLS - 1) / PT::COLS;
+  const int c0 = (int)(blockIdx.x % nb) * PT::COLS, kt = blockIdx.x / nb, e = blockIdx.y, tid = threadIdx.x;
+  const float scale = FULL ? 1.f : rec[1];
   uint4 a[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int pos = kt * kBK + u * 8 + (tid >> 5);
-    const int src = perm ? perm[(size_t)e * F + pos] : pos;
-    a[u] = PackTile::load(w2 + ((size_t)e * F + src) * D, jd * kMfmaBN2 + (tid & 31) * 8, D, vec);
+    const int in = kt % KSp * kBK + u * 8 + (tid >> 5), pos = kt / KSp * Fp + in;
+    const T* row = nullptr;
+    if (in < Fp) row = w2 + ((size_t)e * F + (perm ? perm[(size_t)e * F + pos] : pos)) * D;
+    a[u] = PT::load(row, c0 + (tid & 31) * PT::V, D, vec);
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-    t.put(u * 8 + (tid >> 5), tid & 31, map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); }));
+  for (int u = 0; u < 4; ++u) {
+    if (!FULL) a[u] = map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
+    t.put(u * 8 + (tid >> 5), tid & 31, a[u]);
+  }
   __syncthreads();
-  char* stage = out + (((int64_t)e * nd + jd) * (F / kBK) + kt) * kStageBytes;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int lc = tid & 3, row = (pass * 64 + (tid >> 2)) * 2;
-    uint4 even, odd;
-    t.get(lc, row >> 1, even, odd);
-    *(uint4*)(stage + row * (kBK * 2) + swz_chunk(row, lc) * 16) = even;
-    *(uint4*)(stage + (row + 1) * (kBK * 2) + swz_chunk(row + 1, lc) * 16) = odd;
+  for (int pass = 0; pass < PT::PASSES; ++pass) {
+    const int lc = tid % PT::CH, cg = (pass * 256 + tid) / PT::CH;
+    uint4 o[PT::COLS_GET];
+    t.get(lc, cg, o);
+#pragma unroll
+    for (int i = 0; i < PT::COLS_GET; ++i) {
+      const int c = c0 + cg * PT::COLS_GET + i, jd = c / BN, row = c % BN;
+      if (jd >= nd) continue;
+      char* stage = out + (((int64_t)e * nd + jd) * KT + kt) * (BN * RB);
+      *(uint4*)(stage + row * RB + swz_full<RB / 16>(row, lc) * 16) = o[i];
+    }
   }
 }
 
 // image rows of the neurons past the end of a partition (its last neuron tile is not full): zeros.
 // groups: (expert, partition) pairs of the images at `out`
+template <typename T, bool FULL>
 __global__ __launch_bounds__(256) void pack_w13_padding_kernel(char* out, int groups, int Fp, int NT1, int KS1) {
-  const int pad = NT1 * kMfmaNeur - Fp;  // neurons per group that do not exist
-  const int64_t total = (int64_t)groups * KS1 * pad * 2 * kChunksPerRow;
+  using Im = W13Image<T, FULL>;
+  constexpr int CH = Im::RB / 16;
+  const int pad = NT1 * Im::NEUR - Fp;  // neurons per group that do not exist
+  const int64_t total = (int64_t)groups * KS1 * pad * 2 * CH;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= total) return;
-  const int pc = (int)(t % kChunksPerRow);
-  int64_t r = t / kChunksPerRow;
+  const int pc = (int)(t % CH);
+  int64_t r = t / CH;
   const int gu = (int)(r % 2);
   r /= 2;
   const int nin = Fp + (int)(r % pad);
   r /= pad;
   const int ks = (int)(r % KS1);
   const int64_t ep = r / KS1;  // e * P + p
-  const int jt = nin / kMfmaNeur, q = (nin % kMfmaNeur) >> 5, j = nin & 31;
-  const int row = q * 64 + gu * 32 + j;
-  char* stage = out + ((ep * NT1 + jt) * KS1 + ks) * kStageBytes;
-  *(uint4*)(stage + row * (kBK * 2) + pc * 16) = make_uint4(0, 0, 0, 0);
+  char* stage = out + ((ep * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
+  *(uint4*)(stage + (Im::row(nin) + gu * Im::UP) * Im::RB + pc * 16) = make_uint4(0, 0, 0, 0);
 }
 
 // inv[e][perm[e][pos]] = pos
@@ -270,9 +265,48 @@ __global__ void invert_perm_kernel(const int32_t* perm, int32_t* inv, int F, int
   if (src >= 0 && src < F) inv[e * F + src] = (int32_t)(t % F);  // a bad perm is refused before this runs; stay in bounds regardless
 }
 
+template <typename T, bool FULL>
+static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3, const void* sw2,
+                              const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
+  const dim3 block(256);
+  const float* rec = (const float*)(packed + L.p_scale);
+  const int KS1 = L.Dk / kBK, C = PackTile<T>::COLS;
+  // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
+  // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
+  // (That region has at least E_res * F * 32 * sizeof(T) bytes, the table E_res * F * 4.)
+  int32_t* inv = nullptr;
+  if (perm) {
+    inv = (int32_t*)(packed + L.p_w2);
+    const int64_t n = (int64_t)L.E_res * L.F;
+    invert_perm_kernel<<<dim3((unsigned)((n + 255) / 256)), block, 0, s>>>(perm, inv, L.F, n);
+  }
+  auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
+  auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
+    const int vec = Fs % PackTile<T>::V == 0 && aligned(a, b);
+    pack_w13_kernel<T, FULL><<<dim3((unsigned)((Fs + C - 1) / C * KS1), experts), block, 0, s>>>(
+        (const T*)a, (const T*)b, order, out, L.D, KS1, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
+    const int pad = NT1 * W13Image<T, FULL>::NEUR - Fp, groups = (per_expert ? experts : 1) * P;
+    if (pad > 0) {
+      const int64_t total = (int64_t)groups * KS1 * pad * 2 * PackTile<T>::CH;
+      pack_w13_padding_kernel<T, FULL><<<dim3((unsigned)((total + 255) / 256)), block, 0, s>>>(out, groups, Fp, NT1, KS1);
+    }
+  };
+  auto w2_images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {
+    const int KSp = Fpk / kBK, KT = F / Fp * KSp;
+    pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * KT), experts), block, 0, s>>>(
+        (const T*)w, order, out, rec, L.D, F, Fp, KSp, KT, L.ND2, L.D % PackTile<T>::V == 0 && aligned(w, w));
+  };
+  w13(w1, w3, inv, packed + L.p_w13, L.E_res, L.F, L.Fp, L.P, L.NT1, 1);
+  w2_images(w2, perm, packed + L.p_w2, L.E_res, L.F, L.Fp, L.Fpk);
+  if (n_shared > 0) {
+    w13(sw1, sw3, nullptr, packed + L.p_sw13, n_shared, F_sh, L.F_shT, 1, L.NT1_sh, 0);
+    w2_images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT, L.F_shT, L.Fsk);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
-  dim3 block(256), grid(256 * 64);
   if (L.mfma) {
     // the layer's W2 scale (see the layout comment at the top), from the largest |W2| of routed and shared experts
     uint32_t* rec = (uint32_t*)(packed + L.p_scale);
@@ -281,46 +315,10 @@ hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const vo
     absmax_bf16_kernel<<<dim3(2048), dim3(256), 0, s>>>((const uint16_t*)w2, (int64_t)L.E_res * L.F * L.D, rec);
     if (n_shared > 0) absmax_bf16_kernel<<<dim3(512), dim3(256), 0, s>>>((const uint16_t*)sw2, (int64_t)L.F_shT * L.D, rec);
     w2_scale_kernel<<<dim3(1), dim3(1), 0, s>>>(rec, L.h_shift);
-    // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
-    // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
-    // (That region has E_res * F * D * 2 bytes, the table E_res * F * 4.)
-    int32_t* inv = nullptr;
-    if (perm) {
-      inv = (int32_t*)(packed + L.p_w2);
-      const int64_t n = (int64_t)L.E_res * L.F;
-      invert_perm_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(perm, inv, L.F, n);
-    }
-    auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
-    auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
-      const int vec = Fs % 8 == 0 && aligned(a, b);
-      pack_w13_kernel<<<dim3((unsigned)(((Fs + kTileCols - 1) / kTileCols) * (L.D / kBK)), experts), block, 0, s>>>(
-          (const uint16_t*)a, (const uint16_t*)b, order, out, L.D, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
-      const int pad = NT1 * kMfmaNeur - Fp, groups = (per_expert ? experts : 1) * P;
-      if (pad > 0) {
-        const int64_t total = (int64_t)groups * (L.D / kBK) * pad * 2 * kChunksPerRow;
-        pack_w13_padding_kernel<<<dim3((unsigned)((total + 255) / 256)), block, 0, s>>>(out, groups, Fp, NT1, L.D / kBK);
-      }
-    };
-    auto w2_images = [&](const void* w, const int32_t* order, char* out, int experts, int F) {
-      pack_w2_kernel<<<dim3((unsigned)(L.ND2 * (F / kBK)), experts), block, 0, s>>>((const uint16_t*)w, order, out, (const float*)rec, L.D, F,
-                                                                     L.D % 8 == 0 && aligned(w, w));
-    };
-    w13(w1, w3, inv, packed + L.p_w13, L.E_res, L.F, L.Fp, L.P, L.NT1, 1);
-    w2_images(w2, perm, packed + L.p_w2, L.E_res, L.F);
-    if (n_shared > 0) {
-      w13(sw1, sw3, nullptr, packed + L.p_sw13, n_shared, F_sh, L.F_shT, 1, L.NT1_sh, 0);
-      w2_images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT);
-    }
-  } else if (L.dtype == DSMOE_F32) {
-    pack_generic_kernel<float><<<grid, block, 0, s>>>(L, (const float*)w1, (const float*)w3, (const float*)w2,
-                                                      (const float*)sw1, (const float*)sw3, (const float*)sw2, perm, packed,
-                                                      n_shared, F_sh > 0 ? F_sh : 1);
-  } else {
-    pack_generic_kernel<uint16_t><<<grid, block, 0, s>>>(L, (const uint16_t*)w1, (const uint16_t*)w3, (const uint16_t*)w2,
-                                                         (const uint16_t*)sw1, (const uint16_t*)sw3, (const uint16_t*)sw2,
-                                                         perm, packed, n_shared, F_sh > 0 ? F_sh : 1);
+    return pack_images<uint16_t, false>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
   }
-  return hipGetLastError();
+  if (L.dtype == DSMOE_F32) return pack_images<float, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
+  return pack_images<uint16_t, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
 }
 
 // perm check: scratch[0 .. E_res*F) counts how often each neuron id is named (zeroed by the

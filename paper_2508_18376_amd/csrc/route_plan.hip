@@ -657,10 +657,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     const int W2n = (total_tiles - total_short) * L.ND2;
     int nsplit = 1, first_split = W2n;  // items first_split .. W2n-1 (in list order) are split nsplit ways
     if (L.split_items > 0 && W2n > 0) {
-      int ksp = L.Fp / kBK;
-      if (has_sh) ksp = min(ksp, L.F_shT / kBK);
+      int ksp = L.Fpk / kBK;
+      if (has_sh) ksp = min(ksp, L.Fsk / kBK);
       if (W2n * 2 <= L.split_items) {
-        while (nsplit < kMaxSplit && W2n * nsplit * 2 <= L.split_items && nsplit * 2 <= ksp) nsplit *= 2;
+        while (nsplit < kMaxSplit && W2n * nsplit * 2 <= L.split_items && nsplit * 2 <= ksp && W2n * (nsplit * 2 - 1) <= L.pool_tiles) nsplit *= 2;
         first_split = 0;
       } else {
         // The last round holds `rest` items for split_items compute units.  Cut n ways they are rest * n
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         const int rest = W2n % L.split_items;
         if (rest > 0) {
           float best = 1.0f;
-          const int item_stages = E_res > 0 ? L.P * (L.Fp / kBK) : L.F_shT / kBK;  // K stages of a long item
+          const int item_stages = E_res > 0 ? L.P * (L.Fpk / kBK) : L.Fsk / kBK;  // K stages of a long item
           const float piece = 8.0f / (float)max(item_stages, 1);                  // per-piece overhead in units of such an item
           for (int n = 2; n <= kMaxTailSplit && n <= ksp; ++n) {
             if (rest * (n - 1) > L.pool_tiles) break;
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       const int g = gj / L.ND2, jd = gj % L.ND2;
       const int e = tile_expert(g);
       const int i = g - ts[e];
-      const int ksp = (e < E_res ? L.Fp : L.F_shT) / kBK;
+      const int ksp = (e < E_res ? L.Fpk : L.Fsk) / kBK;
       const int nt_all = tiles_of(ne[e]), sl = short_last(e);
       if (sl && i == nt_all - 1) continue;         // the short last tile: computed by the items of the tile before
       const bool tall = sl && i == nt_all - 2;
@@ -713,10 +713,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         v.ks_n = ksp;
         v.split = 0;
         items2[slot] = v;
-        if (L.split_items > 0) {
-          split_of[gj] = -1;
-          if (tall) split_of[gj + L.ND2] = -1;
-        }
+        split_of[gj] = -1;
+        if (tall) split_of[gj + L.ND2] = -1;
       } else {
         const int q = slot - first_split;  // q-th split item: its extra ranges use pool tiles q*(nsplit-1) ..
         atomicMin(&first_split_tile, g);
@@ -819,7 +817,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       // MFMA path, at most 128 rows, a last neuron tile of at most 64 neurons: the half-tile variant of
       // the kernel takes it as a first half without a second one (half the weight bytes)
       const int live = (e < E_res ? L.Fp : L.F_shT) - jt * kMfmaNeur;
-      v.half = L.split_items > 0 && v.nrows <= kMfmaBM / 2 && live <= kMfmaNeur / 2 ? 1 : 0;
+      v.half = L.mfma && v.nrows <= kMfmaBM / 2 && live <= kMfmaNeur / 2 ? 1 : 0;
       items1[gb[gi] + jt * ga[gi] + rk] = v;
     }
   }
@@ -957,7 +955,7 @@ hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s) {
 // y[t] = sum_k g[t][k] * Yp[row(t,k)] (+ Yp[shared row t]); Eq. 3 restricted to the kept units.
 // One writer per output element, slots added in slot order: no atomics.
 // Partial outputs still carry the powers of two of the packed weights; w2_inv = 2^-(s+k) takes them
-// out here (exact, so the result is the one unscaled weights would give; 1 on the generic path).
+// out here (exact, so the result is the one unscaled weights would give; 1 on the full-precision path).
 // They are fp32, or (HALF) half precision times kYpHalfScale, which is taken out here as well.
 // 16 bytes of partial outputs: VEC = 4 floats, or 8 half-precision values.  The rows of a token are
 // loaded as raw 16-byte vectors (all in flight together) and widened one row at a time, so that the
@@ -1010,7 +1008,7 @@ __global__ __launch_bounds__(256) void combine_kernel(Layout L, int T, const cha
   const int split_row0 = counters[4] * L.BM;  // rows before it belong to tiles without split items
   const int32_t* split_of = (const int32_t*)(ws + L.o_split_of);
   const char* pool = ws + L.o_pool;
-  const int jd = d / kMfmaBN2, dc = d - jd * kMfmaBN2;
+  const int jd = d / L.BN2, dc = d - jd * L.BN2;
   // GEMM-2 split K: the partial-output tiles of the extra K ranges of row r are added in range order
   auto add_extra = [&](int r, float (&into)[VEC]) {
     const int tile = r / L.BM;
@@ -1018,13 +1016,13 @@ __global__ __launch_bounds__(256) void combine_kernel(Layout L, int T, const cha
     if (first < 0) return;
     const int rofs = first & kSplitRowsOffset ? L.BM : 0;  // a short last tile: its rows follow those of the tile before
     first &= ~kSplitRowsOffset;
-    size_t src = ((size_t)first * kPoolRows + (r - tile * L.BM) + rofs) * kMfmaBN2 + dc;
+    size_t src = ((size_t)first * L.pool_rows + (r - tile * L.BM) + rofs) * L.BN2 + dc;
     for (int sp = 1; sp < nsplit; ++sp) {
       float u[VEC];
       PT::widen(PT::load(pool, src), u);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) into[i] += u[i];
-      src += (size_t)kPoolRows * kMfmaBN2;
+      src += (size_t)L.pool_rows * L.BN2;
     }
   };
   if (L.n_shared > 0) {  // the shared experts' rows sit first in the row space (weight 1)
@@ -1071,12 +1069,29 @@ __global__ __launch_bounds__(256) void combine_scalar_kernel(Layout L, int T, co
   if (q >= (int64_t)T * L.D) return;
   const int t = (int)(q / L.D);
   const int d = (int)(q % L.D);
+  const int32_t* counters = (const int32_t*)(ws + L.o_counters);
+  const int nsplit = counters[3], split_row0 = counters[4] * L.BM;
+  const int jd = d / L.BN2;
+  auto partial = [&](int r) {  // row r of Yp and the partial-output tiles of its extra K ranges (see combine_kernel)
+    float v = Yp[(size_t)r * L.D + d];
+    if (nsplit > 1 && r >= split_row0) {
+      const int tile = r / L.BM;
+      int first = ((const int32_t*)(ws + L.o_split_of))[(size_t)tile * L.ND2 + jd];
+      if (first >= 0) {
+        const int rofs = first & kSplitRowsOffset ? L.BM : 0;
+        first &= ~kSplitRowsOffset;
+        const float* pool = (const float*)(ws + L.o_pool) + ((size_t)first * L.pool_rows + (r - tile * L.BM) + rofs) * L.BN2 + (d - jd * L.BN2);
+        for (int sp = 1; sp < nsplit; ++sp) v += pool[(size_t)(sp - 1) * L.pool_rows * L.BN2];
+      }
+    }
+    return v;
+  };
   float acc = 0.f;
   for (int k = 0; k < L.K; ++k) {
     int row = pair_row[(size_t)t * L.K + k];
-    if (row >= 0) acc += w[(size_t)t * L.K + k] * Yp[(size_t)row * L.D + d];
+    if (row >= 0) acc += w[(size_t)t * L.K + k] * partial(row);
   }
-  if (L.n_shared > 0) acc += Yp[(size_t)t * L.D + d];
+  if (L.n_shared > 0) acc += partial(t);
   if constexpr (sizeof(OutT) == 4) ((float*)y)[q] = acc;
   else ((uint16_t*)y)[q] = f32_to_bf16(acc);
 }

@@ -1,0 +1,96 @@
+"""GPU: the full-precision path (fp32 layers, bf16 layers off the matrix-core grid) at the edges of its tiles: row counts
+around 32, 64 and 128 (blocks, tiles, a short last tile taken along), widths that need padding of every K dimension,
+activations that need a padded copy, K splits, and a batch of the static entry point that leaves no room for them.
+
+Both types keep fp32 intermediates and accumulate in fp32, bf16 products are exact: with the output stored as fp32 the
+fp32 bar (1e-5 x RMS of the oracle's output) holds for both.
+"""
+import numpy as np
+import pytest
+
+from synth import make_layer
+from gpu_util import make_gpu_layer, to_dev, to_host64, tau_table, rel_err
+from test_gpu_forward import spec_of, resolve_tau
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ("rows_1", dict(T=1, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_32", dict(T=32, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_33", dict(T=33, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_65", dict(T=65, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_97", dict(T=97, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_128", dict(T=128, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_129", dict(T=129, D=128, F=176, E=1, K=1, P=1), 0.0),
+    ("rows_200_two_column_tiles", dict(T=200, D=260, F=176, E=1, K=1, P=1), 0.0),
+    ("padded_everywhere", dict(T=150, D=73, F=99, E=3, K=2, P=3), "rate0.3"),
+    ("odd_shared", dict(T=100, D=130, F=72, E=4, K=2, P=2, n_shared=2, F_sh=27), "rate0.3"),
+    ("general_masks", dict(T=230, D=96, F=104, E=4, K=3, P=4), "ragged"),
+    ("split_k", dict(T=9, D=200, F=1056, E=4, K=2, P=2), 0.0),
+    ("split_k_under_drop", dict(T=70, D=136, F=2080, E=4, K=2, P=4), "rate0.25"),
+    ("split_k_odd_width", dict(T=80, D=131, F=1056, E=2, K=2, P=1), 0.0),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("name,shape,tau_kind", SHAPES, ids=[s[0] for s in SHAPES])
+def test_full_precision_tiles(oracle, name, shape, tau_kind, dtype):
+    import torch
+    spec = spec_of(dtype=dtype, seed=90, x_std=1.0, w_std=0.05, **shape)
+    t = make_layer(spec)
+    tau = resolve_tau(oracle, spec, t, tau_kind)
+    layer, dev = make_gpu_layer(spec, t, y_fp32=True)
+    if layer.uses_mfma:
+        pytest.skip("the shape is on the matrix-core grid")
+    print("%s %s" % (name, dtype), flush=True)
+    y = layer.forward(dev["x"], dev["logits"], to_dev(tau))
+    # the same activations from an address that is no multiple of 16 bytes
+    buf = torch.empty(spec.T * spec.D + 1, dtype=dev["x"].dtype, device="cuda:0")
+    shifted = buf[1:].view(spec.T, spec.D)
+    shifted.copy_(dev["x"])
+    y2 = layer.forward(shifted, dev["logits"], to_dev(tau))
+    torch.cuda.synchronize()
+    ref = oracle.forward(t["x"], t["logits"], t["w1"], t["w3"], t["w2"], tau, spec.K, spec.P, perm=t["perm"],
+                         sh_w1=t.get("sh_w1"), sh_w3=t.get("sh_w3"), sh_w2=t.get("sh_w2"))
+    assert rel_err(to_host64(y, "f32"), ref) <= 1e-5
+    assert torch.equal(y, y2)
+    layer.close()
+
+
+def test_infinite_activations_stay_infinite_in_the_split_product():
+    """A bf16 layer whose intermediate activation overflows fp32 gives infinities (not NaN) where one term is infinite."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    layer = DualSparseLayer(d_model=40, d_ff=8, n_experts=1, top_k=1, n_part=1, max_tokens=4, dtype="bf16", y_fp32=True)
+    assert not layer.uses_mfma
+    w1 = torch.zeros(1, 40, 8, dtype=torch.bfloat16, device="cuda:0")
+    w3, w2 = torch.zeros_like(w1), torch.zeros(1, 8, 40, dtype=torch.bfloat16, device="cuda:0")
+    w1[0, 0, 0] = w3[0, 0, 0] = 2.0 ** 40
+    w2[0, 0, :] = 0.5
+    layer.partition_weights(w1, w3, w2)
+    x = torch.zeros(2, 40, dtype=torch.bfloat16, device="cuda:0")
+    x[0, 0], x[1, 0] = 2.0 ** 40, 1.0  # Swish(2^80) * 2^80 overflows; Swish(2^40) * 2^40 does not
+    y = layer.forward(x, torch.zeros(2, 1, device="cuda:0"), torch.zeros(1, 1, device="cuda:0"))
+    torch.cuda.synchronize()
+    assert torch.isposinf(y[0]).all() and (y[1] == 2.0 ** 79).all()
+    layer.close()
+
+
+def test_static_batch_without_room_for_k_splits(oracle):
+    import torch
+    import paper_2508_18376_amd as ds
+    spec = spec_of(dtype="f32", T=8, D=1024, F=512, E=4, K=2, P=2, seed=91, w_std=0.05)
+    t = make_layer(spec)
+    T = 20000  # ~40 k rows x (512 + 1024) x 4 bytes: the array holds it only without the pool of partial-output tiles
+    layer, _ = make_gpu_layer(spec, t, max_tokens=T)
+    assert ds.DSMOE_STATIC_SCRATCH_BYTES - (32 << 20) < ds.dsmoe_static_workspace_need(layer.ctx, T) <= ds.DSMOE_STATIC_SCRATCH_BYTES
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    x = torch.randn(T, spec.D, generator=gen, device="cuda:0")
+    logits = torch.randn(T, spec.E, generator=gen, device="cuda:0")
+    tau = to_dev(tau_table(spec, np.zeros(spec.P, np.float32)))
+    y = torch.empty(T, spec.D, device="cuda:0")
+    ds.moe_dualsparse_forward_static(layer.ctx, layer.packed, x, logits, tau, T, y, torch.cuda.current_stream())
+    ref = layer.forward(x, logits, tau)
+    torch.cuda.synchronize()
+    assert float((y - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
+    layer.close()
