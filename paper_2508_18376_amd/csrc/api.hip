@@ -133,8 +133,7 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
     const int64_t yp = (int64_t)L.row_cap * L.D * (L.yp_half ? 2 : 4), xpad = L.mfma ? 0 : (int64_t)Tm * L.Dk * elem;
     L.o_Yp = take_big(yp > xpad ? yp : xpad);
   }
-  L.o_tau0 = take((int64_t)L.E * L.P * 4);
-  L.o_sel = take((int64_t)(L.E + 1) * (kSelBins + 2) * 4);  // directly behind tau0: one fill clears both; row E: resident pairs
+  L.o_sel = take((int64_t)(L.E > kSelBlocks ? L.E : kSelBlocks) * kSelRow * 4);  // score histograms of the threshold selections
   L.o_logits = take((int64_t)Tm * L.E * 4);
   L.o_perm_check = take(((int64_t)L.E_res * L.F + 1) * 4);
   L.o_pool = take_big((int64_t)L.pool_tiles * L.pool_rows * L.BN2 * (L.yp_half ? 2 : 4));  // partial outputs of split K ranges
@@ -520,9 +519,9 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
   // every routed pair takes part: thresholds of zero keep all units
-  hipError_t err = launch_fill_i32((int32_t*)(ws + L.o_tau0), (int64_t)L.E * L.P, 0, s);
-  if (err == hipSuccess && T > 0)
-    err = launch_route(L, logits, T, (const float*)(ws + L.o_tau0), (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
+  hipError_t err = hipSuccess;
+  if (T > 0)
+    err = launch_route(L, logits, T, nullptr, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
                        (uint8_t*)(ws + L.o_keep), (int32_t*)(ws + L.o_bin_count), nullptr, s);
   if (err == hipSuccess) err = launch_plan(L, T, ws, s);
   if (err == hipSuccess) err = launch_scatter(L, T, ws, s);
@@ -552,13 +551,7 @@ int moe_select_thresholds(dsmoe_ctx* ctx_, const float* logits, int32_t T, const
   if (T > L.max_tokens || group_size < 1 || L.E % group_size != 0) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  // zero thresholds for the routing pass and a cleared score histogram (adjacent in the workspace)
-  const int64_t clear = (L.o_sel - L.o_tau0) / 4 + (int64_t)(L.E + 1) * (kSelBins + 2);
-  hipError_t err = launch_fill_i32((int32_t*)(ws + L.o_tau0), clear, 0, s);
-  if (err == hipSuccess && T > 0)
-    err = launch_route(L, logits, T, (const float*)(ws + L.o_tau0), (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
-                       (uint8_t*)(ws + L.o_keep), nullptr, nullptr, s, true);
-  if (err == hipSuccess) err = launch_select_thresholds(L, T, tau_max, group_size, row_cap, ws, tau, pair_count, s);
+  hipError_t err = launch_select_thresholds(L, T, logits, tau_max, group_size, row_cap, ws, tau, pair_count, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   return DSMOE_OK;
 }
@@ -575,14 +568,7 @@ int moe_thresholds_for_drop_rate(dsmoe_ctx* ctx_, const float* logits, int32_t T
     if (offset_bins[p] < -kSelBins || offset_bins[p] > kSelBins) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  // zero thresholds for the routing pass; of the score histograms only the resident row is used here
-  hipError_t err = launch_fill_i32((int32_t*)(ws + L.o_tau0), (int64_t)L.E * L.P, 0, s);
-  if (err == hipSuccess)
-    err = launch_fill_i32((int32_t*)(ws + L.o_sel) + (int64_t)L.E * (kSelBins + 2), kSelBins + 2, 0, s);
-  if (err == hipSuccess && T > 0)
-    err = launch_route(L, logits, T, (const float*)(ws + L.o_tau0), (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
-                       (uint8_t*)(ws + L.o_keep), nullptr, nullptr, s, true);
-  if (err == hipSuccess) err = launch_drop_rate_thresholds(L, T, rate, offset_bins, ws, tau, stats, s);
+  hipError_t err = launch_drop_rate_thresholds(L, T, logits, rate, offset_bins, ws, tau, stats, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   return DSMOE_OK;
 }

@@ -27,6 +27,8 @@ constexpr int kPoolTiles = 768;   // partial-output tiles (256 x 256) the extra 
 // smallest normal one, whatever the scale of the weights (and, through cfg.h_scale_log2, of the activations).
 constexpr float kYpHalfScale = 1.0f / 1024.0f;
 constexpr int kSelBins = 4096;  // grid of the row-budget thresholds: multiples of 2^-12 (a power of two keeps n * kSelBins exact)
+constexpr int kSelRow = kSelBins + 4;  // a score histogram: kSelBins + 1 bins and a pair count, in whole 16-byte groups
+constexpr int kSelBlocks = 16;          // workgroups of the drop-rate histogram, one row each
 constexpr int kRouteBlockTokens = 64;  // tokens per block of the route kernels, one histogram row each ...
 constexpr int kWaveBlockTokens = 16;   // ... except the sixteen-lanes-per-token kernel (E > 32) on small batches: 4 wavefronts x 4 tokens
 constexpr int kWaveSmallBatch = 2048;  // largest batch that uses the small blocks (more blocks would swamp the plan kernel's sum)
@@ -94,7 +96,7 @@ struct Layout {
   // workspace byte offsets
   int64_t o_idx, o_w, o_keep, o_pair_row, o_bin_count, o_cursor, o_exp_nrows, o_exp_row0, o_counters;
   int64_t o_tile_bits, o_act_rank, o_items1, o_items2;
-  int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_tau0, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
+  int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
   // packed weights byte offsets
   int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the W2 scale record (MFMA layout)
   int64_t w13_expert_bytes, w2_expert_bytes;  // strides between experts (mfma layout)
@@ -158,8 +160,12 @@ inline int items2_bound(const Layout& L, int T) {
 
 // launchers (each returns hipError_t of the launch)
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
+// tau == nullptr: thresholds of zero
 hipError_t launch_route(const Layout& L, const float* logits, int T, const float* tau, int32_t* idx, float* w,
-                        uint8_t* keep, int32_t* bin_count, int32_t* group_count, hipStream_t s, bool whole_router_scores = false);
+                        uint8_t* keep, int32_t* bin_count, int32_t* group_count, hipStream_t s);
+// The normalised scores instead of routing results: their histograms per expert of the whole router (sel: rows of kSelRow,
+// cleared by the caller), or the scores themselves (n [T][K], -1 where the expert is not resident; sel == nullptr).
+hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s);
 hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s);
 hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s);
 hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, void* y, hipStream_t s);
@@ -168,14 +174,14 @@ hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, 
 hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
 hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
-hipError_t launch_select_thresholds(const Layout& L, int T, const float* tau_max, int group_size, int row_cap, char* ws,
+hipError_t launch_select_thresholds(const Layout& L, int T, const float* logits, const float* tau_max, int group_size, int row_cap, char* ws,
                                     float* tau, int32_t* pair_count, hipStream_t s);
 hipError_t launch_router_pack(const Layout& L, const void* wg, char* out, hipStream_t s);
 hipError_t launch_router(const Layout& L, int T, const char* router_packed, const void* x, float* logits, hipStream_t s);
 hipError_t launch_transform_complete(const Layout& L, const void* wg, const void* w1, const void* w3, const void* w2,
                                      const int32_t* perm, void* wg_out, void* w1_out, void* w3_out, void* w2_out,
                                      hipStream_t s);
-hipError_t launch_drop_rate_thresholds(const Layout& L, int T, double rate, const int32_t* offset_bins, char* ws, float* tau,
+hipError_t launch_drop_rate_thresholds(const Layout& L, int T, const float* logits, double rate, const int32_t* offset_bins, char* ws, float* tau,
                                        int32_t* stats, hipStream_t s);
 hipError_t launch_colsum(const Layout& L, const char* ws, int metric, float* importance, hipStream_t s);
 hipError_t launch_perm_from_importance(const Layout& L, const float* importance, int32_t* perm, hipStream_t s);

@@ -29,6 +29,8 @@ struct RouteArgs {
   uint8_t* keep;
   int32_t* bin_count;    // forward: [blocks][nbins] sort-bin histogram, one row per block (may be null)
   int32_t* group_count;  // stand-alone: [E*P] kept units per sub-expert (may be null)
+  int32_t* sel;          // score histograms, or scores, in place of idx / w / keep (may be null); see launch_route_scores
+  float* score;
   int T, E, K, P, lo, hi, renorm, nsub_bits, nsub, nhist;
 };
 
@@ -43,6 +45,7 @@ __device__ __forceinline__ int sub_of_bits(int bits, int nsub_bits) {
 __device__ __forceinline__ int keep_bits_of(float n, int e, const RouteArgs& a, const float* tau) {
   int bits = 0;
   if (e >= a.lo && e < a.hi) {
+    if (!a.tau) return n >= 0.f ? (1 << a.P) - 1 : 0;
     for (int p = 0; p < a.P; ++p) bits |= (n >= tau[e * a.P + p] ? 1 : 0) << p;
   }
   return bits;
@@ -56,6 +59,38 @@ __device__ __forceinline__ void count_pair(int32_t* hist, int bits, int e, const
     int32_t* h2 = hist + (a.bin_count ? (a.hi - a.lo) * a.nsub : 0);
     for (int p = 0; p < a.P; ++p)
       if ((bits >> p) & 1) atomicAdd(&h2[e * a.P + p], 1);
+  }
+}
+
+// One pair's results: routing outputs and sort-bin histogram, or its place in the score histograms.  There the bins are
+// spread (two pairs of a wavefront rarely meet in one), while the pair counts of a few experts are not: those are
+// collected in LDS.  (One global atomic per pair on them took 150 us for 32 k pairs over 8 experts.)
+__device__ __forceinline__ void finish_pair(const RouteArgs& a, int32_t* hist, const float* tau, int t, int k, int e, float n, float s) {
+  if (a.sel) {
+    int b = (int)floorf(n * (float)kSelBins);
+    b = b < 0 ? 0 : (b > kSelBins ? kSelBins : b);
+    atomicAdd(&a.sel[(size_t)e * kSelRow + b], 1);
+    atomicAdd(&hist[e], 1);
+    return;
+  }
+  if (a.score) {
+    a.score[(size_t)t * a.K + k] = e >= a.lo && e < a.hi ? n : -1.f;
+    return;
+  }
+  const int bits = keep_bits_of(n, e, a, tau);
+  const size_t o = (size_t)t * a.K + k;
+  a.idx[o] = e;
+  a.w[o] = a.renorm ? n : s;
+  a.keep[o] = (uint8_t)bits;
+  count_pair(hist, bits, e, a);
+}
+// the block's LDS histogram leaves
+__device__ __forceinline__ void flush_hist(const RouteArgs& a, const int32_t* hist, int threads) {
+  const int nb = a.bin_count ? (a.hi - a.lo) * a.nsub : 0;
+  for (int i = threadIdx.x; i < a.nhist; i += threads) {
+    const int c = hist[i];
+    if (i < nb) a.bin_count[(size_t)blockIdx.x * nb + i] = c;  // this block's row of the histogram: no atomics
+    else if (c) atomicAdd(a.sel ? &a.sel[(size_t)i * kSelRow + kSelBins + 1] : &a.group_count[i - nb], c);
   }
 }
 
@@ -106,23 +141,13 @@ __global__ __launch_bounds__(64) void route_lane_kernel(RouteArgs a) {
 #pragma unroll
     for (int k = 0; k < KMAX; ++k) {
       if (k < a.K) {
-        float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
-        int bits = keep_bits_of(n, ik[k], a, a.tau);
-        size_t o = (size_t)t * a.K + k;
-        a.idx[o] = ik[k];
-        a.w[o] = a.renorm ? n : sk[k];
-        a.keep[o] = (uint8_t)bits;
-        count_pair(hist, bits, ik[k], a);
+        const float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
+        finish_pair(a, hist, a.tau, t, k, ik[k], n, sk[k]);
       }
     }
   }
   __syncthreads();
-  const int nb = a.bin_count ? (a.hi - a.lo) * a.nsub : 0;
-  for (int i = threadIdx.x; i < a.nhist; i += 64) {
-    int c = hist[i];
-    if (i < nb) a.bin_count[(size_t)blockIdx.x * nb + i] = c;  // this block's row of the histogram: no atomics
-    else if (c) atomicAdd(&a.group_count[i - nb], c);
-  }
+  flush_hist(a, hist, 64);
 }
 
 // Sixteen lanes per token (one row of the wavefront), NCH * 4 logits per lane: lane r of the row
@@ -147,7 +172,8 @@ __global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
   for (int i = threadIdx.x; i < a.nhist; i += kThreads) hist[i] = 0;
   // the threshold table is fetched now, together with the logits, not after the scores are known
   float* tau_l = (float*)(hist + a.nhist);
-  for (int i = threadIdx.x; i < a.E * a.P; i += kThreads) tau_l[i] = a.tau[i];
+  if (a.tau)
+    for (int i = threadIdx.x; i < a.E * a.P; i += kThreads) tau_l[i] = a.tau[i];
   // (the barrier that publishes hist and tau_l sits right before their first use, after the scores)
   const int r = threadIdx.x & 15, row = threadIdx.x >> 4;  // lane in its row; row in the block (WV * 4 of them)
   const int t_end = min(a.T, ((int)blockIdx.x + 1) * kTokens);
@@ -260,46 +286,26 @@ __global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
       const int e = expert(j);
       if (e < a.E && rank[u][j] < a.K) {
         const float n = sc[u][j] / ssum[u];  // Sec. 4.1: normalise over the K selected
-        const int bits = keep_bits_of(n, e, a, tau_l);
-        const size_t o = (size_t)t * a.K + rank[u][j];
-        a.idx[o] = e;
-        a.w[o] = a.renorm ? n : sc[u][j];
-        a.keep[o] = (uint8_t)bits;
-        count_pair(hist, bits, e, a);
+        finish_pair(a, hist, tau_l, t, rank[u][j], e, n, sc[u][j]);
       }
     }
   }
   __syncthreads();
-  const int nb = a.bin_count ? (a.hi - a.lo) * a.nsub : 0;
-  for (int i = threadIdx.x; i < a.nhist; i += kThreads) {
-    int c = hist[i];
-    if (i < nb) a.bin_count[(size_t)blockIdx.x * nb + i] = c;  // this block's row of the histogram: no atomics
-    else if (c) atomicAdd(&a.group_count[i - nb], c);
-  }
+  flush_hist(a, hist, kThreads);
 }
 
-hipError_t launch_route(const Layout& L, const float* logits, int T, const float* tau, int32_t* idx, float* w,
-                        uint8_t* keep, int32_t* bin_count, int32_t* group_count, hipStream_t s, bool whole_router_scores) {
+static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t s) {
+  const int T = a.T;
   if (T <= 0) return hipSuccess;
-  RouteArgs a;
-  a.logits = logits;
-  a.tau = tau;
-  a.idx = idx;
-  a.w = w;
-  a.keep = keep;
-  a.bin_count = bin_count;
-  a.group_count = group_count;
-  a.T = T;
   a.E = L.E;
   a.K = L.K;
   a.P = L.P;
-  // whole_router_scores: every expert counts as resident and w receives the normalised score
-  a.lo = whole_router_scores ? 0 : L.lo;
-  a.hi = whole_router_scores ? L.E : L.hi;
-  a.renorm = whole_router_scores ? 1 : L.renorm;
+  a.lo = L.lo;
+  a.hi = L.hi;
+  a.renorm = L.renorm;
   a.nsub = L.nsub;
   a.nsub_bits = L.P < kSubBits ? L.P : kSubBits;
-  a.nhist = (bin_count ? L.nbins : 0) + (group_count ? L.E * L.P : 0);
+  a.nhist = a.sel ? L.E : (a.bin_count ? L.nbins : 0) + (a.group_count ? L.E * L.P : 0);
   const size_t sh = sizeof(int32_t) * (size_t)(a.nhist + L.E * L.P);  // histogram + (row kernel) threshold table
   if (L.E <= 32) {  // few experts: a lane per token, no cross-lane traffic
     dim3 grid((T + 63) / 64), block(64);
@@ -320,6 +326,29 @@ hipError_t launch_route(const Layout& L, const float* logits, int T, const float
     else route_row_kernel<8, 1, 4><<<grid, block, sh, s>>>(a);
   }
   return hipGetLastError();
+}
+
+hipError_t launch_route(const Layout& L, const float* logits, int T, const float* tau, int32_t* idx, float* w,
+                        uint8_t* keep, int32_t* bin_count, int32_t* group_count, hipStream_t s) {
+  RouteArgs a = {};
+  a.logits = logits;
+  a.tau = tau;
+  a.idx = idx;
+  a.w = w;
+  a.keep = keep;
+  a.bin_count = bin_count;
+  a.group_count = group_count;
+  a.T = T;
+  return launch_route_kernel(L, a, s);
+}
+
+hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s) {
+  RouteArgs a = {};
+  a.logits = logits;
+  a.sel = sel;
+  a.score = n;
+  a.T = T;
+  return launch_route_kernel(L, a, s);
 }
 
 // ------------------------------------------------------------------------------------- plan
