@@ -57,7 +57,7 @@ struct Item1 {  // one tile of GEMM-1: rows [row0, row0+nrows) x neurons tile jt
   int32_t row0, nrows, e, p, jt;
   int32_t nfill;  // rows of the whole row tile (>= nrows): rows [nrows, nfill) keep nothing of p and get zeros
   int32_t half;   // 0: the whole neuron tile; 1 / 2: its first / second 64 neurons (MFMA path, at most 128 rows)
-  int32_t pad;
+  int32_t once;   // the only item of its expert and partition that reads this weight tile
 };
 struct Item2 {  // one tile of GEMM-2: rows x output column tile jd, summed over partitions in kmask
   int32_t row0, nrows, e, jd, kmask;

@@ -84,14 +84,26 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 
 // 16 bytes per lane from (rsrc base + voff + soff) straight into LDS at (lds_addr + lane * 16);
 // lds_addr (byte address inside the workgroup's LDS) must be wave-uniform.
+// ONCE: the non-temporal hint.
+// Weight tiles that a single item reads (an expert with one row tile: decode steps and short prompts) are loaded with
+// it: they do not push the activation rows that every item of the expert gathers out of the L2 (4 MiB an XCD), and the
+// stream itself runs faster: 64 tokens on 8 experts of 4096 x 14336 500 -> 443 us (2.8 GB of weights: 6.2 -> 7.1 TB/s),
+// 333 tokens on 64 + 2 experts of 2048 x 1408 303 -> 279 us.  Tiles that several row tiles share keep the default policy:
+// with the hint the second reader misses (4096 tokens on 64 experts of 2048 x 1024 425 -> 437 us, 2000 on the first layer 1118
+// -> 1252 us).
+template <bool ONCE = false>
 __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"
-      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-      :
-      : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-      : "memory");
+#define DSMOE_DMA16(POLICY)                                      \
+  asm volatile(                                                  \
+      "s_mov_b32 m0, %0\n\t"                                     \
+      "s_nop 0\n\t"                                              \
+      "buffer_load_dwordx4 %1, %2, %3 offen" POLICY " lds"       \
+      :                                                          \
+      : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)           \
+      : "memory")
+  if (ONCE) DSMOE_DMA16(" nt");
+  else DSMOE_DMA16("");
+#undef DSMOE_DMA16
 }
 
 // byte offset of a __shared__ object inside the workgroup's LDS allocation (what M0 wants)
@@ -347,8 +359,9 @@ struct G1Args {
 // TALL: a full row tile that also takes the 1..64 rows its expert has beyond it (rows 256..319 of the item: each
 // wavefront multiplies its four weight blocks with one more block of 32 rows, see WaveTile), so that those
 // rows do not pull the whole weight tile through a second compute unit.
+// ONCE: no other item reads this item's weight tile (Item1::once).
 template <int I, int J, int NJ, bool PROFILE, int NW = 4, bool HALF = false, class RING = RingWhole, int NX = (J == 8 ? (NJ * 32 + 63) / 64 : 4),
-          bool TALL = false>
+          bool TALL = false, bool ONCE = false>
 __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row0, int b_row0, int w) {
   static_assert(!TALL || (I == 4 && J == 4 && NJ == 4 && NW == 4 && !HALF && NX == 5 && !PROFILE), "tall tiles: 2 x 2 wavefronts, 320 rows, the layer's pass only");
   // Each instantiation derives its lane-dependent offsets from its own copy of the thread id:
@@ -386,7 +399,7 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
     sX = (uint32_t)(st * kRowBytes);
   };
   auto one = [&](int q) {
-    if (q < NW) dma16(g.rsW, slot + q * 4096, woff, sW + q * 4096);
+    if (q < NW) dma16<ONCE>(g.rsW, slot + q * 4096, woff, sW + q * 4096);
     else dma16(g.rsX, slot + BOFF + (q - NW) * 4096, xoff[q - NW], sX);
   };
   t.mainloop(g.KS1, begin, one, lds);
@@ -543,6 +556,37 @@ __device__ __forceinline__ void gemm1_setup(G1Args& g, int item_id, const Layout
   g.lds_w = lds_offset(lds) + (uint32_t)(w * 1024);  // this wavefront's 1 KiB slice of each 4 KiB slab
 }
 
+// half a neuron tile: at most 128 rows (the plan guarantees it); wavefronts 0 and 1 multiply, 64 weight rows each
+template <bool PROFILE, bool ONCE>
+__device__ __forceinline__ void gemm1_half_item(const G1Args& g, char* lds, int w) {
+  if (w < 2) {
+    switch ((g.it.nrows + 31) >> 5) {
+      case 1: gemm1_tile<2, 4, 1, PROFILE, 2, true, RingHalf, 2, false, ONCE>(g, lds, w * 64, 0, w); break;
+      case 2: gemm1_tile<2, 4, 2, PROFILE, 2, true, RingHalf, 2, false, ONCE>(g, lds, w * 64, 0, w); break;
+      case 3: gemm1_tile<2, 4, 3, PROFILE, 2, true, RingHalf, 2, false, ONCE>(g, lds, w * 64, 0, w); break;
+      default: gemm1_tile<2, 4, 4, PROFILE, 2, true, RingHalf, 2, false, ONCE>(g, lds, w * 64, 0, w); break;
+    }
+  } else {
+    gemm1_tile<2, 4, 0, PROFILE, 2, true, RingHalf, 2, false, ONCE>(g, lds, 0, 0, w);
+  }
+}
+// a ragged row tile.  4 x 1 wavefronts: 64 weight rows x the ceil(nrows/32) blocks of pair rows that exist
+template <bool PROFILE, bool ONCE>
+__device__ __forceinline__ void gemm1_ragged_item(const G1Args& g, char* lds, int w) {
+#define DSMOE_RAGGED(N) gemm1_tile<2, 8, N, PROFILE, 4, false, RingWhole, (N * 32 + 63) / 64, false, ONCE>(g, lds, w * 64, 0, w)
+  switch ((g.it.nrows + 31) >> 5) {
+    case 1: DSMOE_RAGGED(1); break;
+    case 2: DSMOE_RAGGED(2); break;
+    case 3: DSMOE_RAGGED(3); break;
+    case 4: DSMOE_RAGGED(4); break;
+    case 5: DSMOE_RAGGED(5); break;
+    case 6: DSMOE_RAGGED(6); break;
+    case 7: DSMOE_RAGGED(7); break;
+    default: DSMOE_RAGGED(8); break;
+  }
+#undef DSMOE_RAGGED
+}
+
 // PROFILE = false is the layer's kernel: it stores Swish(gate) * up.  PROFILE = true is the importance
 // profiling pass: it picks the metric at run time (epi 1..4), sums it over the rows of the tile and
 // stores 128 column sums per item instead of the activation.
@@ -556,17 +600,9 @@ __global__ __launch_bounds__(256) void gemm1_mfma_kernel(Layout L, int T, const 
   gemm1_setup(g, item_id, L, T, packed, x, ws, epi, lds, tid, w);
   if (PROFILE && g.sh) return;  // importance is profiled for the routed experts only
 
-  if (g.it.half) {  // at most 128 rows (the plan guarantees it): wavefronts 0 and 1 multiply, 64 weight rows each
-    if (w < 2) {
-      switch ((g.it.nrows + 31) >> 5) {
-        case 1: gemm1_tile<2, 4, 1, PROFILE, 2, true, RingHalf, 2>(g, lds, w * 64, 0, w); break;
-        case 2: gemm1_tile<2, 4, 2, PROFILE, 2, true, RingHalf, 2>(g, lds, w * 64, 0, w); break;
-        case 3: gemm1_tile<2, 4, 3, PROFILE, 2, true, RingHalf, 2>(g, lds, w * 64, 0, w); break;
-        default: gemm1_tile<2, 4, 4, PROFILE, 2, true, RingHalf, 2>(g, lds, w * 64, 0, w); break;
-      }
-    } else {
-      gemm1_tile<2, 4, 0, PROFILE, 2, true, RingHalf, 2>(g, lds, 0, 0, w);
-    }
+  if (g.it.half) {
+    if (!PROFILE && g.it.once) gemm1_half_item<PROFILE, !PROFILE>(g, lds, w);
+    else gemm1_half_item<PROFILE, false>(g, lds, w);
   } else if (!PROFILE && g.it.nrows > kMfmaBM) {  // a full row tile and the expert's last 1..64 rows (the profiling pass plans without them)
     gemm1_tile<4, 4, 4, false, 4, false, RingTall, 5, true>(g, lds, (w >> 1) * 128, (w & 1) * 128, w);
   } else if (g.it.nrows == kMfmaBM) {
@@ -574,17 +610,10 @@ __global__ __launch_bounds__(256) void gemm1_mfma_kernel(Layout L, int T, const 
     // full takes the first 128 weight rows only (64 x 128 per wavefront)
     if (g.Fp - g.it.jt * kMfmaNeur <= kMfmaNeur / 2) gemm1_tile<2, 4, 4, PROFILE, 2>(g, lds, (w >> 1) * 64, (w & 1) * 128, w);
     else gemm1_tile<4, 4, 4, PROFILE>(g, lds, (w >> 1) * 128, (w & 1) * 128, w);
-  } else {  // 4 x 1: 64 weight rows x the ceil(nrows/32) blocks of pair rows that exist
-    switch ((g.it.nrows + 31) >> 5) {
-      case 1: gemm1_tile<2, 8, 1, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 2: gemm1_tile<2, 8, 2, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 3: gemm1_tile<2, 8, 3, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 4: gemm1_tile<2, 8, 4, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 5: gemm1_tile<2, 8, 5, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 6: gemm1_tile<2, 8, 6, PROFILE>(g, lds, w * 64, 0, w); break;
-      case 7: gemm1_tile<2, 8, 7, PROFILE>(g, lds, w * 64, 0, w); break;
-      default: gemm1_tile<2, 8, 8, PROFILE>(g, lds, w * 64, 0, w); break;
-    }
+  } else if (!PROFILE && g.it.once) {
+    gemm1_ragged_item<PROFILE, !PROFILE>(g, lds, w);
+  } else {
+    gemm1_ragged_item<PROFILE, false>(g, lds, w);
   }
 }
 
@@ -597,6 +626,7 @@ struct G2Args {
   char* Y;       // where row 0, column 0 of this item's output tile goes (float, or half precision: YH)
   int ldy;       // its row stride in elements: D in Yp, 256 in a pool tile
   float yscale;  // YH: the accumulators are stored times this power of two (see kYpHalfScale)
+  bool once;     // the item covers its expert's rows: nobody else reads its part of W2
 };
 
 // MFMA A = pair rows of H, B = output columns of W2 (both half precision).
@@ -604,7 +634,8 @@ struct G2Args {
 // TALL: a full row tile that also takes the 1..64 rows of its expert's short last tile (see gemm1_tile): rows
 // 256..319 of the item, one more block of 32 rows per wavefront, times all four of its column blocks or, when
 // there is only one such block, times two of them (the wavefront that shares the columns takes the other two).
-template <int I, int J, int NI, bool NT, bool YH, class RING = RingWhole, bool TALL = false>
+// ONCE: no other item reads this item's part of W2 (the expert has one row tile).
+template <int I, int J, int NI, bool NT, bool YH, class RING = RingWhole, bool TALL = false, bool ONCE = false>
 __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row0, int b_row0, int w) {
   static_assert(!TALL || (I == 4 && J == 4 && NI == 4), "tall tiles: 2 x 2 wavefronts, 320 rows");
   int tid = fresh_tid(w);  // see gemm1_tile
@@ -641,7 +672,7 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
     sW = (uint32_t)(kt * kStageBytes);
   };
   auto one = [&](int q) {
-    if (q < 4) dma16(g.rsW, slot + RING::BOFF + q * 4096, woff, sW + q * 4096);
+    if (q < 4) dma16<ONCE>(g.rsW, slot + RING::BOFF + q * 4096, woff, sW + q * 4096);
     else dma16(g.rsH, slot + (q - 4) * 4096, hoff[q - 4], sH);
   };
   t.mainloop(g.nstages, begin, one, lds);
@@ -727,10 +758,11 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
 }
 
 // What every GEMM-2 workgroup does first (see gemm1_setup).
-__device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout& L, const char* packed, char* ws, const char* lds, int tid,
+__device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout& L, int T, const char* packed, char* ws, const char* lds, int tid,
                                             int w) {
   g.it = ((const Item2*)(ws + L.o_items2))[item_id];
   const bool sh = g.it.e == L.E_res;
+  g.once = g.it.nrows == (sh ? T : ((const int32_t*)(ws + L.o_exp_nrows))[g.it.e]);
   const int Fp = sh ? L.F_shT : L.Fp;
   const int ld = sh ? L.F_shT : L.F;
   const int KT = ld / kBK;  // stages of the whole expert
@@ -760,6 +792,23 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
   for (int p = 0; p < g.np; ++p) g.nstages += ((g.it.kmask >> p) & 1) ? g.it.ks_n : 0;
 }
 
+// a ragged row tile.  1 x 4 wavefronts: the ceil(nrows/32) blocks of pair rows that exist x 64 columns
+template <bool NT, bool YH, bool ONCE>
+__device__ __forceinline__ void gemm2_ragged_item(const G2Args& g, char* lds, int w) {
+#define DSMOE_RAGGED(N) gemm2_tile<8, 2, N, NT, YH, RingWhole, false, ONCE>(g, lds, 0, w * 64, w)
+  switch ((g.it.nrows + 31) >> 5) {
+    case 1: DSMOE_RAGGED(1); break;
+    case 2: DSMOE_RAGGED(2); break;
+    case 3: DSMOE_RAGGED(3); break;
+    case 4: DSMOE_RAGGED(4); break;
+    case 5: DSMOE_RAGGED(5); break;
+    case 6: DSMOE_RAGGED(6); break;
+    case 7: DSMOE_RAGGED(7); break;
+    default: DSMOE_RAGGED(8); break;
+  }
+#undef DSMOE_RAGGED
+}
+
 // NT: the output leaves with non-temporal stores (for outputs far larger than the caches: the
 // combine step reads them from HBM anyway, and the weight and activation tiles keep their place in L2)
 template <bool NT, bool YH>
@@ -769,23 +818,16 @@ __global__ __launch_bounds__(256) void gemm2_mfma_kernel(Layout L, int T, const 
   if (item_id >= ((const int32_t*)(ws + L.o_counters))[1]) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G2Args g;
-  gemm2_setup(g, item_id, L, packed, ws, lds, tid, w);
+  gemm2_setup(g, item_id, L, T, packed, ws, lds, tid, w);
 
   if (g.it.nrows > kMfmaBM) {  // a full row tile and the expert's last 1..64 rows
     gemm2_tile<4, 4, 4, NT, YH, RingTall2, true>(g, lds, (w >> 1) * 128, (w & 1) * 128, w);
   } else if (g.it.nrows == kMfmaBM) {
     gemm2_tile<4, 4, 4, NT, YH>(g, lds, (w >> 1) * 128, (w & 1) * 128, w);  // 2 x 2 wavefronts
-  } else {  // 1 x 4: the ceil(nrows/32) blocks of pair rows that exist x 64 columns
-    switch ((g.it.nrows + 31) >> 5) {
-      case 1: gemm2_tile<8, 2, 1, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 2: gemm2_tile<8, 2, 2, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 3: gemm2_tile<8, 2, 3, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 4: gemm2_tile<8, 2, 4, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 5: gemm2_tile<8, 2, 5, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 6: gemm2_tile<8, 2, 6, NT, YH>(g, lds, 0, w * 64, w); break;
-      case 7: gemm2_tile<8, 2, 7, NT, YH>(g, lds, 0, w * 64, w); break;
-      default: gemm2_tile<8, 2, 8, NT, YH>(g, lds, 0, w * 64, w); break;
-    }
+  } else if (g.once) {
+    gemm2_ragged_item<NT, YH, true>(g, lds, w);
+  } else {
+    gemm2_ragged_item<NT, YH, false>(g, lds, w);
   }
 }
 

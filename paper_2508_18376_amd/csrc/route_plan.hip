@@ -840,7 +840,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     }
     v.e = e;
     v.p = p;
-    v.pad = 0;
+    v.once = ga[gi] == 1 ? 1 : 0;
     for (int jt = part; jt < nt1; jt += S) {
       v.jt = jt;
       // MFMA path, at most 128 rows, a last neuron tile of at most 64 neurons: the half-tile variant of
