@@ -160,3 +160,14 @@ def test_profile_then_partition_then_forward(oracle):
     y_ref = oracle.forward(t["x"], t["logits"], t["w1"], t["w3"], t["w2"], tau, spec.K, spec.P, perm=perm_h)
     assert_output_close(to_host64(y, "bf16"), y_ref, "bf16")
     layer.close()
+
+
+@pytest.mark.parametrize("F", [1, 3, 255, 257, 1001, 1024, 1300])
+def test_perm_at_the_edges_of_the_rank_kernel(oracle, F):
+    """Around the 256 neurons of a workgroup and the 1024 values of a tile, with ties across them."""
+    from paper_2508_18376_amd import DualSparseLayer
+    imp = np.random.default_rng(F).integers(0, max(2, F // 3), (2, F)).astype(np.float32)
+    layer = DualSparseLayer(d_model=32, d_ff=F, n_experts=2, top_k=1, n_part=1, max_tokens=8, dtype="f32")
+    perm = layer.importance_to_perm(to_dev(imp)).cpu().numpy()
+    np.testing.assert_array_equal(perm, oracle.perm_from_importance(imp.astype(np.float64)))
+    layer.close()
