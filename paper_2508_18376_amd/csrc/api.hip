@@ -300,6 +300,10 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
   // tile boundary after the T rows of THIS call (the plan kernel places them there), so the layout
   // every kernel of the call sees carries that boundary, not the one max_tokens would give.
   Layout L = base;
+  // Few rows per expert: the streaming kernels, without tall items.  The line lies where their weight tiles still get half of the
+  // LDS: 512 tokens on 64 experts top-8 (64 pairs each) 184 -> 174 us, 256 on 8 experts of 4096 x 14336 top-2 (64 each) 473 -> 457;
+  // with 88 pairs each the latter layer lost (495 -> 549 us), smaller ones still gained 5 % (700 tokens on the former 186 -> 177).
+  if (L.mfma && (int64_t)T * L.K <= (int64_t)L.E_res * kStreamRows) L.stream = 1, L.tall_tiles = 0;
   L.sh_rows = L.n_shared > 0 ? (int)align_up(T, L.BM) : 0;
   ctx->last_sh_rows = L.sh_rows;
   const float* logits = logits_buf;

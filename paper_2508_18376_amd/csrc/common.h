@@ -41,6 +41,8 @@ inline __host__ __device__ int route_block_tokens(int E, int T) {
 constexpr int kMfmaBM = 256;
 constexpr int kMfmaNeur = 128;
 constexpr int kMfmaBN2 = 256;
+constexpr int kStreamBM = 128;              // rows that a workgroup of the streaming kernels takes ...
+constexpr int kStreamRows = 64;             // ... in batches of at most that many pairs per resident expert on average
 constexpr int kBK = 32;                     // K values per pipeline stage
 constexpr int kChunksPerRow = kBK / 8;      // 16-byte chunks in one tile row
 constexpr int kStageBytes = 256 * kBK * 2;  // one operand tile of one stage (bf16): 16 KiB
@@ -78,6 +80,7 @@ struct Layout {
   int32_t g2_rows_inner;  // GEMM-2 item order: 1 = (expert, column tile, row tile), 0 = (expert, row tile, column tile)
   int32_t tall_tiles;     // MFMA path: a GEMM item of a full row tile may also take the expert's last row tile if that has at most
                           // kTallExtra rows: 0 never, 1 where the plan's estimate says it pays (GEMM-1; always in GEMM-2), 2 wherever possible
+  int32_t stream;       // MFMA path, set per call: the batch takes the streaming kernels
   int32_t split_items;  // GEMM-2 items that fill the chip: the granularity K splits aim at
   // full-precision path: K dimensions padded to whole stages (equal to the unpadded ones on the matrix-core path)
   int32_t Dk, Fpk, Fh, Fsk;  // D; F/P; row length of H (P * Fpk); F_shT

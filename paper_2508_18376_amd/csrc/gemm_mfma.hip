@@ -65,6 +65,18 @@ using RingTall = Ring<kStages, kStageBytes + kTallRows * (kBK * 2), kStageBytes>
 static_assert(RingTall::BYTES <= kLdsBytes, "same allocation");
 // the same for GEMM-2, whose A tile holds the rows: 320 rows of A + 16 KiB B tile
 using RingTall2 = Ring<kStages, kStageBytes + kTallRows * (kBK * 2), kTallRows * (kBK * 2)>;
+// streaming kernels (see gemm1_stream_kernel): a weight tile (16 KiB) or half of one + up to 64 or 128 rows a stage, two
+// workgroups per compute unit
+constexpr int kStreamLds = 80 * 1024;
+template <int SUBS, int NB>  // parts of the weight tile, 32-row blocks
+struct StreamStage {
+  static constexpr int W = kStageBytes / SUBS, X = (NB <= 2 ? 64 : 128) * (kBK * 2);
+  static constexpr int NS = kStreamLds / (W + X) < 8 ? kStreamLds / (W + X) : 8;
+};
+template <int SUBS, int NB, class S = StreamStage<SUBS, NB>>
+using RingStream = Ring<S::NS, S::W + S::X, S::W>;
+template <int SUBS, int NB, class S = StreamStage<SUBS, NB>>
+using RingStream2 = Ring<S::NS, S::W + S::X, S::X>;  // GEMM-2: the rows first
 constexpr int64_t kStreamOutBytes = 192ll << 20;    // GEMM-2 outputs larger than this bypass the caches (256 MiB of last-level cache, shared with H)
 constexpr int kLoadsPerStage = 2 * (kStageBytes / 16 / 256);  // per thread: 4 (A) + 4 (B)
 constexpr uint32_t kRsrcFlags = 0x00020000u;        // raw buffer, 32-bit elements
@@ -143,7 +155,7 @@ struct Frags {
 };
 
 // One wavefront's share of the tile product.
-//   I x J   MFMA blocks (32 x 32) of this wavefront; I * J == 16, or 8 for a tile of half the weight rows.
+//   I x J   MFMA blocks (32 x 32) of this wavefront; I * J == 16, or 8 (4) for a tile of half the weight rows (columns).
 //   NI / NJ: only the first NI (NJ) blocks of that dimension hold rows (ragged tile); the others
 //   are neither read nor multiplied.  They are template parameters, not run-time values: branches
 //   around single MFMAs would push the accumulators out of their registers.
@@ -166,7 +178,7 @@ struct Frags {
 template <int I, int J, int NI, int NJ, int NLOADS, bool SWAP = false, int NS = kStages, int SB = kStagePair, int BOFF = kStageBytes,
           bool F16 = false, bool EX = false>
 struct WaveTile {
-  static_assert(I * J == 16 || I * J == 8, "256 or 128 accumulator registers");
+  static_assert(I * J == 16 || I * J == 8 || I * J == 4, "256, 128 or 64 accumulator registers");
   static_assert(!EX || (I == 4 && J == 4 && NI == I && NJ == J && SWAP == F16), "extra block: full tiles of GEMM-1 (bf16) or GEMM-2 (f16, operands swapped)");
   static constexpr int M = I * J;  // MFMAs per K substep
   static_assert(NLOADS >= 1 && NLOADS <= kLoadsPerStage + (EX ? 1 : 0), "DMA loads per thread and stage");
@@ -247,7 +259,7 @@ struct WaveTile {
         else
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, acc[i][j], 0, 0, 0);
       }
-      if (M == 16) {  // a DMA slot after every second MFMA, or after every one of 8
+      if (M == 16) {  // a DMA slot after every second MFMA, or after every one of 8 or 4
         if (DMA && (m & 1) && (m >> 1) < NLOADS) one(m >> 1);
         if (DMA && m == 0 && NLOADS > 8) one(8);  // the ninth load of a tall tile
       } else {
@@ -469,6 +481,7 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
   // [256 rows][128 neurons] tile (320 rows in a tall tile; rows padded to 272 bytes against bank conflicts), then written
   // out in whole 256-byte row segments: 16 lanes per row, 16 bytes per lane.
   constexpr int kHsRow = kMfmaNeur * 2 + 16;
+  constexpr int kRowsOut = RING::BYTES >= kTallRows * kHsRow ? kTallRows : kStreamBM;  // (the streaming kernels')
   block_barrier();  // every wave is done reading the last stage
   // one block of 32 rows x 32 neurons: gate and up accumulators of weight blocks i and i + 1, pair row r of this lane
   auto emit = [&](const f32x16& gate, const f32x16& up, int r, bool kept, int i) {
@@ -518,7 +531,7 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
     // branch each read would wait for its own LDS round trip), then the stores
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 #pragma unroll 1
-    for (int c0 = 0; c0 < kTallRows / 16; c0 += 4) {  // up to 320 rows: the tile before an expert's short last tile zero-fills that one's rows too
+    for (int c0 = 0; c0 < kRowsOut / 16; c0 += 4) {  // up to 320 rows: the tile before an expert's short last tile zero-fills that one's rows too
       u32x4_t v[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) v[c] = *(const u32x4_t*)(lds + ((c0 + c) * 16 + (tid >> 4)) * kHsRow + (tid & 15) * 16);
@@ -536,8 +549,11 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
 
 // What every GEMM-1 workgroup does first: its item and the buffer descriptors.
 __device__ __forceinline__ void gemm1_setup(G1Args& g, int item_id, const Layout& L, int T, const char* packed, const uint16_t* x, char* ws,
-                                            int epi, const char* lds, int tid, int w) {
+                                            int epi, const char* lds, int tid, int w, int skip_rows = 0) {
   g.it = ((const Item1*)(ws + L.o_items1))[item_id];
+  g.it.row0 += skip_rows;  // (the streaming kernel's second part of an item)
+  g.it.nrows -= skip_rows;
+  g.it.nfill -= skip_rows;
   g.row_bits = (const uint8_t*)(ws + L.o_row_bits);
   g.row_token = (const int32_t*)(ws + L.o_row_token);
   g.x_row_bytes = (uint32_t)(L.D * 2);
@@ -626,6 +642,7 @@ struct G2Args {
   char* Y;       // where row 0, column 0 of this item's output tile goes (float, or half precision: YH)
   int ldy;       // its row stride in elements: D in Yp, 256 in a pool tile
   float yscale;  // YH: the accumulators are stored times this power of two (see kYpHalfScale)
+  int col0;      // first column of this workgroup's part of the item's column tile
   bool once;     // the item covers its expert's rows: nobody else reads its part of W2
 };
 
@@ -635,13 +652,14 @@ struct G2Args {
 // 256..319 of the item, one more block of 32 rows per wavefront, times all four of its column blocks or, when
 // there is only one such block, times two of them (the wavefront that shares the columns takes the other two).
 // ONCE: no other item reads this item's part of W2 (the expert has one row tile).
-template <int I, int J, int NI, bool NT, bool YH, class RING = RingWhole, bool TALL = false, bool ONCE = false>
+// NW: 4 KiB loads per thread and stage for the weight tile (2: half a tile of 128 columns).
+template <int I, int J, int NI, bool NT, bool YH, class RING = RingWhole, bool TALL = false, bool ONCE = false, int NW = 4>
 __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row0, int b_row0, int w) {
   static_assert(!TALL || (I == 4 && J == 4 && NI == 4), "tall tiles: 2 x 2 wavefronts, 320 rows");
   int tid = fresh_tid(w);  // see gemm1_tile
   const int lane = tid & 63;
-  constexpr int NH = TALL ? 5 : I == 8 ? (NI * 32 + 63) / 64 : 4;  // loads per thread and stage for the rows of H (64 rows each)
-  WaveTile<I, J, NI, J, 4 + NH, true, RING::NS, RING::SB, RING::BOFF, true, TALL> t;
+  constexpr int NH = TALL ? 5 : I * J == 16 && I == 4 ? 4 : (NI * 32 + 63) / 64;  // loads per thread and stage for the rows of H (64 rows each)
+  WaveTile<I, J, NI, J, NW + NH, true, RING::NS, RING::SB, RING::BOFF, true, TALL> t;
   const bool two_blocks = g.it.nrows > kMfmaBM + 32;
   const int bx_row0 = kMfmaBM + (two_blocks ? a_row0 >> 2 : 0);
   const int rot = TALL && !two_blocks && a_row0 ? 2 : 0;  // column block of accumulator j: (j + rot) & 3
@@ -669,11 +687,11 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
     }
     slot = (uint32_t)(st % RING::NS) * RING::SB + g.lds_w;
     sH = (uint32_t)(kt * kRowBytes);
-    sW = (uint32_t)(kt * kStageBytes);
+    sW = (uint32_t)(kt * kStageBytes + g.col0 * kRowBytes);
   };
   auto one = [&](int q) {
-    if (q < 4) dma16<ONCE>(g.rsW, slot + RING::BOFF + q * 4096, woff, sW + q * 4096);
-    else dma16(g.rsH, slot + (q - 4) * 4096, hoff[q - 4], sH);
+    if (q < NW) dma16<ONCE>(g.rsW, slot + RING::BOFF + q * 4096, woff, sW + q * 4096);
+    else dma16(g.rsH, slot + (q - NW) * 4096, hoff[q - NW], sH);
   };
   t.mainloop(g.nstages, begin, one, lds);
   tid = fresh_tid(w);  // see gemm1_tile: the epilogue's addresses are worked out after the main loop
@@ -692,7 +710,7 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
   char* mine = lds + w * (RING::BYTES / 4);
   static_assert(32 * kYsRow <= RING::BYTES / 4, "a block of 32 rows fits a wavefront's quarter of the ring");
   block_barrier();  // every wave is done reading the last stage
-  const int cw = g.it.jd * kMfmaBN2 + b_row0 + (le % kLanesRow) * kColsLane;  // first of this lane's columns in the write-out
+  const int cw = g.it.jd * kMfmaBN2 + g.col0 + b_row0 + (le % kLanesRow) * kColsLane;  // first of this lane's columns in the write-out
   // one block of 32 rows: accumulators A[0..nj) (column block (j + rot) & 3 each), first row row_blk of the item
   auto out_block = [&](const f32x16* A, int nj, int row_blk) {
 #pragma unroll
@@ -742,7 +760,7 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
       for (int k = 0; k < kBatch; ++k) {
         const int r = row_blk + (k0 + k) * kRowsPass + le / kLanesRow;
         if (r < g.it.nrows && cw < g.D && cols_here) {
-          f32x4_t* dst = (f32x4_t*)(g.Y + ((size_t)r * g.ldy + b_row0 + (le % kLanesRow) * kColsLane) * kEl);
+          f32x4_t* dst = (f32x4_t*)(g.Y + ((size_t)r * g.ldy + g.col0 + b_row0 + (le % kLanesRow) * kColsLane) * kEl);
           if (NT) __builtin_nontemporal_store(o[k], dst);
           else *dst = o[k];
         }
@@ -759,10 +777,12 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
 
 // What every GEMM-2 workgroup does first (see gemm1_setup).
 __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout& L, int T, const char* packed, char* ws, const char* lds, int tid,
-                                            int w) {
+                                            int w, int skip_rows = 0) {
   g.it = ((const Item2*)(ws + L.o_items2))[item_id];
   const bool sh = g.it.e == L.E_res;
   g.once = g.it.nrows == (sh ? T : ((const int32_t*)(ws + L.o_exp_nrows))[g.it.e]);
+  g.it.row0 += skip_rows;  // (the streaming kernel's second part of an item)
+  g.it.nrows -= skip_rows;
   const int Fp = sh ? L.F_shT : L.Fp;
   const int ld = sh ? L.F_shT : L.F;
   const int KT = ld / kBK;  // stages of the whole expert
@@ -781,10 +801,11 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
     g.Y = ws + L.o_Yp + ((size_t)g.it.row0 * L.D + g.it.jd * kMfmaBN2) * yel;
     g.ldy = L.D;
   } else {  // an extra K range of a split item: a partial-output tile of the pool
-    g.Y = ws + L.o_pool + (size_t)(g.it.split - 1) * kPoolRows * kMfmaBN2 * yel;
+    g.Y = ws + L.o_pool + ((size_t)(g.it.split - 1) * kPoolRows + skip_rows) * kMfmaBN2 * yel;
     g.ldy = kMfmaBN2;
   }
   g.yscale = kYpHalfScale;
+  g.col0 = 0;
   g.h_row_bytes = (uint32_t)(ld * 2);
 
   g.lds_w = lds_offset(lds) + (uint32_t)(w * 1024);
@@ -831,6 +852,108 @@ __global__ __launch_bounds__(256) void gemm2_mfma_kernel(Layout L, int T, const 
   }
 }
 
+// ------------------------------------------------------------------------------------- streaming
+// Batches with few rows per expert only stream weights (Layout::stream): a workgroup takes a weight tile or half of one (64
+// neurons, resp. 128 output columns) under up to kStreamBM rows of an item, with few enough registers and LDS for two
+// workgroups per compute unit.  The kernels above run one per unit: nothing streams while an item starts (list entry, row list,
+// first tiles) or ends, and a few rounds of items of 1 MiB of weights leave the last one mostly empty (333 tokens on 64 + 2
+// experts of 2048 x 1408: 3.2 rounds, units busy 70 % of the time; 278 -> 266 us for the layer, 64 tokens 228 -> 216 us).
+// Workgroups [0, SUBS * items) take the first kStreamBM rows of every item, the next SUBS * items the rows beyond them, if
+// there are any: those sit at the end, where the ones that find nothing to do leave while the last others are still at work.
+template <int SUBS>
+struct StreamPart {
+  int item, sub, row0;  // list entry, part of its weight tile, first row
+  __device__ __forceinline__ StreamPart(int id, int items) {
+    row0 = id >= SUBS * items ? kStreamBM : 0;
+    id -= row0 ? SUBS * items : 0;
+    item = id / SUBS;
+    sub = id % SUBS;
+  }
+};
+
+template <int SUBS, int NB, bool ONCE>
+__device__ __forceinline__ void gemm1_stream_item(const G1Args& g, char* lds, int w) {
+  using R = RingStream<SUBS, NB>;
+  constexpr int NX = (NB * 32 + 63) / 64;
+  if (SUBS == 1) gemm1_tile<2, 4, NB, false, 4, false, R, NX, false, ONCE>(g, lds, w * 64, 0, w);
+  else if (w < 2) gemm1_tile<2, 4, NB, false, 2, true, R, NX, false, ONCE>(g, lds, w * 64, 0, w);
+  else gemm1_tile<2, 4, 0, false, 2, true, R, NX, false, ONCE>(g, lds, 0, 0, w);  // only helps to load
+}
+template <int SUBS, bool ONCE>
+__device__ __forceinline__ void gemm1_stream_rows(const G1Args& g, char* lds, int w) {
+  switch ((g.it.nrows + 31) >> 5) {
+    case 1: gemm1_stream_item<SUBS, 1, ONCE>(g, lds, w); break;
+    case 2: gemm1_stream_item<SUBS, 2, ONCE>(g, lds, w); break;
+    case 3: gemm1_stream_item<SUBS, 3, ONCE>(g, lds, w); break;
+    default: gemm1_stream_item<SUBS, 4, ONCE>(g, lds, w); break;
+  }
+}
+template <int SUBS>
+__global__ __launch_bounds__(256, 2) void gemm1_stream_kernel(Layout L, int T, const char* packed, const uint16_t* x, char* ws) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int items = ((const int32_t*)(ws + L.o_counters))[0];
+  const StreamPart<SUBS> part(xcd_remap(blockIdx.x), items);
+  if (part.item >= items) return;  // past the end of the list
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  G1Args g;
+  gemm1_setup(g, part.item, L, T, packed, x, ws, 0, lds, tid, w, part.row0);
+  if (g.it.nfill <= 0) return;  // no rows in this part
+  // neurons of this workgroup: [n0, n1) of the tile
+  int n0 = part.sub * (kMfmaNeur / SUBS), n1 = n0 + kMfmaNeur / SUBS;
+  if (g.it.half) {  // an item of one half
+    if (part.sub) return;
+    n0 = (g.it.half - 1) * (kMfmaNeur / 2), n1 = n0 + kMfmaNeur / 2;
+  } else if (SUBS == 2) {
+    g.it.half = 1 + part.sub;
+  }
+  n1 = min(n1, g.Fp - g.it.jt * kMfmaNeur);
+  if (n0 >= n1) return;  // a last neuron tile without a second half
+  if (g.it.nrows <= 0) {  // rows of the tile that keep nothing of this partition: zeros
+    const int n = n0 + (tid & 15) * 8;
+    if (n < n1)
+      for (int r = tid >> 4; r < min(g.it.nfill, kStreamBM); r += 16)
+        *(uint4*)(g.H + (size_t)(g.hrow0 + r) * g.ld + (size_t)g.it.p * g.Fp + g.it.jt * kMfmaNeur + n) = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  g.it.nrows = min(g.it.nrows, kStreamBM);
+  g.it.nfill = min(g.it.nfill, kStreamBM);
+  if (SUBS == 1 && g.it.half) {
+    if (g.it.once) gemm1_stream_rows<2, true>(g, lds, w);
+    else gemm1_stream_rows<2, false>(g, lds, w);
+  } else {
+    if (g.it.once) gemm1_stream_rows<SUBS, true>(g, lds, w);
+    else gemm1_stream_rows<SUBS, false>(g, lds, w);
+  }
+}
+
+template <int SUBS, bool YH, bool ONCE>
+__device__ __forceinline__ void gemm2_stream_item(const G2Args& g, char* lds, int w) {
+#define DSMOE_STREAM(N) gemm2_tile<4, 2 / SUBS, N, false, YH, RingStream2<SUBS, N>, false, ONCE, 4 / SUBS>(g, lds, 0, w * (64 / SUBS), w)
+  switch ((g.it.nrows + 31) >> 5) {
+    case 1: DSMOE_STREAM(1); break;
+    case 2: DSMOE_STREAM(2); break;
+    case 3: DSMOE_STREAM(3); break;
+    default: DSMOE_STREAM(4); break;
+  }
+#undef DSMOE_STREAM
+}
+template <int SUBS, bool YH>
+__global__ __launch_bounds__(256, 2) void gemm2_stream_kernel(Layout L, int T, const char* packed, char* ws) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int items = ((const int32_t*)(ws + L.o_counters))[1];
+  const StreamPart<SUBS> part(xcd_remap(blockIdx.x), items);
+  if (part.item >= items) return;  // past the end of the list
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  G2Args g;
+  gemm2_setup(g, part.item, L, T, packed, ws, lds, tid, w, part.row0);
+  if (g.it.nrows <= 0) return;  // no rows in this part
+  g.it.nrows = min(g.it.nrows, kStreamBM);
+  g.col0 = part.sub * (kMfmaBN2 / SUBS);
+  if (g.it.jd * kMfmaBN2 + g.col0 >= L.D) return;  // a last column tile without a second half
+  if (g.once) gemm2_stream_item<SUBS, YH, true>(g, lds, w);
+  else gemm2_stream_item<SUBS, YH, false>(g, lds, w);
+}
+
 static hipError_t set_lds_attr_now() {
   const struct {
     const void* fn;
@@ -840,6 +963,11 @@ static hipError_t set_lds_attr_now() {
       {(const void*)gemm2_mfma_kernel<false, false>, kLdsBytes}, {(const void*)gemm2_mfma_kernel<true, false>, kLdsBytes},
       {(const void*)gemm2_mfma_kernel<false, true>, kLdsBytes},  {(const void*)gemm2_mfma_kernel<true, true>, kLdsBytes},
   };
+  for (const void* fn : {(const void*)gemm1_stream_kernel<1>, (const void*)gemm1_stream_kernel<2>, (const void*)gemm2_stream_kernel<1, false>,
+                         (const void*)gemm2_stream_kernel<1, true>, (const void*)gemm2_stream_kernel<2, false>, (const void*)gemm2_stream_kernel<2, true>}) {
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+    if (e != hipSuccess) return e;
+  }
   for (const auto& k : kernels) {
     hipError_t e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes);
     if (e != hipSuccess) return e;
@@ -851,11 +979,31 @@ static hipError_t set_lds_attr() {
   return once.run(set_lds_attr_now);
 }
 
+// Experts that can have a row (each has one row tile as a rule).
+static int stream_experts(const Layout& L, int T) { return (int64_t)T * L.K < L.E_res ? T * L.K : L.E_res; }
+// Streaming kernels: half weight tiles where that fills two workgroups per compute unit better: when the last round of `items`
+// whole ones would be at most half full.  Otherwise whole tiles: larger pieces and half the activation reads, measured 1 - 6 %
+// faster where both fit (64 tokens on 8 experts of 4096 x 14336, 3.5 rounds of GEMM-1 per unit: 446 against 465 us).  Up
+// to 128 items the plan itself cuts them.  GEMM-2, 333 tokens on 64 + 2 experts of 2048 x 1408 (528 items): 288 us with whole
+// tiles, 265 with halves; 5 tokens (248 items): 100 and 89 us.
+static bool stream_halves(int items) {
+  const int slots = 2 * kSplitItems, rest = items % slots;
+  return items > slots / 4 && rest > 0 && rest <= slots / 2;
+}
+
 // grids are whole chunks of 256 blocks so that the XCD remap is a bijection
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
+  if (L.stream) {
+    const int parts = T > kStreamBM ? 2 : 1;  // an expert has at most T rows
+    const bool halves = stream_halves(stream_experts(L, T) * L.P * L.NT1 + L.NT1_sh);
+    const dim3 grid((parts * (halves ? 2 : 1) * items1_bound(L, T) + 255) & ~255), block(256);
+    if (halves) gemm1_stream_kernel<2><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
+    else gemm1_stream_kernel<1><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
+    return hipGetLastError();
+  }
   const int g1 = (items1_bound(L, T) + 255) & ~255;
   const uint16_t* xp = (const uint16_t*)x;
   if (epi == 0) gemm1_mfma_kernel<false><<<dim3(g1), dim3(256), kLdsBytes, s>>>(L, T, packed, xp, ws, 0);
@@ -867,6 +1015,18 @@ hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* w
   if (T <= 0) return hipSuccess;
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
+  if (L.stream) {
+    const int parts = T > kStreamBM ? 2 : 1;
+    const bool halves = stream_halves((stream_experts(L, T) + shared_tiles(L, T)) * L.ND2);
+    const dim3 grid((parts * (halves ? 2 : 1) * items2_bound(L, T) + 255) & ~255), block(256);
+#define DSMOE_LAUNCH(SUBS, YH) gemm2_stream_kernel<SUBS, YH><<<grid, block, kStreamLds, s>>>(L, T, packed, ws)
+    if (halves && L.yp_half) DSMOE_LAUNCH(2, true);
+    else if (halves) DSMOE_LAUNCH(2, false);
+    else if (L.yp_half) DSMOE_LAUNCH(1, true);
+    else DSMOE_LAUNCH(1, false);
+#undef DSMOE_LAUNCH
+    return hipGetLastError();
+  }
   const int g2 = (items2_bound(L, T) + 255) & ~255;
   // per-pair outputs of this batch, at most; beyond the size of the last-level cache they stream
   const int64_t out_bytes = (int64_t)T * (L.K + (L.n_shared > 0 ? 1 : 0)) * L.D * (L.yp_half ? 2 : 4);
