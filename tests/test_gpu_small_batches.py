@@ -53,3 +53,44 @@ def test_streaming_rows_of_one_expert(oracle, rows, D, Fp):
 def test_streaming_with_whole_and_half_weight_tiles(oracle, E, F):
     # the numbers of items around which whole weight tiles or halves are taken (2 x 2 .. 2 x 3 neuron tiles, 2 column tiles an expert)
     _check(oracle, spec_of(T=300, D=512, F=F, E=E, K=4, P=2, seed=150, n_shared=1, F_sh=96), "rate0.25")
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 96), ("bf16", 320), ("f32", 72), ("f32", 260)])
+@pytest.mark.parametrize("K,n_shared", [(1, 0), (2, 1), (16, 0), (16, 1)])
+def test_combine_with_one_thread_per_slot(oracle, dtype, D, K, n_shared):
+    # one slot to seventeen, column groups that do not fill a workgroup, partial outputs of split K ranges (few row tiles)
+    spec = spec_of(T=3, D=D, F=1024, E=max(K, 2), K=K, P=2, dtype=dtype, n_shared=n_shared, F_sh=256, seed=160, w_std=0.05)
+    _check(oracle, spec, "rate0.25" if K > 1 else 0.0)
+
+
+def test_combine_on_both_sides_of_the_small_batch_line():
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    D, F, E, T = 512, 128, 4, 513  # 64 column groups: 512 tokens still take the small-batch kernel
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=2, n_part=1, max_tokens=T)
+    w = [torch.randn(E, *s, generator=gen, device="cuda:0", dtype=torch.bfloat16) * 0.05 for s in ((D, F), (D, F), (F, D))]
+    layer.partition_weights(*w)
+    x = torch.randn(T, D, generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    logits, tau = torch.randn(T, E, generator=gen, device="cuda:0"), torch.zeros(E, 1, device="cuda:0")
+    y = layer.forward(x, logits, tau)
+    assert torch.equal(layer.forward(x[:512].contiguous(), logits[:512].contiguous(), tau), y[:512])  # the same sums in the same order
+    layer.close()
+
+
+@pytest.mark.parametrize("T", [1, 15, 17, 4096, 4097])
+@pytest.mark.parametrize("D,E", [(64, 3), (320, 40), (2112, 64), (128, 130)])
+def test_router_token_blocks(T, D, E):
+    """Workgroups of 16 and of 32 tokens, tiles of 16 experts, steps of 64 that do not fill every wavefront.  Products of bf16
+    values are exact, the sum of D of them in fp32 errs by at most (D + 16) x 2^-24 of the sum of their magnitudes."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(T + D)
+    layer = DualSparseLayer(d_model=D, d_ff=32, n_experts=E, top_k=2, n_part=1, max_tokens=T)
+    wg = torch.randn(D, E, generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    x = torch.randn(T, D, generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    layer.pack_router(wg)
+    got = layer.router_logits(x).cpu().double()
+    ref, mag = x.cpu().double() @ wg.cpu().double(), x.cpu().double().abs() @ wg.cpu().double().abs()
+    assert bool(((got - ref).abs() <= (D + 16) * 2.0 ** -24 * mag).all())
+    layer.close()
