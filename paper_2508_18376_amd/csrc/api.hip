@@ -329,10 +329,16 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
   } while (0)
   mark(0);
   if (router_packed && err == hipSuccess) err = launch_router(L, T, router_packed, x, const_cast<float*>(logits_buf), s);
-  DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
-                             (int32_t*)(ws + L.o_bin_count), nullptr, s));
-  DSMOE_STEP(2, launch_plan(L, T, ws, s));
-  DSMOE_STEP(3, launch_scatter(L, T, ws, s));
+  if (small_plan(L, T)) {
+    DSMOE_STEP(1, launch_small_plan(L, T, logits, tau, ws, s));
+    mark(2);
+    mark(3);
+  } else {
+    DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
+                               (int32_t*)(ws + L.o_bin_count), nullptr, s));
+    DSMOE_STEP(2, launch_plan(L, T, ws, s));
+    DSMOE_STEP(3, launch_scatter(L, T, ws, s));
+  }
   DSMOE_STEP(4, L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 0, s)
                        : launch_gemm1_full(L, T, (const char*)packed, x, ws, 0, s));
   DSMOE_STEP(5, L.mfma ? launch_gemm2_mfma(L, T, (const char*)packed, ws, s) : launch_gemm2_full(L, T, (const char*)packed, ws, s));

@@ -170,6 +170,9 @@ hipError_t launch_route(const Layout& L, const float* logits, int T, const float
 // cleared by the caller), or the scores themselves (n [T][K], -1 where the expert is not resident; sel == nullptr).
 hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s);
 hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s);
+// small batches: routing, plan and scatter in one launch
+bool small_plan(const Layout& L, int T);
+hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const float* tau, char* ws, hipStream_t s);
 hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s);
 hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, void* y, hipStream_t s);
 // epi: what GEMM-1 stores per (row, neuron): 0 = Swish(gate)*up (the layer), 1..4 = the profiling

@@ -24,10 +24,11 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 struct RouteArgs {
   const float* logits;
   const float* tau;
-  int32_t* idx;
+  int32_t* idx;  // idx, w, keep: may be null (all three)
   float* w;
   uint8_t* keep;
   int32_t* bin_count;    // forward: [blocks][nbins] sort-bin histogram, one row per block (may be null)
+  int bins;              // the sort bins are counted (in LDS, and from there to bin_count unless that is null)
   int32_t* group_count;  // stand-alone: [E*P] kept units per sub-expert (may be null)
   int32_t* sel;          // score histograms, or scores, in place of idx / w / keep (may be null); see launch_route_scores
   float* score;
@@ -54,9 +55,9 @@ __device__ __forceinline__ int keep_bits_of(float n, int e, const RouteArgs& a, 
 // histogram update of one pair into the block's LDS histogram
 __device__ __forceinline__ void count_pair(int32_t* hist, int bits, int e, const RouteArgs& a) {
   if (bits == 0) return;
-  if (a.bin_count) atomicAdd(&hist[(e - a.lo) * a.nsub + sub_of_bits(bits, a.nsub_bits)], 1);
+  if (a.bins) atomicAdd(&hist[(e - a.lo) * a.nsub + sub_of_bits(bits, a.nsub_bits)], 1);
   if (a.group_count) {
-    int32_t* h2 = hist + (a.bin_count ? (a.hi - a.lo) * a.nsub : 0);
+    int32_t* h2 = hist + (a.bins ? (a.hi - a.lo) * a.nsub : 0);
     for (int p = 0; p < a.P; ++p)
       if ((bits >> p) & 1) atomicAdd(&h2[e * a.P + p], 1);
   }
@@ -65,7 +66,9 @@ __device__ __forceinline__ void count_pair(int32_t* hist, int bits, int e, const
 // One pair's results: routing outputs and sort-bin histogram, or its place in the score histograms.  There the bins are
 // spread (two pairs of a wavefront rarely meet in one), while the pair counts of a few experts are not: those are
 // collected in LDS.  (One global atomic per pair on them took 150 us for 32 k pairs over 8 experts.)
-__device__ __forceinline__ void finish_pair(const RouteArgs& a, int32_t* hist, const float* tau, int t, int k, int e, float n, float s) {
+// pairs (may be null): expert << 8 | keep pattern of every pair, in LDS
+__device__ __forceinline__ void finish_pair(const RouteArgs& a, int32_t* hist, int32_t* pairs, const float* tau, int t, int k, int e, float n,
+                                            float s) {
   if (a.sel) {
     int b = (int)floorf(n * (float)kSelBins);
     b = b < 0 ? 0 : (b > kSelBins ? kSelBins : b);
@@ -79,14 +82,17 @@ __device__ __forceinline__ void finish_pair(const RouteArgs& a, int32_t* hist, c
   }
   const int bits = keep_bits_of(n, e, a, tau);
   const size_t o = (size_t)t * a.K + k;
-  a.idx[o] = e;
-  a.w[o] = a.renorm ? n : s;
-  a.keep[o] = (uint8_t)bits;
+  if (a.idx) {
+    a.idx[o] = e;
+    a.w[o] = a.renorm ? n : s;
+    a.keep[o] = (uint8_t)bits;
+  }
+  if (pairs) pairs[o] = e << 8 | bits;
   count_pair(hist, bits, e, a);
 }
 // the block's LDS histogram leaves
 __device__ __forceinline__ void flush_hist(const RouteArgs& a, const int32_t* hist, int threads) {
-  const int nb = a.bin_count ? (a.hi - a.lo) * a.nsub : 0;
+  const int nb = a.bins ? (a.hi - a.lo) * a.nsub : 0;
   for (int i = threadIdx.x; i < a.nhist; i += threads) {
     const int c = hist[i];
     if (i < nb) a.bin_count[(size_t)blockIdx.x * nb + i] = c;  // this block's row of the histogram: no atomics
@@ -96,56 +102,58 @@ __device__ __forceinline__ void flush_hist(const RouteArgs& a, const int32_t* hi
 
 // One lane per token; all E logits of the token live in that lane's registers (E <= EPAD <= 32).
 template <int EPAD, int KMAX>
+__device__ __forceinline__ void route_lane_token(const RouteArgs& a, int t, int32_t* hist, int32_t* pairs) {
+  float l[EPAD];
+#pragma unroll
+  for (int e = 0; e < EPAD; ++e) l[e] = (e < a.E) ? a.logits[(size_t)t * a.E + e] : -INFINITY;
+  float m = l[0];
+#pragma unroll
+  for (int e = 1; e < EPAD; ++e) m = (e < a.E && l[e] > m) ? l[e] : m;
+  float z = 0.f;
+#pragma unroll
+  for (int e = 0; e < EPAD; ++e)
+    if (e < a.E) z += expf(l[e] - m);
+  // Top-K: K rounds of "largest not yet taken"; a later index wins only if strictly larger.
+  float sk[KMAX];
+  int ik[KMAX];
+  unsigned long long taken = 0ull;
+  float sel = 0.f;
+#pragma unroll
+  for (int k = 0; k < KMAX; ++k) {
+    sk[k] = 0.f;
+    ik[k] = 0;
+    if (k < a.K) {
+      float bv = 0.f;
+      int be = -1;
+#pragma unroll
+      for (int e = 0; e < EPAD; ++e) {
+        bool free_e = (e < a.E) && !((taken >> e) & 1ull);
+        if (free_e && (be < 0 || l[e] > bv)) {
+          bv = l[e];
+          be = e;
+        }
+      }
+      taken |= 1ull << be;
+      ik[k] = be;
+      sk[k] = expf(bv - m) / z;  // Eq. 1
+      sel += sk[k];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < KMAX; ++k) {
+    if (k < a.K) {
+      const float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
+      finish_pair(a, hist, pairs, a.tau, t, k, ik[k], n, sk[k]);
+    }
+  }
+}
+template <int EPAD, int KMAX>
 __global__ __launch_bounds__(64) void route_lane_kernel(RouteArgs a) {
   extern __shared__ int32_t hist[];
   for (int i = threadIdx.x; i < a.nhist; i += 64) hist[i] = 0;
   __syncthreads();
   const int t = blockIdx.x * 64 + threadIdx.x;
-  if (t < a.T) {
-    float l[EPAD];
-#pragma unroll
-    for (int e = 0; e < EPAD; ++e) l[e] = (e < a.E) ? a.logits[(size_t)t * a.E + e] : -INFINITY;
-    float m = l[0];
-#pragma unroll
-    for (int e = 1; e < EPAD; ++e) m = (e < a.E && l[e] > m) ? l[e] : m;
-    float z = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPAD; ++e)
-      if (e < a.E) z += expf(l[e] - m);
-    // Top-K: K rounds of "largest not yet taken"; a later index wins only if strictly larger.
-    float sk[KMAX];
-    int ik[KMAX];
-    unsigned long long taken = 0ull;
-    float sel = 0.f;
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      sk[k] = 0.f;
-      ik[k] = 0;
-      if (k < a.K) {
-        float bv = 0.f;
-        int be = -1;
-#pragma unroll
-        for (int e = 0; e < EPAD; ++e) {
-          bool free_e = (e < a.E) && !((taken >> e) & 1ull);
-          if (free_e && (be < 0 || l[e] > bv)) {
-            bv = l[e];
-            be = e;
-          }
-        }
-        taken |= 1ull << be;
-        ik[k] = be;
-        sk[k] = expf(bv - m) / z;  // Eq. 1
-        sel += sk[k];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < KMAX; ++k) {
-      if (k < a.K) {
-        const float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
-        finish_pair(a, hist, a.tau, t, k, ik[k], n, sk[k]);
-      }
-    }
-  }
+  if (t < a.T) route_lane_token<EPAD, KMAX>(a, t, hist, nullptr);
   __syncthreads();
   flush_hist(a, hist, 64);
 }
@@ -165,19 +173,18 @@ __device__ __forceinline__ int row_min(int v) {
   return v;
 }
 
+// The block's tokens t_first ..; clears hist and ends with every thread past its own updates (no barrier after them).
 template <int NCH, int U, int WV>
-__global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
+__device__ __forceinline__ void route_row_tokens(const RouteArgs& a, int t_first, int32_t* hist, float* tau_l, int32_t* pairs) {
   constexpr int kThreads = WV * 64, kTokens = WV * 4 * U, V = NCH * 4;
-  extern __shared__ int32_t hist[];
   for (int i = threadIdx.x; i < a.nhist; i += kThreads) hist[i] = 0;
   // the threshold table is fetched now, together with the logits, not after the scores are known
-  float* tau_l = (float*)(hist + a.nhist);
   if (a.tau)
     for (int i = threadIdx.x; i < a.E * a.P; i += kThreads) tau_l[i] = a.tau[i];
   // (the barrier that publishes hist and tau_l sits right before their first use, after the scores)
   const int r = threadIdx.x & 15, row = threadIdx.x >> 4;  // lane in its row; row in the block (WV * 4 of them)
-  const int t_end = min(a.T, ((int)blockIdx.x + 1) * kTokens);
-  auto token = [&](int u) { return (int)blockIdx.x * kTokens + u * (WV * 4) + row; };
+  const int t_end = min(a.T, t_first + kTokens);
+  auto token = [&](int u) { return t_first + u * (WV * 4) + row; };
   auto expert = [&](int j) { return 64 * (j >> 2) + 4 * r + (j & 3); };
   float l[U][V];
   const bool vec = (a.E & 3) == 0;  // rows of the logits are 16-byte aligned
@@ -286,17 +293,20 @@ __global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
       const int e = expert(j);
       if (e < a.E && rank[u][j] < a.K) {
         const float n = sc[u][j] / ssum[u];  // Sec. 4.1: normalise over the K selected
-        finish_pair(a, hist, tau_l, t, rank[u][j], e, n, sc[u][j]);
+        finish_pair(a, hist, pairs, tau_l, t, rank[u][j], e, n, sc[u][j]);
       }
     }
   }
+}
+template <int NCH, int U, int WV>
+__global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
+  extern __shared__ int32_t hist[];
+  route_row_tokens<NCH, U, WV>(a, (int)blockIdx.x * (WV * 4 * U), hist, (float*)(hist + a.nhist), nullptr);
   __syncthreads();
-  flush_hist(a, hist, kThreads);
+  flush_hist(a, hist, WV * 64);
 }
 
-static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t s) {
-  const int T = a.T;
-  if (T <= 0) return hipSuccess;
+static void set_route_layer(const Layout& L, RouteArgs& a) {
   a.E = L.E;
   a.K = L.K;
   a.P = L.P;
@@ -305,7 +315,13 @@ static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t 
   a.renorm = L.renorm;
   a.nsub = L.nsub;
   a.nsub_bits = L.P < kSubBits ? L.P : kSubBits;
-  a.nhist = a.sel ? L.E : (a.bin_count ? L.nbins : 0) + (a.group_count ? L.E * L.P : 0);
+  a.bins = a.bins || a.bin_count;
+  a.nhist = a.sel ? L.E : (a.bins ? L.nbins : 0) + (a.group_count ? L.E * L.P : 0);
+}
+static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t s) {
+  const int T = a.T;
+  if (T <= 0) return hipSuccess;
+  set_route_layer(L, a);
   const size_t sh = sizeof(int32_t) * (size_t)(a.nhist + L.E * L.P);  // histogram + (row kernel) threshold table
   if (L.E <= 32) {  // few experts: a lane per token, no cross-lane traffic
     dim3 grid((T + 63) / 64), block(64);
@@ -357,6 +373,14 @@ hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int3
 // for the worst case and read their item count from the counters this kernel writes.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanTilesLds = 2048;  // row tiles whose keep patterns fit in the plan kernel's LDS
+constexpr int kSmallPlanTokens = 64;  // tokens that one workgroup routes at once
+
+// the plan kernel's tables (in the order in which it lays them out)
+__host__ __device__ inline size_t plan_lds_bytes(const Layout& L) {
+  const int E_tot = L.E_res + (L.n_shared > 0 ? 1 : 0), NG = E_tot * L.P;
+  const int groups = 2 * (NG + 1) > L.nbins ? 2 * (NG + 1) : L.nbins;  // (a small batch's bin cursors take the place of the groups' counts)
+  return sizeof(int32_t) * (size_t)(L.nbins + 5 * (E_tot + 2) + groups + kPlanThreads + kPlanTilesLds + kPlanTilesLds / 2 + 8);
+}
 
 // exclusive scan of a[0..n) in LDS (n <= 8 * kPlanThreads); returns the total. tmp: kPlanThreads ints.
 // Each thread owns a run of elements; the runs are scanned inside each wavefront with lane shifts
@@ -418,11 +442,26 @@ __device__ int block_excl_scan(int32_t* a, int n, int32_t* tmp) {
   return total;
 }
 
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, char* ws) {
+// LANES: 0: the batch has been routed (its histograms are in the workspace).  Else the workgroups route it themselves, see
+// launch_small_plan: 8 or 32: a lane per token and at most that many experts; 16: sixteen lanes per token, at most 64 experts.
+template <int LANES>
+__global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, char* ws, RouteArgs ra) {
   extern __shared__ int32_t sm[];
-  // 0. column sums of the route kernel's per-block histograms -> bins[] in LDS
   int32_t* bin_count = sm;  // [nbins]
-  {
+  int32_t* pairs = sm + (int)(plan_lds_bytes(L) / sizeof(int32_t));  // LANES: see finish_pair
+  if constexpr (LANES != 0) {
+    if (blockIdx.x != 2) ra.idx = nullptr;  // one workgroup writes the routing results
+    int32_t* mine = blockIdx.x == 2 ? pairs : nullptr;
+    if constexpr (LANES == 16) {
+      route_row_tokens<1, 1, kPlanThreads / 64>(ra, 0, bin_count, (float*)(pairs + T * L.K), mine);
+    } else {
+      for (int i = threadIdx.x; i < L.nbins; i += kPlanThreads) bin_count[i] = 0;
+      __syncthreads();
+      if ((int)threadIdx.x < T) route_lane_token<LANES, (LANES < 16 ? LANES : 16)>(ra, threadIdx.x, bin_count, mine);
+    }
+    __syncthreads();
+  } else {
+    // 0. column sums of the route kernel's per-block histograms -> bins[] in LDS
     const int32_t* blk_hist = (const int32_t*)(ws + L.o_bin_count);
     const int nblk = (T + route_block_tokens(L.E, T) - 1) / route_block_tokens(L.E, T);
     // rows r0, r0 + step, .. of column c, eight independent loads at a time (the sum is latency bound)
@@ -454,8 +493,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     __syncthreads();
   }
   const int tid = threadIdx.x;
-  // Two workgroups: both work out the tables that the lists are made from (row counts, tile patterns, short
-  // last tiles); then workgroup 0 writes the GEMM-2 list and workgroup 1 the GEMM-1 list, side by side.
+  // All workgroups work out the tables that the lists are made from (row counts, tile patterns, short
+  // last tiles); then workgroup 0 writes the GEMM-2 list and workgroup 1 the GEMM-1 list, side by side
+  // (and workgroup 2 of a small batch the row lists).
   const bool lists2 = blockIdx.x == 0, lists1 = !lists2;
   const int E_res = L.E_res;
   const int has_sh = L.n_shared > 0 ? 1 : 0;
@@ -514,8 +554,36 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       exp_row0[e] = rs[e];
     }
   }
+  if (LANES != 0 && blockIdx.x == 2) {  // what the scatter kernel does for larger batches
+    int32_t* pair_row = (int32_t*)(ws + L.o_pair_row);
+    int32_t* row_token = (int32_t*)(ws + L.o_row_token);
+    uint8_t* row_bits = (uint8_t*)(ws + L.o_row_bits);
+    int32_t* next = ga;  // [nbins] next row of every bin
+    for (int b = tid; b < L.nbins; b += kPlanThreads) {
+      const int e = b / L.nsub, sb = b % L.nsub;
+      int off = rs[e];
+      for (int s2 = 0; s2 < sb; ++s2) off += bin_count[e * L.nsub + s2];
+      next[b] = off;
+    }
+    __syncthreads();
+    for (int pr = tid; pr < T * L.K; pr += kPlanThreads) {
+      const int bits = pairs[pr] & 255, e = (pairs[pr] >> 8) - L.lo;
+      int row = -1;
+      if (bits) {
+        row = atomicAdd(&next[e * L.nsub + sub_of_bits(bits, nsub_bits)], 1);
+        row_token[row] = pr / L.K;
+        row_bits[row] = (uint8_t)bits;
+      }
+      pair_row[pr] = row;
+    }
+    if (has_sh && tid < T) {
+      row_token[tid] = tid;
+      row_bits[tid] = 1;
+    }
+    return;
+  }
   // 3. first row of every bin; the scatter kernel's cursors start there
-  if (lists2) {
+  if (lists2 && LANES == 0) {
     for (int b = tid; b < L.nbins; b += kPlanThreads) {
       int e = b / L.nsub, sb = b % L.nsub;
       int off = rs[e];
@@ -525,7 +593,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   }
   // 4. row tiles are described on the fly from the LDS tables (no round trip through global memory):
   //    tile g belongs to the expert at the last position whose first tile is <= g
-  auto tile_expert = [&](int g) {
+  auto find_expert = [&](int g) {
     int lo_i = 0, hi_i = E_tot;  // first position with pt > g
     while (lo_i < hi_i) {
       int mid = (lo_i + hi_i) >> 1;
@@ -557,10 +625,13 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   // step 6 walks the tiles of an expert one after the other and must not redo this for each)
   // (kept in LDS when there are at most kPlanTilesLds tiles, else in the workspace)
   int32_t* tbits = total_tiles <= kPlanTilesLds ? tmp + kPlanThreads : (int32_t*)(ws + L.o_tile_bits);
+  uint16_t* texp = (uint16_t*)(tmp + kPlanThreads + kPlanTilesLds);  // the tiles' experts, where they fit too
   for (int g = tid; g < total_tiles; g += kPlanThreads) {
-    const int e = tile_expert(g);
+    const int e = find_expert(g);
+    if (g < kPlanTilesLds) texp[g] = (uint16_t)e;
     tbits[g] = tile_bits_of(e, g - ts[e]);
   }
+  auto tile_expert = [&](int g) { return g < kPlanTilesLds ? (int)texp[g] : find_expert(g); };
   __shared__ int est[4];  // see "tall GEMM-1 items" below
   if (tid < 4) est[tid] = 0;
   __syncthreads();
@@ -889,17 +960,37 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   if (tid == 0) counters[0] = total_slots;
 }
 
-hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) {
-  const int E_tot = L.E_res + (L.n_shared > 0 ? 1 : 0);
-  const int NG = E_tot * L.P;
-  size_t sh = sizeof(int32_t) * (size_t)(L.nbins + 5 * (E_tot + 2) + 2 * (NG + 1) + kPlanThreads + kPlanTilesLds + 8);
-  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: up to ~78 KB, above what a launch gets without asking
+template <int LANES>
+static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const RouteArgs& ra, hipStream_t s) {
+  size_t sh = plan_lds_bytes(L);
+  if (LANES != 0) sh += sizeof(int32_t) * (size_t)(T * L.K + L.E * L.P);
+  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: up to ~82 KB, above what a launch gets without asking
     static PerDeviceOnce once;
-    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024); });
+    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES>, hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024); });
     if (e != hipSuccess) return e;
   }
-  plan_kernel<<<dim3(2), dim3(kPlanThreads), sh, s>>>(L, T, ws);  // workgroup 0: GEMM-2 list, workgroup 1: GEMM-1 list
+  plan_kernel<LANES><<<dim3(LANES != 0 ? 3 : 2), dim3(kPlanThreads), sh, s>>>(L, T, ws, ra);
   return hipGetLastError();
+}
+hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) { return launch_plan_kernel<0>(L, T, ws, RouteArgs{}, s); }
+
+// Routing, plan and scatter of a small batch in one launch: one workgroup routes 64 tokens at once, so each of three does it
+// for itself and they write the two work lists and the row lists side by side.  1 token on 64 experts: 18 us in three launches ->
+// 14; 64 tokens on 8 experts 24 -> 13; the 8 x 128 x 256 layer on 64 tokens 31 -> 26 us in all.
+bool small_plan(const Layout& L, int T) { return T <= kSmallPlanTokens && L.E <= 64; }
+hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const float* tau, char* ws, hipStream_t s) {
+  RouteArgs a = {};
+  a.logits = logits;
+  a.tau = tau;
+  a.idx = (int32_t*)(ws + L.o_idx);
+  a.w = (float*)(ws + L.o_w);
+  a.keep = (uint8_t*)(ws + L.o_keep);
+  a.bins = 1;
+  a.T = T;
+  set_route_layer(L, a);
+  if (L.E <= 8) return launch_plan_kernel<8>(L, T, ws, a, s);
+  if (L.E <= 32) return launch_plan_kernel<32>(L, T, ws, a, s);
+  return launch_plan_kernel<16>(L, T, ws, a, s);
 }
 
 // ------------------------------------------------------------------------------------- scatter

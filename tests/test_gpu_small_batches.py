@@ -94,3 +94,33 @@ def test_router_token_blocks(T, D, E):
     ref, mag = x.cpu().double() @ wg.cpu().double(), x.cpu().double().abs() @ wg.cpu().double().abs()
     assert bool(((got - ref).abs() <= (D + 16) * 2.0 ** -24 * mag).all())
     layer.close()
+
+
+@pytest.mark.parametrize("T", [1, 63, 64, 65])
+@pytest.mark.parametrize("E,K,P,n_shared,window", [(8, 2, 4, 0, None), (9, 3, 8, 1, (2, 7)), (32, 8, 2, 0, None), (33, 16, 5, 0, (30, 33)),
+                                                   (64, 8, 2, 1, None), (65, 4, 2, 0, None)])
+def test_lists_of_batches_planned_in_one_launch(oracle, T, E, K, P, n_shared, window):
+    # both sides of 64 tokens and of 64 experts, the three ways a workgroup routes (up to 8, 32 and 64 experts)
+    import numpy as np
+    import torch
+    from plan_cover import check_cover
+    spec = spec_of(T=T, D=64, F=64 * P, E=E, K=K, P=P, n_shared=n_shared, F_sh=64, resident=window, seed=170)
+    t = make_layer(spec)
+    tau = resolve_tau(oracle, spec, t, "ragged")
+    r = oracle.route(t["logits"], K, P, tau, spec.lo, spec.hi)
+    layer, dev = make_gpu_layer(spec, t)
+    layer.forward(dev["x"], dev["logits"], to_dev(tau))
+    torch.cuda.synchronize()
+    plan = {k: (v.cpu().numpy() if hasattr(v, "cpu") else v) for k, v in layer.plan(T).items()}
+    layer.close()
+    np.testing.assert_array_equal(plan["topk_idx"], r.idx)
+    np.testing.assert_array_equal(plan["keep_bits"], r.keep_bits)
+    assert np.array_equal(plan["pair_row"] < 0, r.keep_bits == 0)
+    at = plan["pair_row"][r.keep_bits != 0]
+    assert len(np.unique(at)) == len(at)
+    np.testing.assert_array_equal(plan["row_token"][at], np.nonzero(r.keep_bits)[0])
+    np.testing.assert_array_equal(plan["row_bits"][at], r.keep_bits[r.keep_bits != 0])
+    experts = r.idx[r.keep_bits != 0] - spec.lo
+    row0, n = plan["expert_row0"][experts], plan["expert_nrows"][experts]
+    assert np.all((at >= row0) & (at < row0 + n)) and plan["expert_nrows"].sum() == len(at)
+    check_cover(plan, name="small", T=T, D=spec.D, F=spec.F, P=P, E_res=spec.hi - spec.lo, n_shared=n_shared, F_sh=spec.F_sh)
