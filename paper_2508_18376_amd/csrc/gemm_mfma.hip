@@ -643,7 +643,7 @@ struct G2Args {
   int ldy;       // its row stride in elements: D in Yp, 256 in a pool tile
   float yscale;  // YH: the accumulators are stored times this power of two (see kYpHalfScale)
   int col0;      // first column of this workgroup's part of the item's column tile
-  bool once;     // the item covers its expert's rows: nobody else reads its part of W2
+  bool once;     // the expert has one row tile: nobody else reads this part of W2
 };
 
 // MFMA A = pair rows of H, B = output columns of W2 (both half precision).
@@ -780,7 +780,9 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
                                             int w, int skip_rows = 0) {
   g.it = ((const Item2*)(ws + L.o_items2))[item_id];
   const bool sh = g.it.e == L.E_res;
-  g.once = g.it.nrows == (sh ? T : ((const int32_t*)(ws + L.o_exp_nrows))[g.it.e]);
+  const int32_t* multi = (const int32_t*)(ws + L.o_counters) + 5;  // (both words are fetched with the item, before its expert is known)
+  const uint64_t multi_tile = (uint32_t)multi[0] | (uint64_t)(uint32_t)multi[1] << 32;
+  g.once = sh ? T <= kMfmaBM : !((multi_tile >> (g.it.e & 63)) & 1);
   g.it.row0 += skip_rows;  // (the streaming kernel's second part of an item)
   g.it.nrows -= skip_rows;
   const int Fp = sh ? L.F_shT : L.Fp;

@@ -66,28 +66,31 @@ __device__ __forceinline__ void count_pair(int32_t* hist, int bits, int e, const
 // One pair's results: routing outputs and sort-bin histogram, or its place in the score histograms.  There the bins are
 // spread (two pairs of a wavefront rarely meet in one), while the pair counts of a few experts are not: those are
 // collected in LDS.  (One global atomic per pair on them took 150 us for 32 k pairs over 8 experts.)
-// pairs (may be null): expert << 8 | keep pattern of every pair, in LDS
+// MODE: what becomes of the pairs (decided outside the kernels: a branch per pair cost the large batches 1 us)
+enum { kRoute, kScores, kRouteInLds };
+// pairs (kRouteInLds; may be null): expert << 8 | keep pattern of every pair, in LDS
+template <int MODE>
 __device__ __forceinline__ void finish_pair(const RouteArgs& a, int32_t* hist, int32_t* pairs, const float* tau, int t, int k, int e, float n,
                                             float s) {
-  if (a.sel) {
+  if (MODE == kScores && a.sel) {
     int b = (int)floorf(n * (float)kSelBins);
     b = b < 0 ? 0 : (b > kSelBins ? kSelBins : b);
     atomicAdd(&a.sel[(size_t)e * kSelRow + b], 1);
     atomicAdd(&hist[e], 1);
     return;
   }
-  if (a.score) {
+  if (MODE == kScores) {
     a.score[(size_t)t * a.K + k] = e >= a.lo && e < a.hi ? n : -1.f;
     return;
   }
   const int bits = keep_bits_of(n, e, a, tau);
   const size_t o = (size_t)t * a.K + k;
-  if (a.idx) {
+  if (MODE == kRoute || a.idx) {
     a.idx[o] = e;
     a.w[o] = a.renorm ? n : s;
     a.keep[o] = (uint8_t)bits;
   }
-  if (pairs) pairs[o] = e << 8 | bits;
+  if (MODE == kRouteInLds && pairs) pairs[o] = e << 8 | bits;
   count_pair(hist, bits, e, a);
 }
 // the block's LDS histogram leaves
@@ -101,7 +104,7 @@ __device__ __forceinline__ void flush_hist(const RouteArgs& a, const int32_t* hi
 }
 
 // One lane per token; all E logits of the token live in that lane's registers (E <= EPAD <= 32).
-template <int EPAD, int KMAX>
+template <int EPAD, int KMAX, int MODE>
 __device__ __forceinline__ void route_lane_token(const RouteArgs& a, int t, int32_t* hist, int32_t* pairs) {
   float l[EPAD];
 #pragma unroll
@@ -143,17 +146,17 @@ __device__ __forceinline__ void route_lane_token(const RouteArgs& a, int t, int3
   for (int k = 0; k < KMAX; ++k) {
     if (k < a.K) {
       const float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
-      finish_pair(a, hist, pairs, a.tau, t, k, ik[k], n, sk[k]);
+      finish_pair<MODE>(a, hist, pairs, a.tau, t, k, ik[k], n, sk[k]);
     }
   }
 }
-template <int EPAD, int KMAX>
+template <int EPAD, int KMAX, int MODE>
 __global__ __launch_bounds__(64) void route_lane_kernel(RouteArgs a) {
   extern __shared__ int32_t hist[];
   for (int i = threadIdx.x; i < a.nhist; i += 64) hist[i] = 0;
   __syncthreads();
   const int t = blockIdx.x * 64 + threadIdx.x;
-  if (t < a.T) route_lane_token<EPAD, KMAX>(a, t, hist, nullptr);
+  if (t < a.T) route_lane_token<EPAD, KMAX, MODE>(a, t, hist, nullptr);
   __syncthreads();
   flush_hist(a, hist, 64);
 }
@@ -174,7 +177,7 @@ __device__ __forceinline__ int row_min(int v) {
 }
 
 // The block's tokens t_first ..; clears hist and ends with every thread past its own updates (no barrier after them).
-template <int NCH, int U, int WV>
+template <int NCH, int U, int WV, int MODE>
 __device__ __forceinline__ void route_row_tokens(const RouteArgs& a, int t_first, int32_t* hist, float* tau_l, int32_t* pairs) {
   constexpr int kThreads = WV * 64, kTokens = WV * 4 * U, V = NCH * 4;
   for (int i = threadIdx.x; i < a.nhist; i += kThreads) hist[i] = 0;
@@ -293,15 +296,15 @@ __device__ __forceinline__ void route_row_tokens(const RouteArgs& a, int t_first
       const int e = expert(j);
       if (e < a.E && rank[u][j] < a.K) {
         const float n = sc[u][j] / ssum[u];  // Sec. 4.1: normalise over the K selected
-        finish_pair(a, hist, pairs, tau_l, t, rank[u][j], e, n, sc[u][j]);
+        finish_pair<MODE>(a, hist, pairs, tau_l, t, rank[u][j], e, n, sc[u][j]);
       }
     }
   }
 }
-template <int NCH, int U, int WV>
+template <int NCH, int U, int WV, int MODE>
 __global__ __launch_bounds__(WV * 64) void route_row_kernel(RouteArgs a) {
   extern __shared__ int32_t hist[];
-  route_row_tokens<NCH, U, WV>(a, (int)blockIdx.x * (WV * 4 * U), hist, (float*)(hist + a.nhist), nullptr);
+  route_row_tokens<NCH, U, WV, MODE>(a, (int)blockIdx.x * (WV * 4 * U), hist, (float*)(hist + a.nhist), nullptr);
   __syncthreads();
   flush_hist(a, hist, WV * 64);
 }
@@ -318,6 +321,7 @@ static void set_route_layer(const Layout& L, RouteArgs& a) {
   a.bins = a.bins || a.bin_count;
   a.nhist = a.sel ? L.E : (a.bins ? L.nbins : 0) + (a.group_count ? L.E * L.P : 0);
 }
+template <int MODE>
 static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t s) {
   const int T = a.T;
   if (T <= 0) return hipSuccess;
@@ -325,21 +329,21 @@ static hipError_t launch_route_kernel(const Layout& L, RouteArgs a, hipStream_t 
   const size_t sh = sizeof(int32_t) * (size_t)(a.nhist + L.E * L.P);  // histogram + (row kernel) threshold table
   if (L.E <= 32) {  // few experts: a lane per token, no cross-lane traffic
     dim3 grid((T + 63) / 64), block(64);
-    if (L.E <= 8) route_lane_kernel<8, 8><<<grid, block, sh, s>>>(a);
-    else if (L.E <= 16) route_lane_kernel<16, 16><<<grid, block, sh, s>>>(a);
-    else route_lane_kernel<32, 16><<<grid, block, sh, s>>>(a);
+    if (L.E <= 8) route_lane_kernel<8, 8, MODE><<<grid, block, sh, s>>>(a);
+    else if (L.E <= 16) route_lane_kernel<16, 16, MODE><<<grid, block, sh, s>>>(a);
+    else route_lane_kernel<32, 16, MODE><<<grid, block, sh, s>>>(a);
   } else if (T > kWaveSmallBatch) {  // many experts: sixteen lanes per token, 64 tokens per block
     dim3 grid((T + kRouteBlockTokens - 1) / kRouteBlockTokens);
-    if (L.E <= 64) route_row_kernel<1, 1, 16><<<grid, dim3(1024), sh, s>>>(a);
-    else if (L.E <= 128) route_row_kernel<2, 1, 16><<<grid, dim3(1024), sh, s>>>(a);
-    else if (L.E <= 256) route_row_kernel<4, 1, 16><<<grid, dim3(1024), sh, s>>>(a);
-    else route_row_kernel<8, 1, 16><<<grid, dim3(1024), sh, s>>>(a);
+    if (L.E <= 64) route_row_kernel<1, 1, 16, MODE><<<grid, dim3(1024), sh, s>>>(a);
+    else if (L.E <= 128) route_row_kernel<2, 1, 16, MODE><<<grid, dim3(1024), sh, s>>>(a);
+    else if (L.E <= 256) route_row_kernel<4, 1, 16, MODE><<<grid, dim3(1024), sh, s>>>(a);
+    else route_row_kernel<8, 1, 16, MODE><<<grid, dim3(1024), sh, s>>>(a);
   } else {  // small batch: 16 tokens per block, one per row of four wavefronts
     dim3 grid((T + kWaveBlockTokens - 1) / kWaveBlockTokens), block(256);
-    if (L.E <= 64) route_row_kernel<1, 1, 4><<<grid, block, sh, s>>>(a);
-    else if (L.E <= 128) route_row_kernel<2, 1, 4><<<grid, block, sh, s>>>(a);
-    else if (L.E <= 256) route_row_kernel<4, 1, 4><<<grid, block, sh, s>>>(a);
-    else route_row_kernel<8, 1, 4><<<grid, block, sh, s>>>(a);
+    if (L.E <= 64) route_row_kernel<1, 1, 4, MODE><<<grid, block, sh, s>>>(a);
+    else if (L.E <= 128) route_row_kernel<2, 1, 4, MODE><<<grid, block, sh, s>>>(a);
+    else if (L.E <= 256) route_row_kernel<4, 1, 4, MODE><<<grid, block, sh, s>>>(a);
+    else route_row_kernel<8, 1, 4, MODE><<<grid, block, sh, s>>>(a);
   }
   return hipGetLastError();
 }
@@ -355,7 +359,7 @@ hipError_t launch_route(const Layout& L, const float* logits, int T, const float
   a.bin_count = bin_count;
   a.group_count = group_count;
   a.T = T;
-  return launch_route_kernel(L, a, s);
+  return launch_route_kernel<kRoute>(L, a, s);
 }
 
 hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s) {
@@ -364,7 +368,7 @@ hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int3
   a.sel = sel;
   a.score = n;
   a.T = T;
-  return launch_route_kernel(L, a, s);
+  return launch_route_kernel<kScores>(L, a, s);
 }
 
 // ------------------------------------------------------------------------------------- plan
@@ -453,11 +457,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     if (blockIdx.x != 2) ra.idx = nullptr;  // one workgroup writes the routing results
     int32_t* mine = blockIdx.x == 2 ? pairs : nullptr;
     if constexpr (LANES == 16) {
-      route_row_tokens<1, 1, kPlanThreads / 64>(ra, 0, bin_count, (float*)(pairs + T * L.K), mine);
+      route_row_tokens<1, 1, kPlanThreads / 64, kRouteInLds>(ra, 0, bin_count, (float*)(pairs + T * L.K), mine);
     } else {
       for (int i = threadIdx.x; i < L.nbins; i += kPlanThreads) bin_count[i] = 0;
       __syncthreads();
-      if ((int)threadIdx.x < T) route_lane_token<LANES, (LANES < 16 ? LANES : 16)>(ra, threadIdx.x, bin_count, mine);
+      if ((int)threadIdx.x < T) route_lane_token<LANES, (LANES < 16 ? LANES : 16), kRouteInLds>(ra, threadIdx.x, bin_count, mine);
     }
     __syncthreads();
   } else {
@@ -736,12 +740,18 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     if (L.tall_tiles && nt >= 2 && ne[e] - (nt - 1) * BM <= kTallExtra) s = (tbits[ts[e] + nt - 1] & ~tbits[ts[e] + nt - 2]) == 0 ? 1 : 0;
     abp[i] = s;
   }
+  __shared__ int32_t multi_tile[2];  // bit e & 63: some expert e has more than one row tile
   __shared__ int first_split_tile;  // first row tile (in row order) that has a split item: the combine kernel looks no tile before it up
   if (tid == 0) {
     abp[E_tot] = 0;
     first_split_tile = total_tiles;
+    multi_tile[0] = multi_tile[1] = 0;
   }
   __syncthreads();  // the sums of the pricing pass are complete too
+  if (lists2) {
+    for (int e = tid; e < E_res; e += kPlanThreads)
+      if (ne[e] > BM) atomicOr(&multi_tile[(e >> 5) & 1], 1 << (e & 31));
+  }
   if (price_lists) {
     const int units = max(L.split_items, 1);
     const float t0 = est[0] > 0 ? (float)((est[0] + units - 1) / units) * (float)est[1] / (float)est[0] : 0.f;
@@ -834,6 +844,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       counters[2] = total_tiles - total_short;  // row tiles that have GEMM-2 items
       counters[3] = nsplit;
       counters[4] = first_split_tile;
+      counters[5] = multi_tile[0];
+      counters[6] = multi_tile[1];
     }
     return;
   }
