@@ -58,12 +58,15 @@ __device__ __forceinline__ int xcd_run(int b) {  // runs of 32 consecutive items
   return (chunk << 8) + ((within & 7) << 5) + (within >> 3);
 }
 
-// One tile product: 128 weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
-template <int WE, int XE, int NJ>
+// One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
+// SUBS = 2: two wavefronts share 32 weight rows; each multiplies one half of every stage's K values, and the sums meet in
+// the first one (w < 2) at the end.
+template <int WE, int XE, int NJ, int SUBS>
 struct FullTile {
   static constexpr int WR = kBK * WE, XR = kBK * XE;           // bytes of a tile row
   static constexpr int WCH = WR / 16, XCH = XR / 16;           // 16-byte chunks of a row
-  static constexpr int NW = 128 * WR / 4096;                   // 4 KiB loads of the weight tile per stage
+  static constexpr int WROWS = 128 / SUBS;
+  static constexpr int NW = WROWS * WR / 4096;                 // 4 KiB loads of the weight tile per stage
   static constexpr int XROWS = XE == 2 ? (NJ + 1) / 2 * 64 : NJ * 32;
   static constexpr int NX = XROWS * XR / 4096;
   static constexpr int NL = NW + NX;
@@ -112,15 +115,38 @@ struct FullTile {
       asm volatile("s_barrier" ::: "memory");
       multiply(lds + (st % NS) * SB, w, lane);
     }
+    if constexpr (SUBS == 2) {
+      asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
+      f32x4* part = (f32x4*)const_cast<char*>(lds) + (w & 1) * (NJ * 256) + lane;  // [4 NJ][64 lanes]
+      if (w >= 2) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) part[(j * 4 + q) * 64] = f32x4{acc[j][q * 4], acc[j][q * 4 + 1], acc[j][q * 4 + 2], acc[j][q * 4 + 3]};
+      }
+      __syncthreads();
+      if (w < 2) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 o = part[(j * 4 + q) * 64];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[j][q * 4 + c] += o[c];
+          }
+      }
+    }
   }
 
   __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
     const int r32 = lane & 31, h = lane >> 5;
-    const char* wrow = stage + (w * 32 + r32) * WR;
+    const int k0 = SUBS == 2 ? w >> 1 : 0;  // this wavefront's half of the stage
+    const char* wrow = stage + (w % (4 / SUBS) * 32 + r32) * WR;
     const char* xrow = stage + NW * 4096 + r32 * XR;
     if constexpr (WE == 4) {  // fp32 x fp32: chunk 2s + h of a row holds K values 8s + 4h .. 8s + 4h + 3
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
+      for (int s0 = 0; s0 < 4 / SUBS; ++s0) {
+        const int s = s0 + k0 * 2;
         const f32x4 a = *(const f32x4*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
         f32x4 b[NJ];
 #pragma unroll
@@ -132,7 +158,8 @@ struct FullTile {
       }
     } else if constexpr (XE == 2) {  // bf16 x bf16: K values 16s + 8h .. 16s + 8h + 7
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s0 = 0; s0 < 2 / SUBS; ++s0) {
+        const int s = s0 + k0;
         const bf16x8 a = *(const bf16x8*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
@@ -142,7 +169,8 @@ struct FullTile {
       }
     } else {  // bf16 weights x fp32 activations
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s0 = 0; s0 < 2 / SUBS; ++s0) {
+        const int s = s0 + k0;
         const bf16x8 a = *(const bf16x8*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
@@ -180,18 +208,18 @@ struct FullTile {
 };
 
 // ------------------------------------------------------------------------------------- GEMM-1
-template <typename T, int NJ>
-__device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it, const char* packed, const char* x, int64_t x_row, char* ws, int epi,
-                                                char* lds, int w, int lane) {
+template <typename T, int NJ, int SUBS>
+__device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it, int sub, const char* packed, const char* x, int64_t x_row, char* ws,
+                                                int epi, char* lds, int w, int lane) {
   constexpr int E = sizeof(T);
-  using Tile = FullTile<E, E, NJ>;
+  using Tile = FullTile<E, E, NJ, SUBS>;
   const int tid = w * 64 + lane;
   const bool sh = it.e == L.E_res;
   const int Fpk = sh ? L.Fsk : L.Fpk, ld = sh ? L.Fsk : L.Fh, NT1 = sh ? L.NT1_sh : L.NT1;
   const int KS = L.Dk / kBK;
   const int32_t* row_token = (const int32_t*)(ws + L.o_row_token) + it.row0;
   const uint8_t* row_bits = (const uint8_t*)(ws + L.o_row_bits) + it.row0;
-  const char* wsrc = packed + (sh ? L.p_sw13 : L.p_w13) + (((int64_t)(sh ? 0 : it.e * L.P + it.p) * NT1 + it.jt) * KS) * (128 * Tile::WR) + tid * 16;
+  const char* wsrc = packed + (sh ? L.p_sw13 : L.p_w13) + (((int64_t)(sh ? 0 : it.e * L.P + it.p) * NT1 + it.jt) * KS) * (128 * Tile::WR) + sub * (Tile::WROWS * Tile::WR) + tid * 16;
   const char* rowp[Tile::NX];
 #pragma unroll
   for (int i = 0; i < Tile::NX; ++i) {
@@ -209,7 +237,8 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
   // acc[j][v]: weight row 8*(v/4) + 4*h + v%4 of the wavefront's 32 (16 gate rows, then the 16 up rows of the same
   // neurons), pair row j*32 + lane%32
   float* H = (float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld + (size_t)it.p * Fpk;
-  const int n0 = it.jt * kFullNeur + w * 16 + (lane >> 5) * 4;
+  if (SUBS == 2 && w >= 2) return;
+  const int n0 = it.jt * kFullNeur + sub * (kFullNeur / SUBS) + w * 16 + (lane >> 5) * 4;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int r = j * 32 + (lane & 31);
@@ -229,32 +258,34 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
   }
 }
 
-template <typename T>
+template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm1_full_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_run(blockIdx.x);
-  if (id >= ((const int32_t*)(ws + L.o_counters))[0]) return;
-  const Item1 it = ((const Item1*)(ws + L.o_items1))[id];
+  const int id = xcd_run(blockIdx.x), sub = id % SUBS;
+  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[0]) return;
+  const Item1 it = ((const Item1*)(ws + L.o_items1))[id / SUBS];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define DSMOE_ROWS(N) gemm1_full_tile<T, N, SUBS>(L, it, sub, packed, x, x_row, ws, epi, lds, w, lane)
   switch ((it.nrows + 31) >> 5) {
-    case 1: gemm1_full_tile<T, 1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-    case 2: gemm1_full_tile<T, 2>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-    case 3: gemm1_full_tile<T, 3>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-    default: gemm1_full_tile<T, 4>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 1: DSMOE_ROWS(1); break;
+    case 2: DSMOE_ROWS(2); break;
+    case 3: DSMOE_ROWS(3); break;
+    default: DSMOE_ROWS(4); break;
   }
+#undef DSMOE_ROWS
 }
 
 // ------------------------------------------------------------------------------------- GEMM-2
-template <typename T, int NJ>
-__device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it, const char* packed, char* ws, char* lds, int w, int lane) {
+template <typename T, int NJ, int SUBS>
+__device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it, int sub, const char* packed, char* ws, char* lds, int w, int lane) {
   constexpr int E = sizeof(T);
-  using Tile = FullTile<E, 4, NJ>;
+  using Tile = FullTile<E, 4, NJ, SUBS>;
   const int tid = w * 64 + lane;
   const bool sh = it.e == L.E_res;
   const int ld = sh ? L.Fsk : L.Fh;
   const int KSp = (sh ? L.Fsk : L.Fpk) / kBK, np = sh ? 1 : L.P;  // stages of one partition, partitions
   const float* H = (const float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld;
-  const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.ND2 + it.jd) * (np * KSp) * (128 * Tile::WR) + tid * 16;
+  const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.ND2 + it.jd) * (np * KSp) * (128 * Tile::WR) + sub * (Tile::WROWS * Tile::WR) + tid * 16;
   const char* rowp[Tile::NX];
 #pragma unroll
   for (int i = 0; i < Tile::NX; ++i) {
@@ -288,7 +319,8 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
     Y = (float*)(ws + L.o_pool) + (size_t)(it.split - 1) * L.pool_rows * kFullBN2;
     ldy = kFullBN2;
   }
-  const int c0 = w * 32 + (lane >> 5) * 4, d0 = it.jd * kFullBN2 + c0;
+  if (SUBS == 2 && w >= 2) return;
+  const int c0 = sub * (kFullBN2 / SUBS) + w * 32 + (lane >> 5) * 4, d0 = it.jd * kFullBN2 + c0;
   const bool vec = (L.D & 3) == 0;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
@@ -308,19 +340,21 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
   }
 }
 
-template <typename T>
+template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_run(blockIdx.x);
-  if (id >= ((const int32_t*)(ws + L.o_counters))[1]) return;
-  const Item2 it = ((const Item2*)(ws + L.o_items2))[id];
+  const int id = xcd_run(blockIdx.x), sub = id % SUBS;
+  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[1]) return;
+  const Item2 it = ((const Item2*)(ws + L.o_items2))[id / SUBS];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define DSMOE_ROWS(N) gemm2_full_tile<T, N, SUBS>(L, it, sub, packed, ws, lds, w, lane)
   switch ((it.nrows + 31) >> 5) {
-    case 1: gemm2_full_tile<T, 1>(L, it, packed, ws, lds, w, lane); break;
-    case 2: gemm2_full_tile<T, 2>(L, it, packed, ws, lds, w, lane); break;
-    case 3: gemm2_full_tile<T, 3>(L, it, packed, ws, lds, w, lane); break;
-    default: gemm2_full_tile<T, 4>(L, it, packed, ws, lds, w, lane); break;
+    case 1: DSMOE_ROWS(1); break;
+    case 2: DSMOE_ROWS(2); break;
+    case 3: DSMOE_ROWS(3); break;
+    default: DSMOE_ROWS(4); break;
   }
+#undef DSMOE_ROWS
 }
 
 // x with every row at the start of a 16-byte group and zeros up to a multiple of 32 values: made where the layer's width or
@@ -337,14 +371,21 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* x, T* out, int D
 static hipError_t set_lds_attr() {
   static PerDeviceOnce once;
   return once.run([] {
-    for (const void* fn : {(const void*)gemm1_full_kernel<float>, (const void*)gemm1_full_kernel<uint16_t>, (const void*)gemm2_full_kernel<float>,
-                           (const void*)gemm2_full_kernel<uint16_t>}) {
+    for (const void* fn : {(const void*)gemm1_full_kernel<float, 1>, (const void*)gemm1_full_kernel<float, 2>, (const void*)gemm1_full_kernel<uint16_t, 1>,
+                           (const void*)gemm1_full_kernel<uint16_t, 2>, (const void*)gemm2_full_kernel<float, 1>, (const void*)gemm2_full_kernel<float, 2>,
+                           (const void*)gemm2_full_kernel<uint16_t, 1>, (const void*)gemm2_full_kernel<uint16_t, 2>}) {
       hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFullLds);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   });
 }
+
+// Workgroups that share a weight tile.  With a few rows per expert the kernels stream weights in items that are too few or too
+// long for the chip, and two halves are better: 64 tokens on 8 experts of 128 x 256 (16 pairs each) 27.0 -> 24.2 us, 16 tokens
+// top-8 on 64 experts of 2048 x 1024 in fp32 280 -> 265, 100 top-6 on 64 + 2 of 2048 x 1408 in parts of 176 319 -> 305.  Beyond,
+// the rows are read twice for nothing: 300 tokens (37 pairs each) on the former 390 -> 414 us, 400 on the latter 335 -> 354.
+static int full_parts(const Layout& L, int T) { return (int64_t)T * L.K <= (int64_t)L.E_res * 16 ? 2 : 1; }
 
 hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
   if (T <= 0) return hipSuccess;
@@ -363,9 +404,14 @@ hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const v
     xs = ws + L.o_Yp;
     x_row = L.Dk * elem;
   }
-  const dim3 block(256), grid((items1_bound(L, T) + 255) & ~255);  // whole chunks of 256: the XCD order is a bijection on them
-  if (elem == 4) gemm1_full_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
-  else gemm1_full_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
+  const int subs = full_parts(L, T);
+  const dim3 block(256), grid((subs * items1_bound(L, T) + 255) & ~255);  // whole chunks of 256: the XCD order is a bijection on them
+#define DSMOE_LAUNCH(TYPE, SUBS) gemm1_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi)
+  if (elem == 4 && subs == 2) DSMOE_LAUNCH(float, 2);
+  else if (elem == 4) DSMOE_LAUNCH(float, 1);
+  else if (subs == 2) DSMOE_LAUNCH(uint16_t, 2);
+  else DSMOE_LAUNCH(uint16_t, 1);
+#undef DSMOE_LAUNCH
   return hipGetLastError();
 }
 
@@ -373,9 +419,14 @@ hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* w
   if (T <= 0) return hipSuccess;
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
-  const dim3 block(256), grid((items2_bound(L, T) + 255) & ~255);
-  if (L.dtype == DSMOE_F32) gemm2_full_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, ws);
-  else gemm2_full_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, ws);
+  const int subs = full_parts(L, T);
+  const dim3 block(256), grid((subs * items2_bound(L, T) + 255) & ~255);
+#define DSMOE_LAUNCH(TYPE, SUBS) gemm2_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, ws)
+  if (L.dtype == DSMOE_F32 && subs == 2) DSMOE_LAUNCH(float, 2);
+  else if (L.dtype == DSMOE_F32) DSMOE_LAUNCH(float, 1);
+  else if (subs == 2) DSMOE_LAUNCH(uint16_t, 2);
+  else DSMOE_LAUNCH(uint16_t, 1);
+#undef DSMOE_LAUNCH
   return hipGetLastError();
 }
 

@@ -124,3 +124,13 @@ def test_lists_of_batches_planned_in_one_launch(oracle, T, E, K, P, n_shared, wi
     row0, n = plan["expert_row0"][experts], plan["expert_nrows"][experts]
     assert np.all((at >= row0) & (at < row0 + n)) and plan["expert_nrows"].sum() == len(at)
     check_cover(plan, name="small", T=T, D=spec.D, F=spec.F, P=P, E_res=spec.hi - spec.lo, n_shared=n_shared, F_sh=spec.F_sh)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,E", [(1, 1), (16, 1), (17, 1), (33, 8), (70, 8), (100, 8), (128, 8), (129, 8)])
+def test_full_precision_halves_of_weight_tiles(oracle, rows, E, dtype):
+    # both sides of 16 pairs per expert on average; one to four blocks of 32 rows under half a weight tile; the last neuron tile
+    # of a partition (44 of 64 neurons, 12 of 64) and the last column tile (136 of 2 x 128) end inside one of the halves
+    for F in (88, 152):
+        _check(oracle, spec_of(T=rows, D=136, F=F, E=E, K=1, P=2, dtype=dtype, n_shared=1, F_sh=40, seed=180 + rows, w_std=0.05), 0.0,
+               to_expert_0=rows if E > 1 else 0)
