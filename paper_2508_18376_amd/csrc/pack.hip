@@ -25,8 +25,15 @@
 
 namespace dsmoe {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 load_once(const void* p) {  // non-temporal
+  const u32x4 v = __builtin_nontemporal_load((const u32x4*)p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out.  One read of W2,
-// bound by HBM: four 16-byte loads in flight per thread.
+// bound by HBM: four 16-byte loads in flight per thread, non-temporal, and one atomic per workgroup (all on one address).
+// 0.94 GB: 205 us with plain loads and an atomic per wavefront -> 160.
 __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int64_t n, uint32_t* out) {
   uint32_t m = 0;
   auto one = [&](uint32_t a) { m = a < 0x7f80u && a > m ? a : m; };
@@ -37,7 +44,7 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
     for (; i + 3 * step + 8 <= n; i += 4 * step) {
       uint4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *(const uint4*)(w + i + u * step);
+      for (int u = 0; u < 4; ++u) v[u] = load_once(w + i + u * step);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const uint32_t d[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
@@ -52,7 +59,13 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
   for (; i < n; i += step)
     for (int64_t k = i; k < n && k < i + 8; ++k) one(w[k] & 0x7fffu);
   for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
-  if ((threadIdx.x & 63) == 0 && m) atomicMax(out, m);
+  __shared__ uint32_t wave_max[4];
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
+    if (m) atomicMax(out, m);
+  }
 }
 
 // rec[0] = largest |W2| bits  ->  rec[1] = 2^s, rec[2] = 2^-(s + h_shift), rec[3] = s, with largest * 2^s in
@@ -79,9 +92,12 @@ __device__ __forceinline__ uint16_t bf16_to_scaled_half(uint16_t b, float scale)
 // The MFMA stage images are made by transposing tiles of 32 source rows x 512 bytes through LDS: rows come in
 // as whole 512-byte segments (16 bytes per lane), image rows leave as 64-byte runs (four 16-byte chunks of
 // neighbouring lanes), so both directions move a tensor once and in wide pieces; bound by HBM.  Weights of 8
-// experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 850 us = 4.4 TB/s, W2 (1.88 GB) 390 us
-// = 4.8 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took
-// 1295 and 1181 us: 2.9 and 1.6 TB/s.)
+// experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 835 us = 4.5 TB/s, W2 (1.88 GB) 390 us
+// = 4.8 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took 1295 and
+// 1181 us: 2.9 and 1.6 TB/s.)  W1 / W3 are read with the non-temporal hint (850 -> 835 us).  Nothing else is: the scattered
+// 64-byte runs need the caches to become whole lines (835 -> 900 us), and the hint on W2's rows or images gained nothing for
+// the pass and the first batch together.  (W2: 430 us since absmax_bf16_kernel, in front of it, leaves no part of W2 in the
+// last-level cache; that kernel gained more.)
 constexpr int kTileStride = 128 + 2;  // dwords between tile rows in LDS: a wavefront reads 4 chunks x 16 column pairs (bf16) or
                                       // 8 chunks x 8 columns (fp32) at once, whose rows then lie on 64 different banks
 template <typename T>
@@ -93,10 +109,11 @@ struct PackTile {
   static constexpr int PASSES = COLS * CH / COLS_GET / 256;
   uint32_t at[kBK * kTileStride];
   // sixteen bytes of a source row from column col on (zeros past the end; nullptr: a row of zeros)
+  template <bool ONCE>
   static __device__ __forceinline__ uint4 load(const T* row, int col, int ncols, bool vec) {
     uint4 v = make_uint4(0, 0, 0, 0);
     if (row == nullptr || col >= ncols) return v;
-    if (vec) return *(const uint4*)(row + col);
+    if (vec) return ONCE ? load_once(row + col) : *(const uint4*)(row + col);
     uint32_t u[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < V; ++i)
@@ -163,8 +180,8 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
   for (int u = 0; u < 4; ++u) {
     const int d = ks * kBK + u * 8 + (tid >> 5);
     const size_t row = ((size_t)e * D + d) * Fs;
-    a[u] = PT::load(d < D ? w1 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
-    b[u] = PT::load(d < D ? w3 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
+    a[u] = PT::template load<true>(d < D ? w1 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
+    b[u] = PT::template load<true>(d < D ? w3 + row : nullptr, c0 + (tid & 31) * PT::V, Fs, vec);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -211,7 +228,7 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
     const int in = kt % KSp * kBK + u * 8 + (tid >> 5), pos = kt / KSp * Fp + in;
     const T* row = nullptr;
     if (in < Fp) row = w2 + ((size_t)e * F + (perm ? perm[(size_t)e * F + pos] : pos)) * D;
-    a[u] = PT::load(row, c0 + (tid & 31) * PT::V, D, vec);
+    a[u] = PT::template load<false>(row, c0 + (tid & 31) * PT::V, D, vec);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
