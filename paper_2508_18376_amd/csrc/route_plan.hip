@@ -1202,18 +1202,19 @@ __global__ __launch_bounds__(1024) void combine_slots_kernel(Layout L, const cha
   using PT = Partials<HALF>;
   constexpr int VEC = PT::VEC;
   extern __shared__ __attribute__((aligned(16))) float part[];  // [slots][kSlotCols * VEC]
+  __shared__ float weight[kMaxTopK + 1];  // of every slot; 0 where nothing was kept: a dropped pair's own weight may be NaN
   const int32_t* counters = (const int32_t*)(ws + L.o_counters);
   const int nsplit = counters[3], split_row0 = counters[4] * L.BM;
   const int has_sh = L.n_shared > 0 ? 1 : 0, slots = L.K + has_sh;
   const int DV = L.D / VEC, per = (DV + kSlotCols - 1) / kSlotCols;
   const int t = blockIdx.x / per, c0 = (blockIdx.x % per) * kSlotCols, tid = threadIdx.x;
   const int slot = tid / kSlotCols, c = c0 + tid % kSlotCols;  // slot 0: the shared experts, where there are any
-  const float* w = (const float*)(ws + L.o_w) + (size_t)t * L.K;
   if (slot < slots) {
     float v[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) v[i] = 0.f;
     const int row = slot < has_sh ? t : ((const int32_t*)(ws + L.o_pair_row))[(size_t)t * L.K + slot - has_sh];
+    if (tid % kSlotCols == 0) weight[slot] = slot < has_sh ? 1.f : row >= 0 ? ((const float*)(ws + L.o_w))[(size_t)t * L.K + slot - has_sh] : 0.f;
     if (row >= 0 && c < DV) {
       const int d = c * VEC, tile = row / L.BM;
       const uint4 raw = PT::load(ws + L.o_Yp, (size_t)row * L.D + d);
@@ -1248,7 +1249,7 @@ __global__ __launch_bounds__(1024) void combine_slots_kernel(Layout L, const cha
   for (int o = tid; o < kSlotCols * VEC && c0 * VEC + o < L.D; o += blockDim.x) {
     float acc = has_sh ? part[o] * w2_inv : 0.f;
     for (int k = 0; k < L.K; ++k) {
-      const float g = w[k] * w2_inv;
+      const float g = weight[k + has_sh] * w2_inv;
       acc += g * part[(k + has_sh) * kSlotCols * VEC + o];
     }
     if constexpr (sizeof(OutT) == 4) ((float*)y)[(size_t)t * L.D + c0 * VEC + o] = acc;

@@ -78,6 +78,43 @@ def test_combine_on_both_sides_of_the_small_batch_line():
     layer.close()
 
 
+@pytest.mark.parametrize("n_shared", [0, 1])
+@pytest.mark.parametrize("dtype,T", [("bf16", 512), ("f32", 256)])
+def test_tokens_without_a_kept_pair_on_both_sides_of_the_small_batch_line(dtype, T, n_shared):
+    """Tokens whose scores are NaN (all logits -inf, as for masked padding; a logit of +inf; a NaN one, with a lane per token)
+    or all below the thresholds keep nothing: their output is the shared experts' alone, exact zeros without any, from
+    both combine kernels (512 columns: 64 groups of 8 bf16, 128 of 4 fp32 values, up to 32768 in the small-batch kernel)."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    D, F, E, dt = 512, 128, 4, torch.bfloat16 if dtype == "bf16" else torch.float32
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=2, n_part=1, max_tokens=T + 1, dtype=dtype, n_shared=n_shared,
+                            d_ff_shared=64 * n_shared, y_fp32=True)
+    def normal(*s, std=1.0):
+        return (torch.randn(*s, generator=gen, device="cuda:0") * std).to(dt)
+    sh = dict(sh_w1=normal(1, D, 64, std=0.05), sh_w3=normal(1, D, 64, std=0.05), sh_w2=normal(1, 64, D, std=0.05)) if n_shared else {}
+    layer.partition_weights(normal(E, D, F, std=0.05), normal(E, D, F, std=0.05), normal(E, F, D, std=0.05), **sh)
+    x, logits = normal(T + 1, D), torch.randn(T + 1, E, generator=gen, device="cuda:0")
+    tau = torch.full((E, 1), 0.4, device="cuda:0")  # one pair of most tokens is dropped, the other kept
+    shared_only = layer.forward(x, logits, torch.full((E, 1), 2.0, device="cuda:0"))
+    if not n_shared:
+        assert torch.equal(shared_only, torch.zeros_like(shared_only))
+    nan = float("nan")
+    for i, row in enumerate(([-float("inf")] * 4, [float("inf"), 0.0, 0.0, 0.0], [nan, 0.0, 0.0, 0.0], [nan] * 4)):
+        logits[i::16] = torch.tensor(row, device="cuda:0")
+    small = layer.forward(x[:T].contiguous(), logits[:T].contiguous(), tau)
+    large = layer.forward(x, logits, tau)
+    torch.cuda.synchronize()
+    layer.close()
+    assert bool(torch.isfinite(small).all()) and bool(torch.isfinite(large).all())
+    rms = float(large.square().mean().sqrt())
+    tol = (2e-2 if dtype == "bf16" else 1e-5) * rms
+    for i in range(4):
+        assert float((small[i::16] - shared_only[:T][i::16]).abs().max()) <= (tol if n_shared else 0.0)
+        assert float((large[i::16] - shared_only[i::16]).abs().max()) <= (tol if n_shared else 0.0)
+    assert float((small - large[:T]).abs().max()) <= tol
+
+
 @pytest.mark.parametrize("T", [1, 15, 17, 4096, 4097])
 @pytest.mark.parametrize("D,E", [(64, 3), (320, 40), (2112, 64), (128, 130)])
 def test_router_token_blocks(T, D, E):
