@@ -239,6 +239,8 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
   float* H = (float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld + (size_t)it.p * Fpk;
   if (SUBS == 2 && w >= 2) return;
   const int n0 = it.jt * kFullNeur + sub * (kFullNeur / SUBS) + w * 16 + (lane >> 5) * 4;
+  // the neurons that pad a partition to whole stages are zeros whatever came out: zero weights times an infinite x are NaN
+  const int Fp = sh ? L.F_shT : L.Fp;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int r = j * 32 + (lane & 31);
@@ -248,7 +250,7 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
     for (int g = 0; g < 2; ++g) {
       f32x4 o;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) o[c] = kept ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
+      for (int c = 0; c < 4; ++c) o[c] = kept && n0 + g * 8 + c < Fp ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
       if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = o;
     }
   }

@@ -76,6 +76,35 @@ def test_infinite_activations_stay_infinite_in_the_split_product():
     layer.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [5, 70])
+@pytest.mark.parametrize("D,F,P,F_sh", [(64, 40, 5, 0), (73, 99, 3, 27), (100, 88, 2, 24)])
+def test_infinite_inputs_stay_out_of_the_padding(D, F, P, F_sh, T, dtype):
+    """Every weight is positive, so a token with an infinite value has infinite activations and outputs.  The neurons that pad a
+    partition to whole stages have zero weights, and infinity times zero must not get into the sums."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(8)
+    n_sh, dt = int(F_sh > 0), torch.float32 if dtype == "f32" else torch.bfloat16
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=2, top_k=1, n_part=P, max_tokens=T, dtype=dtype, n_shared=n_sh, d_ff_shared=F_sh, y_fp32=True)
+    assert not layer.uses_mfma
+    def weights(*s):
+        return torch.rand(*s, generator=gen, device="cuda:0").add_(0.1).to(dt)
+    sh = dict(sh_w1=weights(1, D, F_sh), sh_w3=weights(1, D, F_sh), sh_w2=weights(1, F_sh, D)) if n_sh else {}
+    layer.partition_weights(weights(2, D, F), weights(2, D, F), weights(2, F, D), **sh)
+    x = torch.rand(T, D, generator=gen, device="cuda:0").to(dt)
+    x[1::3, 0] = float("inf")
+    logits = torch.randn(T, 2, generator=gen, device="cuda:0")
+    y = layer.forward(x, logits, torch.zeros(2, P, device="cuda:0"))
+    importance = layer.profile_importance(x, logits, 3)
+    torch.cuda.synchronize()
+    layer.close()
+    hot = torch.zeros(T, dtype=torch.bool, device="cuda:0")
+    hot[1::3] = True
+    assert torch.isposinf(y[hot]).all() and torch.isfinite(y[~hot]).all()
+    assert not torch.isnan(importance).any()
+
+
 def test_static_batch_without_room_for_k_splits(oracle):
     import torch
     import paper_2508_18376_amd as ds
