@@ -163,6 +163,7 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
     L.p_w2 = takep(L.w2_expert_bytes * L.E_res);
     L.p_sw13 = takep((int64_t)L.NT1_sh * (2 * kFullNeur) * L.Dk * elem);
     L.p_sw2 = takep((int64_t)L.ND2 * kFullBN2 * L.Fsk * elem);
+    L.p_scale = takep(elem == 2 ? 16 : 0);
   }
   // the permutation check borrows the start of the packed buffer for its counters
   const int64_t need_check = ((int64_t)L.E_res * L.F + 1) * 4;

@@ -101,7 +101,7 @@ struct Layout {
   int64_t o_tile_bits, o_act_rank, o_items1, o_items2;
   int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
   // packed weights byte offsets
-  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the W2 scale record (MFMA layout)
+  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the W2 scale record (MFMA layout); int32: W2 has an infinity or NaN (full-precision layout)
   int64_t w13_expert_bytes, w2_expert_bytes;  // strides between experts (mfma layout)
 };
 

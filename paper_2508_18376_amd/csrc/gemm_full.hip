@@ -9,8 +9,10 @@
 // Matrix instructions: fp32 layers multiply with v_mfma_f32_32x32x2_f32 (the precision of an fmaf chain, 256 flop
 // per clock and compute unit, the chip's fp32 peak of ~155 TFLOP/s; without packed fp32 the vector units reach
 // half of that).  bf16 layers multiply x with W1 / W3 by v_mfma_f32_32x32x16_bf16 (exact products); for GEMM-2 the fp32
-// activation is cut into three bf16 values h = hi + mid + lo (8 + 8 + 8 significant bits: exact) and multiplied with
-// the bf16 weights in three such instructions, which keeps all 24 bits of H at 5 x the rate of the fp32 instruction.
+// activation is cut into three bf16 values h = hi + mid + lo (8 + 8 + 8 significant bits: exact from |h| = 2^-110 on, below that
+// to within bf16's smallest value, 2^-133) and multiplied with the bf16 weights in three such instructions, which keeps all 24
+// bits of H at 5 x the rate of the fp32 instruction.  mid and lo can be zero: layers with an infinity or NaN in W2 (the packed
+// weights say so) leave those weights out of the two smaller products.
 //
 // A workgroup is 4 wavefronts; wavefront w owns the weight rows 32 w .. 32 w + 31 of the tile's 128 and multiplies them
 // with all pair rows, so a tile of r rows costs ceil(r/32) blocks.  The 32 weight rows of a GEMM-1 wavefront are the gate
@@ -61,7 +63,8 @@ __device__ __forceinline__ int xcd_run(int b) {  // runs of 32 consecutive items
 // One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
 // SUBS = 2: two wavefronts share 32 weight rows; each multiplies one half of every stage's K values, and the sums meet in
 // the first one (w < 2) at the end.
-template <int WE, int XE, int NJ, int SUBS>
+// NONFINITE (bf16 weights x fp32 activations): some weights are infinite or NaN, see above
+template <int WE, int XE, int NJ, int SUBS, bool NONFINITE = false>
 struct FullTile {
   static constexpr int WR = kBK * WE, XR = kBK * XE;           // bytes of a tile row
   static constexpr int WCH = WR / 16, XCH = XR / 16;           // 16-byte chunks of a row
@@ -172,6 +175,7 @@ struct FullTile {
       for (int s0 = 0; s0 < 2 / SUBS; ++s0) {
         const int s = s0 + k0;
         const bf16x8 a = *(const bf16x8*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
+        const bf16x8 small = NONFINITE ? finite_only(a) : a;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
           const char* x = xrow + j * 32 * XR;
@@ -181,10 +185,21 @@ struct FullTile {
           split3(v0, v1, part);
 #pragma unroll
           for (int k = 2; k >= 0; --k)  // the small parts first
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, part[k]), acc[j], 0, 0, 0);
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k == 0 ? a : small, __builtin_bit_cast(bf16x8, part[k]), acc[j], 0, 0, 0);
         }
       }
     }
+  }
+
+  // eight weights with zeros in place of infinities and NaN
+  static __device__ __forceinline__ bf16x8 finite_only(const bf16x8& a) {
+    u32x4 v = __builtin_bit_cast(u32x4, a);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if ((v[i] & 0x7f80u) == 0x7f80u) v[i] &= 0xffff0000u;
+      if ((v[i] & 0x7f800000u) == 0x7f800000u) v[i] &= 0xffffu;
+    }
+    return __builtin_bit_cast(bf16x8, v);
   }
 
   // eight fp32 values as sums of three bf16 values each: the top 16 bits, the top 16 bits of the (exact) rest, the rest
@@ -278,10 +293,10 @@ __global__ __launch_bounds__(256, 2) void gemm1_full_kernel(Layout L, const char
 }
 
 // ------------------------------------------------------------------------------------- GEMM-2
-template <typename T, int NJ, int SUBS>
+template <typename T, int NJ, int SUBS, bool NONFINITE>
 __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it, int sub, const char* packed, char* ws, char* lds, int w, int lane) {
   constexpr int E = sizeof(T);
-  using Tile = FullTile<E, 4, NJ, SUBS>;
+  using Tile = FullTile<E, 4, NJ, SUBS, NONFINITE>;
   const int tid = w * 64 + lane;
   const bool sh = it.e == L.E_res;
   const int ld = sh ? L.Fsk : L.Fh;
@@ -349,12 +364,17 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
   if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[1]) return;
   const Item2 it = ((const Item2*)(ws + L.o_items2))[id / SUBS];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#define DSMOE_ROWS(N) gemm2_full_tile<T, N, SUBS>(L, it, sub, packed, ws, lds, w, lane)
-  switch ((it.nrows + 31) >> 5) {
-    case 1: DSMOE_ROWS(1); break;
-    case 2: DSMOE_ROWS(2); break;
-    case 3: DSMOE_ROWS(3); break;
-    default: DSMOE_ROWS(4); break;
+#define DSMOE_ROWS(NONFINITE)                                                                              \
+  switch ((it.nrows + 31) >> 5) {                                                                     \
+    case 1: gemm2_full_tile<T, 1, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
+    case 2: gemm2_full_tile<T, 2, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
+    case 3: gemm2_full_tile<T, 3, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
+    default: gemm2_full_tile<T, 4, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;          \
+  }
+  if (sizeof(T) == 2 && *(const int32_t*)(packed + L.p_scale)) {
+    DSMOE_ROWS(sizeof(T) == 2)
+  } else {
+    DSMOE_ROWS(false)
   }
 #undef DSMOE_ROWS
 }

@@ -6,6 +6,7 @@
 //        (gu=0) or W3 (gu=1)
 //   W2   stage (e*ND2 + jd)*(P*Fpk/32) + kt : 128 output columns x 32 neurons; every partition is padded with zeros to
 //        whole stages (Fpk), as is D (Dk)
+//   bf16 layers: int32 at p_scale, 1 if some W2 value is infinite or NaN (GEMM-2 then treats such weights apart)
 // MFMA layout (bf16): 16 KiB "stage images", each the exact LDS contents of one operand tile of
 //   one pipeline stage, rows of kBK = 32 K-values with the 16-byte chunks XOR-rotated (swz_chunk):
 //   W13  stage ((e*P + p)*NT1 + jt)*(D/32) + ks : 256 weight rows x 32 values of d; weight row
@@ -152,6 +153,12 @@ __device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
   return v;
 }
 
+// some of the eight bf16 values is infinite or NaN
+__device__ __forceinline__ bool not_finite(uint4 v) {
+  auto one = [](uint32_t u) { return (u & 0x7f80u) == 0x7f80u || (u & 0x7f800000u) == 0x7f800000u; };
+  return one(v.x) || one(v.y) || one(v.z) || one(v.w);
+}
+
 // Where neuron nin of a partition sits in its W13 images: neuron tile, image row of its gate projection; the up row is UP
 // rows further down.  FULL: the full-precision layout.
 template <typename T, bool FULL>
@@ -214,7 +221,7 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
 // (source rows, in permuted order; zeros past the end of a partition) x COLS output columns: one stage image, or two
 // of 128 columns.  w2: [experts][P * Fp][D]; KSp: stages of a partition, KT: of the expert, nd: column tiles of the images.
 template <typename T, bool FULL>
-__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, const float* rec, int D, int F, int Fp,
+__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, float* rec, int D, int F, int Fp,
                                                       int KSp, int KT, int nd, int vec) {
   using PT = PackTile<T>;
   constexpr int BN = FULL ? kFullBN2 : kMfmaBN2, RB = kBK * sizeof(T);
@@ -233,6 +240,7 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     if (!FULL) a[u] = map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
+    if (FULL && sizeof(T) == 2 && not_finite(a[u])) *(int32_t*)rec = 1;
     t.put(u * 8 + (tid >> 5), tid & 31, a[u]);
   }
   __syncthreads();
@@ -286,7 +294,7 @@ template <typename T, bool FULL>
 static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3, const void* sw2,
                               const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
   const dim3 block(256);
-  const float* rec = (const float*)(packed + L.p_scale);
+  float* rec = (float*)(packed + L.p_scale);
   const int KS1 = L.Dk / kBK, C = PackTile<T>::COLS;
   // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
   // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
@@ -335,6 +343,8 @@ hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const vo
     return pack_images<uint16_t, false>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
   }
   if (L.dtype == DSMOE_F32) return pack_images<float, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
+  hipError_t e1 = launch_fill_i32((int32_t*)(packed + L.p_scale), 4, 0, s);
+  if (e1 != hipSuccess) return e1;
   return pack_images<uint16_t, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
 }
 

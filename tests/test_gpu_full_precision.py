@@ -105,6 +105,39 @@ def test_infinite_inputs_stay_out_of_the_padding(D, F, P, F_sh, T, dtype):
     assert not torch.isnan(importance).any()
 
 
+@pytest.mark.parametrize("shared", [0, 1])
+@pytest.mark.parametrize("T", [2, 40])
+def test_infinite_weights_in_the_split_product(T, shared):
+    """bf16 layers multiply W2 with three parts of an activation, of which some are zero: an infinite weight still gives an
+    infinity with the activation's sign, a NaN weight NaN, and the other columns are as without them."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    D, F, inf = 40, 24, float("inf")
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=1, top_k=1, n_part=1, max_tokens=T, dtype="bf16", y_fp32=True, n_shared=shared, d_ff_shared=F * shared)
+    assert not layer.uses_mfma
+    def zeros(*s):
+        return torch.zeros(*s, dtype=torch.bfloat16, device="cuda:0")
+    w1, w3, w2 = zeros(1, D, F), zeros(1, D, F), zeros(1, F, D)
+    w1[0, 0, 1] = 1.0
+    w3[0, 0, 1] = 1.0
+    w2[0, 1, :] = 0.5
+    finite = w2.clone()
+    w2[0, 1, 3], w2[0, 1, 4], w2[0, 1, 39] = inf, -inf, float("nan")
+    sh = dict(sh_w1=w1, sh_w3=w3, sh_w2=w2) if shared else {}
+    layer.partition_weights(w1, w3, finite if shared else w2, **sh)
+    x = zeros(T, D)
+    x[:, 0] = 1024.0  # Swish(1024) * 1024 = 2^20: its second and third part are zero
+    x[1::2, 0] = 3.0  # all parts
+    y = layer.forward(x, zeros(T, 1).float(), zeros(1, 1).float())
+    torch.cuda.synchronize()
+    layer.close()
+    assert torch.isposinf(y[:, 3]).all() and torch.isneginf(y[:, 4]).all() and torch.isnan(y[:, 39]).all()
+    others = [d for d in range(D) if d not in (3, 4, 39)]
+    assert (y[::2][:, others] == 2.0 ** 19 * (1 + shared)).all()
+    h3 = 9.0 / (1.0 + np.exp(-3.0))
+    assert float((y[1::2][:, others] - 0.5 * h3 * (1 + shared)).abs().max()) <= 1e-5 * h3
+
+
 def test_static_batch_without_room_for_k_splits(oracle):
     import torch
     import paper_2508_18376_amd as ds
