@@ -162,6 +162,9 @@ int moe_dualsparse_forward(dsmoe_ctx* ctx, const void* packed, const void* x, co
  *     than the array returns DSMOE_ENOSPC and launches nothing.  dsmoe_static_workspace_need(ctx, T)
  *     tells the bytes a batch of T tokens takes (0 for an invalid argument).  Decode-sized batches of
  *     the large layers fit (a Mixtral-shaped layer up to about 900 tokens).
+ *   - A full-precision layer's batch (see dsmoe_uses_mfma) that would fit but for the padding of its
+ *     intermediate arrays runs in pieces, one after the other on the stream: sums may then
+ *     differ in their last bits, and dsmoe_profile_begin's calls count every piece.
  *   - The first call on a device looks the array's address up (no allocation, but a runtime query):
  *     make one call with T = 0 before a graph capture starts.
  *   - Every call on a GPU uses that GPU's one array and overwrites what the last call left: calls

@@ -14,8 +14,16 @@ namespace {
 inline int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// full_pool = false: no partial-output tiles on the full-precision path (GEMM-2 does not split K then)
-bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
+// What the workspace has room for.
+enum class Room {
+  kContext,  // every call of a context
+  kBatch,    // one forward call with given logits
+  kNoSplit,  // the same without partial-output tiles on the full-precision path (GEMM-2 does not split K then)
+  kPiece,    // the same for a few tokens: no more row tiles than pairs
+  kBare,     // kNoSplit without the full-precision path's padding: no call runs in it, see static_layout
+};
+
+bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) {
   memset(&L, 0, sizeof(L));
   if (c.d_model < 1 || c.d_ff < 1) return false;
   if (c.n_experts < 1 || c.n_experts > kMaxExperts) return false;
@@ -59,10 +67,11 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
   L.BM = L.mfma ? kMfmaBM : kFullBM;
   const int neur = L.mfma ? kMfmaNeur : kFullNeur;
   L.BN2 = L.mfma ? kMfmaBN2 : kFullBN2;
-  L.Dk = (int)align_up(L.D, kBK);
-  L.Fpk = (int)align_up(L.Fp, kBK);
+  const int pad = room == Room::kBare ? 1 : kBK;
+  L.Dk = (int)align_up(L.D, pad);
+  L.Fpk = (int)align_up(L.Fp, pad);
   L.Fh = L.P * L.Fpk;
-  L.Fsk = (int)align_up(L.F_shT, kBK);
+  L.Fsk = (int)align_up(L.F_shT, pad);
   L.NT1 = cdiv(L.Fp, neur);
   L.NT1_sh = L.n_shared > 0 ? cdiv(L.F_shT, neur) : 0;
   L.ND2 = cdiv(L.D, L.BN2);
@@ -82,17 +91,18 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
   L.nbins = L.E_res * L.nsub;
   const int Tm = c.max_tokens;
   L.sh_rows = L.n_shared > 0 ? (int)align_up(Tm, L.BM) : 0;
-  const int rt = routed_tiles_bound(L, Tm);
+  int rt = routed_tiles_bound(L, Tm);
+  if (room == Room::kPiece && (int64_t)Tm * L.K < L.E_res) rt -= L.E_res - Tm * L.K;  // at most one ragged tile per pair
   L.row_cap = L.sh_rows + rt * L.BM;
   L.max_tiles = rt + shared_tiles(L, Tm);
-  L.max_items1 = items1_whole_bound(L, Tm) + (L.mfma ? L.split_items / 2 : 0);  // a smaller batch may cut its last items in two
+  L.max_items1 = rt * L.P * L.NT1 + shared_tiles(L, Tm) * L.NT1_sh + (L.mfma ? L.split_items / 2 : 0);  // a smaller batch may cut its last items in two
   // partial-output tiles the K splits of GEMM-2 can need: contexts whose largest batch has so few row
   // tiles that every item is split (decode sizes) stay within one extra tile per compute unit
   L.pool_tiles = (int64_t)L.max_tiles * L.ND2 * 2 <= L.split_items ? kSplitItems : kPoolTiles;
   L.pool_rows = kPoolRows;
   if (!L.mfma) {  // at most kMaxSplit - 1 extra tiles per item, and fewer than split_items in all
     const int64_t most = (int64_t)L.max_tiles * L.ND2 * (kMaxSplit - 1);
-    L.pool_tiles = !full_pool ? 0 : most < L.split_items ? (int)most : L.split_items;
+    L.pool_tiles = room > Room::kBatch ? 0 : most < L.split_items ? (int)most : L.split_items;
     L.pool_rows = align_up(Tm, 32) < kFullRows ? (int)align_up(Tm, 32) : kFullRows;
   }
   L.max_items2 = L.max_tiles * L.ND2 + L.pool_tiles;
@@ -130,14 +140,16 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
   L.o_H = take_big((int64_t)(L.row_cap - L.sh_rows) * L.Fh * helem);
   L.o_Hs = take_big((int64_t)L.sh_rows * L.Fsk * helem);
   {  // (the full-precision path may keep a padded copy of x here until GEMM-2)
-    const int64_t yp = (int64_t)L.row_cap * L.D * (L.yp_half ? 2 : 4), xpad = L.mfma ? 0 : (int64_t)Tm * L.Dk * elem;
+    const int64_t yp = (int64_t)L.row_cap * L.D * (L.yp_half ? 2 : 4), xpad = L.mfma || room == Room::kBare ? 0 : (int64_t)Tm * L.Dk * elem;
     L.o_Yp = take_big(yp > xpad ? yp : xpad);
   }
-  L.o_sel = take((int64_t)(L.E > kSelBlocks ? L.E : kSelBlocks) * kSelRow * 4);  // score histograms of the threshold selections
+  L.o_sel = take(room == Room::kContext ? (int64_t)(L.E > kSelBlocks ? L.E : kSelBlocks) * kSelRow * 4 : 0);  // score histograms of the threshold selections
   L.o_logits = take((int64_t)Tm * L.E * 4);
   L.o_perm_check = take(((int64_t)L.E_res * L.F + 1) * 4);
-  L.o_pool = take_big((int64_t)L.pool_tiles * L.pool_rows * L.BN2 * (L.yp_half ? 2 : 4));  // partial outputs of split K ranges
-  L.o_split_of = take((int64_t)L.max_tiles * L.ND2 * 4);  // (row tile, column tile) -> first pool tile, or -1
+  if (L.pool_tiles > 0) {
+    L.o_pool = take_big((int64_t)L.pool_tiles * L.pool_rows * L.BN2 * (L.yp_half ? 2 : 4));  // partial outputs of split K ranges
+    L.o_split_of = take((int64_t)L.max_tiles * L.ND2 * 4);                                   // (row tile, column tile) -> first pool tile, or -1
+  }
   L.ws_bytes = o;
 
   // packed weights
@@ -171,6 +183,36 @@ bool build_layout(const dsmoe_config& c, Layout& L, bool full_pool = true) {
   L.packed_bytes = q;
   L.router_mfma = (c.dtype == DSMOE_BF16 && L.D % 64 == 0) ? 1 : 0;
   L.router_bytes = L.router_mfma ? (int64_t)L.D * ((L.E + 31) / 32 * 32) * 2 : (int64_t)L.D * L.E * 4;
+  return true;
+}
+
+// The workspace of moe_dualsparse_forward_static for T tokens: a layout for exactly this batch (the offsets depend on T, so a
+// small batch of a large layer fits the array even if the context's own max_tokens would not), run in pieces of `piece`
+// tokens, one as a rule.  The call takes every batch whose arrays fit without padding and K splits: where only the
+// full-precision path's padding (partitions of a few neurons, widths off the grid of 32) is too much, the batch
+// goes through in pieces, which use the array one after the other.  L.ws_bytes is beyond the array if the batch does not fit.
+bool static_layout(const Ctx* ctx, int32_t T, Layout& L, int32_t& piece) {
+  dsmoe_config c = ctx->cfg;
+  auto layout = [&](int32_t tokens, Room room, Layout& into) {
+    c.max_tokens = tokens;
+    return build_layout(c, into, room);
+  };
+  auto fits = [](const Layout& l) { return l.ws_bytes <= (int64_t)DSMOE_STATIC_SCRATCH_BYTES; };
+  piece = T > 0 ? T : 1;
+  if (!layout(piece, Room::kBatch, L)) return false;
+  if (fits(L) || L.mfma) return true;
+  Layout l;
+  if (!layout(piece, Room::kNoSplit, L) || !layout(piece, Room::kBare, l)) return false;
+  if (fits(L) || !fits(l)) return true;
+  for (int32_t n = 1; n <= T; n += 1 + n / 8) {
+    const int32_t tokens = (T + n - 1) / n;
+    if (!layout(tokens, Room::kPiece, l)) return false;
+    if (fits(l) && !l.mfma) {  // (the weights are packed for the context's path)
+      L = l;
+      piece = tokens;
+      return true;
+    }
+  }
   return true;
 }
 
@@ -368,32 +410,30 @@ int moe_dualsparse_forward_static(dsmoe_ctx* ctx_, const void* packed, const voi
   if (T > 0 && (!x || !logits || !y)) return DSMOE_EINVAL;
   if (((uintptr_t)packed & 15) != 0) return DSMOE_EINVAL;
   if (T > ctx->L.max_tokens) return DSMOE_EINVAL;
-  // the workspace layout of a context made for exactly this batch: the offsets depend on T, so a
-  // small batch of a large layer fits the array even if the context's own max_tokens would not
-  dsmoe_config c = ctx->cfg;
-  c.max_tokens = T > 0 ? T : 1;
   Layout L;
-  if (!build_layout(c, L)) return DSMOE_EINVAL;
+  int32_t piece;
+  if (!static_layout(ctx, T, L, piece)) return DSMOE_EINVAL;
   // the packed weights were laid out for the context's own layout: the two must agree on the kernels
   if (L.mfma != ctx->L.mfma || L.packed_bytes != ctx->L.packed_bytes) return DSMOE_EINVAL;
-  // (a batch that only fits without room for K splits runs without them)
-  if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES && !build_layout(c, L, false)) return DSMOE_EINVAL;
   if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES) return DSMOE_ENOSPC;
   void* ws = nullptr;
   hipError_t e = static_scratch(&ws);
   if (e != hipSuccess) return hip_fail(ctx, e);
-  return forward_impl(ctx, L, packed, nullptr, x, logits, tau, T, y, ws, stream);
+  const int64_t x_row = (int64_t)L.D * (L.dtype == DSMOE_F32 ? 4 : 2), y_row = (int64_t)L.D * (L.y_f32 ? 4 : 2);
+  for (int32_t t0 = 0; t0 == 0 || t0 < T; t0 += piece) {
+    const int rc = forward_impl(ctx, L, packed, nullptr, (const char*)x + t0 * x_row, logits + (int64_t)t0 * L.E, tau,
+                                T - t0 < piece ? T - t0 : piece, (char*)y + t0 * y_row, ws, stream);
+    if (rc != DSMOE_OK) return rc;
+  }
+  return DSMOE_OK;
 }
 
 size_t dsmoe_static_workspace_need(const dsmoe_ctx* ctx_, int32_t T) {
   const Ctx* ctx = reinterpret_cast<const Ctx*>(ctx_);
   if (!ctx || T < 0) return 0;
-  dsmoe_config c = ctx->cfg;
-  c.max_tokens = T > 0 ? T : 1;
   Layout L;
-  if (!build_layout(c, L)) return 0;
-  if (L.ws_bytes > (int64_t)DSMOE_STATIC_SCRATCH_BYTES && !build_layout(c, L, false)) return 0;
-  return (size_t)L.ws_bytes;
+  int32_t piece;
+  return static_layout(ctx, T, L, piece) ? (size_t)L.ws_bytes : 0;
 }
 
 int moe_pack_router(dsmoe_ctx* ctx_, const void* wg, void* router_packed, void* stream) {

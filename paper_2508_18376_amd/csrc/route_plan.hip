@@ -823,8 +823,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         v.ks_n = ksp;
         v.split = 0;
         items2[slot] = v;
-        split_of[gj] = -1;
-        if (tall) split_of[gj + L.ND2] = -1;
+        if (L.pool_tiles > 0) {  // (without a pool there is no table either, and nothing looks it up)
+          split_of[gj] = -1;
+          if (tall) split_of[gj + L.ND2] = -1;
+        }
       } else {
         const int q = slot - first_split;  // q-th split item: its extra ranges use pool tiles q*(nsplit-1) ..
         atomicMin(&first_split_tile, g);

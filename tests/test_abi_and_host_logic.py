@@ -286,3 +286,27 @@ def test_header_is_plain_c(lib, tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.split()[0] != "0", (r.returncode, r.stdout, r.stderr)
+
+
+STATIC_BATCHES = [  # layer, tokens: what fits 256 MiB without padding and K splits
+    (dict(d_model=2048, d_ff=1408, n_experts=64, top_k=6, n_part=8, n_shared=2, d_ff_shared=1408, dtype=1), 2015),
+    (dict(d_model=2048, d_ff=1024, n_experts=64, top_k=8, n_part=2, dtype=0), 2183),
+    (dict(d_model=1024, d_ff=264, n_experts=32, top_k=4, n_part=8, dtype=0), 12287),  # parts of 33 neurons
+    (dict(d_model=64, d_ff=10, n_experts=4, top_k=2, n_part=2, dtype=0), 412799),  # parts of 5
+    (dict(d_model=64, d_ff=8, n_experts=512, top_k=2, n_part=8, dtype=1), 78208),  # parts of 1
+    (dict(d_model=1800, d_ff=40, n_experts=512, top_k=16, n_part=8, dtype=0), 135),  # a row tile of every expert is too much
+    (dict(d_model=1, d_ff=1, n_experts=1, top_k=1, n_part=1, dtype=0), 8497408),
+    (dict(d_model=100, d_ff=56, n_experts=3, top_k=2, n_part=2, n_shared=3, d_ff_shared=5, dtype=0), 149727),
+    (dict(d_model=256, d_ff=128, n_experts=4, top_k=1, n_part=1, dtype=1), 171263),  # the matrix-core path
+    (dict(d_model=4096, d_ff=14336, n_experts=8, top_k=2, n_part=4, dtype=1), 895),
+]
+
+
+@pytest.mark.parametrize("layer,tokens", STATIC_BATCHES, ids=lambda v: "%dx%d" % (v["d_model"], v["d_ff"]) if isinstance(v, dict) else str(v))
+def test_static_scratch_takes_what_fits_without_padding(layer, tokens):
+    import paper_2508_18376_amd as ds
+    ctx = ds.dsmoe_create(max_tokens=4 * tokens, **layer)
+    for T in (1, tokens // 3, tokens):
+        assert 0 < ds.dsmoe_static_workspace_need(ctx, max(T, 1)) <= ds.DSMOE_STATIC_SCRATCH_BYTES
+    assert ds.dsmoe_static_workspace_need(ctx, 2 * tokens) > ds.DSMOE_STATIC_SCRATCH_BYTES
+    ds.dsmoe_destroy(ctx)

@@ -156,3 +156,29 @@ def test_static_batch_without_room_for_k_splits(oracle):
     torch.cuda.synchronize()
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
     layer.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,F,P,E,K,F_sh,T", [(1024, 264, 8, 32, 4, 0, 12287), (99, 24, 8, 8, 2, 5, 150001), (1800, 40, 8, 512, 16, 0, 135)],
+                         ids=["parts_of_33", "odd_width_shared", "a_tile_of_every_expert_is_too_much"])
+def test_static_batch_in_pieces(D, F, P, E, K, F_sh, T, dtype):
+    """Batches that fit the static array only without the padding of the intermediate arrays: same results as with a workspace.
+    (Odd widths: the later pieces of x start at any address.)"""
+    import torch
+    import paper_2508_18376_amd as ds
+    gen = torch.Generator(device="cuda:0").manual_seed(12)
+    n_sh, dt = int(F_sh > 0), torch.float32 if dtype == "f32" else torch.bfloat16
+    layer = ds.DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=K, n_part=P, max_tokens=T, dtype=dtype, n_shared=n_sh, d_ff_shared=F_sh, y_fp32=True)
+    assert not layer.uses_mfma
+    def normal(*s, std=0.05):
+        return (torch.randn(*s, generator=gen, device="cuda:0") * std).to(dt)
+    sh = dict(sh_w1=normal(1, D, F_sh), sh_w3=normal(1, D, F_sh), sh_w2=normal(1, F_sh, D)) if n_sh else {}
+    layer.partition_weights(normal(E, D, F), normal(E, D, F), normal(E, F, D), **sh)
+    x, logits = normal(T, D, std=1.0), torch.randn(T, E, generator=gen, device="cuda:0")
+    tau = torch.full((E, P), 0.5 / K, device="cuda:0")
+    y = torch.full((T, D), float("nan"), device="cuda:0")
+    ds.moe_dualsparse_forward_static(layer.ctx, layer.packed, x, logits, tau, T, y, torch.cuda.current_stream())
+    ref = layer.forward(x, logits, tau)
+    torch.cuda.synchronize()
+    layer.close()
+    assert float((y - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
