@@ -343,10 +343,11 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
   // tile boundary after the T rows of THIS call (the plan kernel places them there), so the layout
   // every kernel of the call sees carries that boundary, not the one max_tokens would give.
   Layout L = base;
-  // Few rows per expert: the streaming kernels, without tall items.  The line lies where their weight tiles still get half of the
-  // LDS: 512 tokens on 64 experts top-8 (64 pairs each) 184 -> 174 us, 256 on 8 experts of 4096 x 14336 top-2 (64 each) 473 -> 457;
-  // with 88 pairs each the latter layer lost (495 -> 549 us), smaller ones still gained 5 % (700 tokens on the former 186 -> 177).
-  if (L.mfma && (int64_t)T * L.K <= (int64_t)L.E_res * kStreamRows) L.stream = 1, L.tall_tiles = 0;
+  // The streaming kernels, for batches in which no expert can have more rows than they take at once.  Larger batches gain from them
+  // only as long as every expert has few rows, which the host does not know: 512 tokens on 64 experts of 2048 x 1024 top-8 164 -> 152 us
+  // and 333 on 64 + 2 of 2048 x 1408 267 -> 254 under even routing, but 100 of the former 93 -> 114 and 200 on 8 of 4096 x 14336
+  // top-2 511 -> 652 with popularity rank^-1.2.
+  if (L.mfma && T <= kStreamRows) L.stream = 1;
   L.sh_rows = L.n_shared > 0 ? (int)align_up(T, L.BM) : 0;
   ctx->last_sh_rows = L.sh_rows;
   const float* logits = logits_buf;

@@ -41,8 +41,7 @@ inline __host__ __device__ int route_block_tokens(int E, int T) {
 constexpr int kMfmaBM = 256;
 constexpr int kMfmaNeur = 128;
 constexpr int kMfmaBN2 = 256;
-constexpr int kStreamBM = 128;              // rows that a workgroup of the streaming kernels takes ...
-constexpr int kStreamRows = 64;             // ... in batches of at most that many pairs per resident expert on average
+constexpr int kStreamRows = 64;             // rows that a workgroup of the streaming kernels takes: batches of at most that many tokens
 constexpr int kBK = 32;                     // K values per pipeline stage
 constexpr int kChunksPerRow = kBK / 8;      // 16-byte chunks in one tile row
 constexpr int kStageBytes = 256 * kBK * 2;  // one operand tile of one stage (bf16): 16 KiB

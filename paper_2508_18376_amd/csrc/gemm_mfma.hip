@@ -65,17 +65,16 @@ using RingTall = Ring<kStages, kStageBytes + kTallRows * (kBK * 2), kStageBytes>
 static_assert(RingTall::BYTES <= kLdsBytes, "same allocation");
 // the same for GEMM-2, whose A tile holds the rows: 320 rows of A + 16 KiB B tile
 using RingTall2 = Ring<kStages, kStageBytes + kTallRows * (kBK * 2), kTallRows * (kBK * 2)>;
-// streaming kernels (see gemm1_stream_kernel): a weight tile (16 KiB) or half of one + up to 64 or 128 rows a stage, two
+// streaming kernels (see gemm1_stream_kernel): a weight tile (16 KiB) or half of one + up to 64 rows a stage, two
 // workgroups per compute unit
 constexpr int kStreamLds = 80 * 1024;
-template <int SUBS, int NB>  // parts of the weight tile, 32-row blocks
+template <int SUBS>  // parts of the weight tile
 struct StreamStage {
-  static constexpr int W = kStageBytes / SUBS, X = (NB <= 2 ? 64 : 128) * (kBK * 2);
-  static constexpr int NS = kStreamLds / (W + X) < 8 ? kStreamLds / (W + X) : 8;
+  static constexpr int W = kStageBytes / SUBS, X = kStreamRows * (kBK * 2), NS = kStreamLds / (W + X);
 };
-template <int SUBS, int NB, class S = StreamStage<SUBS, NB>>
+template <int SUBS, class S = StreamStage<SUBS>>
 using RingStream = Ring<S::NS, S::W + S::X, S::W>;
-template <int SUBS, int NB, class S = StreamStage<SUBS, NB>>
+template <int SUBS, class S = StreamStage<SUBS>>
 using RingStream2 = Ring<S::NS, S::W + S::X, S::X>;  // GEMM-2: the rows first
 constexpr int64_t kStreamOutBytes = 192ll << 20;    // GEMM-2 outputs larger than this bypass the caches (256 MiB of last-level cache, shared with H)
 constexpr int kLoadsPerStage = 2 * (kStageBytes / 16 / 256);  // per thread: 4 (A) + 4 (B)
@@ -102,7 +101,8 @@ __device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
 // stream itself runs faster: 64 tokens on 8 experts of 4096 x 14336 500 -> 443 us (2.8 GB of weights: 6.2 -> 7.1 TB/s),
 // 333 tokens on 64 + 2 experts of 2048 x 1408 303 -> 279 us.  Tiles that several row tiles share keep the default policy:
 // with the hint the second reader misses (4096 tokens on 64 experts of 2048 x 1024 425 -> 437 us, 2000 on the first layer 1118
-// -> 1252 us).
+// -> 1252 us).  The hint costs a program whose weights would all stay in the last-level cache (256 MiB): 600 tokens on 8 experts of
+// 1024 x 2048 again and again 71 -> 76 us for that one layer (100 MB), 77 -> 73 us for three of them in turn.
 template <bool ONCE = false>
 __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
 #define DSMOE_DMA16(POLICY)                                      \
@@ -481,7 +481,7 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
   // [256 rows][128 neurons] tile (320 rows in a tall tile; rows padded to 272 bytes against bank conflicts), then written
   // out in whole 256-byte row segments: 16 lanes per row, 16 bytes per lane.
   constexpr int kHsRow = kMfmaNeur * 2 + 16;
-  constexpr int kRowsOut = RING::BYTES >= kTallRows * kHsRow ? kTallRows : kStreamBM;  // (the streaming kernels')
+  constexpr int kRowsOut = RING::BYTES >= kTallRows * kHsRow ? kTallRows : kStreamRows;  // (the streaming kernels')
   block_barrier();  // every wave is done reading the last stage
   // one block of 32 rows x 32 neurons: gate and up accumulators of weight blocks i and i + 1, pair row r of this lane
   auto emit = [&](const f32x16& gate, const f32x16& up, int r, bool kept, int i) {
@@ -549,11 +549,8 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
 
 // What every GEMM-1 workgroup does first: its item and the buffer descriptors.
 __device__ __forceinline__ void gemm1_setup(G1Args& g, int item_id, const Layout& L, int T, const char* packed, const uint16_t* x, char* ws,
-                                            int epi, const char* lds, int tid, int w, int skip_rows = 0) {
+                                            int epi, const char* lds, int tid, int w) {
   g.it = ((const Item1*)(ws + L.o_items1))[item_id];
-  g.it.row0 += skip_rows;  // (the streaming kernel's second part of an item)
-  g.it.nrows -= skip_rows;
-  g.it.nfill -= skip_rows;
   g.row_bits = (const uint8_t*)(ws + L.o_row_bits);
   g.row_token = (const int32_t*)(ws + L.o_row_token);
   g.x_row_bytes = (uint32_t)(L.D * 2);
@@ -777,14 +774,12 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
 
 // What every GEMM-2 workgroup does first (see gemm1_setup).
 __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout& L, int T, const char* packed, char* ws, const char* lds, int tid,
-                                            int w, int skip_rows = 0) {
+                                            int w) {
   g.it = ((const Item2*)(ws + L.o_items2))[item_id];
   const bool sh = g.it.e == L.E_res;
   const int32_t* multi = (const int32_t*)(ws + L.o_counters) + 5;  // (both words are fetched with the item, before its expert is known)
   const uint64_t multi_tile = (uint32_t)multi[0] | (uint64_t)(uint32_t)multi[1] << 32;
   g.once = sh ? T <= kMfmaBM : !((multi_tile >> (g.it.e & 63)) & 1);
-  g.it.row0 += skip_rows;  // (the streaming kernel's second part of an item)
-  g.it.nrows -= skip_rows;
   const int Fp = sh ? L.F_shT : L.Fp;
   const int ld = sh ? L.F_shT : L.F;
   const int KT = ld / kBK;  // stages of the whole expert
@@ -803,7 +798,7 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
     g.Y = ws + L.o_Yp + ((size_t)g.it.row0 * L.D + g.it.jd * kMfmaBN2) * yel;
     g.ldy = L.D;
   } else {  // an extra K range of a split item: a partial-output tile of the pool
-    g.Y = ws + L.o_pool + ((size_t)(g.it.split - 1) * kPoolRows + skip_rows) * kMfmaBN2 * yel;
+    g.Y = ws + L.o_pool + (size_t)(g.it.split - 1) * kPoolRows * kMfmaBN2 * yel;
     g.ldy = kMfmaBN2;
   }
   g.yscale = kYpHalfScale;
@@ -855,70 +850,36 @@ __global__ __launch_bounds__(256) void gemm2_mfma_kernel(Layout L, int T, const 
 }
 
 // ------------------------------------------------------------------------------------- streaming
-// Batches with few rows per expert only stream weights (Layout::stream): a workgroup takes a weight tile or half of one (64
-// neurons, resp. 128 output columns) under up to kStreamBM rows of an item, with few enough registers and LDS for two
-// workgroups per compute unit.  The kernels above run one per unit: nothing streams while an item starts (list entry, row list,
-// first tiles) or ends, and a few rounds of items of 1 MiB of weights leave the last one mostly empty (333 tokens on 64 + 2
-// experts of 2048 x 1408: 3.2 rounds, units busy 70 % of the time; 278 -> 266 us for the layer, 64 tokens 228 -> 216 us).
-// Workgroups [0, SUBS * items) take the first kStreamBM rows of every item, the next SUBS * items the rows beyond them, if
-// there are any: those sit at the end, where the ones that find nothing to do leave while the last others are still at work.
-template <int SUBS>
-struct StreamPart {
-  int item, sub, row0;  // list entry, part of its weight tile, first row
-  __device__ __forceinline__ StreamPart(int id, int items) {
-    row0 = id >= SUBS * items ? kStreamBM : 0;
-    id -= row0 ? SUBS * items : 0;
-    item = id / SUBS;
-    sub = id % SUBS;
-  }
-};
-
+// Batches of at most kStreamRows tokens (Layout::stream), which no expert can have more rows of, only stream weights: a workgroup
+// takes a weight tile or half of one (64 neurons, resp. 128 output columns) under an item's rows, with few enough registers and
+// LDS for two workgroups per compute unit.  The kernels above run one per unit: nothing streams while an item starts (list
+// entry, row list, first tiles) or ends, and a few rounds of items of 1 MiB of weights leave the last one mostly empty.
+// Layer times with the kernels above -> with these: 8 tokens on 64 experts of 2048 x 1024 104 -> 95 us, 5 and 64 tokens on 64 + 2
+// experts of 2048 x 1408 118 -> 102 and 227 -> 212 us, 64 on 8 experts of 4096 x 14336 429 -> 432.
 template <int SUBS, int NB, bool ONCE>
 __device__ __forceinline__ void gemm1_stream_item(const G1Args& g, char* lds, int w) {
-  using R = RingStream<SUBS, NB>;
-  constexpr int NX = (NB * 32 + 63) / 64;
-  if (SUBS == 1) gemm1_tile<2, 4, NB, false, 4, false, R, NX, false, ONCE>(g, lds, w * 64, 0, w);
-  else if (w < 2) gemm1_tile<2, 4, NB, false, 2, true, R, NX, false, ONCE>(g, lds, w * 64, 0, w);
-  else gemm1_tile<2, 4, 0, false, 2, true, R, NX, false, ONCE>(g, lds, 0, 0, w);  // only helps to load
+  using R = RingStream<SUBS>;
+  if (SUBS == 1) gemm1_tile<2, 4, NB, false, 4, false, R, 1, false, ONCE>(g, lds, w * 64, 0, w);
+  else if (w < 2) gemm1_tile<2, 4, NB, false, 2, true, R, 1, false, ONCE>(g, lds, w * 64, 0, w);
+  else gemm1_tile<2, 4, 0, false, 2, true, R, 1, false, ONCE>(g, lds, 0, 0, w);  // only helps to load
 }
 template <int SUBS, bool ONCE>
 __device__ __forceinline__ void gemm1_stream_rows(const G1Args& g, char* lds, int w) {
-  switch ((g.it.nrows + 31) >> 5) {
-    case 1: gemm1_stream_item<SUBS, 1, ONCE>(g, lds, w); break;
-    case 2: gemm1_stream_item<SUBS, 2, ONCE>(g, lds, w); break;
-    case 3: gemm1_stream_item<SUBS, 3, ONCE>(g, lds, w); break;
-    default: gemm1_stream_item<SUBS, 4, ONCE>(g, lds, w); break;
-  }
+  if (g.it.nrows <= 32) gemm1_stream_item<SUBS, 1, ONCE>(g, lds, w);
+  else gemm1_stream_item<SUBS, 2, ONCE>(g, lds, w);
 }
 template <int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm1_stream_kernel(Layout L, int T, const char* packed, const uint16_t* x, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int items = ((const int32_t*)(ws + L.o_counters))[0];
-  const StreamPart<SUBS> part(xcd_remap(blockIdx.x), items);
-  if (part.item >= items) return;  // past the end of the list
+  const int id = xcd_remap(blockIdx.x), sub = id % SUBS;
+  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[0]) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G1Args g;
-  gemm1_setup(g, part.item, L, T, packed, x, ws, 0, lds, tid, w, part.row0);
-  if (g.it.nfill <= 0) return;  // no rows in this part
-  // neurons of this workgroup: [n0, n1) of the tile
-  int n0 = part.sub * (kMfmaNeur / SUBS), n1 = n0 + kMfmaNeur / SUBS;
-  if (g.it.half) {  // an item of one half
-    if (part.sub) return;
-    n0 = (g.it.half - 1) * (kMfmaNeur / 2), n1 = n0 + kMfmaNeur / 2;
-  } else if (SUBS == 2) {
-    g.it.half = 1 + part.sub;
+  gemm1_setup(g, id / SUBS, L, T, packed, x, ws, 0, lds, tid, w);
+  if (SUBS == 2) {
+    if (sub && g.it.half) return;  // an item of one half (so is a last neuron tile without a second one)
+    if (!g.it.half) g.it.half = 1 + sub;
   }
-  n1 = min(n1, g.Fp - g.it.jt * kMfmaNeur);
-  if (n0 >= n1) return;  // a last neuron tile without a second half
-  if (g.it.nrows <= 0) {  // rows of the tile that keep nothing of this partition: zeros
-    const int n = n0 + (tid & 15) * 8;
-    if (n < n1)
-      for (int r = tid >> 4; r < min(g.it.nfill, kStreamBM); r += 16)
-        *(uint4*)(g.H + (size_t)(g.hrow0 + r) * g.ld + (size_t)g.it.p * g.Fp + g.it.jt * kMfmaNeur + n) = make_uint4(0, 0, 0, 0);
-    return;
-  }
-  g.it.nrows = min(g.it.nrows, kStreamBM);
-  g.it.nfill = min(g.it.nfill, kStreamBM);
   if (SUBS == 1 && g.it.half) {
     if (g.it.once) gemm1_stream_rows<2, true>(g, lds, w);
     else gemm1_stream_rows<2, false>(g, lds, w);
@@ -930,27 +891,19 @@ __global__ __launch_bounds__(256, 2) void gemm1_stream_kernel(Layout L, int T, c
 
 template <int SUBS, bool YH, bool ONCE>
 __device__ __forceinline__ void gemm2_stream_item(const G2Args& g, char* lds, int w) {
-#define DSMOE_STREAM(N) gemm2_tile<4, 2 / SUBS, N, false, YH, RingStream2<SUBS, N>, false, ONCE, 4 / SUBS>(g, lds, 0, w * (64 / SUBS), w)
-  switch ((g.it.nrows + 31) >> 5) {
-    case 1: DSMOE_STREAM(1); break;
-    case 2: DSMOE_STREAM(2); break;
-    case 3: DSMOE_STREAM(3); break;
-    default: DSMOE_STREAM(4); break;
-  }
-#undef DSMOE_STREAM
+  using R = RingStream2<SUBS>;
+  if (g.it.nrows <= 32) gemm2_tile<4, 2 / SUBS, 1, false, YH, R, false, ONCE, 4 / SUBS>(g, lds, 0, w * (64 / SUBS), w);
+  else gemm2_tile<4, 2 / SUBS, 2, false, YH, R, false, ONCE, 4 / SUBS>(g, lds, 0, w * (64 / SUBS), w);
 }
 template <int SUBS, bool YH>
 __global__ __launch_bounds__(256, 2) void gemm2_stream_kernel(Layout L, int T, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int items = ((const int32_t*)(ws + L.o_counters))[1];
-  const StreamPart<SUBS> part(xcd_remap(blockIdx.x), items);
-  if (part.item >= items) return;  // past the end of the list
+  const int id = xcd_remap(blockIdx.x), sub = id % SUBS;
+  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[1]) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G2Args g;
-  gemm2_setup(g, part.item, L, T, packed, ws, lds, tid, w, part.row0);
-  if (g.it.nrows <= 0) return;  // no rows in this part
-  g.it.nrows = min(g.it.nrows, kStreamBM);
-  g.col0 = part.sub * (kMfmaBN2 / SUBS);
+  gemm2_setup(g, id / SUBS, L, T, packed, ws, lds, tid, w);
+  g.col0 = sub * (kMfmaBN2 / SUBS);
   if (g.it.jd * kMfmaBN2 + g.col0 >= L.D) return;  // a last column tile without a second half
   if (g.once) gemm2_stream_item<SUBS, YH, true>(g, lds, w);
   else gemm2_stream_item<SUBS, YH, false>(g, lds, w);
@@ -981,13 +934,12 @@ static hipError_t set_lds_attr() {
   return once.run(set_lds_attr_now);
 }
 
-// Experts that can have a row (each has one row tile as a rule).
+// Experts that can have a row (each has one row tile).
 static int stream_experts(const Layout& L, int T) { return (int64_t)T * L.K < L.E_res ? T * L.K : L.E_res; }
 // Streaming kernels: half weight tiles where that fills two workgroups per compute unit better: when the last round of `items`
-// whole ones would be at most half full.  Otherwise whole tiles: larger pieces and half the activation reads, measured 1 - 6 %
-// faster where both fit (64 tokens on 8 experts of 4096 x 14336, 3.5 rounds of GEMM-1 per unit: 446 against 465 us).  Up
-// to 128 items the plan itself cuts them.  GEMM-2, 333 tokens on 64 + 2 experts of 2048 x 1408 (528 items): 288 us with whole
-// tiles, 265 with halves; 5 tokens (248 items): 100 and 89 us.
+// whole ones would be at most half full.  Otherwise whole tiles: larger pieces and half the activation reads.  Up to 128 items
+// the plan itself cuts them.  Whole tiles -> halves: 64 tokens on 64 + 2 experts of 2048 x 1408 (GEMM-2: 520 items) 222 -> 212 us, 5 tokens
+// (248 items) 111 -> 102; 64 tokens on 8 experts of 4096 x 14336, 3.5 rounds of GEMM-1 per unit, 431 -> 451.
 static bool stream_halves(int items) {
   const int slots = 2 * kSplitItems, rest = items % slots;
   return items > slots / 4 && rest > 0 && rest <= slots / 2;
@@ -999,9 +951,8 @@ hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const v
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
   if (L.stream) {
-    const int parts = T > kStreamBM ? 2 : 1;  // an expert has at most T rows
     const bool halves = stream_halves(stream_experts(L, T) * L.P * L.NT1 + L.NT1_sh);
-    const dim3 grid((parts * (halves ? 2 : 1) * items1_bound(L, T) + 255) & ~255), block(256);
+    const dim3 grid(((halves ? 2 : 1) * items1_bound(L, T) + 255) & ~255), block(256);
     if (halves) gemm1_stream_kernel<2><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
     else gemm1_stream_kernel<1><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
     return hipGetLastError();
@@ -1018,9 +969,8 @@ hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* w
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
   if (L.stream) {
-    const int parts = T > kStreamBM ? 2 : 1;
     const bool halves = stream_halves((stream_experts(L, T) + shared_tiles(L, T)) * L.ND2);
-    const dim3 grid((parts * (halves ? 2 : 1) * items2_bound(L, T) + 255) & ~255), block(256);
+    const dim3 grid(((halves ? 2 : 1) * items2_bound(L, T) + 255) & ~255), block(256);
 #define DSMOE_LAUNCH(SUBS, YH) gemm2_stream_kernel<SUBS, YH><<<grid, block, kStreamLds, s>>>(L, T, packed, ws)
     if (halves && L.yp_half) DSMOE_LAUNCH(2, true);
     else if (halves) DSMOE_LAUNCH(2, false);

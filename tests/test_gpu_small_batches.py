@@ -2,7 +2,7 @@
 
 Row counts around one row tile (an expert with one row tile is the only reader of its weight tiles, which are then loaded
 with the non-temporal hint; with two, or with a short last tile taken along, they are not), around the blocks of 32 rows, and
-around the 128 rows that a workgroup of the streaming kernels takes (batches of at most 64 pairs per expert on average).
+around the 64 tokens up to which a batch takes the streaming kernels.
 """
 import pytest
 
@@ -42,17 +42,39 @@ def test_one_tile_experts_beside_larger_ones(oracle, T):
 @pytest.mark.parametrize("rows", [1, 31, 33, 64, 65, 97, 128, 129, 160, 255, 256, 257])
 @pytest.mark.parametrize("D,Fp", [(96, 32), (160, 160), (320, 192)], ids=["no_second_halves", "short_last_tiles", "two_column_tiles"])
 def test_streaming_rows_of_one_expert(oracle, rows, D, Fp):
-    # 8 x 64 pairs at most: `rows` of them (about) on one expert; halves of weight tiles that do not exist; a general mask
+    # `rows` pairs (about) on one expert, up to 64 of them in the streaming kernels; halves of weight tiles that do not exist; a general mask
     # leaves row tiles whose later rows keep nothing of a partition
     _check(oracle, spec_of(T=rows, D=D, F=2 * Fp, E=8, K=1, P=2, seed=140 + rows), 0.0, to_expert_0=rows)
     if rows > 100:
         _check(oracle, spec_of(T=rows, D=D, F=4 * Fp, E=8, K=2, P=4, seed=141 + rows), "ragged", to_expert_0=rows)
 
 
+@pytest.mark.parametrize("T", [64, 65, 300, 511])
+def test_hot_expert_in_a_batch_of_few_rows_on_average(oracle, T):
+    """All first choices on one of 32 experts: from 257 of its rows on tall items take its short last tile along, and a weight
+    tile that is marked as read once has one item of at most a row tile."""
+    import torch
+    spec = spec_of(T=T, D=96, F=256, E=32, K=2, P=2, seed=145)
+    t = make_layer(spec)
+    t["logits"][:, 0] += 8.0
+    tau = resolve_tau(oracle, spec, t, 0.0)
+    layer, dev = make_gpu_layer(spec, t, y_fp32=True, tall_items=1)
+    y = layer.forward(dev["x"], dev["logits"], to_dev(tau))
+    torch.cuda.synchronize()
+    plan = layer.plan(T)
+    layer.close()
+    ref = oracle.forward(t["x"], t["logits"], t["w1"], t["w3"], t["w2"], tau, spec.K, spec.P, perm=t["perm"])
+    assert_output_close(to_host64(y, "f32"), ref, spec.dtype, y_fp32=True)
+    rows = int(plan["expert_nrows"][0])
+    tallest = rows if rows <= 256 + 64 else 256
+    assert rows == T and int(plan["items2"][:, 1].max()) == tallest and int(plan["items1"][:, 1].max()) == tallest
+
+
+@pytest.mark.parametrize("T", [60, 300])  # (60: every expert has rows, in the streaming kernels)
 @pytest.mark.parametrize("E,F", [(40, 512), (64, 512), (66, 512), (64, 768)], ids=["items_160_480", "items_512", "items_528", "items_768"])
-def test_streaming_with_whole_and_half_weight_tiles(oracle, E, F):
+def test_streaming_with_whole_and_half_weight_tiles(oracle, E, F, T):
     # the numbers of items around which whole weight tiles or halves are taken (2 x 2 .. 2 x 3 neuron tiles, 2 column tiles an expert)
-    _check(oracle, spec_of(T=300, D=512, F=F, E=E, K=4, P=2, seed=150, n_shared=1, F_sh=96), "rate0.25")
+    _check(oracle, spec_of(T=T, D=512, F=F, E=E, K=4, P=2, seed=150, n_shared=1, F_sh=96), "rate0.25")
 
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 96), ("bf16", 320), ("f32", 72), ("f32", 260)])
