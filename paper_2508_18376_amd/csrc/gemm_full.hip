@@ -404,10 +404,12 @@ static hipError_t set_lds_attr() {
 }
 
 // Workgroups that share a weight tile.  With a few rows per expert the kernels stream weights in items that are too few or too
-// long for the chip, and two halves are better: 64 tokens on 8 experts of 128 x 256 (16 pairs each) 27.0 -> 24.2 us, 16 tokens
-// top-8 on 64 experts of 2048 x 1024 in fp32 280 -> 265, 100 top-6 on 64 + 2 of 2048 x 1408 in parts of 176 319 -> 305.  Beyond,
-// the rows are read twice for nothing: 300 tokens (37 pairs each) on the former 390 -> 414 us, 400 on the latter 335 -> 354.
-static int full_parts(const Layout& L, int T) { return (int64_t)T * L.K <= (int64_t)L.E_res * 16 ? 2 : 1; }
+// long for the chip, and two halves are better: 64 tokens on 8 experts of 128 x 256 (16 pairs each) 27.0 -> 24.2 us, 64 tokens
+// top-8 on 64 experts of 2048 x 1024 in fp32 311 -> 301, 100 top-6 on 64 + 2 of 2048 x 1408 in parts of 176 318 -> 303; under uneven
+// routing more so (127 of the fp32 ones with popularity rank^-1.2 280 -> 204).  Beyond, the rows are read twice for nothing: 300
+// tokens (37 pairs each) on the former 390 -> 414 us, 400 on the latter 335 -> 354.  An expert's share of the pairs does not
+// depend on how many experts are resident: 64 tokens on 8 of those 64 experts 82 -> 68 us, on 2 of 8 of 1024 x 2048 49 -> 40.
+static int full_parts(const Layout& L, int T) { return (int64_t)T * L.K <= (int64_t)L.E * 16 ? 2 : 1; }
 
 hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
   if (T <= 0) return hipSuccess;

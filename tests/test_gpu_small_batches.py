@@ -8,7 +8,7 @@ import pytest
 
 from synth import make_layer
 from gpu_util import make_gpu_layer, to_dev, to_host64, assert_output_close
-from test_gpu_forward import spec_of, resolve_tau
+from test_gpu_forward import spec_of, resolve_tau, oracle_forward
 
 pytestmark = pytest.mark.gpu
 
@@ -193,3 +193,17 @@ def test_full_precision_halves_of_weight_tiles(oracle, rows, E, dtype):
     for F in (88, 152):
         _check(oracle, spec_of(T=rows, D=136, F=F, E=E, K=1, P=2, dtype=dtype, n_shared=1, F_sh=40, seed=180 + rows, w_std=0.05), 0.0,
                to_expert_0=rows if E > 1 else 0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [4, 5, 64, 65])
+def test_full_precision_halves_of_weight_tiles_on_a_resident_window(oracle, T, dtype):
+    # 16 pairs per expert of the whole layer (64 tokens) and of the window alone (4 tokens), one step on either side of both
+    spec = spec_of(T=T, D=136, F=88, E=16, K=4, P=2, dtype=dtype, resident=(3, 4), n_shared=1, F_sh=40, seed=190 + T, w_std=0.05)
+    t = make_layer(spec)
+    tau = resolve_tau(oracle, spec, t, 0.0)
+    layer, dev = make_gpu_layer(spec, t, y_fp32=True)
+    y = layer.forward(dev["x"], dev["logits"], to_dev(tau))
+    layer.close()
+    ref = oracle_forward(oracle, spec, t, tau)
+    assert_output_close(to_host64(y, "f32"), ref, spec.dtype, y_fp32=True)
