@@ -160,6 +160,10 @@ inline int items2_bound(const Layout& L, int T) {
   return whole + L.pool_tiles;  // every extra K range of a split item is one more item
 }
 
+// Workgroups of 256 threads for n values, one each up to 2^30 and in turns beyond: a launch of 2^32 threads and more is
+// silently cut short.
+inline int64_t blocks_of_256(int64_t n) { return n < (int64_t)1 << 30 ? (n + 255) / 256 : 1 << 22; }
+
 // launchers (each returns hipError_t of the launch)
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 // tau == nullptr: thresholds of zero

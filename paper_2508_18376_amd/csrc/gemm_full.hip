@@ -383,11 +383,11 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
 // the caller's pointer does not give that (one small pass; kept where GEMM-2 later writes Yp)
 template <typename T>
 __global__ __launch_bounds__(256) void pad_rows_kernel(const T* x, T* out, int D, int Dk, int64_t n) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= n) return;
-  const int64_t t = q / Dk;
-  const int d = (int)(q - t * Dk);
-  out[q] = d < D ? x[t * D + d] : (T)0;
+  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < n; q += (int64_t)gridDim.x * 256) {
+    const int64_t t = q / Dk;
+    const int d = (int)(q - t * Dk);
+    out[q] = d < D ? x[t * D + d] : (T)0;
+  }
 }
 
 static hipError_t set_lds_attr() {
@@ -420,7 +420,7 @@ hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const v
   int64_t x_row = L.D * elem;
   if (L.D != L.Dk || ((uintptr_t)x & 15) != 0) {
     const int64_t n = (int64_t)T * L.Dk;
-    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    const dim3 grid((unsigned)blocks_of_256(n)), block(256);
     if (elem == 4) pad_rows_kernel<float><<<grid, block, 0, s>>>((const float*)x, (float*)(ws + L.o_Yp), L.D, L.Dk, n);
     else pad_rows_kernel<uint16_t><<<grid, block, 0, s>>>((const uint16_t*)x, (uint16_t*)(ws + L.o_Yp), L.D, L.Dk, n);
     e = hipGetLastError();

@@ -267,18 +267,18 @@ __global__ __launch_bounds__(256) void pack_w13_padding_kernel(char* out, int gr
   constexpr int CH = Im::RB / 16;
   const int pad = NT1 * Im::NEUR - Fp;  // neurons per group that do not exist
   const int64_t total = (int64_t)groups * KS1 * pad * 2 * CH;
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= total) return;
-  const int pc = (int)(t % CH);
-  int64_t r = t / CH;
-  const int gu = (int)(r % 2);
-  r /= 2;
-  const int nin = Fp + (int)(r % pad);
-  r /= pad;
-  const int ks = (int)(r % KS1);
-  const int64_t ep = r / KS1;  // e * P + p
-  char* stage = out + ((ep * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
-  *(uint4*)(stage + (Im::row(nin) + gu * Im::UP) * Im::RB + pc * 16) = make_uint4(0, 0, 0, 0);
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+    const int pc = (int)(t % CH);
+    int64_t r = t / CH;
+    const int gu = (int)(r % 2);
+    r /= 2;
+    const int nin = Fp + (int)(r % pad);
+    r /= pad;
+    const int ks = (int)(r % KS1);
+    const int64_t ep = r / KS1;  // e * P + p
+    char* stage = out + ((ep * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
+    *(uint4*)(stage + (Im::row(nin) + gu * Im::UP) * Im::RB + pc * 16) = make_uint4(0, 0, 0, 0);
+  }
 }
 
 // inv[e][perm[e][pos]] = pos
@@ -313,7 +313,7 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
     const int pad = NT1 * W13Image<T, FULL>::NEUR - Fp, groups = (per_expert ? experts : 1) * P;
     if (pad > 0) {
       const int64_t total = (int64_t)groups * KS1 * pad * 2 * PackTile<T>::CH;
-      pack_w13_padding_kernel<T, FULL><<<dim3((unsigned)((total + 255) / 256)), block, 0, s>>>(out, groups, Fp, NT1, KS1);
+      pack_w13_padding_kernel<T, FULL><<<dim3((unsigned)blocks_of_256(total)), block, 0, s>>>(out, groups, Fp, NT1, KS1);
     }
   };
   auto w2_images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {

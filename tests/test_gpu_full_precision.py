@@ -182,3 +182,24 @@ def test_static_batch_in_pieces(D, F, P, E, K, F_sh, T, dtype):
     torch.cuda.synchronize()
     layer.close()
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
+
+
+def test_padded_copy_of_a_very_large_batch():
+    """A padded copy of x of more than 2^32 values (the most threads a launch may have): 1048448 tokens of 4100 values, 34 GB in all."""
+    import torch
+    import paper_2508_18376_amd as ds
+    gen = torch.Generator(device="cuda:0").manual_seed(14)
+    D, F, n, times = 4100, 4, 8191, 128
+    layer = ds.DualSparseLayer(d_model=D, d_ff=F, n_experts=1, top_k=1, n_part=1, max_tokens=n * times, dtype="bf16")
+    assert not layer.uses_mfma and n * times * 4128 > 2 ** 32
+    w = [torch.randn(1, *s, generator=gen, device="cuda:0").mul_(0.05).bfloat16() for s in ((D, F), (D, F), (F, D))]
+    layer.partition_weights(*w)
+    x = torch.randn(n, D, generator=gen, device="cuda:0").bfloat16()
+    tau = torch.zeros(1, 1, device="cuda:0")
+    ref = layer.forward(x, torch.zeros(n, 1, device="cuda:0"), tau).float()
+    y = layer.forward(x.repeat(times, 1), torch.zeros(n * times, 1, device="cuda:0"), tau)
+    torch.cuda.synchronize()
+    layer.close()
+    bound = 2.0 ** -7 * ref.abs() + 1e-5 * ref.square().mean().sqrt()  # two roundings to bf16 of sums that differ by 1e-5 x RMS
+    for part in (0, 1, times // 2, times - 1):
+        assert bool(((y[part * n:(part + 1) * n].float() - ref).abs() <= bound).all())
