@@ -1259,13 +1259,13 @@ __global__ __launch_bounds__(1024) void combine_slots_kernel(Layout L, const cha
   }
 }
 
-// any D (no vector access): one thread per output element
+// any D (no vector access): one thread per output element, from q0 on
 template <typename OutT>
-__global__ __launch_bounds__(256) void combine_scalar_kernel(Layout L, int T, const char* ws, OutT* y) {
+__global__ __launch_bounds__(256) void combine_scalar_kernel(Layout L, int T, const char* ws, OutT* y, int64_t q0) {
   const float* Yp = (const float*)(ws + L.o_Yp);
   const float* w = (const float*)(ws + L.o_w);
   const int32_t* pair_row = (const int32_t*)(ws + L.o_pair_row);
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t q = q0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (q >= (int64_t)T * L.D) return;
   const int t = (int)(q / L.D);
   const int d = (int)(q % L.D);
@@ -1332,10 +1332,12 @@ hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, 
     else DSMOE_COMBINE(16);
 #undef DSMOE_COMBINE
   } else {
-    int64_t n = (int64_t)T * L.D;
-    dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    if (L.y_f32) combine_scalar_kernel<float><<<grid, block, 0, s>>>(L, T, ws, (float*)y);
-    else combine_scalar_kernel<uint16_t><<<grid, block, 0, s>>>(L, T, ws, (uint16_t*)y);
+    const int64_t n = (int64_t)T * L.D, most = (int64_t)1 << 31;  // (a launch of 2^32 threads and more is silently cut short)
+    for (int64_t q0 = 0; q0 < n; q0 += most) {
+      const dim3 grid((unsigned)(((n - q0 < most ? n - q0 : most) + 255) / 256)), block(256);
+      if (L.y_f32) combine_scalar_kernel<float><<<grid, block, 0, s>>>(L, T, ws, (float*)y, q0);
+      else combine_scalar_kernel<uint16_t><<<grid, block, 0, s>>>(L, T, ws, (uint16_t*)y, q0);
+    }
   }
   return hipGetLastError();
 }

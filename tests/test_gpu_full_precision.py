@@ -184,14 +184,15 @@ def test_static_batch_in_pieces(D, F, P, E, K, F_sh, T, dtype):
     assert float((y - ref).abs().max()) <= 1e-5 * float(ref.square().mean().sqrt())
 
 
-def test_padded_copy_of_a_very_large_batch():
-    """A padded copy of x of more than 2^32 values (the most threads a launch may have): 1048448 tokens of 4100 values, 34 GB in all."""
+@pytest.mark.parametrize("D", [4100, 4101], ids=["padded_copy", "and_outputs_one_by_one"])
+def test_more_values_than_a_launch_has_threads(D):
+    """A padded copy of x, and outputs whose rows are not whole vectors, of more than 2^32 values: 1048448 tokens, 34 GB in all."""
     import torch
     import paper_2508_18376_amd as ds
     gen = torch.Generator(device="cuda:0").manual_seed(14)
-    D, F, n, times = 4100, 4, 8191, 128
+    F, n, times = 4, 8191, 128
     layer = ds.DualSparseLayer(d_model=D, d_ff=F, n_experts=1, top_k=1, n_part=1, max_tokens=n * times, dtype="bf16")
-    assert not layer.uses_mfma and n * times * 4128 > 2 ** 32
+    assert not layer.uses_mfma and n * times * 4128 > 2 ** 32 and (D % 4 == 0 or n * times * D > 2 ** 32)
     w = [torch.randn(1, *s, generator=gen, device="cuda:0").mul_(0.05).bfloat16() for s in ((D, F), (D, F), (F, D))]
     layer.partition_weights(*w)
     x = torch.randn(n, D, generator=gen, device="cuda:0").bfloat16()
