@@ -111,8 +111,8 @@ int dsmoe_uses_mfma(const dsmoe_ctx* ctx);
  *   sh_w1, sh_w3 device [n_shared][D][F_sh], sh_w2 device [n_shared][F_sh][D]; NULL iff n_shared == 0
  *   perm     device int32 [E_res][F]: perm[e][j] = ORIGINAL neuron placed at new position j;
  *            sub-expert p owns positions [p*F/P, (p+1)*F/P).  NULL = identity.
- *   packed_out device, dsmoe_packed_bytes(ctx) bytes: receives the weights in the library's
- *            kernel layout; inputs are not modified.
+ *   packed_out device, dsmoe_packed_bytes(ctx) bytes, 16-byte aligned: receives the weights in the
+ *            library's kernel layout; inputs are not modified.
  * Returns DSMOE_EPERM (packed_out contents then undefined) if perm is not a permutation.
  */
 int moe_partition_weights(dsmoe_ctx* ctx, const void* w1, const void* w3, const void* w2, const void* sh_w1,
@@ -135,7 +135,7 @@ int moe_route_and_mask(dsmoe_ctx* ctx, const float* logits, int32_t T, const flo
  * The whole layer: gating + mask, compacted per-expert row lists, grouped GEMM gate/up with
  * Swish*mul, grouped GEMM down over the kept partitions only, gate-weighted combine (Eq. 1-4 with
  * the dropped units of Sec. 4 removed).
- *   packed  device, written by moe_partition_weights for this ctx
+ *   packed  device, written by moe_partition_weights for this ctx (16-byte aligned)
  *   x       device [T][D] (cfg.dtype), logits device float [T][E], tau device float [E][P]
  *   y       device [T][D] (cfg.dtype, or float if cfg.y_fp32), fully overwritten; a token with every
  *           unit dropped gets exact zeros (plus the shared experts' output)

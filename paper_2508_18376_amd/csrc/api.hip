@@ -297,7 +297,7 @@ const char* dsmoe_strerror(int status) {
 int moe_partition_weights(dsmoe_ctx* ctx_, const void* w1, const void* w3, const void* w2, const void* sh_w1,
                           const void* sh_w3, const void* sh_w2, const int32_t* perm, void* packed_out, void* stream) {
   Ctx* ctx = reinterpret_cast<Ctx*>(ctx_);
-  if (!ctx || !w1 || !w3 || !w2 || !packed_out) return DSMOE_EINVAL;
+  if (!ctx || !w1 || !w3 || !w2 || !packed_out || ((uintptr_t)packed_out & 15) != 0) return DSMOE_EINVAL;
   const Layout& L = ctx->L;
   if (L.n_shared > 0 && (!sh_w1 || !sh_w3 || !sh_w2)) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
@@ -562,7 +562,7 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
   Ctx* ctx = reinterpret_cast<Ctx*>(ctx_);
   if (!ctx || T < 0 || !packed || !importance || !workspace || metric < 0 || metric > 3) return DSMOE_EINVAL;
   if (T > 0 && (!x || !logits)) return DSMOE_EINVAL;
-  if (((uintptr_t)workspace & 255) != 0) return DSMOE_EINVAL;
+  if (((uintptr_t)workspace & 255) != 0 || ((uintptr_t)packed & 15) != 0) return DSMOE_EINVAL;
   if (T > ctx->L.max_tokens) return DSMOE_EINVAL;
   Layout L = ctx->L;  // per-call boundary of the shared rows, as in the forward call
   L.tall_tiles = 0;   // the profiling variant of GEMM-1 has no tall form

@@ -182,6 +182,10 @@ def test_later_entry_points_validate_before_touching_the_gpu(lib):
     assert lib.moe_profile_importance(ctx, fake, fake, fake, 65, 0, fake, fake, None) == -1   # T > max_tokens
     assert lib.moe_profile_importance(ctx, fake, fake, fake, 4, 0, fake, odd, None) == -1     # workspace alignment
     assert lib.moe_profile_importance(ctx, fake, None, fake, 4, 0, fake, fake, None) == -1    # x missing
+    assert lib.moe_profile_importance(ctx, odd, fake, fake, 4, 0, fake, fake, None) == -1     # packed weights: 16-byte aligned
+    lib.moe_partition_weights.restype = ctypes.c_int
+    lib.moe_partition_weights.argtypes = [vp] * 10
+    assert lib.moe_partition_weights(ctx, fake, fake, fake, None, None, None, None, odd, None) == -1
     lib.moe_importance_to_perm.restype = ctypes.c_int
     lib.moe_importance_to_perm.argtypes = [vp, vp, vp, vp]
     assert lib.moe_importance_to_perm(ctx, None, fake, None) == -1
