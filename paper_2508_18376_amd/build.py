@@ -23,10 +23,13 @@ def _needs_build() -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
-# The MFMA GEMM kernels use the whole register file (256 accumulators + 256 others per lane).  A
-# spill to scratch memory inside a main loop makes the loop wait for every outstanding load each
-# time round, and a small edit of the kernel is enough to cause one: the build refuses it.
-NO_SCRATCH = {"gemm_mfma.hip": ("gemm1_mfma_kernel", "gemm2_mfma_kernel")}
+# The GEMM kernels wait for their loads by hand, and those of gemm_mfma.hip use the whole register file (256 accumulators +
+# 256 others per lane).  A spill to scratch memory inside a main loop makes the loop wait for every outstanding load each
+# time round, and a small edit of a kernel is enough to cause one: the build refuses it.
+NO_SCRATCH = {
+    "gemm_mfma.hip": ("gemm1_mfma_kernel", "gemm2_mfma_kernel", "gemm1_stream_kernel", "gemm2_stream_kernel"),
+    "gemm_full.hip": ("gemm1_full_kernel", "gemm2_full_kernel"),
+}
 
 
 def _scratch_users(remarks: str, kernels) -> list:

@@ -257,6 +257,10 @@ def test_build_refuses_register_spills_in_the_gemm_kernels():
     bad = build._scratch_users(remarks, build.NO_SCRATCH["gemm_mfma.hip"])
     assert len(bad) == 1 and "gemm1_mfma_kernel" in bad[0] and "20" in bad[0]
     assert build._scratch_users(remarks.replace(": 20 ", ": 0 "), build.NO_SCRATCH["gemm_mfma.hip"]) == []
+    for source in build.SOURCES:  # every kernel that multiplies tiles is among those looked at
+        with open(os.path.join(build.CSRC, source)) as f:
+            kernels = re.findall(r"__global__[^;{]*?\b(gemm\w+_kernel)\(", f.read())
+        assert sorted(set(kernels)) == sorted(build.NO_SCRATCH.get(source, ()))
 
 
 def test_header_is_plain_c(lib, tmp_path):
