@@ -4,6 +4,7 @@ Row counts around one row tile (an expert with one row tile is the only reader o
 with the non-temporal hint; with two, or with a short last tile taken along, they are not), around the blocks of 32 rows, and
 around the 64 tokens up to which a batch takes the streaming kernels.
 """
+import numpy as np
 import pytest
 
 from synth import make_layer
@@ -160,7 +161,6 @@ def test_router_token_blocks(T, D, E):
                                                    (64, 8, 2, 1, None), (65, 4, 2, 0, None)])
 def test_lists_of_batches_planned_in_one_launch(oracle, T, E, K, P, n_shared, window):
     # both sides of 64 tokens and of 64 experts, the three ways a workgroup routes (up to 8, 32 and 64 experts)
-    import numpy as np
     import torch
     from plan_cover import check_cover
     spec = spec_of(T=T, D=64, F=64 * P, E=E, K=K, P=P, n_shared=n_shared, F_sh=64, resident=window, seed=170)
@@ -207,3 +207,30 @@ def test_full_precision_halves_of_weight_tiles_on_a_resident_window(oracle, T, d
     layer.close()
     ref = oracle_forward(oracle, spec, t, tau)
     assert_output_close(to_host64(y, "f32"), ref, spec.dtype, y_fp32=True)
+
+
+@pytest.mark.parametrize("E,F,D,where", [(1, 32, 32, 0), (1, 32, 32, -1), (2, 96, 160, 9), (8, 1024, 2048, 2048 * 256 * 8 - 1), (8, 1024, 2048, -1),
+                                         (9, 1024, 2048, -8), (33, 1024, 2048, 4 * 2048 * 256 * 8 - 8), (33, 1024, 2048, -1)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_scale_of_the_largest_w2(E, F, D, where, offset):
+    """W2 is scaled by a power of two that its largest value decides, wherever that sits: in the four loads at a time, the single ones
+    behind them, or a tensor at any address.  Were it missed, it would overflow half precision."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(20)
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=1, n_part=1, max_tokens=E, y_fp32=True)
+    assert layer.uses_mfma
+    w1 = torch.randn(E, D, F, generator=gen, device="cuda:0").mul_(D ** -0.5).bfloat16()
+    w2 = torch.zeros(E * F * D + offset, dtype=torch.bfloat16, device="cuda:0")[offset:]
+    w2[::7] = 1e-3
+    w2[where] = 4096.0
+    layer.partition_weights(w1, w1, w2.view(E, F, D))
+    x = torch.randn(E, D, generator=gen, device="cuda:0").bfloat16()
+    y = layer.forward(x, 10.0 * torch.eye(E, device="cuda:0"), torch.zeros(E, 1, device="cuda:0"))
+    torch.cuda.synchronize()
+    layer.close()
+    e, f, d = np.unravel_index(where % (E * F * D), (E, F, D))
+    gate = (x[e].double() @ w1[e, :, f].double()).item()
+    g = 1.0 / (1.0 + (E - 1) * np.exp(-10.0))
+    want = g * gate * gate / (1.0 + np.exp(-gate)) * 4096.0
+    assert abs(float(y[e, d]) - want) <= 2e-2 * max(abs(want), 4096.0)
