@@ -91,7 +91,11 @@ typedef struct {
 int dsmoe_create(const dsmoe_config* cfg, dsmoe_ctx** out);
 int dsmoe_destroy(dsmoe_ctx* ctx);
 
-/* Bytes of the packed-weight buffer / of the workspace the caller must allocate (device). */
+/* Bytes of the packed-weight buffer / of the workspace the caller must allocate (device).
+ * The packed weights take the size of the weights plus padding: the matrix-core path pads a sub-expert to 128 neurons
+ * in W1 and W3, and D to 256 columns in W2; the full-precision path pads it to 64 neurons in W1 and W3 and to 32 in
+ * W2 and in the workspace's activations, and D to 32 (in W2 to 128 columns).  Sub-experts of a few neurons cost
+ * most: twice the weights for 33 neurons, eleven times for 5. */
 size_t dsmoe_packed_bytes(const dsmoe_ctx* ctx);
 size_t dsmoe_workspace_bytes(const dsmoe_ctx* ctx);
 

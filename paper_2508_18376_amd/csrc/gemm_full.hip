@@ -23,9 +23,9 @@
 // per compute unit, so that one streams while the other starts or ends an item.
 //
 // Measured, before (vector FMAs on 64 x 64 tiles with guarded loads) -> now:
-//   fp32, 64 experts of 2048 x 1024, 512 tokens top-8, 25 % dropped: GEMM-1 1250 -> 370 us (2.9 TB/s of weights), GEMM-2 545 -> 194 us
-//   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 207 us (4 TB/s), GEMM-2 1041 -> 215 us
-//   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 7 us, GEMM-2 33 -> 5 us (K split over several workgroups)
+//   fp32, 64 experts of 2048 x 1024, 512 tokens top-8, 25 % dropped: GEMM-1 1250 -> 375 us (2.9 TB/s of weights), GEMM-2 545 -> 189 us
+//   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 208 us (4 TB/s), GEMM-2 1041 -> 224 us
+//   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 6 us, GEMM-2 33 -> 4 us (K split over several workgroups)
 #include "common.h"
 
 namespace dsmoe {

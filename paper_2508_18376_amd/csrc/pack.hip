@@ -96,12 +96,12 @@ __device__ __forceinline__ uint16_t bf16_to_scaled_half(uint16_t b, float scale)
 // The MFMA stage images are made by transposing tiles of 32 source rows x 512 bytes through LDS: rows come in
 // as whole 512-byte segments (16 bytes per lane), image rows leave as 64-byte runs (four 16-byte chunks of
 // neighbouring lanes), so both directions move a tensor once and in wide pieces; bound by HBM.  Weights of 8
-// experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 835 us = 4.5 TB/s, W2 (1.88 GB) 390 us
-// = 4.8 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took 1295 and
+// experts of 4096 x 14336: W1 / W3 (3.76 GB read + written, random order) 835 us = 4.5 TB/s, W2 (1.88 GB) 430 us
+// = 4.4 TB/s.  (One thread per column with 32 2-byte loads, resp. per 16-byte chunk with eight of them, took 1295 and
 // 1181 us: 2.9 and 1.6 TB/s.)  W1 / W3 are read with the non-temporal hint (850 -> 835 us).  Nothing else is: the scattered
 // 64-byte runs need the caches to become whole lines (835 -> 900 us), and the hint on W2's rows or images gained nothing for
-// the pass and the first batch together.  (W2: 430 us since absmax_bf16_kernel, in front of it, leaves no part of W2 in the
-// last-level cache; that kernel gained more.)
+// the pass and the first batch together.  (W2 took 390 us while absmax_bf16_kernel, in front of it, still left a part of W2 in
+// the last-level cache; that kernel gained more.)
 constexpr int kTileStride = 128 + 2;  // dwords between tile rows in LDS: a wavefront reads 4 chunks x 16 column pairs (bf16) or
                                       // 8 chunks x 8 columns (fp32) at once, whose rows then lie on 64 different banks
 template <typename T>

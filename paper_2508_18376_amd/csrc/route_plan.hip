@@ -372,9 +372,10 @@ hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int3
 }
 
 // ------------------------------------------------------------------------------------- plan
-// Single-workgroup kernel: turns the bin histogram into row offsets, the row-tile table and the
-// two work lists of the grouped GEMMs.  Everything stays on the device: the GEMM grids are sized
-// for the worst case and read their item count from the counters this kernel writes.
+// Turns the bin histogram into row offsets, the row-tile table and the two work lists of the grouped
+// GEMMs: two workgroups, each of which works out the tables and writes one list (and a third for the row
+// lists of a batch that the kernel routes itself, see launch_small_plan).  Everything stays on the device: the
+// GEMM grids are sized for the worst case and read their item count from the counters this kernel writes.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanTilesLds = 2048;  // row tiles whose keep patterns fit in the plan kernel's LDS
 constexpr int kSmallPlanTokens = 64;  // tokens that one workgroup routes at once
@@ -978,7 +979,7 @@ template <int LANES>
 static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const RouteArgs& ra, hipStream_t s) {
   size_t sh = plan_lds_bytes(L);
   if (LANES != 0) sh += sizeof(int32_t) * (size_t)(T * L.K + L.E * L.P);
-  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: up to ~82 KB, above what a launch gets without asking
+  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: up to 92324 bytes (512, shared ones), above what a launch gets without asking
     static PerDeviceOnce once;
     hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES>, hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024); });
     if (e != hipSuccess) return e;
@@ -990,7 +991,7 @@ hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) { return
 
 // Routing, plan and scatter of a small batch in one launch: one workgroup routes 64 tokens at once, so each of three does it
 // for itself and they write the two work lists and the row lists side by side.  1 token on 64 experts: 18 us in three launches ->
-// 14; 64 tokens on 8 experts 24 -> 13; the 8 x 128 x 256 layer on 64 tokens 31 -> 26 us in all.
+// 14; 64 tokens on 8 experts 24 -> 16; the 8 x 128 x 256 layer on 64 tokens 31 -> 26 us in all.
 bool small_plan(const Layout& L, int T) { return T <= kSmallPlanTokens && L.E <= 64; }
 hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const float* tau, char* ws, hipStream_t s) {
   RouteArgs a = {};
