@@ -55,11 +55,6 @@ __device__ __forceinline__ uint32_t lds_byte(const char* p) {
   return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const char*)p);
 }
 
-__device__ __forceinline__ int xcd_run(int b) {  // runs of 32 consecutive items per XCD (see gemm_mfma.hip)
-  const int chunk = b >> 8, within = b & 255;
-  return (chunk << 8) + ((within & 7) << 5) + (within >> 3);
-}
-
 // One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
 // SUBS = 2: two wavefronts share 32 weight rows; each multiplies one half of every stage's K values, and the sums meet in
 // the first one (w < 2) at the end.
@@ -278,8 +273,9 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
 template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm1_full_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_run(blockIdx.x), sub = id % SUBS;
-  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[0]) return;
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n = counters[0] * SUBS, id = take_piece<true>(n, counters + 8, lds), sub = id % SUBS;
+  if (id >= n) return;
   const Item1 it = ((const Item1*)(ws + L.o_items1))[id / SUBS];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #define DSMOE_ROWS(N) gemm1_full_tile<T, N, SUBS>(L, it, sub, packed, x, x_row, ws, epi, lds, w, lane)
@@ -360,8 +356,9 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
 template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_run(blockIdx.x), sub = id % SUBS;
-  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[1]) return;
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n = counters[1] * SUBS, id = take_piece<true>(n, counters + 9, lds), sub = id % SUBS;
+  if (id >= n) return;
   const Item2 it = ((const Item2*)(ws + L.o_items2))[id / SUBS];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #define DSMOE_ROWS(NONFINITE)                                                                              \
@@ -429,7 +426,7 @@ hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const v
     x_row = L.Dk * elem;
   }
   const int subs = full_parts(L, T);
-  const dim3 block(256), grid((subs * items1_bound(L, T) + 255) & ~255);  // whole chunks of 256: the XCD order is a bijection on them
+  const dim3 block(256), grid(piece_blocks(true, subs * items1_bound(L, T)));
 #define DSMOE_LAUNCH(TYPE, SUBS) gemm1_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi)
   if (elem == 4 && subs == 2) DSMOE_LAUNCH(float, 2);
   else if (elem == 4) DSMOE_LAUNCH(float, 1);
@@ -444,7 +441,7 @@ hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* w
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
   const int subs = full_parts(L, T);
-  const dim3 block(256), grid((subs * items2_bound(L, T) + 255) & ~255);
+  const dim3 block(256), grid(piece_blocks(true, subs * items2_bound(L, T)));
 #define DSMOE_LAUNCH(TYPE, SUBS) gemm2_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, ws)
   if (L.dtype == DSMOE_F32 && subs == 2) DSMOE_LAUNCH(float, 2);
   else if (L.dtype == DSMOE_F32) DSMOE_LAUNCH(float, 1);

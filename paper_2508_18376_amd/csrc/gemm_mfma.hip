@@ -139,14 +139,6 @@ __device__ __forceinline__ int fresh_tid(int w) {
   return (w << 6) | lane;
 }
 
-// XCD-aware order: consecutive block ids land on different XCDs (round robin over 8), so give
-// each XCD a run of 32 consecutive work items out of every 256: items that share a weight tile
-// then share an L2.
-__device__ __forceinline__ int xcd_remap(int b) {
-  const int chunk = b >> 8, within = b & 255;
-  return (chunk << 8) + ((within & 7) << 5) + (within >> 3);
-}
-
 // Operand fragments of one K substep (16 values of K): I blocks of 32 A rows, J blocks of 32 B rows.
 template <int I, int J>
 struct Frags {
@@ -606,8 +598,9 @@ __device__ __forceinline__ void gemm1_ragged_item(const G1Args& g, char* lds, in
 template <bool PROFILE>
 __global__ __launch_bounds__(256) void gemm1_mfma_kernel(Layout L, int T, const char* packed, const uint16_t* x, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int item_id = xcd_remap(blockIdx.x);
-  if (item_id >= ((const int32_t*)(ws + L.o_counters))[0]) return;  // past the end of the list
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n_items = counters[0], item_id = take_piece<true>(n_items, counters + 8, lds);
+  if (item_id >= n_items) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G1Args g;
   gemm1_setup(g, item_id, L, T, packed, x, ws, epi, lds, tid, w);
@@ -832,8 +825,9 @@ __device__ __forceinline__ void gemm2_ragged_item(const G2Args& g, char* lds, in
 template <bool NT, bool YH>
 __global__ __launch_bounds__(256) void gemm2_mfma_kernel(Layout L, int T, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int item_id = xcd_remap(blockIdx.x);
-  if (item_id >= ((const int32_t*)(ws + L.o_counters))[1]) return;  // past the end of the list
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n_items = counters[1], item_id = take_piece<true>(n_items, counters + 9, lds);
+  if (item_id >= n_items) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G2Args g;
   gemm2_setup(g, item_id, L, T, packed, ws, lds, tid, w);
@@ -871,8 +865,9 @@ __device__ __forceinline__ void gemm1_stream_rows(const G1Args& g, char* lds, in
 template <int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm1_stream_kernel(Layout L, int T, const char* packed, const uint16_t* x, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_remap(blockIdx.x), sub = id % SUBS;
-  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[0]) return;  // past the end of the list
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n = counters[0] * SUBS, id = take_piece<false>(n, counters + 8, lds), sub = id % SUBS;
+  if (id >= n) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G1Args g;
   gemm1_setup(g, id / SUBS, L, T, packed, x, ws, 0, lds, tid, w);
@@ -898,8 +893,9 @@ __device__ __forceinline__ void gemm2_stream_item(const G2Args& g, char* lds, in
 template <int SUBS, bool YH>
 __global__ __launch_bounds__(256, 2) void gemm2_stream_kernel(Layout L, int T, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  const int id = xcd_remap(blockIdx.x), sub = id % SUBS;
-  if (id / SUBS >= ((const int32_t*)(ws + L.o_counters))[1]) return;  // past the end of the list
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  const int n = counters[1] * SUBS, id = take_piece<false>(n, counters + 9, lds), sub = id % SUBS;
+  if (id >= n) return;  // past the end of the list
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G2Args g;
   gemm2_setup(g, id / SUBS, L, T, packed, ws, lds, tid, w);
@@ -945,19 +941,18 @@ static bool stream_halves(int items) {
   return items > slots / 4 && rest > 0 && rest <= slots / 2;
 }
 
-// grids are whole chunks of 256 blocks so that the XCD remap is a bijection
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
   if (L.stream) {
     const bool halves = stream_halves(stream_experts(L, T) * L.P * L.NT1 + L.NT1_sh);
-    const dim3 grid(((halves ? 2 : 1) * items1_bound(L, T) + 255) & ~255), block(256);
+    const dim3 grid(piece_blocks(false, (halves ? 2 : 1) * items1_bound(L, T))), block(256);
     if (halves) gemm1_stream_kernel<2><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
     else gemm1_stream_kernel<1><<<grid, block, kStreamLds, s>>>(L, T, packed, (const uint16_t*)x, ws);
     return hipGetLastError();
   }
-  const int g1 = (items1_bound(L, T) + 255) & ~255;
+  const int g1 = piece_blocks(true, items1_bound(L, T));
   const uint16_t* xp = (const uint16_t*)x;
   if (epi == 0) gemm1_mfma_kernel<false><<<dim3(g1), dim3(256), kLdsBytes, s>>>(L, T, packed, xp, ws, 0);
   else gemm1_mfma_kernel<true><<<dim3(g1), dim3(256), kLdsBytes, s>>>(L, T, packed, xp, ws, epi);
@@ -970,7 +965,7 @@ hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* w
   if (e != hipSuccess) return e;
   if (L.stream) {
     const bool halves = stream_halves((stream_experts(L, T) + shared_tiles(L, T)) * L.ND2);
-    const dim3 grid(((halves ? 2 : 1) * items2_bound(L, T) + 255) & ~255), block(256);
+    const dim3 grid(piece_blocks(false, (halves ? 2 : 1) * items2_bound(L, T))), block(256);
 #define DSMOE_LAUNCH(SUBS, YH) gemm2_stream_kernel<SUBS, YH><<<grid, block, kStreamLds, s>>>(L, T, packed, ws)
     if (halves && L.yp_half) DSMOE_LAUNCH(2, true);
     else if (halves) DSMOE_LAUNCH(2, false);
@@ -979,7 +974,7 @@ hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* w
 #undef DSMOE_LAUNCH
     return hipGetLastError();
   }
-  const int g2 = (items2_bound(L, T) + 255) & ~255;
+  const int g2 = piece_blocks(true, items2_bound(L, T));
   // per-pair outputs of this batch, at most; beyond the size of the last-level cache they stream
   const int64_t out_bytes = (int64_t)T * (L.K + (L.n_shared > 0 ? 1 : 0)) * L.D * (L.yp_half ? 2 : 4);
   const bool nt = out_bytes > kStreamOutBytes;

@@ -843,6 +843,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     }
     __syncthreads();  // first_split_tile is final
     if (tid == 0) {
+      counters[9] = 0;  // see take_piece
       counters[1] = first_split + (W2n - first_split) * nsplit;
       counters[2] = total_tiles - total_short;  // row tiles that have GEMM-2 items
       counters[3] = nsplit;
@@ -972,7 +973,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     __syncthreads();
     total_slots = slots_all;
   }
-  if (tid == 0) counters[0] = total_slots;
+  if (tid == 0) {
+    counters[0] = total_slots;
+    counters[8] = 0;  // see take_piece
+  }
 }
 
 template <int LANES>
