@@ -247,18 +247,21 @@ __device__ __forceinline__ float row_sum(float v) {  // every step adds two part
 // The piece of a list of n pieces of work that this workgroup takes (n: none).  Consecutive workgroups land on different XCDs
 // (round robin over 8), so each XCD gets a run of 32 consecutive pieces out of every 256 (the last ones: eight equal runs): pieces
 // that share a weight tile then share an L2.
-// FREE: the XCDs' shares are never equally long, so of a list of more than one round the last 128 to 383 pieces are handed out one
+// FREE: the XCDs' shares are never equally long, so of a list of several rounds the last 128 to 383 pieces are handed out one
 // by one (*taken counts them; twice as many workgroups ask, so that an XCD that is ahead takes over from the others).  Runs of 32 to
 // the end left whole rounds to the first XCDs: 834 items of GEMM-1 (333 tokens on 64 + 2 experts of 2048 x 1408) were 128 each for two
 // XCDs and 96 for the others, the former done after 166 us, the latter after 122.  Layers of the sizes in perf/cases.py gain 0.5 - 1.5 %
 // (8192 tokens on 64 experts of 2048 x 1024 724 -> 715 us, 16384 on two of 8 of 4096 x 14336 1961 -> 1942), 1 token on the former 49.7 ->
-// 47.8.  The dealt part is whole runs: with the last 128 or 256 free exactly, its last runs are cut at other places than the items that
-// share a tile, and half of the gain is lost.  The streaming kernels, two workgroups to a unit, gain nothing from free pieces.
+// 47.8.  Below kFreeFrom pieces the free ones are too large a part of the list for what their neighbours could share: free from 257
+// on, 128 / 512 tokens on the former lost 162 -> 167 and 186 -> 193 us.  The dealt part is whole runs: with the last 128 or 256 free
+// exactly, its last runs are cut at other places than the items that share a tile, and half of the gain is lost.  The streaming
+// kernels, two workgroups to a unit, gain nothing from free pieces.
 // lds: scratch of the workgroup, free again on return.
+constexpr int kFreeFrom = 1024;
 template <bool FREE>
 __device__ __forceinline__ int take_piece(int n, int32_t* taken, char* lds) {
   const int b = blockIdx.x, base = b & ~255, x = b & 7, i = (b & 255) >> 3;
-  const int dealt = !FREE || n <= 256 ? n : n < 512 ? 256 : (n - 128) & ~255;
+  const int dealt = !FREE || n < kFreeFrom ? n : (n - 128) & ~255;
   if (b < dealt) {
     const int left = min(dealt - base, 256), q = left >> 3, r = left & 7;
     return base + x * q + min(x, r) + i;
@@ -271,7 +274,7 @@ __device__ __forceinline__ int take_piece(int n, int32_t* taken, char* lds) {
   return id < n ? id : n;
 }
 // workgroups that take_piece<FREE> needs for at most n pieces
-inline int piece_blocks(bool free, int n) { return n + (free && n > 256 ? 384 : 0); }
+inline int piece_blocks(bool free, int n) { return n + (free && n >= kFreeFrom ? 384 : 0); }
 
 // Position of the 16-byte chunk `chunk` (0..3) of row `row` inside a [rows][32] bf16 LDS tile
 // (64-byte rows).  The chunks of a row are XOR-rotated by bits 2..3 of the row so that an MFMA

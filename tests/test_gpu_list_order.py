@@ -1,5 +1,5 @@
-"""GPU: the order in which the work lists are handed out, where it changes: lists of about one round of workgroups, of up to two,
-and beyond (the last pieces are then handed out one by one), and layers whose shared experts have one row tile or several.
+"""GPU: the order in which the work lists are handed out, where it changes: lists of about one round of workgroups, and of so
+many that the last pieces are handed out one by one, and layers whose shared experts have one row tile or several.
 """
 import numpy as np
 import pytest
@@ -29,7 +29,7 @@ def _check(oracle, spec, tau_kind, cover=True):
     return plan
 
 
-@pytest.mark.parametrize("dtype,n", [("bf16", n) for n in (255, 256, 257, 263, 511, 512, 639, 640, 641, 900)] + [("f32", n) for n in (256, 259, 515, 700)])
+@pytest.mark.parametrize("dtype,n", [("bf16", n) for n in (255, 256, 257, 263, 511, 900, 1023, 1024, 1151, 1152, 1300)] + [("f32", n) for n in (256, 259, 1027, 1400)])
 def test_pieces_of_a_list_of_n_items(oracle, dtype, n):
     # one expert, one row tile of 130 rows (fp32: three), n neuron tiles
     rows, tiles = (130, 1) if dtype == "bf16" else (160, 3)
