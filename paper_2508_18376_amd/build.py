@@ -28,7 +28,7 @@ def _needs_build() -> bool:
 # time round, and a small edit of a kernel is enough to cause one: the build refuses it.
 NO_SCRATCH = {
     "gemm_mfma.hip": ("gemm1_mfma_kernel", "gemm2_mfma_kernel", "gemm1_stream_kernel", "gemm2_stream_kernel"),
-    "gemm_full.hip": ("gemm1_full_kernel", "gemm2_full_kernel"),
+    "gemm_full.hip": ("gemm1_full_kernel", "gemm2_full_kernel", "gemm1_wide_kernel", "gemm2_wide_kernel"),
 }
 
 

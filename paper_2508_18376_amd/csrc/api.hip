@@ -75,6 +75,9 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
   L.NT1 = cdiv(L.Fp, neur);
   L.NT1_sh = L.n_shared > 0 ? cdiv(L.F_shT, neur) : 0;
   L.ND2 = cdiv(L.D, L.BN2);
+  L.NI1 = L.NT1;
+  L.NI1_sh = L.NT1_sh;
+  L.NI2 = L.ND2;
   L.split_items = L.mfma ? kSplitItems : kFullSplitItems;
   // GEMM-2 item order.  Long contractions (a 256-column tile of W2 of 1 MiB or more) do not stay in an
   // XCD's L2 from one row tile to the next: the row tiles that share a column tile are then made
@@ -348,6 +351,14 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
   // and 333 on 64 + 2 of 2048 x 1408 267 -> 254 under even routing, but 100 of the former 93 -> 114 and 200 on 8 of 4096 x 14336
   // top-2 511 -> 652 with popularity rank^-1.2.
   if (L.mfma && T <= kStreamRows) L.stream = 1;
+  if (!L.mfma && full_wide(L, T)) {  // two weight images to a tile: fewer and larger tiles in the same arrays
+    L.wide = 1;
+    L.NT1 = cdiv(L.NI1, 2);
+    L.NT1_sh = cdiv(L.NI1_sh, 2);
+    L.ND2 = cdiv(L.NI2, 2);
+    L.BN2 = 2 * kFullBN2;
+    L.pool_tiles /= 2;
+  }
   L.sh_rows = L.n_shared > 0 ? (int)align_up(T, L.BM) : 0;
   ctx->last_sh_rows = L.sh_rows;
   const float* logits = logits_buf;

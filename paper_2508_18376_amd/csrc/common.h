@@ -51,6 +51,7 @@ constexpr int kStageBytes = 256 * kBK * 2;  // one operand tile of one stage (bf
 constexpr int kFullBM = 64;
 constexpr int kFullNeur = 64;
 constexpr int kFullBN2 = 128;
+constexpr int kFullRow = 64;  // bytes of a weight row in a stage of the packed weights
 constexpr int kFullRows = kFullBM + kTallExtra;
 constexpr int kFullSplitItems = 512;  // two GEMM-2 workgroups per compute unit
 
@@ -89,6 +90,8 @@ struct Layout {
   int32_t BM;                 // row tile height
   int32_t NT1, NT1_sh;        // neuron tiles per partition (routed / shared)
   int32_t ND2;                // output column tiles of GEMM-2
+  int32_t wide;               // full-precision path, set per call: tiles of two weight images (NT1, NT1_sh, ND2, BN2 are then those of such tiles)
+  int32_t NI1, NI1_sh, NI2;   // full-precision path: weight images of a partition (routed / shared), and of W2
   int32_t nsub, nbins;        // sort bins: E_res * nsub
   int32_t sh_rows;            // rows of the shared region (multiple of BM), first in the row space: the context holds the
                               // capacity for max_tokens, the copy a call hands to its kernels the boundary for its T
@@ -180,6 +183,7 @@ hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s);
 hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, void* y, hipStream_t s);
 // epi: what GEMM-1 stores per (row, neuron): 0 = Swish(gate)*up (the layer), 1..4 = the profiling
 // metrics Swish(gate), |Swish(gate)|, Swish(gate)*up, |Swish(gate)*up|
+bool full_wide(const Layout& L, int T);
 hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
 hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s);
