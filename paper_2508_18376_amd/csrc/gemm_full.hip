@@ -399,6 +399,10 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
 }
 
 // ------------------------------------------------------------------------------------- two images to a tile
+// Barrier behind which a stage may be overwritten: this wavefront's LDS reads have arrived.  (Where two stages are multiplied between
+// the same two ends of a loop, the compiler would let reads of the first one cross the barrier of the second.)
+__device__ __forceinline__ void read_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // The product of both images of a tile (2 x 128 weight rows) with NJ blocks of 32 pair rows, fp32 operands cut into bf16 parts (see
 // the top).  A stage is 64 bytes of every weight row: 32 bf16 or 16 fp32 values of K.
 template <int WE, int XE, int NJ>
@@ -452,7 +456,7 @@ struct WideTile {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         wait_loads<(NS - 2) * NL>();  // stage st + g has landed (for this wavefront; the barrier makes it so for all)
-        asm volatile("s_barrier" ::: "memory");
+        read_barrier();
         issue(st + g + NS - 1);       // into the slot of the stage before, which every wavefront has finished reading
         multiply<SAFE>(lds + ((st + g) % NS) * SB, sum, g, w, lane);
       }
@@ -465,12 +469,12 @@ struct WideTile {
         if (left >= NS - 2) wait_loads<(NS - 2) * NL>();
         else if (NS > 3 && left == 1) wait_loads<NL>();
         else wait_loads<0>();
-        asm volatile("s_barrier" ::: "memory");
+        read_barrier();
         if (left >= NS - 1) issue(st + g + NS - 1);
         multiply<SAFE>(lds + ((st + g) % NS) * SB, sum, g, w, lane);
       }
     }
-    asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
+    read_barrier();  // every wavefront is done reading the last stage
   }
 
   // run(), and where fp32 operands were cut and some sum came out infinite or NaN, again in the form that is right for every value
