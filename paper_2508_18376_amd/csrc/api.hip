@@ -577,6 +577,9 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
   if (T > ctx->L.max_tokens) return DSMOE_EINVAL;
   Layout L = ctx->L;  // per-call boundary of the shared rows, as in the forward call
   L.tall_tiles = 0;   // the profiling variant of GEMM-1 has no tall form
+  // No items for the shared experts: only routed ones are profiled.  (Items that the kernel left at once, first in the list, emptied the
+  // shares of the first XCDs, and the others had a round more.)
+  L.NT1_sh = 0;
   L.sh_rows = L.n_shared > 0 ? (int)align_up(T, L.BM) : 0;
   ctx->last_sh_rows = L.sh_rows;
   hipStream_t s = (hipStream_t)stream;

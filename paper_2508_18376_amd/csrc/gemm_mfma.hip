@@ -604,8 +604,6 @@ __global__ __launch_bounds__(256) void gemm1_mfma_kernel(Layout L, int T, const 
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   G1Args g;
   gemm1_setup(g, item_id, L, T, packed, x, ws, epi, lds, tid, w);
-  if (PROFILE && g.sh) return;  // importance is profiled for the routed experts only
-
   if (g.it.half) {
     if (!PROFILE && g.it.once) gemm1_half_item<PROFILE, !PROFILE>(g, lds, w);
     else gemm1_half_item<PROFILE, false>(g, lds, w);
