@@ -171,3 +171,19 @@ def test_perm_at_the_edges_of_the_rank_kernel(oracle, F):
     perm = layer.importance_to_perm(to_dev(imp)).cpu().numpy()
     np.testing.assert_array_equal(perm, oracle.perm_from_importance(imp.astype(np.float64)))
     layer.close()
+
+
+@pytest.mark.parametrize("dtype,T", [("bf16", 40), ("bf16", 700), ("f32", 200)])
+def test_shared_experts_are_not_profiled(oracle, dtype, T):
+    """Shared experts of one row tile and of several: the same sums as without them, and no items of theirs in GEMM-1's list."""
+    import torch
+    spec = spec_of(T=T, n_shared=2, F_sh=192, dtype=dtype, seed=38)
+    t = make_layer(spec)
+    imp_ref, abs_ref = oracle.importance(t["x"], t["logits"], t["w1"], t["w3"], spec.K, 3)
+    t["perm"] = None
+    layer, dev = make_gpu_layer(spec, t)
+    got = layer.profile_importance(dev["x"], dev["logits"], 3).cpu().numpy().astype(np.float64)
+    items = layer.plan(T)["items1"].cpu().numpy()
+    layer.close()
+    assert len(items) and (items[:, 2] < spec.E).all()
+    assert np.all(np.abs(got - imp_ref) <= IMP_TOL * abs_ref + 1e-6 * abs_ref.max())
