@@ -295,7 +295,7 @@ int moe_thresholds_for_drop_rate(dsmoe_ctx* ctx, const float* logits, int32_t T,
  *  13 work list of the second grouped GEMM, counters[1] records of 8 int32: first row, rows, expert, output column
  *     tile, bit mask of the partitions it sums over, first K stage and number of K stages inside every such
  *     partition, 0 or 1 + the partial-output tile it writes instead of the rows of the per-pair output
- * (fields 12 and 13 describe the lists of the matrix-core path and of the full-precision path alike; full-precision batches
+ * (fields 12 and 13 describe the lists of the matrix-core path and of the full-precision path alike; full-precision bf16 batches
  *  of many rows on layers of many experts count tiles of two weight images: 128 neurons, resp. 256 output columns)
  */
 #define DSMOE_PLAN_FIELDS 14

@@ -51,7 +51,6 @@ constexpr int kStageBytes = 256 * kBK * 2;  // one operand tile of one stage (bf
 constexpr int kFullBM = 64;
 constexpr int kFullNeur = 64;
 constexpr int kFullBN2 = 128;
-constexpr int kFullRow = 64;  // bytes of a weight row in a stage of the packed weights
 constexpr int kFullRows = kFullBM + kTallExtra;
 constexpr int kFullSplitItems = 512;  // two GEMM-2 workgroups per compute unit
 
@@ -90,7 +89,7 @@ struct Layout {
   int32_t BM;                 // row tile height
   int32_t NT1, NT1_sh;        // neuron tiles per partition (routed / shared)
   int32_t ND2;                // output column tiles of GEMM-2
-  int32_t wide;               // full-precision path, set per call: tiles of two weight images (NT1, NT1_sh, ND2, BN2 are then those of such tiles)
+  int32_t wide;               // full-precision path, set per call (bf16 layers): tiles of two weight images (NT1, NT1_sh, ND2, BN2 are then those of such tiles)
   int32_t NI1, NI1_sh, NI2;   // full-precision path: weight images of a partition (routed / shared), and of W2
   int32_t nsub, nbins;        // sort bins: E_res * nsub
   int32_t sh_rows;            // rows of the shared region (multiple of BM), first in the row space: the context holds the

@@ -4,8 +4,8 @@
 //   GEMM-1  H[row][p*Fpk + j] = Swish(x_row . W1[:, j]) * (x_row . W3[:, j])      (Eq. 4, gate/up)
 //   GEMM-2  Yp[row][d] = sum over kept partitions p, neurons j of H[row][p*Fpk + j] * W2[p*Fpk + j][d]
 // Same work lists and row lists as the other path, with tiles of 64 rows (up to 128 where an item takes the expert's
-// short last tile along) x 64 neurons, resp. x 128 output columns: a weight image of 128 rows (see pack.hip); in large batches on
-// many experts two images (full_wide).
+// short last tile along) x 64 neurons, resp. x 128 output columns: a weight image of 128 rows (see pack.hip); in large batches of
+// bf16 layers of many experts two images (full_wide).
 //
 // Matrix instructions: fp32 layers multiply with v_mfma_f32_32x32x2_f32 (the precision of an fmaf chain, 256 flop
 // per clock and compute unit, the chip's fp32 peak of ~155 TFLOP/s; without packed fp32 the vector units reach
@@ -15,14 +15,11 @@
 // bits of H at 5 x the rate of the fp32 instruction.  mid and lo can be zero: layers with an infinity or NaN in W2 (the packed
 // weights say so) leave those weights out of the two smaller products.
 //
-// Tiles of two images cut every fp32 operand, also the fp32 layers' weights and x, and multiply the parts of both in six
-// instructions, 2.7 x the rate of the fp32 one (the three products left out are below 2^-22 of the whole).  Cutting eight values takes
-// 44 vector instructions, 176 cycles: with one image to a tile that was the limit (560 us where the fp32 instructions took 520).  The
-// bf16 instruction cuts its sums off towards zero, so the products of 32 values of K are summed on their own, the small ones
-// first, and join the tile's sums by rounded additions.  Distance of fp32 layers from 64 bits (2-norms; N(0, 1) tokens, weights of
-// deviation 0.02, 512 tokens on 64 experts of 2048 x 1024) 1.4e-6 -> 3.7e-7; all values of one sign 2.1e-7 -> 1.5e-7 (6e-6 without the
-// rounded additions).  A tile in which some sum comes out infinite or NaN is computed again without cutting (fp32 instructions),
-// resp. without infinite weights in the smaller products.
+// Tiles of two images (bf16 layers) read the pair rows and cut fp32 activations half as often; the sums are the same bit for bit.  There a tile in
+// which some sum comes out infinite or NaN is computed again without infinite weights in the smaller products.
+// fp32 layers keep single images and the fp32 instruction: six products of bf16 parts of both operands are 2.7 x as fast (512 tokens on 64 experts of
+// 2048 x 1024 559 -> 503 us), but they leave products of up to 2^-21 out and the bf16 instruction cuts its sums off towards zero, so that sums
+// carried by one term are less exact than fp32 (2.6e-8 -> 6.5e-8), as are products of values below 2^-110.
 //
 // A workgroup is 4 wavefronts; wavefront w owns the weight rows 32 w .. 32 w + 31 of the tile's 128 and multiplies them
 // with all pair rows, so a tile of r rows costs ceil(r/32) blocks.  The 32 weight rows of a GEMM-1 wavefront are the gate
@@ -36,11 +33,7 @@
 //   fp32, 64 experts of 2048 x 1024, 512 tokens top-8, 25 % dropped: GEMM-1 1250 -> 375 us (2.9 TB/s of weights), GEMM-2 545 -> 189 us
 //   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 208 us (4 TB/s), GEMM-2 1041 -> 224 us
 //   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 6 us, GEMM-2 33 -> 4 us (K split over several workgroups)
-// and with tiles of two images, the whole layer: fp32, 300 / 400 / 512 tokens of the first 400 -> 340, 474 -> 370, 505 -> 460 us; 777
-// tokens of the second 430 -> 395 (GEMM-2 224 -> 160).  512 fp32 tokens fill the chip with one round of 512 items of unequal speed: a
-// compute unit idles 31 % of it, the matrix cores work 28 %.  Tried there: workgroups that stay for item after item with the next
-// item's loads under the epilogue (no gain: while one starts, the others stream faster), and rests of a cut by two-element
-// dot products (fewer instructions, but 477 -> 540 us).
+// and with tiles of two images, the whole layer: 777 tokens of the second 431 -> 399 (GEMM-2 224 -> 150).
 #include "common.h"
 
 namespace dsmoe {
@@ -76,36 +69,36 @@ __device__ __forceinline__ uint32_t lds_byte(const char* p) {
   return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const char*)p);
 }
 
-  // eight fp32 values as sums of three bf16 values each: the top 16 bits, the top 16 bits of the (exact) rest, the rest
-  // CLAMP: an infinite value leaves NaN as the rest: it is clamped (no finite value has a rest beyond 2^120), so that the first part decides
-  template <bool CLAMP>
-  __device__ __forceinline__ void split3(const f32x4& v0, const f32x4& v1, u32x4 (&part)[3]) {
-    float r[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+// eight fp32 values as sums of three bf16 values each: the top 16 bits, the top 16 bits of the (exact) rest, the rest
+// CLAMP: an infinite value leaves NaN as the rest: it is clamped (no finite value has a rest beyond 2^120), so that the first part decides
+template <bool CLAMP>
+__device__ __forceinline__ void split3(const f32x4& v0, const f32x4& v1, u32x4 (&part)[3]) {
+  float r[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < 3; ++k) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        part[k][i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302);
-      if (k < 2) {
+    for (int i = 0; i < 4; ++i)
+      part[k][i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302);
+    if (k < 2) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          r[i] -= __uint_as_float(__float_as_uint(r[i]) & 0xffff0000u);
-          if (CLAMP && k == 0) r[i] = __builtin_amdgcn_fmed3f(r[i], -1.4e36f, 1.4e36f);
-        }
+      for (int i = 0; i < 8; ++i) {
+        r[i] -= __uint_as_float(__float_as_uint(r[i]) & 0xffff0000u);
+        if (CLAMP && k == 0) r[i] = __builtin_amdgcn_fmed3f(r[i], -1.4e36f, 1.4e36f);
       }
     }
   }
+}
 
-  // eight weights with zeros in place of infinities and NaN
-  __device__ __forceinline__ bf16x8 finite_only(const bf16x8& a) {
-    u32x4 v = __builtin_bit_cast(u32x4, a);
+// eight weights with zeros in place of infinities and NaN
+__device__ __forceinline__ bf16x8 finite_only(const bf16x8& a) {
+  u32x4 v = __builtin_bit_cast(u32x4, a);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if ((v[i] & 0x7f80u) == 0x7f80u) v[i] &= 0xffff0000u;
-      if ((v[i] & 0x7f800000u) == 0x7f800000u) v[i] &= 0xffffu;
-    }
-    return __builtin_bit_cast(bf16x8, v);
+  for (int i = 0; i < 4; ++i) {
+    if ((v[i] & 0x7f80u) == 0x7f80u) v[i] &= 0xffff0000u;
+    if ((v[i] & 0x7f800000u) == 0x7f800000u) v[i] &= 0xffffu;
   }
+  return __builtin_bit_cast(bf16x8, v);
+}
 
 // One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
 // SUBS = 2: two wavefronts share 32 weight rows; each multiplies one half of every stage's K values, and the sums meet in
@@ -141,7 +134,7 @@ struct FullTile {
       next(xo, wo);
       const uint32_t slot = base + (uint32_t)(st % NS) * SB;
 #pragma unroll
-      for (int q = 0; q < NW; ++q) dma16g(wsrc + wo + q * (4096 * (WE == 4 ? SUBS : 1)), slot + q * 4096);
+      for (int q = 0; q < NW; ++q) dma16g(wsrc + wo + q * 4096, slot + q * 4096);
 #pragma unroll
       for (int q = 0; q < NX; ++q) dma16g(rowp[q] + xo, slot + (NW + q) * 4096);
     };
@@ -191,13 +184,13 @@ struct FullTile {
   __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
     const int r32 = lane & 31, h = lane >> 5;
     const int k0 = SUBS == 2 ? w >> 1 : 0;  // this wavefront's half of the stage
-    const char* wrow = stage + (w % (4 / SUBS) * 32 + r32) * WR;  // (bf16)
+    const char* wrow = stage + (w % (4 / SUBS) * 32 + r32) * WR;
     const char* xrow = stage + NW * 4096 + r32 * XR;
     if constexpr (WE == 4) {  // fp32 x fp32: chunk 2s + h of a row holds K values 8s + 4h .. 8s + 4h + 3
 #pragma unroll
       for (int s0 = 0; s0 < 4 / SUBS; ++s0) {
         const int s = s0 + k0 * 2;
-        const f32x4 a = *(const f32x4*)(stage + (s >> 1) * (WROWS * kFullRow) + (w % (4 / SUBS) * 32 + r32) * kFullRow + swz_chunk(r32, 2 * (s & 1) + h) * 16);
+        const f32x4 a = *(const f32x4*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
         f32x4 b[NJ];
 #pragma unroll
         for (int j = 0; j < NJ; ++j) b[j] = *(const f32x4*)(xrow + j * 32 * XR + swz_full<XCH>(r32, 2 * s + h) * 16);
@@ -251,7 +244,7 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
   const int KS = L.Dk / kBK;
   const int32_t* row_token = (const int32_t*)(ws + L.o_row_token) + it.row0;
   const uint8_t* row_bits = (const uint8_t*)(ws + L.o_row_bits) + it.row0;
-  const char* wsrc = packed + (sh ? L.p_sw13 : L.p_w13) + (((int64_t)(sh ? 0 : it.e * L.P + it.p) * NI1 + it.jt) * KS) * (128 * Tile::WR) + sub * (Tile::WROWS * kFullRow) + tid * 16;
+  const char* wsrc = packed + (sh ? L.p_sw13 : L.p_w13) + (((int64_t)(sh ? 0 : it.e * L.P + it.p) * NI1 + it.jt) * KS) * (128 * Tile::WR) + sub * (Tile::WROWS * Tile::WR) + tid * 16;
   const char* rowp[Tile::NX];
 #pragma unroll
   for (int i = 0; i < Tile::NX; ++i) {
@@ -320,7 +313,7 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
   const int ld = sh ? L.Fsk : L.Fh;
   const int KSp = (sh ? L.Fsk : L.Fpk) / kBK, np = sh ? 1 : L.P;  // stages of one partition, partitions
   const float* H = (const float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld;
-  const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.NI2 + it.jd) * (np * KSp) * (128 * Tile::WR) + sub * (Tile::WROWS * kFullRow) + tid * 16;
+  const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.NI2 + it.jd) * (np * KSp) * (128 * Tile::WR) + sub * (Tile::WROWS * Tile::WR) + tid * 16;
   const char* rowp[Tile::NX];
 #pragma unroll
   for (int i = 0; i < Tile::NX; ++i) {
@@ -399,24 +392,21 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
 }
 
 // ------------------------------------------------------------------------------------- two images to a tile
-// Barrier behind which a stage may be overwritten: this wavefront's LDS reads have arrived.  (Where two stages are multiplied between
-// the same two ends of a loop, the compiler would let reads of the first one cross the barrier of the second.)
+// Barrier behind which a stage may be overwritten: this wavefront's LDS reads have arrived.
 __device__ __forceinline__ void read_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// The product of both images of a tile (2 x 128 weight rows) with NJ blocks of 32 pair rows, fp32 operands cut into bf16 parts (see
-// the top).  A stage is 64 bytes of every weight row: 32 bf16 or 16 fp32 values of K.
-template <int WE, int XE, int NJ>
+// The product of both images of a tile (2 x 128 weight rows, bf16) with NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
+template <int XE, int NJ>
 struct WideTile {
-  static constexpr int K = kFullRow / WE;                      // K values of a stage
-  static constexpr int XR = K * XE, XCH = XR / 16;             // bytes of a pair row in a stage, 16-byte chunks of it
-  static constexpr int IMG = 128 * kFullRow;                   // bytes of a stage of an image
+  static constexpr int XR = kBK * XE, XCH = XR / 16;           // bytes of a pair row in a stage, 16-byte chunks of it
+  static constexpr int WR = kBK * 2;                           // bytes of a weight row in a stage
+  static constexpr int IMG = 128 * WR;                         // bytes of a stage of an image
   static constexpr int NW = 2 * IMG / 4096;                    // 4 KiB loads of the weights per stage
   static constexpr int XROWS_LOAD = 4096 / XR;                 // pair rows per load
   static constexpr int NX = (NJ * 32 + XROWS_LOAD - 1) / XROWS_LOAD;
   static constexpr int NL = NW + NX;
   static constexpr int SB = NL * 4096;                         // bytes of a stage
   static constexpr int NS = kFullLds / SB;
-  static constexpr int G = WE == 4 ? 2 : 1;                    // stages whose sums meet before they join the tile's (K is a multiple of 32)
   static_assert(NS >= 2 && NS <= 4, "ring");
 
   f32x16 acc[2][NJ];
@@ -451,33 +441,24 @@ struct WideTile {
     for (int s = 0; s < NS - 1; ++s)
       if (s < n) issue(s);
     int st = 0;
-    for (; st + NS - 1 + G - 1 < n; st += G) {
-      f32x16 sum[2][NJ];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        wait_loads<(NS - 2) * NL>();  // stage st + g has landed (for this wavefront; the barrier makes it so for all)
-        read_barrier();
-        issue(st + g + NS - 1);       // into the slot of the stage before, which every wavefront has finished reading
-        multiply<SAFE>(lds + ((st + g) % NS) * SB, sum, g, w, lane);
-      }
+    for (; st + NS - 1 < n; ++st) {
+      wait_loads<(NS - 2) * NL>();  // stage st has landed (for this wavefront; the barrier makes it so for all)
+      read_barrier();
+      issue(st + NS - 1);           // into the slot of stage st - 1, which every wavefront has finished reading
+      multiply<SAFE>(lds + (st % NS) * SB, w, lane);
     }
-    for (; st < n; st += G) {
-      f32x16 sum[2][NJ];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int left = n - 1 - st - g;  // later stages still to come
-        if (left >= NS - 2) wait_loads<(NS - 2) * NL>();
-        else if (NS > 3 && left == 1) wait_loads<NL>();
-        else wait_loads<0>();
-        read_barrier();
-        if (left >= NS - 1) issue(st + g + NS - 1);
-        multiply<SAFE>(lds + ((st + g) % NS) * SB, sum, g, w, lane);
-      }
+    for (; st < n; ++st) {
+      const int left = n - 1 - st;  // later stages still in flight
+      if (left >= NS - 2) wait_loads<(NS - 2) * NL>();
+      else if (NS > 3 && left == 1) wait_loads<NL>();
+      else wait_loads<0>();
+      read_barrier();
+      multiply<SAFE>(lds + (st % NS) * SB, w, lane);
     }
     read_barrier();  // every wavefront is done reading the last stage
   }
 
-  // run(), and where fp32 operands were cut and some sum came out infinite or NaN, again in the form that is right for every value
+  // run(), and where fp32 activations were cut and some sum came out infinite or NaN, again in the form that is right for every value
   template <class Next>
   __device__ __forceinline__ void product(int n, const char* const (&rowp)[NX], const char* wsrc, int64_t img, bool once, const Next& next, char* lds, int w, int lane) {
     run<false>(n, rowp, wsrc, img, once, next, lds, w, lane);
@@ -499,84 +480,41 @@ struct WideTile {
     }
   }
 
-  // SAFE: right for infinite and NaN operands as well: fp32 weights by fp32 instructions; bf16 weights without the infinite and NaN
-  // ones in the two smaller products, whose other operand may be zero.
-  // sum, g: see G
+  // SAFE (fp32 activations): right for infinite and NaN operands as well: the infinite and NaN weights are left out of the two smaller
+  // products, whose other operand may be zero.
   template <bool SAFE>
-  __device__ __forceinline__ void multiply(const char* stage, f32x16 (&sum)[2][NJ], int g, int w, int lane) {
+  __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
     const int r32 = lane & 31, h = lane >> 5;
-    const char* wrow = stage + (w * 32 + r32) * kFullRow;
+    const char* wrow = stage + (w * 32 + r32) * WR;
     const char* xrow = stage + NW * 4096 + r32 * XR;
     auto wchunk = [&](int b, int c) { return wrow + b * IMG + swz_chunk(r32, c) * 16; };
     auto xchunk = [&](int j, int c) { return xrow + j * 32 * XR + swz_full<XCH>(r32, c) * 16; };
-    if constexpr (WE == 4 && SAFE) {  // this lane's K values are 8h .. 8h + 7 of the stage's sixteen
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        f32x4 a[2], x[NJ];
+    for (int s = 0; s < 2; ++s) {  // K values 16s + 8h .. 16s + 8h + 7
+      bf16x8 a[2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) a[b] = *(const f32x4*)wchunk(b, 2 * h + q);
+      for (int b = 0; b < 2; ++b) a[b] = *(const bf16x8*)wchunk(b, 2 * s + h);
+      if constexpr (XE == 2) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) x[j] = *(const f32x4*)xchunk(j, 2 * h + q);
+        for (int j = 0; j < NJ; ++j) {
+          const bf16x8 x = *(const bf16x8*)xchunk(j, 2 * s + h);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+          for (int b = 0; b < 2; ++b) acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[b], x, acc[b][j], 0, 0, 0);
+        }
+      } else {
+        bf16x8 small[2];
 #pragma unroll
-          for (int j = 0; j < NJ; ++j)
+        for (int b = 0; b < 2; ++b) small[b] = SAFE ? finite_only(a[b]) : a[b];
 #pragma unroll
-            for (int b = 0; b < 2; ++b) acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b][i], x[j][i], acc[b][j], 0, 0, 0);
-      }
-    } else if constexpr (WE == 4) {
-      u32x4 a[2][3], x[NJ][3];
+        for (int j = 0; j < NJ; ++j) {
+          u32x4 part[3];
+          split3<SAFE>(*(const f32x4*)xchunk(j, 4 * s + 2 * h), *(const f32x4*)xchunk(j, 4 * s + 2 * h + 1), part);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) split3<false>(*(const f32x4*)wchunk(b, 2 * h), *(const f32x4*)wchunk(b, 2 * h + 1), a[b]);
+          for (int k = 2; k >= 0; --k)  // the small parts first
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) split3<false>(*(const f32x4*)xchunk(j, 2 * h), *(const f32x4*)xchunk(j, 2 * h + 1), x[j]);
-      constexpr int kPart[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};  // (weight, pair row), the small products first
-#pragma unroll
-      for (int k = 0; k < 6; ++k)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            f32x16 c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (g > 0 || k > 0) c = sum[b][j];
-            sum[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[b][kPart[k][0]]), __builtin_bit_cast(bf16x8, x[j][kPart[k][1]]), c, 0, 0, 0);
-          }
-      if (g == G - 1) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[b][j][v] += sum[b][j][v];
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {  // K values 16s + 8h .. 16s + 8h + 7
-        bf16x8 a[2];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) a[b] = *(const bf16x8*)wchunk(b, 2 * s + h);
-        if constexpr (XE == 2) {  // bf16 x bf16
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            const bf16x8 x = *(const bf16x8*)xchunk(j, 2 * s + h);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[b], x, acc[b][j], 0, 0, 0);
-          }
-        } else {  // bf16 weights x fp32 activations
-          bf16x8 small[2];
-#pragma unroll
-          for (int b = 0; b < 2; ++b) small[b] = SAFE ? finite_only(a[b]) : a[b];
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            u32x4 part[3];
-            split3<SAFE>(*(const f32x4*)xchunk(j, 4 * s + 2 * h), *(const f32x4*)xchunk(j, 4 * s + 2 * h + 1), part);
-#pragma unroll
-            for (int k = 2; k >= 0; --k)  // the small parts first
-#pragma unroll
-              for (int b = 0; b < 2; ++b)
-                acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k == 0 ? a[b] : small[b], __builtin_bit_cast(bf16x8, part[k]), acc[b][j], 0, 0, 0);
-            if (SAFE) __builtin_amdgcn_sched_barrier(0);  // (registers)
-          }
+            for (int b = 0; b < 2; ++b)
+              acc[b][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k == 0 ? a[b] : small[b], __builtin_bit_cast(bf16x8, part[k]), acc[b][j], 0, 0, 0);
+          if (SAFE) __builtin_amdgcn_sched_barrier(0);  // (registers)
         }
       }
     }
@@ -584,15 +522,14 @@ struct WideTile {
 };
 
 // it.jt: the tile
-template <typename T, int NJ>
+template <int NJ>
 __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it, const char* packed, const char* x, int64_t x_row, char* ws, int epi, char* lds,
                                                 int w, int lane) {
-  constexpr int E = sizeof(T);
-  using Tile = WideTile<E, E, NJ>;
+  using Tile = WideTile<2, NJ>;
   const int tid = w * 64 + lane;
   const bool sh = it.e == L.E_res;
   const int Fpk = sh ? L.Fsk : L.Fpk, ld = sh ? L.Fsk : L.Fh, NI1 = sh ? L.NI1_sh : L.NI1;
-  const int KS = L.Dk / Tile::K;
+  const int KS = L.Dk / kBK;
   const int32_t* row_token = (const int32_t*)(ws + L.o_row_token) + it.row0;
   const uint8_t* row_bits = (const uint8_t*)(ws + L.o_row_bits) + it.row0;
   const int64_t img = (int64_t)KS * Tile::IMG;  // bytes of an image
@@ -638,71 +575,53 @@ __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it
   }
 }
 
-// The pieces of a list: whole items, of bf16 layers the last kFullHalved as their two images.  (fp32 layers multiply single images by
-// fp32 instructions.)
+// The pieces of a list: whole items, the last kFullHalved as their two images.
 constexpr int kFullHalved = 256;
 struct WidePiece {
   int item, image;  // image -1: both
 };
-template <typename T>
-__device__ __forceinline__ int wide_pieces(int items) { return sizeof(T) == 4 ? items : items + min(items, kFullHalved); }
-template <typename T>
+__device__ __forceinline__ int wide_pieces(int items) { return items + min(items, kFullHalved); }
 __device__ __forceinline__ WidePiece wide_piece(int items, int id) {
   const int whole = max(items - kFullHalved, 0), cut = id - whole;
-  return sizeof(T) == 4 || cut < 0 ? WidePiece{id, -1} : WidePiece{whole + (cut >> 1), cut & 1};
+  return cut < 0 ? WidePiece{id, -1} : WidePiece{whole + (cut >> 1), cut & 1};
 }
 
-template <typename T>
 __global__ __launch_bounds__(256, 2) void gemm1_wide_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int items = counters[0], n = wide_pieces<T>(items), id = take_piece<true>(n, counters + 8, lds);
+  const int items = counters[0], n = wide_pieces(items), id = take_piece<true>(n, counters + 8, lds);
   if (id >= n) return;
-  const WidePiece piece = wide_piece<T>(items, id);
+  const WidePiece piece = wide_piece(items, id);
   Item1 it = ((const Item1*)(ws + L.o_items1))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min((it.e == L.E_res ? L.NI1_sh : L.NI1) - 2 * it.jt, 2);
   if (piece.image >= images) return;
   if (piece.image < 0 && images == 2) {
-    if (sizeof(T) == 4 && blocks > 2) {  // the parts of more than two blocks of fp32 rows do not fit the registers: 64 rows, then the others
-      Item1 part = it;
-      part.nrows = kFullBM;
-      part.nfill = min(it.nfill, kFullBM);
-      gemm1_wide_tile<T, 2>(L, part, packed, x, x_row, ws, epi, lds, w, lane);
-      __syncthreads();  // every wavefront is done with the ring
-      part.row0 = it.row0 + kFullBM;
-      part.nrows = it.nrows - kFullBM;
-      part.nfill = max(it.nfill - kFullBM, 0);
-      if (blocks == 3) gemm1_wide_tile<T, 1>(L, part, packed, x, x_row, ws, epi, lds, w, lane);
-      else gemm1_wide_tile<T, 2>(L, part, packed, x, x_row, ws, epi, lds, w, lane);
-      return;
-    }
     switch (blocks) {
-      case 1: gemm1_wide_tile<T, 1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-      case 2: gemm1_wide_tile<T, 2>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-      case 3: gemm1_wide_tile<T, sizeof(T) == 2 ? 3 : 1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
-      default: gemm1_wide_tile<T, sizeof(T) == 2 ? 4 : 1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+      case 1: gemm1_wide_tile<1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+      case 2: gemm1_wide_tile<2>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+      case 3: gemm1_wide_tile<3>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
+      default: gemm1_wide_tile<4>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
     }
     return;
   }
   it.jt = 2 * it.jt + max(piece.image, 0);
   switch (blocks) {
-    case 1: gemm1_full_tile<T, 1, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
-    case 2: gemm1_full_tile<T, 2, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
-    case 3: gemm1_full_tile<T, 3, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
-    default: gemm1_full_tile<T, 4, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 1: gemm1_full_tile<uint16_t, 1, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 2: gemm1_full_tile<uint16_t, 2, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
+    case 3: gemm1_full_tile<uint16_t, 3, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
+    default: gemm1_full_tile<uint16_t, 4, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
   }
 }
 
-// it.jd: the tile; skip: rows of the item before these
-template <typename T, int NJ>
-__device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it, int skip, const char* packed, char* ws, char* lds, int w, int lane) {
-  using Tile = WideTile<sizeof(T), 4, NJ>;
-  constexpr int M = kBK / Tile::K;  // stages of kBK values of K
+// it.jd: the tile
+template <int NJ>
+__device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it, const char* packed, char* ws, char* lds, int w, int lane) {
+  using Tile = WideTile<4, NJ>;
   const int tid = w * 64 + lane;
   const bool sh = it.e == L.E_res;
   const int ld = sh ? L.Fsk : L.Fh;
-  const int KSp = (sh ? L.Fsk : L.Fpk) / Tile::K, np = sh ? 1 : L.P;  // stages of one partition, partitions
+  const int KSp = (sh ? L.Fsk : L.Fpk) / kBK, np = sh ? 1 : L.P;  // stages of one partition, partitions
   const float* H = (const float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld;
   const int64_t img = (int64_t)np * KSp * Tile::IMG;  // bytes of an image
   const char* wsrc = packed + (sh ? L.p_sw2 : L.p_w2) + ((int64_t)(sh ? 0 : it.e) * L.NI2 + 2 * it.jd) * img + tid * 16;
@@ -716,7 +635,7 @@ __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it
   const int32_t* multi = (const int32_t*)(ws + L.o_counters) + 5;  // see gemm2_setup in gemm_mfma.hip
   const bool once = !sh && !((multi[(it.e >> 5) & 1] >> (it.e & 31)) & 1);
   // stages run over the partitions that some row of the tile keeps, see gemm2_full_tile
-  const int ks_n = it.ks_n * M, ks_lo = it.ks_lo * M, kmask = it.kmask;
+  const int ks_n = it.ks_n, ks_lo = it.ks_lo, kmask = it.kmask;
   int n = 0;
   for (int p = 0; p < np; ++p) n += ((kmask >> p) & 1) ? ks_n : 0;
   int p_cur = 0;
@@ -739,7 +658,7 @@ __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it
     Y = (float*)(ws + L.o_Yp) + (size_t)it.row0 * L.D + it.jd * (2 * kFullBN2);
     ldy = L.D;
   } else {
-    Y = (float*)(ws + L.o_pool) + ((size_t)(it.split - 1) * L.pool_rows + skip) * (2 * kFullBN2);
+    Y = (float*)(ws + L.o_pool) + (size_t)(it.split - 1) * L.pool_rows * (2 * kFullBN2);
     ldy = 2 * kFullBN2;
   }
   const int c0 = w * 32 + (lane >> 5) * 4;
@@ -765,47 +684,35 @@ __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it
   }
 }
 
-template <typename T>
 __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int items = counters[1], n = wide_pieces<T>(items), id = take_piece<true>(n, counters + 9, lds);
+  const int items = counters[1], n = wide_pieces(items), id = take_piece<true>(n, counters + 9, lds);
   if (id >= n) return;
-  const WidePiece piece = wide_piece<T>(items, id);
+  const WidePiece piece = wide_piece(items, id);
   Item2 it = ((const Item2*)(ws + L.o_items2))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min(L.NI2 - 2 * it.jd, 2);
   if (piece.image >= images) return;
   if (piece.image < 0 && images == 2) {
-    if (sizeof(T) == 4 && blocks > 2) {  // see gemm1_wide_kernel
-      Item2 part = it;
-      part.nrows = kFullBM;
-      gemm2_wide_tile<T, 2>(L, part, 0, packed, ws, lds, w, lane);
-      __syncthreads();  // every wavefront is done with the ring
-      part.row0 = it.row0 + kFullBM;
-      part.nrows = it.nrows - kFullBM;
-      if (blocks == 3) gemm2_wide_tile<T, 1>(L, part, kFullBM, packed, ws, lds, w, lane);
-      else gemm2_wide_tile<T, 2>(L, part, kFullBM, packed, ws, lds, w, lane);
-      return;
-    }
     switch (blocks) {
-      case 1: gemm2_wide_tile<T, 1>(L, it, 0, packed, ws, lds, w, lane); break;
-      case 2: gemm2_wide_tile<T, 2>(L, it, 0, packed, ws, lds, w, lane); break;
-      case 3: gemm2_wide_tile<T, sizeof(T) == 2 ? 3 : 1>(L, it, 0, packed, ws, lds, w, lane); break;
-      default: gemm2_wide_tile<T, sizeof(T) == 2 ? 4 : 1>(L, it, 0, packed, ws, lds, w, lane); break;
+      case 1: gemm2_wide_tile<1>(L, it, packed, ws, lds, w, lane); break;
+      case 2: gemm2_wide_tile<2>(L, it, packed, ws, lds, w, lane); break;
+      case 3: gemm2_wide_tile<3>(L, it, packed, ws, lds, w, lane); break;
+      default: gemm2_wide_tile<4>(L, it, packed, ws, lds, w, lane); break;
     }
     return;
   }
   it.jd = 2 * it.jd + max(piece.image, 0);
-#define DSMOE_ROWS(NONFINITE)                                                                              \
-  switch (blocks) {                                                                                        \
-    case 1: gemm2_full_tile<T, 1, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;                \
-    case 2: gemm2_full_tile<T, 2, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;                \
-    case 3: gemm2_full_tile<T, 3, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;                \
-    default: gemm2_full_tile<T, 4, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;               \
+#define DSMOE_ROWS(NONFINITE)                                                                                 \
+  switch (blocks) {                                                                                           \
+    case 1: gemm2_full_tile<uint16_t, 1, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;            \
+    case 2: gemm2_full_tile<uint16_t, 2, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;            \
+    case 3: gemm2_full_tile<uint16_t, 3, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;            \
+    default: gemm2_full_tile<uint16_t, 4, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;           \
   }
-  if (sizeof(T) == 2 && *(const int32_t*)(packed + L.p_scale)) {
-    DSMOE_ROWS(sizeof(T) == 2)
+  if (*(const int32_t*)(packed + L.p_scale)) {
+    DSMOE_ROWS(true)
   } else {
     DSMOE_ROWS(false)
   }
@@ -826,8 +733,8 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* x, T* out, int D
 static hipError_t set_lds_attr() {
   static PerDeviceOnce once;
   return once.run([] {
-    for (const void* fn : {(const void*)gemm1_wide_kernel<float>, (const void*)gemm1_wide_kernel<uint16_t>, (const void*)gemm2_wide_kernel<float>,
-                           (const void*)gemm2_wide_kernel<uint16_t>, (const void*)gemm1_full_kernel<float, 1>, (const void*)gemm1_full_kernel<float, 2>, (const void*)gemm1_full_kernel<uint16_t, 1>,
+    for (const void* fn : {(const void*)gemm1_wide_kernel, (const void*)gemm2_wide_kernel,
+                           (const void*)gemm1_full_kernel<float, 1>, (const void*)gemm1_full_kernel<float, 2>, (const void*)gemm1_full_kernel<uint16_t, 1>,
                            (const void*)gemm1_full_kernel<uint16_t, 2>, (const void*)gemm2_full_kernel<float, 1>, (const void*)gemm2_full_kernel<float, 2>,
                            (const void*)gemm2_full_kernel<uint16_t, 1>, (const void*)gemm2_full_kernel<uint16_t, 2>}) {
       hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kFullLds);
@@ -845,14 +752,18 @@ static hipError_t set_lds_attr() {
 // depend on how many experts are resident: 64 tokens on 8 of those 64 experts 82 -> 68 us, on 2 of 8 of 1024 x 2048 49 -> 40.
 static int full_parts(const Layout& L, int T) { return (int64_t)T * L.K <= (int64_t)L.E * 16 ? 2 : 1; }
 
-// Tiles of two images pay where experts have rows enough to reuse what was cut and the list is long enough for items of twice the
-// size.  Single images -> two, us per layer: fp32, 64 experts of 2048 x 1024 top-8, 180 / 256 / 300 / 400 tokens (22 / 32 / 37 / 50
-// pairs per expert) 329 -> 343, 355 -> 335, 400 -> 340, 474 -> 370; bf16, 64 + 2 of 2048 x 1408 in parts of 176 top-6, 300 / 500 / 777
-// tokens (28 / 47 / 73) 346 -> 352, 378 -> 379, 430 -> 395; 64 of 2048 x 1000 top-8, 400 / 777 tokens (50 / 97) 221 -> 228, 281 -> 279.  8 fp32
-// experts of 128 x 256, 32 items, lose at any size (100 tokens 30.2 -> 34.4).
+// Tiles of two images: bf16 layers, where experts have rows enough to reuse what was cut.  The line is in pairs per expert before any drop, as
+// the host knows no more.  Single images -> two, us per layer, 700 / 777 / 1500 tokens on 64 + 2 experts of 2048 x 1408 in parts of 176, top-6
+// (66 / 73 / 141 pairs per expert): nothing dropped 449 -> 440, 467 -> 422, 723 -> 632; 25 % dropped 419 -> 418, 431 -> 399, 641 -> 587;
+// 50 % 383 -> 391, 399 -> 375, 550 -> 499; 25 % and popularity rank^-1.2 450 -> 408, 466 -> 437, 685 -> 612.  520 / 777 / 1500 on 64 of
+// 2048 x 1000 in parts of 250, top-8 (65 / 97 / 188): 263 -> 266, 319 -> 320, 544 -> 448; 242 -> 237, 285 -> 286, 462 -> 427; 223 -> 219,
+// 255 -> 250, 370 -> 329; 300 -> 249, 333 -> 292, 471 -> 395.  300 / 500 tokens (28 / 47 pairs) of the first 346 -> 352, 378 -> 379.
+// Layers of few weight images (short lists) are not measured and keep single ones.
+// fp32 layers: with both images to a tile and the fp32 instructions 250 / 300 / 400 / 512 tokens on 64 experts of 2048 x 1024, top-8, 25 % dropped,
+// took 409 -> 432, 423 -> 440, 486 -> 454, 559 -> 571, and 488 -> 735 at 250 with popularity rank^-1.2.
 bool full_wide(const Layout& L, int T) {
-  const int64_t rows = (int64_t)T * L.K, per = L.dtype == DSMOE_F32 ? 30 : 64;
-  return rows > per * L.E && (int64_t)L.E_res * L.P * L.NI1 >= 2 * kFullSplitItems && (int64_t)L.E_res * L.NI2 >= 2 * kFullSplitItems;
+  return L.dtype == DSMOE_BF16 && (int64_t)T * L.K > 64 * (int64_t)L.E && (int64_t)L.E_res * L.P * L.NI1 >= 2 * kFullSplitItems &&
+         (int64_t)L.E_res * L.NI2 >= 2 * kFullSplitItems;
 }
 
 hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
@@ -874,8 +785,7 @@ hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const v
   }
   if (L.wide) {
     const dim3 grid(piece_blocks(true, items1_bound(L, T) + kFullHalved)), block(256);
-    if (elem == 4) gemm1_wide_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
-    else gemm1_wide_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
+    gemm1_wide_kernel<<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi);
     return hipGetLastError();
   }
   const int subs = full_parts(L, T);
@@ -895,8 +805,7 @@ hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* w
   if (e != hipSuccess) return e;
   if (L.wide) {
     const dim3 grid(piece_blocks(true, items2_bound(L, T) + kFullHalved)), block(256);
-    if (L.dtype == DSMOE_F32) gemm2_wide_kernel<float><<<grid, block, kFullLds, s>>>(L, packed, ws);
-    else gemm2_wide_kernel<uint16_t><<<grid, block, kFullLds, s>>>(L, packed, ws);
+    gemm2_wide_kernel<<<grid, block, kFullLds, s>>>(L, packed, ws);
     return hipGetLastError();
   }
   const int subs = full_parts(L, T);

@@ -1,8 +1,7 @@
 // moe_partition_weights kernels: neuron reorder through perm (Sec. 4.2 b), even split into P
 // sub-experts with no W2 scaling (Sec. 3.2), written in the layout the GEMM kernels read.
 //
-// Full-precision layout (element type = layer dtype): the same idea with tiles of 128 weight rows x 32 K values (fp32: 16 KiB, the
-// 64-byte rows of the first 16 K values, then those of the others):
+// Full-precision layout (element type = layer dtype): the same idea with tiles of 128 weight rows x 32 K values:
 //   W13  stage ((e*P + p)*NT1 + jt)*(Dk/32) + ks : weight row q*32 + gu*16 + j is neuron p*Fp + jt*64 + q*16 + j of W1
 //        (gu=0) or W3 (gu=1)
 //   W2   stage (e*ND2 + jd)*(P*Fpk/32) + kt : 128 output columns x 32 neurons; every partition is padded with zeros to
@@ -163,9 +162,6 @@ __device__ __forceinline__ bool not_finite(uint4 v) {
   return one(v.x) || one(v.y) || one(v.z) || one(v.w);
 }
 
-// Where 16-byte chunk lc of a row of 32 values of K sits in an image of `rows` rows
-__device__ __forceinline__ int image_at(int rows, int row, int lc) { return (lc >> 2) * (rows * 64) + row * 64 + swz_chunk(row, lc & 3) * 16; }
-
 // Where neuron nin of a partition sits in its W13 images: neuron tile, image row of its gate projection; the up row is UP
 // rows further down.  FULL: the full-precision layout.
 template <typename T, bool FULL>
@@ -173,7 +169,7 @@ struct W13Image {
   static constexpr int NEUR = FULL ? kFullNeur : kMfmaNeur, UP = FULL ? 16 : 32, RB = kBK * sizeof(T);
   static constexpr int64_t STAGE = 2 * NEUR * RB;
   static __device__ __forceinline__ int row(int nin) { return nin % NEUR / UP * (2 * UP) + nin % UP; }
-  static __device__ __forceinline__ int at(int row, int lc) { return image_at(2 * NEUR, row, lc); }
+  static __device__ __forceinline__ int at(int row, int lc) { return row * RB + swz_full<RB / 16>(row, lc) * 16; }
 };
 
 // W1 / W3 -> W13 images.  A workgroup takes the COLS original neurons (columns) of one expert and one K stage (32
@@ -261,7 +257,7 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
       const int c = c0 + cg * PT::COLS_GET + i, jd = c / BN, row = c % BN;
       if (jd >= nd) continue;
       char* stage = out + (((int64_t)e * nd + jd) * KT + kt) * (BN * RB);
-      *(uint4*)(stage + image_at(BN, row, lc)) = o[i];
+      *(uint4*)(stage + row * RB + swz_full<RB / 16>(row, lc) * 16) = o[i];
     }
   }
 }
@@ -284,7 +280,7 @@ __global__ __launch_bounds__(256) void pack_w13_padding_kernel(char* out, int gr
     const int ks = (int)(r % KS1);
     const int64_t ep = r / KS1;  // e * P + p
     char* stage = out + ((ep * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
-    *(uint4*)(stage + Im::at(Im::row(nin) + gu * Im::UP, pc)) = make_uint4(0, 0, 0, 0);
+    *(uint4*)(stage + (Im::row(nin) + gu * Im::UP) * Im::RB + pc * 16) = make_uint4(0, 0, 0, 0);
   }
 }
 
