@@ -128,7 +128,7 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
   L.o_cursor = take((int64_t)L.nbins * 4);
   L.o_exp_nrows = take((int64_t)L.E_res * 4);
   L.o_exp_row0 = take((int64_t)L.E_res * 4);
-  L.o_counters = take(40);
+  L.o_counters = take((kNonfiniteH + 1) * 4);
   L.o_tile_bits = take((int64_t)L.max_tiles * 4);
   L.o_act_rank = take((int64_t)L.max_tiles * L.P * 4);
   L.o_items1 = take((int64_t)L.max_items1 * sizeof(Item1));

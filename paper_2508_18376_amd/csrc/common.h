@@ -53,6 +53,7 @@ constexpr int kFullNeur = 64;
 constexpr int kFullBN2 = 128;
 constexpr int kFullRows = kFullBM + kTallExtra;
 constexpr int kFullSplitItems = 512;  // two GEMM-2 workgroups per compute unit
+constexpr int kNonfiniteH = 10;       // counter that tiles of two weight images set: some activation is infinite or NaN (cleared by the plan)
 
 struct Item1 {  // one tile of GEMM-1: rows [row0, row0+nrows) x neurons tile jt of partition p
   int32_t row0, nrows, e, p, jt;

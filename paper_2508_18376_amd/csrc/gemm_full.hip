@@ -15,8 +15,9 @@
 // bits of H at 5 x the rate of the fp32 instruction.  mid and lo can be zero: layers with an infinity or NaN in W2 (the packed
 // weights say so) leave those weights out of the two smaller products.
 //
-// Tiles of two images (bf16 layers) read the pair rows and cut fp32 activations half as often; the sums are the same bit for bit.  There a tile in
-// which some sum comes out infinite or NaN is computed again without infinite weights in the smaller products.
+// Tiles of two images (bf16 layers) read the pair rows and cut fp32 activations half as often; the sums are the same bit for bit.  There
+// GEMM-1 notes whether an activation came out infinite or NaN (kNonfiniteH), and GEMM-2 of other batches does without the clamp: 777 tokens on 64 + 2
+// experts of 2048 x 1408 in parts of 176 408 -> 397 us; with an infinite token or infinities in W2 427 (single images 431 and 453).
 // fp32 layers keep single images and the fp32 instruction: six products of bf16 parts of both operands are 2.7 x as fast (512 tokens on 64 experts of
 // 2048 x 1024 559 -> 503 us), but they leave products of up to 2^-21 out and the bf16 instruction cuts its sums off towards zero, so that sums
 // carried by one term are less exact than fp32 (2.6e-8 -> 6.5e-8), as are products of values below 2^-110.
@@ -266,6 +267,7 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
   const int n0 = it.jt * kFullNeur + sub * (kFullNeur / SUBS) + w * 16 + (lane >> 5) * 4;
   // the neurons that pad a partition to whole stages are zeros whatever came out: zero weights times an infinite x are NaN
   const int Fp = sh ? L.F_shT : L.Fp;
+  float z = 0.f;  // stays zero as long as every activation is finite
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int r = j * 32 + (lane & 31);
@@ -275,10 +277,14 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
     for (int g = 0; g < 2; ++g) {
       f32x4 o;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) o[c] = kept && n0 + g * 8 + c < Fp ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
+      for (int c = 0; c < 4; ++c) {
+        o[c] = kept && n0 + g * 8 + c < Fp ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
+        z = __builtin_fmaf(o[c], 0.f, z);
+      }
       if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = o;
     }
   }
+  if (sizeof(T) == 2 && SUBS == 1 && L.wide && z != 0.f) ((int32_t*)(ws + L.o_counters))[kNonfiniteH] = 1;  // (true for NaN)
   for (int r = NJ * 32 + (lane & 31); r < it.nfill; r += 32) {  // rows that keep nothing of this partition, beyond the blocks multiplied: zeros
     for (int g = 0; g < 2; ++g)
       if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -455,33 +461,10 @@ struct WideTile {
       read_barrier();
       multiply<SAFE>(lds + (st % NS) * SB, w, lane);
     }
-    read_barrier();  // every wavefront is done reading the last stage
   }
 
-  // run(), and where fp32 activations were cut and some sum came out infinite or NaN, again in the form that is right for every value
-  template <class Next>
-  __device__ __forceinline__ void product(int n, const char* const (&rowp)[NX], const char* wsrc, int64_t img, bool once, const Next& next, char* lds, int w, int lane) {
-    run<false>(n, rowp, wsrc, img, once, next, lds, w, lane);
-    if constexpr (XE == 4) {
-      float z = 0.f;  // stays zero as long as every sum is finite
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) z = __builtin_fmaf(acc[b][j][v], 0.f, z);
-      volatile int* flag = (volatile int*)lds;
-      const bool bad = __any(z != 0.f);  // (true for NaN)
-      if (lane == 0) flag[w] = bad;
-      __syncthreads();
-      const int redo = __builtin_amdgcn_readfirstlane(flag[0] | flag[1] | flag[2] | flag[3]);
-      __syncthreads();
-      if (redo) run<true>(n, rowp, wsrc, img, once, next, lds, w, lane);
-    }
-  }
-
-  // SAFE (fp32 activations): right for infinite and NaN operands as well: the infinite and NaN weights are left out of the two smaller
-  // products, whose other operand may be zero.
+  // SAFE (fp32 activations): right for infinite and NaN operands as well: activations are clamped (see split3), and infinite and NaN weights left out
+  // of the two smaller products, whose other operand may be zero.
   template <bool SAFE>
   __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
     const int r32 = lane & 31, h = lane >> 5;
@@ -542,7 +525,7 @@ __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it
     rowp[i] = x + (int64_t)row_token[rr] * x_row + swz_full<Tile::XCH>(r, tid % Tile::XCH) * 16;
   }
   Tile t;
-  t.product(KS, rowp, wsrc, img, it.once, [k = (int64_t)0](int64_t& xo, int64_t& wo) mutable {
+  t.template run<false>(KS, rowp, wsrc, img, it.once, [k = (int64_t)0](int64_t& xo, int64_t& wo) mutable {
     xo = k * Tile::XR;
     wo = k * Tile::IMG;
     ++k;
@@ -551,6 +534,7 @@ __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it
   float* H = (float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld + (size_t)it.p * Fpk;
   const int n0 = it.jt * (2 * kFullNeur) + w * 16 + (lane >> 5) * 4;
   const int Fp = sh ? L.F_shT : L.Fp;  // the neurons that pad a partition are zeros, see gemm1_full_tile
+  float z = 0.f;                       // stays zero as long as every activation is finite
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int r = j * 32 + (lane & 31);
@@ -563,10 +547,14 @@ __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it
         const int n = n0 + b * kFullNeur + g * 8;
         f32x4 o;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) o[c] = kept && n + c < Fp ? epi_value<false>(epi, t.acc[b][j][g * 4 + c], t.acc[b][j][8 + g * 4 + c]) : 0.f;
+        for (int c = 0; c < 4; ++c) {
+          o[c] = kept && n + c < Fp ? epi_value<false>(epi, t.acc[b][j][g * 4 + c], t.acc[b][j][8 + g * 4 + c]) : 0.f;
+          z = __builtin_fmaf(o[c], 0.f, z);
+        }
         if (n < Fpk) *(f32x4*)(H + (size_t)r * ld + n) = o;
       }
   }
+  if (z != 0.f) ((int32_t*)(ws + L.o_counters))[kNonfiniteH] = 1;  // (true for NaN)
   for (int r = NJ * 32 + (lane & 31); r < it.nfill; r += 32) {  // rows that keep nothing of this partition, beyond the blocks multiplied: zeros
     for (int q = 0; q < 4; ++q) {
       const int n = n0 + (q >> 1) * kFullNeur + (q & 1) * 8;
@@ -615,7 +603,7 @@ __global__ __launch_bounds__(256, 2) void gemm1_wide_kernel(Layout L, const char
 }
 
 // it.jd: the tile
-template <int NJ>
+template <int NJ, bool SAFE>
 __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it, const char* packed, char* ws, char* lds, int w, int lane) {
   using Tile = WideTile<4, NJ>;
   const int tid = w * 64 + lane;
@@ -641,7 +629,7 @@ __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it
   int p_cur = 0;
   while (p_cur < np && !((kmask >> p_cur) & 1)) ++p_cur;
   Tile t;
-  t.product(n, rowp, wsrc, img, once, [=, k_in = 0](int64_t& xo, int64_t& wo) mutable {
+  t.template run<SAFE>(n, rowp, wsrc, img, once, [=, k_in = 0](int64_t& xo, int64_t& wo) mutable {
     const int64_t kt = p_cur * KSp + ks_lo + k_in;
     if (++k_in == ks_n) {
       k_in = 0;
@@ -693,14 +681,22 @@ __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char
   Item2 it = ((const Item2*)(ws + L.o_items2))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min(L.NI2 - 2 * it.jd, 2);
+  const bool nonfinite = *(const int32_t*)(packed + L.p_scale) != 0;  // some weight of W2 is infinite or NaN
   if (piece.image >= images) return;
   if (piece.image < 0 && images == 2) {
-    switch (blocks) {
-      case 1: gemm2_wide_tile<1>(L, it, packed, ws, lds, w, lane); break;
-      case 2: gemm2_wide_tile<2>(L, it, packed, ws, lds, w, lane); break;
-      case 3: gemm2_wide_tile<3>(L, it, packed, ws, lds, w, lane); break;
-      default: gemm2_wide_tile<4>(L, it, packed, ws, lds, w, lane); break;
+#define DSMOE_ROWS(SAFE)                                                                 \
+  switch (blocks) {                                                                      \
+    case 1: gemm2_wide_tile<1, SAFE>(L, it, packed, ws, lds, w, lane); break;            \
+    case 2: gemm2_wide_tile<2, SAFE>(L, it, packed, ws, lds, w, lane); break;            \
+    case 3: gemm2_wide_tile<3, SAFE>(L, it, packed, ws, lds, w, lane); break;            \
+    default: gemm2_wide_tile<4, SAFE>(L, it, packed, ws, lds, w, lane); break;           \
+  }
+    if (nonfinite || counters[kNonfiniteH]) {
+      DSMOE_ROWS(true)
+    } else {
+      DSMOE_ROWS(false)
     }
+#undef DSMOE_ROWS
     return;
   }
   it.jd = 2 * it.jd + max(piece.image, 0);
@@ -711,7 +707,7 @@ __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char
     case 3: gemm2_full_tile<uint16_t, 3, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;            \
     default: gemm2_full_tile<uint16_t, 4, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;           \
   }
-  if (*(const int32_t*)(packed + L.p_scale)) {
+  if (nonfinite) {
     DSMOE_ROWS(true)
   } else {
     DSMOE_ROWS(false)

@@ -985,6 +985,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   if (tid == 0) {
     counters[0] = total_slots;
     counters[8] = 0;  // see take_piece
+    counters[kNonfiniteH] = 0;
   }
 }
 

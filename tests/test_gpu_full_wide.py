@@ -41,16 +41,18 @@ def test_two_images_to_a_tile(oracle, dtype, T, D, F, P, tau_kind):
     assert (np.abs(to_host64(y, "f32") - ref) <= 1e-5 * rms).all()
 
 
-def _positive_layer(T, D, F, E, K):
+def _positive_layer(T, D, F, E, K, dtype="f32"):
     import torch
     from paper_2508_18376_amd import DualSparseLayer
     gen = torch.Generator(device="cuda:0").manual_seed(9)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
     def rand(*s):
         return torch.rand(*s, generator=gen, device="cuda:0")
-    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=K, n_part=1, max_tokens=T, dtype="f32")
-    w1, w3, w2 = rand(E, D, F).mul_(0.01), rand(E, D, F).mul_(0.01), rand(E, F, D).mul_(0.01)
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=K, n_part=1, max_tokens=T, dtype=dtype, y_fp32=True)
+    assert not layer.uses_mfma
+    w1, w3, w2 = (rand(E, *s).mul_(0.01).to(dt) for s in ((D, F), (D, F), (F, D)))
     layer.partition_weights(w1, w3, w2)
-    return layer, w1, w3, w2, rand(T, D), torch.randn(T, E, generator=gen, device="cuda:0")
+    return layer, w1, w3, w2, rand(T, D).to(dt), torch.randn(T, E, generator=gen, device="cuda:0")
 
 
 def test_sums_of_one_sign():
@@ -103,11 +105,12 @@ def test_sums_of_one_term_do_not_depend_on_the_batch(sx, s3, s2):
     assert torch.equal(y[:64], few)
 
 
-def test_infinite_tokens():
+@pytest.mark.parametrize("dtype,T,D,F", [("f32", 2100, 256, 128), ("bf16", 4300, 260, 176), ("bf16", 4300, 256, 136)])
+def test_infinite_tokens(dtype, T, D, F):
     """A token with an infinite value has infinite outputs (all weights are positive), the others what they have without it."""
     import torch
-    T, D, F, E, K = 2100, 256, 128, 512, 8
-    layer, w1, w3, w2, x, logits = _positive_layer(T, D, F, E, K)
+    E, K = 512, 8
+    layer, w1, w3, w2, x, logits = _positive_layer(T, D, F, E, K, dtype)
     tau = torch.zeros(E, 1, device="cuda:0")
     clean = layer.forward(x, logits, tau)
     x[5::400, 3] = float("inf")
@@ -118,3 +121,41 @@ def test_infinite_tokens():
     hot[5::400] = True
     assert torch.isposinf(y[hot]).all()
     assert torch.allclose(y[~hot], clean[~hot], rtol=1e-5, atol=0.0)
+
+
+@pytest.mark.parametrize("hot_tokens", [False, True])
+def test_infinite_weights_in_both_images(hot_tokens):
+    """bf16, W2 with infinities and NaN in some experts, in a column of each of a tile's two images and of a tile of one image: where one neuron is
+    active, whose activation has one part that is not zero (1024 -> 2^20) or three (3), these columns are infinite or NaN for the tokens of those
+    experts, and everything else is bit for bit as with finite weights.  A token with an infinite value is infinite or NaN as a whole."""
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    T, D, F, E, K, inf = 4300, 260, 176, 512, 8, float("inf")
+    gen = torch.Generator(device="cuda:0").manual_seed(11)
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=K, n_part=1, max_tokens=T, dtype="bf16", y_fp32=True)
+    assert not layer.uses_mfma
+    w1 = torch.zeros(E, D, F, dtype=torch.bfloat16, device="cuda:0")
+    w1[:, 0, 1] = 1.0
+    w2 = torch.rand(E, F, D, generator=gen, device="cuda:0").add_(0.1).bfloat16()
+    x = torch.zeros(T, D, dtype=torch.bfloat16, device="cuda:0")
+    x[:, 0] = 1024.0
+    x[1::2, 0] = 3.0
+    logits, tau = torch.randn(T, E, generator=gen, device="cuda:0"), torch.zeros(E, 1, device="cuda:0")
+    layer.partition_weights(w1, w1, w2)
+    clean = layer.forward(x, logits, tau).clone()
+    assert torch.isfinite(clean).all()
+    w2[::9, 1, 3], w2[::9, 1, 130], w2[::9, 1, 258] = inf, -inf, float("nan")
+    layer.partition_weights(w1, w1, w2)
+    if hot_tokens:
+        x[7::500, 0] = inf
+    y = layer.forward(x, logits, tau)
+    torch.cuda.synchronize()
+    layer.close()
+    struck = (torch.topk(logits, K, dim=1).indices % 9 == 0).any(1)
+    hot = torch.isinf(x[:, 0])
+    assert struck.any() and not struck.all()
+    cold = struck & ~hot
+    assert torch.isposinf(y[cold, 3]).all() and torch.isneginf(y[cold, 130]).all() and torch.isnan(y[cold, 258]).all()
+    others = [d for d in range(D) if d not in (3, 130, 258)]
+    assert torch.equal(y[~hot][:, others], clean[~hot][:, others]) and torch.equal(y[~struck & ~hot], clean[~struck & ~hot])
+    assert not torch.isfinite(y[hot]).any()
