@@ -383,6 +383,7 @@ class DualSparseLayer:
             "tile_rows": lay[9],
             "shared_rows": lay[10],
             "counters": view(lay[11], 5, torch.int32),
+            "tile_neurons": int(view(lay[11], 8, torch.int32)[7]),
             "items1": view(lay[12], 8 * int(view(lay[11], 1, torch.int32)[0]), torch.int32).view(-1, 8),
             "items2": view(lay[13], 8 * int(view(lay[11], 2, torch.int32)[1]), torch.int32).view(-1, 8),
         }

@@ -854,6 +854,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       counters[4] = first_split_tile;
       counters[5] = multi_tile[0];
       counters[6] = multi_tile[1];
+      counters[7] = L.BN2 / 2;  // neurons of a neuron tile; an output column tile is twice as wide
     }
     return;
   }

@@ -32,6 +32,15 @@ CASES = [
     ("decode_split_and_halves", spec_of(T=24, D=512, F=2048, E=8, K=2, P=2, seed=83), 0.0, 0),
     ("last_round_split", spec_of(T=8500, D=1024, F=2048, E=4, K=2, P=2, seed=45), 0.0, 0),
     ("half_full_last_neuron_tile", spec_of(T=540, D=128, F=384, E=4, K=2, P=2, seed=66), "rate0.25", 0),
+    # full-precision path: tiles of 64 rows, of one weight image or (bf16, many rows on many experts) of two
+    ("full_one_image", spec_of(T=300, D=260, F=176, E=4, K=2, P=1, seed=85), "rate0.25", 0),
+    ("full_one_image_fp32", spec_of(T=700, D=384, F=640, E=8, K=2, P=2, dtype="f32", seed=86), "rate0.25", 0),
+    ("full_fp32_many_rows", spec_of(T=2100, D=256, F=128, E=512, K=8, P=1, dtype="f32", seed=87), 0.0, 0),
+    ("full_split", spec_of(T=9, D=200, F=1056, E=4, K=2, P=2, dtype="f32", seed=88), 0.0, 0),
+    ("full_shared_odd_widths", spec_of(T=100, D=130, F=72, E=4, K=2, P=2, n_shared=2, F_sh=27, seed=89), "rate0.3", 0),
+    ("full_two_images", spec_of(T=4300, D=260, F=176, E=512, K=8, P=1, seed=90), "rate0.25", 0),
+    ("full_two_images_shared", spec_of(T=4200, D=520, F=280, E=256, K=4, P=4, n_shared=2, F_sh=100, seed=91), "ragged", 0),
+    ("full_two_images_split", spec_of(T=850, D=1400, F=600, E=104, K=8, P=1, seed=92), 0.0, 0),
     ("resident_window", spec_of(T=1500, D=128, F=512, E=8, K=2, P=2, seed=84, resident=(2, 7)), "rate0.25", 0),
 ]
 
@@ -42,10 +51,12 @@ def test_work_lists_cover_every_kept_unit_once(oracle, name, spec, tau_kind, tal
     t = make_layer(spec)
     tau = resolve_tau(oracle, spec, t, tau_kind)
     layer, dev = make_gpu_layer(spec, t, tall_items=tall_items)
-    assert layer.uses_mfma
+    assert layer.uses_mfma == (not name.startswith("full"))
     layer.forward(dev["x"], dev["logits"], to_dev(tau))
     torch.cuda.synchronize()
     plan = {k: (v.cpu().numpy() if hasattr(v, "cpu") else v) for k, v in layer.plan(spec.T).items()}
     layer.close()
+    assert plan["tile_neurons"] == (64 if name.startswith("full") and "two_images" not in name else 128)
+    assert "split" not in name or plan["counters"][3] > 1
 
     check_cover(plan, name=name, T=spec.T, D=spec.D, F=spec.F, P=spec.P, E_res=spec.hi - spec.lo, n_shared=spec.n_shared, F_sh=spec.F_sh)

@@ -35,7 +35,7 @@ def plain_plan(seed=0):
             for jd in range(2):
                 items2.append([r0 + a, cnt, e, jd, tb, 0, 8, 0])
     it1, it2 = np.array(items1, np.int32), np.array(items2, np.int32)
-    return {"tile_rows": BM, "shared_rows": 0, "row_bits": bits, "expert_row0": row0, "expert_nrows": nrows,
+    return {"tile_rows": BM, "tile_neurons": 128, "shared_rows": 0, "row_bits": bits, "expert_row0": row0, "expert_nrows": nrows,
             "counters": np.array([len(it1), len(it2), 0, 1, 0]), "items1": it1, "items2": it2}
 
 
