@@ -1,5 +1,5 @@
 """GPU: large batches on layers of many experts in the full-precision path: bf16 layers take tiles of two weight images there (tiles with one
-image, pieces of one image, one to four blocks of 32 rows), fp32 layers keep fp32 products (sums of one sign and of one term); infinities.
+image, pieces of one image, one to four blocks of 32 rows, K splits), fp32 layers keep fp32 products (sums of one sign and of one term); infinities.
 """
 import numpy as np
 import pytest
@@ -55,6 +55,33 @@ def _positive_layer(T, D, F, E, K, dtype="f32"):
     return layer, w1, w3, w2, rand(T, D).to(dt), torch.randn(T, E, generator=gen, device="cuda:0")
 
 
+def _reference64(w1, w3, w2, x, logits, K):
+    import torch
+    s, idx = torch.softmax(logits.double(), 1), torch.topk(logits, K, dim=1).indices
+    ref = torch.zeros(x.shape, dtype=torch.float64, device="cuda:0")
+    for e in range(w1.shape[0]):
+        t = (idx == e).any(1).nonzero().flatten()
+        g = x[t].double() @ w1[e].double()
+        h = g * torch.sigmoid(g) * (x[t].double() @ w3[e].double())
+        ref.index_add_(0, t, s[t, e].unsqueeze(1) * (h @ w2[e].double()))
+    return ref
+
+
+def test_split_items_of_two_images():
+    """bf16: the items of GEMM-2's last round are cut along K; their extra ranges go to partial-output tiles of 256 columns, written by items of both
+    images, by halves of the list's last items and, the last column tile, by single images."""
+    import torch
+    layer, w1, w3, w2, x, logits = _positive_layer(850, 1400, 600, 104, 8, "bf16")
+    x = x.float().sub_(0.5).bfloat16()
+    y = layer.forward(x, logits, torch.zeros(104, 1, device="cuda:0"))
+    torch.cuda.synchronize()
+    counters = layer.plan(850)["counters"].cpu().numpy()
+    layer.close()
+    assert counters[3] == 3 and counters[1] == 512 + 3 * 112
+    ref = _reference64(w1, w3, w2, x, logits, 8)
+    assert ((y - ref).abs() <= 1e-5 * ref.square().mean(1, keepdim=True).sqrt()).all()  # the fp32 bar, see above
+
+
 def test_sums_of_one_sign():
     """fp32 sums round every addition to nearest, so sums of up to 2048 terms of one sign are right on average (measured: mean -1e-9 .. 1e-9,
     largest 1.1e-6).  An instruction that cuts its sums off towards zero leaves them 6e-6 short (bf16 parts), and
@@ -64,15 +91,7 @@ def test_sums_of_one_sign():
     T, D, F, E, K = 256, 2048, 1024, 64, 8
     layer, w1, w3, w2, x, logits = _positive_layer(T, D, F, E, K)
     y = layer.forward(x, logits, torch.zeros(E, 1, device="cuda:0")).double()
-    s = torch.softmax(logits.double(), 1)
-    idx = torch.topk(logits, K, dim=1).indices
-    ref = torch.zeros(T, D, dtype=torch.float64, device="cuda:0")
-    for e in range(E):
-        t = (idx == e).any(1).nonzero().flatten()
-        g = x[t].double() @ w1[e].double()
-        h = g * torch.sigmoid(g) * (x[t].double() @ w3[e].double())
-        ref.index_add_(0, t, s[t, e].unsqueeze(1) * (h @ w2[e].double()))
-    torch.cuda.synchronize()
+    ref = _reference64(w1, w3, w2, x, logits, K)
     layer.close()
     err = (y - ref) / ref
     assert err.abs().max().item() <= 3e-6
