@@ -27,7 +27,7 @@ def _needs_build() -> bool:
 # 256 others per lane).  A spill to scratch memory inside a main loop makes the loop wait for every outstanding load each
 # time round, and a small edit of a kernel is enough to cause one: the build refuses it.
 NO_SCRATCH = {
-    "gemm_mfma.hip": ("gemm1_mfma_kernel", "gemm2_mfma_kernel", "gemm1_stream_kernel", "gemm1_few_kernel", "gemm2_stream_kernel"),
+    "gemm_mfma.hip": ("gemm1_mfma_kernel", "gemm2_mfma_kernel", "gemm1_stream_kernel", "gemm2_stream_kernel"),
     "gemm_full.hip": ("gemm1_full_kernel", "gemm2_full_kernel", "gemm1_wide_kernel", "gemm2_wide_kernel"),
 }
 

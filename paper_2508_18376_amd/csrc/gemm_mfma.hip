@@ -882,98 +882,6 @@ __global__ __launch_bounds__(256, 2) void gemm1_stream_kernel(Layout L, int T, c
   }
 }
 
-// Lists of at most 256 items of at most kFewRows rows (few_items): a workgroup takes 32 neurons of an item, its wavefronts a quarter of K
-// each.  Weights and rows go from memory to the registers they are multiplied in, kFewAhead stages ahead, without LDS and without a barrier
-// in the loop: with one of the workgroups above to a unit the stages follow each other at the pace of their barriers and LDS round trips,
-// 64 of them for 2048 values of K (a deeper ring gave nothing).  16 rows of a weight image by its 32 K values are 1 KiB in a row, one load.
-// One token on 64 experts of 2048 x 1024 (48 MiB of weights): 16.4 -> 15.0 us, 10 at best (5 TB/s).
-constexpr int kFewRows = 16, kFewAhead = 8;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-struct FewStage {
-  u32x4 w[4], x;  // 16 gate rows, the next 16, the up rows of both; pair rows
-};
-template <bool ONCE>
-__device__ __forceinline__ void gemm1_few_product(const char* wp, const char* xp, int n, f32x4 (&acc)[4]) {
-  FewStage s[kFewAhead];
-  auto load = [&](FewStage& f, int st) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const u32x4* p = (const u32x4*)(wp + (size_t)st * kStageBytes + b * 1024);
-      f.w[b] = ONCE ? __builtin_nontemporal_load(p) : *p;
-    }
-    f.x = *(const u32x4*)(xp + (size_t)st * kRowBytes);
-    __builtin_amdgcn_sched_barrier(0);  // here, not where the values are needed
-  };
-  auto multiply = [&](const FewStage& f) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-      acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, f.w[b]), __builtin_bit_cast(bf16x8, f.x), acc[b], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-#pragma unroll
-  for (int u = 0; u < kFewAhead; ++u)
-    if (u < n) load(s[u], u);
-  int st = 0;
-  for (; st + 2 * kFewAhead <= n; st += kFewAhead) {
-#pragma unroll
-    for (int u = 0; u < kFewAhead; ++u) {
-      multiply(s[u]);
-      load(s[u], st + kFewAhead + u);
-    }
-  }
-  for (; st < n; st += kFewAhead) {
-#pragma unroll
-    for (int u = 0; u < kFewAhead; ++u) {
-      if (st + u < n) multiply(s[u]);
-      if (st + kFewAhead + u < n) load(s[u], st + kFewAhead + u);
-    }
-  }
-}
-__global__ __launch_bounds__(256, 2) void gemm1_few_kernel(Layout L, int T, const char* packed, const uint16_t* x, char* ws) {
-  __shared__ float part[4][16][64];  // wavefront, block * 4 + value, lane
-  int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int n = counters[0] * 4, id = take_piece<false>(n, counters + 8, (char*)part), q = id & 3;
-  if (id >= n) return;  // past the end of the list
-  const Item1 it = ((const Item1*)(ws + L.o_items1))[id >> 2];
-  if (it.half && q >= 2) return;
-  const bool sh = it.e == L.E_res;
-  const int Fp = sh ? L.F_shT : L.Fp, ld = sh ? L.F_shT : L.F, blk = (it.half == 2 ? 2 : 0) + q;
-  if (it.jt * kMfmaNeur + blk * 32 >= Fp) return;  // a last neuron tile that is not full
-  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r16 = lane & 15, c = lane >> 4;
-  const int KS1 = L.D / kBK, k0 = w * KS1 / 4, k1 = (w + 1) * KS1 / 4;
-  const int64_t tile = sh ? it.jt : ((int64_t)it.e * L.P + it.p) * L.NT1 + it.jt;
-  const char* wp = packed + (sh ? L.p_sw13 : L.p_w13) + (tile * KS1 + k0) * kStageBytes + (blk * 64 + r16) * kRowBytes + swz_chunk(r16, c) * 16;
-  const int rr = min(r16, it.nrows - 1);  // rows past the end re-read the last one
-  const char* xp = (const char*)x + (int64_t)((const int32_t*)(ws + L.o_row_token))[it.row0 + rr] * (L.D * 2) + k0 * kRowBytes + c * 16;
-  const int kept_bits = ((const uint8_t*)(ws + L.o_row_bits))[it.row0 + rr];
-  f32x4 acc[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (it.once) gemm1_few_product<true>(wp, xp, k1 - k0, acc);
-  else gemm1_few_product<false>(wp, xp, k1 - k0, acc);
-  // acc[b][i]: neuron 4 * (lane / 16) + i of the block, pair row lane % 16.  Each wavefront adds up and finishes two of the eight values.
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) part[w][b * 4 + i][lane] = acc[b][i];
-  __syncthreads();
-  const int b = w >> 1, i0 = (w & 1) * 2;
-  float h[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int v = b * 4 + i0 + i;
-    const float gate = (part[0][v][lane] + part[1][v][lane]) + (part[2][v][lane] + part[3][v][lane]);
-    const float up = (part[0][8 + v][lane] + part[1][8 + v][lane]) + (part[2][8 + v][lane] + part[3][8 + v][lane]);
-    h[i] = __uint_as_float(__float_as_uint(epi_value<true>(0, gate, up)) + 0x1000u);  // rounded as in gemm1_tile
-  }
-  const bool kept = r16 < it.nrows && ((kept_bits >> it.p) & 1);
-  uint16_t* H = sh ? (uint16_t*)(ws + L.o_Hs) : (uint16_t*)(ws + L.o_H);
-  const int row = (sh ? it.row0 : it.row0 - L.sh_rows) + r16, neuron = it.jt * kMfmaNeur + blk * 32 + b * 16 + c * 4 + i0;
-  if (r16 < it.nfill)  // rows [nrows, nfill) keep nothing of this partition: zeros
-    *(uint32_t*)(H + (size_t)row * ld + (size_t)it.p * Fp + neuron) = kept ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h[0], h[1])) : 0u;
-}
-
 template <int SUBS, bool YH, bool ONCE>
 __device__ __forceinline__ void gemm2_stream_item(const G2Args& g, char* lds, int w) {
   using R = RingStream2<SUBS>;
@@ -1031,20 +939,10 @@ static bool stream_halves(int items) {
   return items > slots / 4 && rest > 0 && rest <= slots / 2;
 }
 
-// Batches for gemm1_few_kernel.  Streaming kernel -> this one, us per layer, 25 % dropped, weights not cached: 1 / 3 tokens on 64 experts
-// of 2048 x 1024 (64 / 192 items) 40.8 -> 39.9 and 64.6 -> 60.6; 1 / 3 on 64 + 2 of 2048 x 1408 (94 / 238) 43.8 -> 44.0 and 70.0 -> 68.7; 1 on
-// four of 8 of 4096 x 14336 (224) 99.2 -> 96.3.  Longer lists fill the chip with larger pieces: 3 / 8 / 16 tokens on the last (448) 140 -> 147,
-// 179 -> 188, 209 -> 217; 8 / 16 on the first (512) 93.4 -> 91.4 and 115.2 -> 114.9.
-static bool few_items(const Layout& L, int T) { return T <= kFewRows && stream_experts(L, T) * L.P * L.NT1 + L.NT1_sh <= kSplitItems; }
-
 hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const void* x, char* ws, int epi, hipStream_t s) {
   if (T <= 0) return hipSuccess;
   hipError_t e = set_lds_attr();
   if (e != hipSuccess) return e;
-  if (L.stream && few_items(L, T) && ((uintptr_t)x & 15) == 0) {
-    gemm1_few_kernel<<<dim3(piece_blocks(false, 4 * items1_bound(L, T))), dim3(256), 0, s>>>(L, T, packed, (const uint16_t*)x, ws);
-    return hipGetLastError();
-  }
   if (L.stream) {
     const bool halves = stream_halves(stream_experts(L, T) * L.P * L.NT1 + L.NT1_sh);
     const dim3 grid(piece_blocks(false, (halves ? 2 : 1) * items1_bound(L, T))), block(256);

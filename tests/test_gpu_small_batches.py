@@ -51,10 +51,10 @@ def test_streaming_rows_of_one_expert(oracle, rows, D, Fp):
 
 
 @pytest.mark.parametrize("T", [1, 2, 15, 16, 17])
-@pytest.mark.parametrize("D,Fp", [(32, 32), (160, 96), (1056, 160), (2208, 288)], ids=["wavefronts_without_k", "one_or_two_stages", "stages_8_9", "stages_17_18"])
+@pytest.mark.parametrize("D,Fp", [(32, 32), (160, 96), (1056, 160), (2208, 288)], ids=["one_stage", "five_stages", "stages_33", "stages_69"])
 def test_few_rows(oracle, T, D, Fp):
-    # up to 16 tokens, 32 neurons to a workgroup and a quarter of K to a wavefront: quarters of 0, 1, 2, 8, 9, 17 and 18 stages; last neuron
-    # tiles of 32 to 96 neurons; whole items and halves (up to 128 items the list is cut); rows that keep nothing of a partition
+    # a few tokens: K of 1, 5, 33 and 69 stages; last neuron tiles of 32 to 96 neurons; whole items and halves (up to 128 items the list is
+    # cut); rows that keep nothing of a partition
     _check(oracle, spec_of(T=T, D=D, F=2 * Fp, E=8, K=2, P=2, n_shared=1, F_sh=Fp, seed=170 + T), "ragged", to_expert_0=T)
     _check(oracle, spec_of(T=T, D=D, F=4 * Fp, E=24, K=16, P=4, seed=171 + T), "rate0.25")
 
