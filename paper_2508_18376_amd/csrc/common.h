@@ -251,15 +251,18 @@ __device__ __forceinline__ float row_sum(float v) {  // every step adds two part
 // The piece of a list of n pieces of work that this workgroup takes (n: none).  Consecutive workgroups land on different XCDs
 // (round robin over 8), so each XCD gets a run of 32 consecutive pieces out of every 256 (the last ones: eight equal runs): pieces
 // that share a weight tile then share an L2.
-// FREE: the XCDs' shares are never equally long, so of a list of several rounds the last 128 to 383 pieces are handed out one
-// by one (*taken counts them; twice as many workgroups ask, so that an XCD that is ahead takes over from the others).  Runs of 32 to
-// the end left whole rounds to the first XCDs: 834 items of GEMM-1 (333 tokens on 64 + 2 experts of 2048 x 1408) were 128 each for two
-// XCDs and 96 for the others, the former done after 166 us, the latter after 122.  Layers of the sizes in perf/cases.py gain 0.5 - 1.5 %
-// (8192 tokens on 64 experts of 2048 x 1024 724 -> 715 us, 16384 on two of 8 of 4096 x 14336 1961 -> 1942), 1 token on the former 49.7 ->
-// 47.8.  Below kFreeFrom pieces the free ones are too large a part of the list for what their neighbours could share: free from 257
-// on, 128 / 512 tokens on the former lost 162 -> 167 and 186 -> 193 us.  The dealt part is whole runs: with the last 128 or 256 free
-// exactly, its last runs are cut at other places than the items that share a tile, and half of the gain is lost.  The streaming
-// kernels, two workgroups to a unit, gain nothing from free pieces.
+// Runs of 32 to the end left whole rounds to the first XCDs: 834 items of GEMM-1 (333 tokens on 64 + 2 experts of 2048 x 1408) were 128 each
+// for two XCDs and 96 for the others, the former done after 166 us, the latter after 122; with equal runs 1 token on 64 experts of
+// 2048 x 1024 takes 47.8 us instead of 49.7.
+// FREE: the XCDs' shares are never equally long, so of a list of kFreeFrom pieces and more the last 128 to 383 are handed out one by one
+// (*taken counts them; twice as many workgroups ask, so that an XCD that is ahead takes over from the others).  Dealt to the end -> free, us:
+// 7001 tokens on 64 + 2 of 2048 x 1408 853 -> 838, 16384 on two of 8 of 4096 x 14336 1974 -> 1963, calibration with 8192 tokens on 64 of
+// 2048 x 1024 592 -> 587; 4096 tokens on 8 of 4096 x 14336 and 8192 on 64 of 2048 x 1024 no difference.  Full-precision path: 777 tokens on
+// 64 + 2 in parts of 176 416 -> 399, 250 / 1024 fp32 tokens on 64 of 2048 x 1024 439 -> 420 and 1169 -> 1090, 512 by the box 552 -> 544 or
+// 521 -> 528, 64 on 64 of 2048 x 1000 in parts of 250 177 -> 179.  In shorter lists the free pieces are too large a part of the list for what their
+// neighbours could share: free from 257 on, 128 / 512 tokens on 64 of 2048 x 1024 lost 162 -> 167 and 186 -> 193 us.  The dealt part is whole
+// runs: with the last 128 or 256 free exactly, its last runs are cut at other places than the items that share a tile, and half of the gain is
+// lost.  The streaming kernels, two workgroups to a unit, gain nothing from free pieces.
 // lds: scratch of the workgroup, free again on return.
 constexpr int kFreeFrom = 1024;
 template <bool FREE>

@@ -34,7 +34,7 @@
 //   fp32, 64 experts of 2048 x 1024, 512 tokens top-8, 25 % dropped: GEMM-1 1250 -> 375 us (2.9 TB/s of weights), GEMM-2 545 -> 189 us
 //   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 208 us (4 TB/s), GEMM-2 1041 -> 224 us
 //   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 6 us, GEMM-2 33 -> 4 us (K split over several workgroups)
-// and with tiles of two images, the whole layer: 777 tokens of the second 431 -> 399 (GEMM-2 224 -> 150).
+// and with tiles of two images, the whole layer: 777 tokens of the second 431 -> 399 (GEMM-2 224 -> 160).
 #include "common.h"
 
 namespace dsmoe {
