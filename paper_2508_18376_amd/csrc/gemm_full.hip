@@ -15,7 +15,7 @@
 // bits of H at 5 x the rate of the fp32 instruction.  mid and lo can be zero: layers with an infinity or NaN in W2 (the packed
 // weights say so) leave those weights out of the two smaller products.
 //
-// Tiles of two images (bf16 layers) read the pair rows and cut fp32 activations half as often; the sums are the same bit for bit.  There
+// Tiles of two images (bf16 layers) read the pair rows and cut fp32 activations half as often; the sums are the same bit for bit (K splits apart).  There
 // GEMM-1 notes whether an activation came out infinite or NaN (kNonfiniteH), and GEMM-2 of other batches does without the clamp: 777 tokens on 64 + 2
 // experts of 2048 x 1408 in parts of 176 408 -> 397 us; with an infinite token or infinities in W2 427 (single images 431 and 453).
 // fp32 layers keep single images and the fp32 instruction: six products of bf16 parts of both operands are 2.7 x as fast (512 tokens on 64 experts of
