@@ -129,8 +129,6 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
   L.o_exp_nrows = take((int64_t)L.E_res * 4);
   L.o_exp_row0 = take((int64_t)L.E_res * 4);
   L.o_counters = take((kNonfiniteH + 1) * 4);
-  L.o_tile_bits = take((int64_t)L.max_tiles * 4);
-  L.o_act_rank = take((int64_t)L.max_tiles * L.P * 4);
   L.o_items1 = take((int64_t)L.max_items1 * sizeof(Item1));
   L.o_items2 = take((int64_t)L.max_items2 * sizeof(Item2));
   L.o_row_token = take((int64_t)L.row_cap * 4);
@@ -392,7 +390,7 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
     DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
                                (int32_t*)(ws + L.o_bin_count), nullptr, s));
     DSMOE_STEP(2, launch_plan(L, T, ws, s));
-    DSMOE_STEP(3, launch_scatter(L, T, ws, s));
+    mark(3);
   }
   DSMOE_STEP(4, L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 0, s)
                        : launch_gemm1_full(L, T, (const char*)packed, x, ws, 0, s));
@@ -590,7 +588,6 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
     err = launch_route(L, logits, T, nullptr, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
                        (uint8_t*)(ws + L.o_keep), (int32_t*)(ws + L.o_bin_count), nullptr, s);
   if (err == hipSuccess) err = launch_plan(L, T, ws, s);
-  if (err == hipSuccess) err = launch_scatter(L, T, ws, s);
   if (err == hipSuccess)
     err = L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 1 + metric, s)
                  : launch_gemm1_full(L, T, (const char*)packed, x, ws, 1 + metric, s);

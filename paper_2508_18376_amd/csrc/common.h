@@ -100,7 +100,7 @@ struct Layout {
   int32_t pool_tiles;         // partial-output tiles of the workspace (GEMM-2 K splits)
   // workspace byte offsets
   int64_t o_idx, o_w, o_keep, o_pair_row, o_bin_count, o_cursor, o_exp_nrows, o_exp_row0, o_counters;
-  int64_t o_tile_bits, o_act_rank, o_items1, o_items2;
+  int64_t o_items1, o_items2;
   int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
   // packed weights byte offsets
   int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the W2 scale record (MFMA layout); int32: W2 has an infinity or NaN (full-precision layout)
@@ -175,8 +175,9 @@ hipError_t launch_route(const Layout& L, const float* logits, int T, const float
 // The normalised scores instead of routing results: their histograms per expert of the whole router (sel: rows of kSelRow,
 // cleared by the caller), or the scores themselves (n [T][K], -1 where the expert is not resident; sel == nullptr).
 hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s);
+// plan and row lists
 hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s);
-// small batches: routing, plan and scatter in one launch
+// small batches: routing, plan and row lists in one launch
 bool small_plan(const Layout& L, int T);
 hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const float* tau, char* ws, hipStream_t s);
 hipError_t launch_scatter(const Layout& L, int T, char* ws, hipStream_t s);

@@ -42,7 +42,7 @@ __device__ __forceinline__ int sub_of_bits(int bits, int nsub_bits) {
   return (1 << nsub_bits) - 1 - rev;
 }
 
-// tau: the [E][P] threshold table (the sixteen-lanes-per-token kernel keeps a copy in LDS)
+// tau: the [E][P] threshold table (in LDS)
 __device__ __forceinline__ int keep_bits_of(float n, int e, const RouteArgs& a, const float* tau) {
   int bits = 0;
   if (e >= a.lo && e < a.hi) {
@@ -104,59 +104,65 @@ __device__ __forceinline__ void flush_hist(const RouteArgs& a, const int32_t* hi
 }
 
 // One lane per token; all E logits of the token live in that lane's registers (E <= EPAD <= 32).
+// tau: the threshold table in LDS.  All threads of the workgroup take part: the barrier that publishes it and the cleared histogram sits right
+// before their first use, so that the table is fetched together with the logits.
 template <int EPAD, int KMAX, int MODE>
-__device__ __forceinline__ void route_lane_token(const RouteArgs& a, int t, int32_t* hist, int32_t* pairs) {
-  float l[EPAD];
-#pragma unroll
-  for (int e = 0; e < EPAD; ++e) l[e] = (e < a.E) ? a.logits[(size_t)t * a.E + e] : -INFINITY;
-  float m = l[0];
-#pragma unroll
-  for (int e = 1; e < EPAD; ++e) m = (e < a.E && l[e] > m) ? l[e] : m;
-  float z = 0.f;
-#pragma unroll
-  for (int e = 0; e < EPAD; ++e)
-    if (e < a.E) z += expf(l[e] - m);
-  // Top-K: K rounds of "largest not yet taken"; a later index wins only if strictly larger.
-  float sk[KMAX];
+__device__ __forceinline__ void route_lane_token(const RouteArgs& a, int t, int32_t* hist, int32_t* pairs, const float* tau) {
+  float sk[KMAX], sel = 0.f;
   int ik[KMAX];
-  unsigned long long taken = 0ull;
-  float sel = 0.f;
+  if (t < a.T) {
+    float l[EPAD];
 #pragma unroll
-  for (int k = 0; k < KMAX; ++k) {
-    sk[k] = 0.f;
-    ik[k] = 0;
-    if (k < a.K) {
-      float bv = 0.f;
-      int be = -1;
+    for (int e = 0; e < EPAD; ++e) l[e] = (e < a.E) ? a.logits[(size_t)t * a.E + e] : -INFINITY;
+    float m = l[0];
 #pragma unroll
-      for (int e = 0; e < EPAD; ++e) {
-        bool free_e = (e < a.E) && !((taken >> e) & 1ull);
-        if (free_e && (be < 0 || l[e] > bv)) {
-          bv = l[e];
-          be = e;
+    for (int e = 1; e < EPAD; ++e) m = (e < a.E && l[e] > m) ? l[e] : m;
+    float z = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPAD; ++e)
+      if (e < a.E) z += expf(l[e] - m);
+    // Top-K: K rounds of "largest not yet taken"; a later index wins only if strictly larger.
+    unsigned long long taken = 0ull;
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k) {
+      sk[k] = 0.f;
+      ik[k] = 0;
+      if (k < a.K) {
+        float bv = 0.f;
+        int be = -1;
+#pragma unroll
+        for (int e = 0; e < EPAD; ++e) {
+          bool free_e = (e < a.E) && !((taken >> e) & 1ull);
+          if (free_e && (be < 0 || l[e] > bv)) {
+            bv = l[e];
+            be = e;
+          }
         }
+        taken |= 1ull << be;
+        ik[k] = be;
+        sk[k] = expf(bv - m) / z;  // Eq. 1
+        sel += sk[k];
       }
-      taken |= 1ull << be;
-      ik[k] = be;
-      sk[k] = expf(bv - m) / z;  // Eq. 1
-      sel += sk[k];
     }
   }
+  __syncthreads();
+  if (t >= a.T) return;
 #pragma unroll
   for (int k = 0; k < KMAX; ++k) {
     if (k < a.K) {
       const float n = sk[k] / sel;  // Sec. 4.1: normalise over the K selected
-      finish_pair<MODE>(a, hist, pairs, a.tau, t, k, ik[k], n, sk[k]);
+      finish_pair<MODE>(a, hist, pairs, tau, t, k, ik[k], n, sk[k]);
     }
   }
 }
 template <int EPAD, int KMAX, int MODE>
 __global__ __launch_bounds__(64) void route_lane_kernel(RouteArgs a) {
   extern __shared__ int32_t hist[];
+  float* tau_l = (float*)(hist + a.nhist);
+  if (a.tau)
+    for (int i = threadIdx.x; i < a.E * a.P; i += 64) tau_l[i] = a.tau[i];
   for (int i = threadIdx.x; i < a.nhist; i += 64) hist[i] = 0;
-  __syncthreads();
-  const int t = blockIdx.x * 64 + threadIdx.x;
-  if (t < a.T) route_lane_token<EPAD, KMAX, MODE>(a, t, hist, nullptr);
+  route_lane_token<EPAD, KMAX, MODE>(a, blockIdx.x * 64 + threadIdx.x, hist, nullptr, tau_l);
   __syncthreads();
   flush_hist(a, hist, 64);
 }
@@ -376,598 +382,622 @@ hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int3
 }
 
 // ------------------------------------------------------------------------------------- plan
-// Turns the bin histogram into row offsets, the row-tile table and the two work lists of the grouped
-// GEMMs: two workgroups, each of which works out the tables and writes one list (and a third for the row
-// lists of a batch that the kernel routes itself, see launch_small_plan).  Everything stays on the device: the
-// GEMM grids are sized for the worst case and read their item count from the counters this kernel writes.
+// Turns the bin histogram into row offsets, the row lists and the two work lists of the grouped GEMMs, all in one launch: workgroup 0
+// writes the GEMM-2 list, workgroup 1 the GEMM-1 list, the others the row lists; small batches are routed here as well.  Every workgroup
+// works the tables that it needs out for itself.  Everything stays on the device: the GEMM grids are sized for the worst case and
+// read their item count from the counters this kernel writes.
+//
+// The kernel is latency and nothing else: one workgroup's chain of memory and LDS round trips, barriers and instructions that a single compute unit
+// issues.  So the chain is short: one wavefront makes the table of the experts (lane = expert, scans in registers) while the others
+// count the tiles of the (expert, partition) groups, and whatever depends on an expert's sort bins (rows of a tile that keep a
+// partition, a tile's place among those that do) is worked out from the bins' counts in one loop, by one thread.
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanTilesLds = 2048;  // row tiles whose keep patterns fit in the plan kernel's LDS
-constexpr int kSmallPlanTokens = 64;  // tokens that one workgroup routes at once
+constexpr int kPlanTilesLds = 2048;   // row tiles whose experts fit in the plan kernel's LDS (beyond: a search)
+constexpr int kPlanRecords = kPlanThreads - 64;  // (row tile, partition) pairs that are looked at in one go
+constexpr int kHalvedMost = kSplitItems / 2;  // GEMM-1 items of a last round that may be cut in two
+constexpr int kLanePlanPairs = 2048;  // routed here with a lane per token: up to so many pairs (and tokens a workgroup has threads for)
+constexpr int kRowPlanTokens = 64;    // with sixteen lanes per token: what one workgroup routes at once
+constexpr int kListPairs = 4;         // pairs per thread of a workgroup that writes row lists
 
 // the plan kernel's tables (in the order in which it lays them out)
-__host__ __device__ inline size_t plan_lds_bytes(const Layout& L) {
+__host__ __device__ inline int plan_lds_words(const Layout& L) {
   const int E_tot = L.E_res + (L.n_shared > 0 ? 1 : 0), NG = E_tot * L.P;
-  const int groups = 2 * (NG + 1) > L.nbins ? 2 * (NG + 1) : L.nbins;  // (a small batch's bin cursors take the place of the groups' counts)
-  return sizeof(int32_t) * (size_t)(L.nbins + 5 * (E_tot + 2) + groups + kPlanThreads + kPlanTilesLds + kPlanTilesLds / 2 + 8);
+  const int groups = 2 * NG > L.nbins ? 2 * NG : L.nbins;  // (the workgroups with the row lists keep the next row of every bin there)
+  return ((L.nbins + 3) & ~3) + ((3 * E_tot + 3) & ~3) + ((groups + 3) & ~3) + kPlanTilesLds / 2 + kPlanRecords * 4 + kHalvedMost * (int)(sizeof(Item1) / 4);
+}
+constexpr int kSumWords = 8192;  // partial column sums of the histograms (LANES == 0), behind the tables
+
+// inclusive sum over the lanes of a wavefront, in registers
+__device__ __forceinline__ int wave_incl_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // from 1, 2, 4, 8 lanes before, inside a row of sixteen
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // the last lane of rows 0 and 2 to the rows after them
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // the sum of the first half to the second
+  return v;
 }
 
-// exclusive scan of a[0..n) in LDS (n <= 8 * kPlanThreads); returns the total. tmp: kPlanThreads ints.
-// Each thread owns a run of elements; the runs are scanned inside each wavefront with lane shifts
-// and the sixteen wavefront totals by the first wavefront: three barriers in all (one for short arrays).
-__device__ int block_excl_scan(int32_t* a, int n, int32_t* tmp) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (n <= 512) {  // short arrays (experts, groups): the first wavefront alone, one barrier
-    if (wv == 0) {
-      const int per = (n + 63) >> 6;
-      const int lo = lane * per, hi = min(n, lo + per);
-      int sum = 0;
-      for (int i = lo; i < hi; ++i) sum += a[i];
-      int incl = sum;
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
+// Orders LDS accesses only: the workgroups of the plan kernel hand each other nothing through global memory, and waiting for its
+// stores at every barrier (as __syncthreads does) would cost a round trip to memory each time.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The sort bins of an expert: the rows are sorted by keep pattern, so every bin is a range of rows.  Loops over them stay loops: unrolled
+// over sixteen bins at every use they were 10 KiB more instructions, which a launch fetches from memory, and slower.
+template <int NSB>  // partitions in the sort key
+struct Bins {
+  static constexpr int N = 1 << NSB;
+  // does bin sb keep partition p? (partitions outside the sort key: assumed kept)
+  static __device__ __forceinline__ bool keeps(int sb, int p) { return p >= NSB || (((N - 1 - sb) >> (NSB - 1 - p)) & 1); }
+  static __device__ __forceinline__ int pattern(int sb, int P) {
+    return (int)(__brev((unsigned)(N - 1 - sb)) >> (32 - NSB)) | (((1 << P) - 1) & ~(N - 1));
+  }
+  // f(sb, first row, end) for every bin that has rows, in row order; returns the expert's rows
+  template <class F>
+  static __device__ __forceinline__ int each(const int32_t* bin_count, int e, F&& f) {
+    int off = 0;
+    const int32_t* src = bin_count + e * N;
+    auto one = [&](int sb, int c) {
+      if (c > 0) f(sb, off, off + c);
+      off += c;
+    };
+    if constexpr (N >= 4) {
+#pragma unroll 1
+      for (int b = 0; b < N; b += 4) {
+        const int4 v = *(const int4*)(src + b);
+        one(b, v.x), one(b + 1, v.y), one(b + 2, v.z), one(b + 3, v.w);
       }
-      int run = incl - sum;
-      for (int i = lo; i < hi; ++i) {
-        const int v = a[i];
-        a[i] = run;
-        run += v;
-      }
-      if (lane == 63) tmp[128] = incl;
+    } else {
+      const int2 v = *(const int2*)src;
+      one(0, v.x), one(1, v.y);
     }
-    __syncthreads();
-    return tmp[128];
+    return off;
   }
-  const int per = (n + kPlanThreads - 1) / kPlanThreads;
-  const int lo = tid * per, hi = min(n, lo + per);
-  int sum = 0;
-  for (int i = lo; i < hi; ++i) sum += a[i];
-  int incl = sum;  // inclusive scan over the lanes of this wavefront
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
+  static __device__ __forceinline__ int rows(const int32_t* bin_count, int e) {
+    return each(bin_count, e, [](int, int, int) {});
   }
-  if (lane == 63) tmp[wv] = incl;
-  __syncthreads();
-  if (wv == 0) {
-    const int t = lane < kPlanThreads / 64 ? tmp[lane] : 0;
-    int inc = t;
-    for (int o = 1; o < kPlanThreads / 64; o <<= 1) {
-      const int v = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += v;
+  // partitions kept by some row of the rows [r0, r1), of [r1, r2)
+  static __device__ __forceinline__ int2 kept(const int32_t* bin_count, int e, int r0, int r1, int r2, int P) {
+    int2 bits = make_int2(0, 0);
+    each(bin_count, e, [&](int sb, int off, int end) {
+      const int pat = pattern(sb, P);
+      bits.x |= off < r1 && end > r0 ? pat : 0;
+      bits.y |= off < r2 && end > r1 ? pat : 0;
+    });
+    return bits;
+  }
+};
+// Partition p in an expert's row tiles of 2^bm rows.  With thresholds that grow with p the rows that keep p are a prefix of the
+// expert's rows; in general the counts bound them (rows in between that lack p are zeroed by the GEMM-1 epilogue).
+struct TileUse {
+  int rows;         // rows of the tile up to the last one that keeps p (0: none does)
+  int next_rows;    // the same for the next tile
+  int before;       // tiles before it of which some row keeps p
+  bool full_before; // the last row of the tile before keeps p
+};
+template <int NSB>
+__device__ __forceinline__ TileUse tile_use(const int32_t* bin_count, int e, int i, int bm, int p) {
+  const int r0 = i << bm, r1 = r0 + (1 << bm), r2 = r1 + (1 << bm);
+  TileUse u = {0, 0, 0, false};
+  int next = 0;  // first tile that has not been looked at
+  Bins<NSB>::each(bin_count, e, [&](int sb, int off, int end) {
+    if (Bins<NSB>::keeps(sb, p)) {
+      if (off < r1 && end > r0) u.rows = min(r1, end) - r0;
+      if (off < r2 && end > r1) u.next_rows = min(r2, end) - r1;
+      if (off < r0 && end >= r0) u.full_before = true;
+      const int hi = min((end - 1) >> bm, i - 1), lo = max(off >> bm, next);
+      if (hi >= lo) u.before += hi - lo + 1, next = hi + 1;
     }
-    if (lane < kPlanThreads / 64) tmp[64 + lane] = inc - t;  // exclusive offset of each wavefront
-    if (lane == kPlanThreads / 64 - 1) tmp[128] = inc;       // grand total
-  }
-  __syncthreads();
-  int run = tmp[64 + wv] + incl - sum;
-  const int total = tmp[128];
-  for (int i = lo; i < hi; ++i) {
-    const int v = a[i];
-    a[i] = run;
-    run += v;
-  }
-  __syncthreads();
-  return total;
+  });
+  return u;
 }
 
-// LANES: 0: the batch has been routed (its histograms are in the workspace).  Else the workgroups route it themselves, see
+// LANES: 0: the batch has been routed (its histograms are in the workspace).  Else every workgroup routes it, see
 // launch_small_plan: 8 or 32: a lane per token and at most that many experts; 16: sixteen lanes per token, at most 64 experts.
-template <int LANES>
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, char* ws, RouteArgs ra) {
-  extern __shared__ int32_t sm[];
-  int32_t* bin_count = sm;  // [nbins]
-  int32_t* pairs = sm + (int)(plan_lds_bytes(L) / sizeof(int32_t));  // LANES: see finish_pair
+// chunk: LANES == 0: route blocks whose pairs a workgroup of the row lists takes (0: no such workgroups, launch_scatter follows).
+template <int LANES, int NSB>
+__global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, char* ws, RouteArgs ra, int chunk) {
+  extern __shared__ __attribute__((aligned(16))) int32_t sm[];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int E_res = L.E_res, P = NSB < kSubBits ? NSB : L.P, BM = L.BM;
+  const int units_log2 = 31 - __clz(max(L.split_items, 1));  // (powers of two)
+  const int has_sh = L.n_shared > 0 ? 1 : 0;
+  const int E_tot = E_res + has_sh, NG = E_tot * P;  // (expert, partition) groups; the shared pseudo-expert only uses p = 0
+  const int bm = 31 - __clz(BM);                     // the tile heights are powers of two
+  auto tiles_of = [&](int rows) { return (rows + BM - 1) >> bm; };
+  auto short_rows = [&](int n) {  // rows of a last tile that the one before it can take along, else 0
+    const int nt = tiles_of(n), last = n - (nt - 1) * BM;
+    return nt >= 2 && last <= kTallExtra ? last : 0;
+  };
+  int32_t* bin_count = sm;                         // [nbins]
+  int32_t* ne = sm + ((L.nbins + 3) & ~3);         // [E_tot] rows of each expert
+  int32_t* ts = ne + E_tot;                        // [E_tot] first tile.  Order in the row space: the shared pseudo-expert (id E_res), then the others by id
+  int32_t* ab = ts + E_tot;                        // [E_tot] 2 x (short last tiles of the experts before) + (this one's is short), see below
+  int32_t* ga = ab + E_tot;                        // [NG] active tiles of each group
+  int32_t* gb = ga + NG;                           // [NG] item base of each group
+  int32_t* next = ga;                              // row lists: [nbins] next row of every bin
+  int32_t* tail = sm + plan_lds_words(L) - kHalvedMost * (int)(sizeof(Item1) / 4);  // the items of a last round that may be cut
+  int4* rec = (int4*)(tail - kPlanRecords * 4);    // what step 4 finds out about the (row tile, partition) pairs
+  uint8_t* kmask_l = (uint8_t*)rec;                // GEMM-2: partitions of the first tiles
+  uint16_t* texp = (uint16_t*)rec - kPlanTilesLds; // experts of the first kPlanTilesLds tiles
+  int32_t* pairs = sm + plan_lds_words(L);         // LANES: see finish_pair; else partial sums
+  __shared__ int total_tiles_l, total_short_l, multi_l[2], est[4], split_l[2], k_lo[2][kMaxSplit + 1];
+  static_assert(kPlanRecords * 16 >= kPlanTilesLds && kMaxTailSplit <= kMaxSplit, "");
+  const bool lists2 = blockIdx.x == 0, lists1 = blockIdx.x == 1, rows_list = blockIdx.x >= 2;
+
+  // 0. rows of every sort bin
+  int pr_keep[kListPairs], pr_e[kListPairs];  // row lists, LANES == 0: this thread's pairs, fetched with the histograms
+  int64_t pr0 = 0, pr1 = 0;                   // the pairs of this workgroup
+  if (tid < 4) est[tid] = 0;
   if constexpr (LANES != 0) {
-    if (blockIdx.x != 2) ra.idx = nullptr;  // one workgroup writes the routing results
-    int32_t* mine = blockIdx.x == 2 ? pairs : nullptr;
+    if (!rows_list) ra.idx = nullptr;  // one workgroup writes the routing results
+    int32_t* mine = rows_list ? pairs : nullptr;
     if constexpr (LANES == 16) {
       route_row_tokens<1, 1, kPlanThreads / 64, kRouteInLds>(ra, 0, bin_count, (float*)(pairs + T * L.K), mine);
     } else {
-      for (int i = threadIdx.x; i < L.nbins; i += kPlanThreads) bin_count[i] = 0;
-      __syncthreads();
-      if ((int)threadIdx.x < T) route_lane_token<LANES, (LANES < 16 ? LANES : 16), kRouteInLds>(ra, threadIdx.x, bin_count, mine);
+      float* tau_l = (float*)(pairs + T * L.K);  // fetched now, together with the logits, not after the scores are known
+      for (int i = tid; i < L.E * P; i += kPlanThreads) tau_l[i] = ra.tau[i];
+      for (int i = tid; i < L.nbins; i += kPlanThreads) bin_count[i] = 0;
+      route_lane_token<LANES, (LANES < 16 ? LANES : 16), kRouteInLds>(ra, tid, bin_count, mine, tau_l);
     }
-    __syncthreads();
+    pr1 = (int64_t)T * L.K;
   } else {
-    // 0. column sums of the route kernel's per-block histograms -> bins[] in LDS
+    // column sums of the route kernel's per-block histograms; for the row lists also of the blocks before this workgroup's
     const int32_t* blk_hist = (const int32_t*)(ws + L.o_bin_count);
-    const int nblk = (T + route_block_tokens(L.E, T) - 1) / route_block_tokens(L.E, T);
-    // rows r0, r0 + step, .. of column c, eight independent loads at a time (the sum is latency bound)
-    auto col_sum = [&](int c, int r0, int step) {
-      const int32_t* col = blk_hist + c;
-      int sum = 0, r = r0;
-      for (; r + 7 * step < nblk; r += 8 * step) {
-        int v[8];
+    const int bt = route_block_tokens(L.E, T), nblk = (T + bt - 1) / bt;
+    const int blk0 = rows_list ? ((int)blockIdx.x - 2) * chunk : 0;
+    if (rows_list) {
+      const uint8_t* keep = (const uint8_t*)(ws + L.o_keep);
+      const int32_t* idx = (const int32_t*)(ws + L.o_idx);
+      pr0 = (int64_t)blk0 * bt * L.K;
+      pr1 = min((int64_t)T * L.K, pr0 + (int64_t)chunk * bt * L.K);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = col[(size_t)(r + u * step) * L.nbins];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sum += v[u];
+      for (int u = 0; u < kListPairs; ++u) {
+        const int64_t pr = min(pr0 + u * kPlanThreads + tid, pr1 - 1);
+        pr_keep[u] = keep[pr];
+        pr_e[u] = idx[pr];
       }
-      for (; r < nblk; r += step) sum += col[(size_t)r * L.nbins];
-      return sum;
-    };
-    const int G = kPlanThreads / L.nbins;  // threads that share a column (0: more columns than threads)
-    if (G <= 1) {
-      for (int c = threadIdx.x; c < L.nbins; c += kPlanThreads) bin_count[c] = col_sum(c, 0, 1);
-    } else {
-      for (int i = threadIdx.x; i < L.nbins; i += kPlanThreads) bin_count[i] = 0;
-      __syncthreads();
-      const int c = threadIdx.x % L.nbins, g = threadIdx.x / L.nbins;
+    }
+    // Four columns to a thread, up to sixteen threads to a column, up to sixteen rows in flight each; the partial sums meet in LDS.
+    const int nb = L.nbins;
+    if ((nb & 3) == 0 && nb <= kSumWords / 2) {
+      const int cols = nb >> 2, G = min(16, kPlanThreads / cols);
+      const int g = tid / cols, c4 = tid - g * cols;
+      int4 sum = make_int4(0, 0, 0, 0), before = sum;
       if (g < G) {
-        const int sum = col_sum(c, g, G);
-        if (sum) atomicAdd(&bin_count[c], sum);
+        for (int r = 0; r < nblk; r += 16 * G) {
+          int4 v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (r + u * G < nblk) v[u] = *(const int4*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c4 * 4);
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (r + u * G < nblk) {
+              const int row = r + u * G + g, in = row < nblk ? -1 : 0, pre = row < blk0 ? -1 : 0;
+              sum.x += v[u].x & in, sum.y += v[u].y & in, sum.z += v[u].z & in, sum.w += v[u].w & in;
+              before.x += v[u].x & pre, before.y += v[u].y & pre, before.z += v[u].z & pre, before.w += v[u].w & pre;
+            }
+        }
+        *(int4*)(pairs + g * nb + c4 * 4) = sum;
+        if (rows_list) *(int4*)(pairs + kSumWords / 2 + g * nb + c4 * 4) = before;
+      }
+      lds_barrier();
+      for (int c = tid; c < nb; c += kPlanThreads) {
+        int n = 0, m = 0;
+        for (int q = 0; q < G; ++q) {
+          n += pairs[q * nb + c];
+          if (rows_list) m += pairs[kSumWords / 2 + q * nb + c];
+        }
+        bin_count[c] = n;
+        if (rows_list) next[c] = m;
+      }
+    } else {
+      for (int c = tid; c < nb; c += kPlanThreads) {
+        int n = 0, m = 0;
+        for (int r = 0; r < nblk; ++r) {
+          const int v = blk_hist[(size_t)r * nb + c];
+          n += v;
+          m += r < blk0 ? v : 0;
+        }
+        bin_count[c] = n;
+        if (rows_list) next[c] = m;
       }
     }
-    __syncthreads();
   }
-  const int tid = threadIdx.x;
-  // All workgroups work out the tables that the lists are made from (row counts, tile patterns, short
-  // last tiles); then workgroup 0 writes the GEMM-2 list and workgroup 1 the GEMM-1 list, side by side
-  // (and workgroup 2 of a small batch the row lists).
-  const bool lists2 = blockIdx.x == 0, lists1 = !lists2;
-  const int E_res = L.E_res;
-  const int has_sh = L.n_shared > 0 ? 1 : 0;
-  const int E_tot = E_res + has_sh;
-  const int NG = E_tot * L.P;  // (expert, partition) groups; the shared pseudo-expert only uses p = 0
-  int32_t* ne = sm + L.nbins;       // [E_tot] rows of each expert
-  int32_t* rs = ne + E_tot + 1;     // [E_tot] first row (tile aligned)
-  int32_t* ts = rs + E_tot + 1;     // [E_tot] first tile
-  int32_t* pt = ts + E_tot + 1;     // [E_tot+1] first tile by POSITION in the row space
-  int32_t* ga = pt + E_tot + 2;     // [NG] active tiles of each group
-  int32_t* gb = ga + NG + 1;        // [NG+1] item base of each group
-  int32_t* abp = gb + NG + 1;       // [E_tot+1] by POSITION: short last tiles (absorbed by tall items) of the experts before
-  int32_t* tmp = abp + E_tot + 2;   // [kPlanThreads]
+  lds_barrier();
 
-  int32_t* cursor = (int32_t*)(ws + L.o_cursor);
-  int32_t* exp_nrows = (int32_t*)(ws + L.o_exp_nrows);
-  int32_t* exp_row0 = (int32_t*)(ws + L.o_exp_row0);
-  int32_t* counters = (int32_t*)(ws + L.o_counters);
-  int32_t* act_rank = (int32_t*)(ws + L.o_act_rank);
-  Item1* items1 = (Item1*)(ws + L.o_items1);
-  Item2* items2 = (Item2*)(ws + L.o_items2);
-  const int BM = L.BM;
-  const int bm_sh = 31 - __clz(BM);  // the tile heights are powers of two
-  auto tiles_of = [&](int rows) { return (rows + BM - 1) >> bm_sh; };
-  const int nsub_bits = L.P < kSubBits ? L.P : kSubBits;
-
-  // 1. rows per expert.  Order of the experts in the row space: the shared pseudo-expert first
-  //    (its size is known without the histogram), then the resident experts by id.
-  //    position i -> expert: with shared experts, position 0 is id E_res and position i is id i-1.
-  for (int e = tid; e < E_tot; e += kPlanThreads) {
-    int n = 0;
-    if (e < E_res)
-      for (int sb = 0; sb < L.nsub; ++sb) n += bin_count[e * L.nsub + sb];
-    else
-      n = T;
-    ne[e] = n;
-  }
-  __syncthreads();
-  // 2. tile-aligned row starts: exclusive scan of the tile counts in position order
-  for (int i = tid; i < E_tot; i += kPlanThreads) {
-    int e = has_sh ? (i == 0 ? E_res : i - 1) : i;
-    pt[i] = tiles_of(ne[e]);
-  }
-  __syncthreads();
-  const int total_tiles = block_excl_scan(pt, E_tot, tmp);
-  if (tid == 0) pt[E_tot] = total_tiles;
-  for (int i = tid; i < E_tot; i += kPlanThreads) {
-    int e = has_sh ? (i == 0 ? E_res : i - 1) : i;
-    ts[e] = pt[i];
-    rs[e] = pt[i] * BM;
-  }
-  __syncthreads();
-  if (lists2) {
-    for (int e = tid; e < E_res; e += kPlanThreads) {
-      exp_nrows[e] = ne[e];
-      exp_row0[e] = rs[e];
+  // 1. The experts' table, by the first wavefront.
+  // A short last tile of an expert (at most kTallExtra rows) has no GEMM-2 items of its own: the items of the tile before it are
+  // tall and compute its rows too.  Only if the short tile keeps no partition that the tile before it drops: the tall items run over
+  // the partitions of the full tile, and where the short tile lacks one of them its rows of H are zeros (written by the
+  // GEMM-1 item of the full tile, see step 4).
+  if (wv == 0) {
+    int tiles = 0, shorts = 0;
+    uint64_t multi = 0;  // bit e & 63: some expert e has more than one row tile
+    if (has_sh) {
+      const int nt = tiles_of(T), s = L.tall_tiles && short_rows(T) ? 1 : 0;
+      if (lane == 0) ne[E_res] = T, ts[E_res] = 0, ab[E_res] = s;
+      if (!rows_list)
+        for (int i = lane; i < min(nt, kPlanTilesLds); i += 64) texp[i] = (uint16_t)E_res;
+      tiles = nt, shorts = s;
+    }
+    for (int e0 = 0; e0 < E_res; e0 += 64) {
+      const int e = e0 + lane;
+      const int n = e < E_res ? Bins<NSB>::rows(bin_count, e) : 0, nt = tiles_of(n);
+      int s = 0;
+      if (!rows_list && L.tall_tiles && short_rows(n)) {
+        const int2 bits = Bins<NSB>::kept(bin_count, e, (nt - 2) * BM, (nt - 1) * BM, n, P);
+        s = (bits.y & ~bits.x) == 0 ? 1 : 0;
+      }
+      const int incl = wave_incl_sum(nt), t0 = tiles + incl - nt;
+      const uint64_t short_m = __ballot(s);
+      multi |= __ballot(nt > 1);
+      if (e < E_res) {
+        ne[e] = n;
+        ts[e] = t0;
+        ab[e] = 2 * (shorts + __popcll(short_m & ((1ull << lane) - 1))) + s;
+        if (rows_list || (lists2 && LANES == 0 && chunk == 0)) {
+          int32_t* cursor = (int32_t*)(ws + L.o_cursor);  // where the scatter kernel starts
+          int off = t0 * BM;
+          for (int bin = e * Bins<NSB>::N; bin < (e + 1) * Bins<NSB>::N; ++bin) {
+            if (!rows_list) cursor[bin] = off;
+            else next[bin] = (LANES == 0 ? next[bin] : 0) + off;  // (behind the rows of the blocks before this workgroup's)
+            off += bin_count[bin];
+          }
+        }
+        if (!rows_list)
+          for (int i = t0; i < min(t0 + nt, kPlanTilesLds); ++i) texp[i] = (uint16_t)e;
+        if (lists2) {
+          ((int32_t*)(ws + L.o_exp_nrows))[e] = n;
+          ((int32_t*)(ws + L.o_exp_row0))[e] = t0 * BM;
+        }
+      }
+      tiles += __builtin_amdgcn_readlane(incl, 63);
+      shorts += __popcll(short_m);
+    }
+    if (lane == 0) {
+      total_tiles_l = tiles;
+      total_short_l = shorts;
+      multi_l[0] = (int)(uint32_t)multi, multi_l[1] = (int)(uint32_t)(multi >> 32);
     }
   }
-  if (LANES != 0 && blockIdx.x == 2) {  // what the scatter kernel does for larger batches
+
+  // 2. The row lists.  The order inside a bin is arbitrary (it is decided by atomics); the layer output does not depend on it because
+  // every row is computed independently of its tile neighbours.
+  if (rows_list) {
     int32_t* pair_row = (int32_t*)(ws + L.o_pair_row);
     int32_t* row_token = (int32_t*)(ws + L.o_row_token);
     uint8_t* row_bits = (uint8_t*)(ws + L.o_row_bits);
-    int32_t* next = ga;  // [nbins] next row of every bin
-    for (int b = tid; b < L.nbins; b += kPlanThreads) {
-      const int e = b / L.nsub, sb = b % L.nsub;
-      int off = rs[e];
-      for (int s2 = 0; s2 < sb; ++s2) off += bin_count[e * L.nsub + s2];
-      next[b] = off;
-    }
-    __syncthreads();
-    for (int pr = tid; pr < T * L.K; pr += kPlanThreads) {
-      const int bits = pairs[pr] & 255, e = (pairs[pr] >> 8) - L.lo;
+    lds_barrier();
+    auto place = [&](int64_t pr, int bits, int e) {
       int row = -1;
       if (bits) {
-        row = atomicAdd(&next[e * L.nsub + sub_of_bits(bits, nsub_bits)], 1);
-        row_token[row] = pr / L.K;
+        row = atomicAdd(&next[(e - L.lo) * Bins<NSB>::N + sub_of_bits(bits, NSB)], 1);
+        row_token[row] = (int32_t)(pr / L.K);
         row_bits[row] = (uint8_t)bits;
       }
       pair_row[pr] = row;
+    };
+    if constexpr (LANES != 0) {
+      for (int pr = tid; pr < (int)pr1; pr += kPlanThreads) place(pr, pairs[pr] & 255, pairs[pr] >> 8);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kListPairs; ++u)
+        if (pr0 + u * kPlanThreads + tid < pr1) place(pr0 + u * kPlanThreads + tid, pr_keep[u], pr_e[u]);
     }
-    if (has_sh && tid < T) {
-      row_token[tid] = tid;
-      row_bits[tid] = 1;
-    }
+    if (has_sh)  // the shared pseudo-expert's rows are the tokens themselves, at the start of the row space
+      for (int t = (int)(pr0 / L.K) + tid; t < (int)(pr1 / L.K); t += kPlanThreads) {
+        row_token[t] = t;
+        row_bits[t] = 1;
+      }
     return;
   }
-  // 3. first row of every bin; the scatter kernel's cursors start there
-  if (lists2 && LANES == 0) {
-    for (int b = tid; b < L.nbins; b += kPlanThreads) {
-      int e = b / L.nsub, sb = b % L.nsub;
-      int off = rs[e];
-      for (int s2 = 0; s2 < sb; ++s2) off += bin_count[e * L.nsub + s2];
-      cursor[b] = off;
-    }
-  }
-  // 4. row tiles are described on the fly from the LDS tables (no round trip through global memory):
-  //    tile g belongs to the expert at the last position whose first tile is <= g
-  auto find_expert = [&](int g) {
-    int lo_i = 0, hi_i = E_tot;  // first position with pt > g
-    while (lo_i < hi_i) {
-      int mid = (lo_i + hi_i) >> 1;
-      if (pt[mid] > g) hi_i = mid;
-      else lo_i = mid + 1;
-    }
-    const int pos = lo_i - 1;
-    return has_sh ? (pos == 0 ? E_res : pos - 1) : pos;
-  };
-  // partitions kept by some row of tile i of expert e (OR of the keep patterns of the bins it overlaps)
-  auto tile_bits_of = [&](int e, int i) {
-    if (e >= E_res) return 1;
-    const int r0 = i * BM, r1 = min(ne[e], r0 + BM);
-    int bits = 0, off = 0;
-    for (int sb = 0; sb < L.nsub; ++sb) {
-      int c = bin_count[e * L.nsub + sb];
-      if (c > 0 && off < r1 && off + c > r0) {
-        int rev = L.nsub - 1 - sb;
-        int pat = 0;
-        for (int p = 0; p < nsub_bits; ++p) pat |= ((rev >> (nsub_bits - 1 - p)) & 1) << p;
-        if (L.P > nsub_bits) pat |= ((1 << L.P) - 1) & ~((1 << nsub_bits) - 1);  // partitions outside the sort key: assume kept
-        bits |= pat;
-      }
-      off += c;
-    }
-    return bits;
-  };
-  // the keep pattern of every row tile, worked out once and in parallel (the per-group loop of
-  // step 6 walks the tiles of an expert one after the other and must not redo this for each)
-  // (kept in LDS when there are at most kPlanTilesLds tiles, else in the workspace)
-  int32_t* tbits = total_tiles <= kPlanTilesLds ? tmp + kPlanThreads : (int32_t*)(ws + L.o_tile_bits);
-  uint16_t* texp = (uint16_t*)(tmp + kPlanThreads + kPlanTilesLds);  // the tiles' experts, where they fit too
-  for (int g = tid; g < total_tiles; g += kPlanThreads) {
-    const int e = find_expert(g);
-    if (g < kPlanTilesLds) texp[g] = (uint16_t)e;
-    tbits[g] = tile_bits_of(e, g - ts[e]);
-  }
-  auto tile_expert = [&](int g) { return g < kPlanTilesLds ? (int)texp[g] : find_expert(g); };
-  __shared__ int est[4];  // see "tall GEMM-1 items" below
-  if (tid < 4) est[tid] = 0;
-  __syncthreads();
-  // rows of tile i of expert e up to the last one that keeps partition p.  The rows are sorted by
-  // keep pattern, so with thresholds that grow with p this is exactly the number of rows that need
-  // p; in general it bounds them (rows before it that lack p are zeroed by the GEMM-1 epilogue).
-  auto tile_rows_for = [&](int e, int i, int p) {
-    const int r0 = i * BM, r1 = min(ne[e], r0 + BM);
-    if (e >= E_res || p >= nsub_bits) return r1 - r0;
-    int last = 0, off = 0;
-    for (int sb = 0; sb < L.nsub; ++sb) {
-      const int c = bin_count[e * L.nsub + sb];
-      const int rev = L.nsub - 1 - sb;
-      const bool has = (rev >> (nsub_bits - 1 - p)) & 1;
-      if (has && c > 0 && off < r1 && off + c > r0) last = max(last, min(r1, off + c) - r0);
-      off += c;
-    }
-    return last;
-  };
+
   // Tall GEMM-1 items: when an expert's last row tile has at most kTallExtra rows, the item of the tile
   // before it (if that is full for the partition) computes them too, and the last tile gets no item of
   // its own: a few rows would otherwise pull the whole weight tile through another compute unit.
-  auto absorbable = [&](int e, int i, int p) {
-    if (i == 0) return false;
-    if (i != tiles_of(ne[e]) - 1 || ne[e] - i * BM > kTallExtra) return false;
-    if (!((tbits[ts[e] + i] >> p) & 1)) return false;
-    return tile_rows_for(e, i - 1, p) == BM;
-  };
-  // Whether the batch gets them is decided by pricing both lists.  Items in 1/256 of a full one: a ragged
-  // item of r rows 128 + r / 2 (half of every stage is its weight tile), a tall one 256 + 33 with up to 32
-  // extra rows and 256 + 56 beyond (measured).  A list of N items of mean cost c is taken to last
-  // ceil(N / units) * c, whole rounds of one item per compute unit: removing a tenth of the items is worth
-  // a round or nothing, and the longer items of a list that still needs the same rounds make it slower.
-  // est[]: items and summed cost of the list without / with tall items
-  bool use_tall1 = L.tall_tiles == 2;
-  const bool price_lists = lists1 && L.tall_tiles == 1 && (int64_t)T * L.K > BM;  // (no expert of a smaller batch has a second tile)
-  if (price_lists) {
-    // one thread per (expert, partition): the rows that need p are a prefix of the expert's rows (exactly so
-    // with thresholds that grow with p; an estimate otherwise), so the group's items follow from one count
+  // Groups in the order of the experts; the shared pseudo-expert's go first once it has several row tiles: its full tiles are the
+  // longest items of a batch with a few rows per expert, and last they started last and ended long after the others
+  // (333 tokens on 64 + 2 experts of 2048 x 1408: the layer 267 -> 252 us).
+  const int sh_first = has_sh && T > BM ? 1 : 0;
+  const bool price_lists = L.tall_tiles == 1 && (int64_t)T * L.K > BM;  // (no expert of a smaller batch has a second tile)
+  if (lists1 && wv > 0) {
+    // Whether the batch gets them is decided by pricing both lists.  Items in 1/256 of a full one: a ragged
+    // item of r rows 128 + r / 2 (half of every stage is its weight tile), a tall one 256 + 33 with up to 32
+    // extra rows and 256 + 56 beyond (measured).  A list of N items of mean cost c is taken to last
+    // ceil(N / units) * c, whole rounds of one item per compute unit: removing a tenth of the items is worth
+    // a round or nothing, and the longer items of a list that still needs the same rounds make it slower.
+    // est[]: items and summed cost of the list without / with tall items
     int n0 = 0, w0 = 0, n1 = 0, w1 = 0;
-    for (int gidx = tid; gidx < NG; gidx += kPlanThreads) {
-      const int e = gidx / L.P, p = gidx % L.P;
-      if (e >= E_res && p > 0) continue;
-      int rows = ne[e];
-      if (e < E_res && p < nsub_bits) {
+    for (int gi = tid - 64; gi < NG; gi += kPlanThreads - 64) {
+      const int pos = gi / P, p = gi - pos * P, e = sh_first ? (pos == 0 ? E_res : pos - 1) : pos;
+      int n_e = p == 0 ? T : 0, rows = n_e, tiles = tiles_of(n_e), merged = short_rows(n_e) > 0;
+      if (e < E_res) {
+        n_e = Bins<NSB>::rows(bin_count, e);
+        const int nt = tiles_of(n_e);
         rows = 0;
-        int off = 0;
-        for (int sb = 0; sb < L.nsub; ++sb) {
-          const int c = bin_count[e * L.nsub + sb];
-          const int rev = L.nsub - 1 - sb;
-          if (c > 0 && ((rev >> (nsub_bits - 1 - p)) & 1)) rows = off + c;
-          off += c;
-        }
+        Bins<NSB>::each(bin_count, e, [&](int sb, int, int end) { rows = Bins<NSB>::keeps(sb, p) ? end : rows; });
+        const TileUse u = tile_use<NSB>(bin_count, e, nt - 1, bm, p);
+        tiles = u.before + (u.rows > 0);
+        merged = short_rows(n_e) && u.rows > 0 && u.full_before;
       }
-      if (rows == 0) continue;
-      const int nt1 = e < E_res ? L.NT1 : L.NT1_sh;
-      const int full = rows >> bm_sh, rem = rows & (BM - 1);
-      const int n = full + (rem ? 1 : 0), w = full * 256 + (rem ? 128 + rem / 2 : 0);
-      n0 += nt1 * n;
-      w0 += nt1 * w;
-      const int nt = tiles_of(ne[e]);
-      if (nt >= 2 && ne[e] - (nt - 1) * BM <= kTallExtra && rows > (nt - 1) * BM) {  // the last tile's item goes into the one before
-        n1 += nt1 * (n - 1);
-        w1 += nt1 * (full * 256 + (rem <= 32 ? 33 : 56));
-      } else {
-        n1 += nt1 * n;
-        w1 += nt1 * w;
+      ga[gi] = 2 * tiles + merged;  // the tiles that have an item, and whether the last one's goes into a tall one
+      if (price_lists && rows > 0) {
+        // (the rows that need p are taken to be a prefix of the expert's rows: exactly so with thresholds that grow with p)
+        const int nt1 = e < E_res ? L.NT1 : L.NT1_sh;
+        const int full = rows >> bm, rem = rows & (BM - 1);
+        const int n = full + (rem ? 1 : 0), w = full * 256 + (rem ? 128 + rem / 2 : 0);
+        const bool tall = short_rows(n_e) && rows > (tiles_of(n_e) - 1) * BM;  // the last tile's item goes into the one before
+        n0 += nt1 * n;
+        w0 += nt1 * w;
+        n1 += nt1 * (tall ? n - 1 : n);
+        w1 += nt1 * (tall ? full * 256 + (rem <= 32 ? 33 : 56) : w);
       }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      n0 += __shfl_down(n0, o, 64);
-      w0 += __shfl_down(w0, o, 64);
-      n1 += __shfl_down(n1, o, 64);
-      w1 += __shfl_down(w1, o, 64);
-    }
-    if ((tid & 63) == 0) {  // integer sums: the same in any order
-      atomicAdd(&est[0], n0);
-      atomicAdd(&est[1], w0);
-      atomicAdd(&est[2], n1);
-      atomicAdd(&est[3], w1);
+    if (price_lists) {
+      n0 = wave_incl_sum(n0), w0 = wave_incl_sum(w0), n1 = wave_incl_sum(n1), w1 = wave_incl_sum(w1);
+      if (lane == 63 && n0 > 0) {  // integer sums: the same in any order
+        atomicAdd(&est[0], n0);
+        atomicAdd(&est[1], w0);
+        atomicAdd(&est[2], n1);
+        atomicAdd(&est[3], w1);
+      }
     }
   }
-  auto absorbed = [&](int e, int i, int p) { return use_tall1 && absorbable(e, i, p); };
-  // 5. GEMM-2 items: every tile x every output column tile.  The compute units take the items in
-  //    list order, one each.  Where that leaves units idle, items are split along K: every extra K
-  //    range is an item of its own that writes a partial-output tile into a pool, and the combine
-  //    kernel adds those tiles to the item's rows of Yp in a fixed order.
-  //    (a) few row tiles (decode-sized batches): fewer items than units, each streaming a whole
-  //        column tile of W2 alone -> all items are split, into as many ranges as keep the list
-  //        within one item per unit;
-  //    (b) the last round of a longer list is only partly full -> its items are split where the shorter
-  //        pieces fill the units better (see below).
-  //    A short last tile of an expert (at most kTallExtra rows) has no items of its own: the items of the
-  //    tile before it are tall and compute its rows too (as in GEMM-1; here for all partitions at once).
-  //    Only if the short tile keeps no partition that the tile before it drops: the tall items run over the
-  //    partitions of the full tile, and where the short tile lacks one of them its rows of H are zeros
-  //    (written by the GEMM-1 item of the full tile, see step 7).
-  for (int i = tid; i < E_tot; i += kPlanThreads) {
-    const int e = has_sh ? (i == 0 ? E_res : i - 1) : i;
-    const int nt = tiles_of(ne[e]);
-    int s = 0;
-    if (L.tall_tiles && nt >= 2 && ne[e] - (nt - 1) * BM <= kTallExtra) s = (tbits[ts[e] + nt - 1] & ~tbits[ts[e] + nt - 2]) == 0 ? 1 : 0;
-    abp[i] = s;
-  }
-  __shared__ int32_t multi_tile[2];  // bit e & 63: some expert e has more than one row tile
-  __shared__ int first_split_tile;  // first row tile (in row order) that has a split item: the combine kernel looks no tile before it up
-  if (tid == 0) {
-    abp[E_tot] = 0;
-    first_split_tile = total_tiles;
-    multi_tile[0] = multi_tile[1] = 0;
-  }
-  __syncthreads();  // the sums of the pricing pass are complete too
-  if (lists2) {
-    for (int e = tid; e < E_res; e += kPlanThreads)
-      if (ne[e] > BM) atomicOr(&multi_tile[(e >> 5) & 1], 1 << (e & 31));
-  }
-  if (price_lists) {
-    const int units = max(L.split_items, 1);
-    const float t0 = est[0] > 0 ? (float)((est[0] + units - 1) / units) * (float)est[1] / (float)est[0] : 0.f;
-    const float t1 = est[2] > 0 ? (float)((est[2] + units - 1) / units) * (float)est[3] / (float)est[2] : 0.f;
-    use_tall1 = est[2] < est[0] && t1 <= t0;
-  }
-  const int total_short = block_excl_scan(abp, E_tot + 1, tmp);  // abp[E_tot] = total
-  auto short_last = [&](int e) {  // read back from the scanned flags
-    const int pos = has_sh ? (e == E_res ? 0 : e + 1) : e;
-    return abp[pos + 1] - abp[pos];
+  lds_barrier();
+  const int total_tiles = total_tiles_l, total_short = total_short_l;
+  int32_t* counters = (int32_t*)(ws + L.o_counters);
+  // tile g belongs to the expert at the last position whose first tile is <= g (and which has a tile)
+  auto tile_expert = [&](int g) {
+    if (g < kPlanTilesLds) return (int)texp[g];
+    if (has_sh && g < tiles_of(T)) return E_res;
+    int lo_i = 0, hi_i = E_res;  // first expert with ts > g
+    while (lo_i < hi_i) {
+      const int mid = (lo_i + hi_i) >> 1;
+      if (ts[mid] > g) hi_i = mid;
+      else lo_i = mid + 1;
+    }
+    return lo_i - 1;
   };
+
   if (lists2) {
+    // 3. GEMM-2 items: every tile x every output column tile.  The compute units take the items in
+    //    list order, one each.  Where that leaves units idle, items are split along K: every extra K
+    //    range is an item of its own that writes a partial-output tile into a pool, and the combine
+    //    kernel adds those tiles to the item's rows of Yp in a fixed order.
+    //    (a) few row tiles (decode-sized batches): fewer items than units, each streaming a whole
+    //        column tile of W2 alone -> all items are split, into as many ranges as keep the list
+    //        within one item per unit;
+    //    (b) the last round of a longer list is only partly full -> its items are split where the shorter
+    //        pieces fill the units better (see below).
+    Item2* items2 = (Item2*)(ws + L.o_items2);
     const int W2n = (total_tiles - total_short) * L.ND2;
-    int nsplit = 1, first_split = W2n;  // items first_split .. W2n-1 (in list order) are split nsplit ways
-    if (L.split_items > 0 && W2n > 0) {
-      int ksp = L.Fpk / kBK;
-      if (has_sh) ksp = min(ksp, L.Fsk / kBK);
-      if (W2n * 2 <= L.split_items) {
-        while (nsplit < kMaxSplit && W2n * nsplit * 2 <= L.split_items && nsplit * 2 <= ksp && W2n * (nsplit * 2 - 1) <= L.pool_tiles) nsplit *= 2;
-        first_split = 0;
-      } else {
-        // The last round holds `rest` items for split_items compute units.  Cut n ways they are rest * n
-        // shorter items, which take ceil(rest * n / units) turns of 1/n of a round each (plus a fill and a
-        // write-out per piece, worth about eight K stages): 192 items cut in four are three turns of a
-        // quarter instead of a whole round at three quarters of the units.  The cheapest n that the pool
-        // of partial tiles can hold wins; n = 1 (cost: one round) if none is cheaper.
-        const int rest = W2n % L.split_items;
-        if (rest > 0) {
-          float best = 1.0f;
-          const int item_stages = E_res > 0 ? L.P * (L.Fpk / kBK) : L.Fsk / kBK;  // K stages of a long item
+    if (wv == 0) {  // items first_split .. W2n-1 (in list order) are split nsplit ways
+      int nsplit = 1, first_split = W2n;
+      if (L.split_items > 0 && W2n > 0) {
+        int ksp = L.Fpk / kBK;
+        if (has_sh) ksp = min(ksp, L.Fsk / kBK);
+        if (W2n * 2 <= L.split_items) {
+          while (nsplit < kMaxSplit && W2n * nsplit * 2 <= L.split_items && nsplit * 2 <= ksp && W2n * (nsplit * 2 - 1) <= L.pool_tiles) nsplit *= 2;
+          first_split = 0;
+        } else {
+          // The last round holds `rest` items for split_items compute units.  Cut n ways they are rest * n
+          // shorter items, which take ceil(rest * n / units) turns of 1/n of a round each (plus a fill and a
+          // write-out per piece, worth about eight K stages): 192 items cut in four are three turns of a
+          // quarter instead of a whole round at three quarters of the units.  The cheapest n that the pool
+          // of partial tiles can hold wins; n = 1 (cost: one round) if none is cheaper.  (Lane n prices n pieces.)
+          const int rest = W2n & (L.split_items - 1);
+          const int item_stages = E_res > 0 ? P * (L.Fpk / kBK) : L.Fsk / kBK;   // K stages of a long item
           const float piece = 8.0f / (float)max(item_stages, 1);                  // per-piece overhead in units of such an item
-          for (int n = 2; n <= kMaxTailSplit && n <= ksp; ++n) {
-            if (rest * (n - 1) > L.pool_tiles) break;
-            const int turns = (rest * n + L.split_items - 1) / L.split_items;
-            const float cost = (float)turns * (1.0f / (float)n + piece);
-            if (cost < best - 0.04f) {  // a clear gain only: every extra range costs a partial tile written and read
-              best = cost;
-              nsplit = n;
+          const int n = max(lane, 1), turns = (rest * n + L.split_items - 1) >> units_log2;
+          const float cost = (float)turns * (1.0f / (float)n + piece);
+          float best = 1.0f;
+          for (int m = 2; m <= kMaxTailSplit && m <= ksp && rest > 0 && rest * (m - 1) <= L.pool_tiles; ++m) {
+            const float cm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cost), m));
+            if (cm < best - 0.04f) {  // a clear gain only: every extra range costs a partial tile written and read
+              best = cm;
+              nsplit = m;
             }
           }
           if (nsplit > 1) first_split = W2n - rest;
         }
+        if (nsplit == 1) first_split = W2n;
       }
-      if (nsplit == 1) first_split = W2n;
+      if (lane <= nsplit) {  // (at most a few thousand stages times 8)
+        k_lo[0][lane] = L.Fpk / kBK * lane / nsplit;
+        k_lo[1][lane] = L.Fsk / kBK * lane / nsplit;
+      }
+      if (lane == 0) split_l[0] = nsplit, split_l[1] = first_split;
+    } else {  // the partitions that some row of a tile keeps
+      for (int g = tid - 64; g < min(total_tiles, kPlanTilesLds); g += kPlanThreads - 64) {
+        const int e = tile_expert(g), i = g - ts[e], r1 = (i + 1) * BM;
+        const int2 bits = e < E_res ? Bins<NSB>::kept(bin_count, e, i * BM, r1, r1 + BM, P) : make_int2(1, 1);
+        kmask_l[g] = (uint8_t)(bits.x | ((ab[e] & 1) && i + 2 == tiles_of(ne[e]) ? bits.y : 0));  // a tall item's: of both tiles
+      }
     }
+    lds_barrier();
+    const int nsplit = split_l[0], first_split = split_l[1];
     int32_t* split_of = (int32_t*)(ws + L.o_split_of);
-    for (int gj = tid; gj < total_tiles * L.ND2; gj += kPlanThreads) {
-      const int g = gj / L.ND2, jd = gj % L.ND2;
+    // threads that share the column tiles of a row tile: a power of two
+    int ls = 0;
+    while ((1 << ls) < L.ND2 && total_tiles << (ls + 1) <= kPlanThreads) ++ls;
+    const int S = 1 << ls;
+    for (int qs = tid; qs < total_tiles << ls; qs += kPlanThreads) {
+      const int g = qs >> ls, jd0 = qs & (S - 1);
       const int e = tile_expert(g);
-      const int i = g - ts[e];
-      const int ksp = (e < E_res ? L.Fpk : L.Fsk) / kBK;
-      const int nt_all = tiles_of(ne[e]), sl = short_last(e);
+      const int n = ne[e], i = g - ts[e], nt_all = tiles_of(n), sl = ab[e] & 1, shorts = ab[e] >> 1;
       if (sl && i == nt_all - 1) continue;         // the short last tile: computed by the items of the tile before
       const bool tall = sl && i == nt_all - 2;
+      const int ksp = (e < E_res ? L.Fpk : L.Fsk) / kBK;
       Item2 v;
-      v.row0 = rs[e] + i * BM;
-      v.nrows = min(ne[e] - i * BM, BM) + (tall ? ne[e] - (i + 1) * BM : 0);
+      v.row0 = g * BM;
+      v.nrows = min(n - i * BM, BM) + (tall ? n - (i + 1) * BM : 0);
       v.e = e;
-      v.jd = jd;
-      v.kmask = tbits[g] | (tall ? tbits[g + 1] : 0);
+      if (g < kPlanTilesLds) {
+        v.kmask = kmask_l[g];
+      } else {
+        const int2 bits = e < E_res ? Bins<NSB>::kept(bin_count, e, i * BM, (i + 1) * BM, (i + 2) * BM, P) : make_int2(1, 1);
+        v.kmask = bits.x | (tall ? bits.y : 0);
+      }
       // list order (expert, column tile, row tile) if g2_rows_inner: the row tiles that share one column
       // tile of W2 are adjacent, run at the same time on one XCD and fetch the weights once;
       // else (row tile, column tile)
-      const int nt_e = nt_all - sl;                                         // tiles of the expert that have items
-      const int ts_e = ts[e] - abp[has_sh ? (e == E_res ? 0 : e + 1) : e];  // and of the experts before it
-      const int slot = L.g2_rows_inner ? ts_e * L.ND2 + jd * nt_e + i : (ts_e + i) * L.ND2 + jd;
-      if (slot < first_split) {
-        v.ks_lo = 0;
-        v.ks_n = ksp;
-        v.split = 0;
-        items2[slot] = v;
-        if (L.pool_tiles > 0) {  // (without a pool there is no table either, and nothing looks it up)
-          split_of[gj] = -1;
-          if (tall) split_of[gj + L.ND2] = -1;
+      const int nt_e = nt_all - sl;        // tiles of the expert that have items
+      const int ts_e = ts[e] - shorts;     // and of the experts before it
+      if (jd0 == 0) {
+        // The first row tile that has a split item (the combine kernel looks no tile before it up): later tiles have later last items.
+        // (By comparison: an LDS minimum over all the split items took 2 us.)
+        const int last = L.g2_rows_inner ? (ts_e + nt_e) * L.ND2 - nt_e + i : (ts_e + i + 1) * L.ND2 - 1;
+        const int last_before = L.g2_rows_inner ? (i > 0 ? last - 1 : ts_e * L.ND2 - 1) : last - L.ND2;
+        if (last >= first_split && last_before < first_split) counters[4] = g;
+      }
+      for (int jd = jd0; jd < L.ND2; jd += S) {
+        v.jd = jd;
+        const int gj = g * L.ND2 + jd;
+        const int slot = L.g2_rows_inner ? ts_e * L.ND2 + jd * nt_e + i : (ts_e + i) * L.ND2 + jd;
+        if (slot < first_split) {
+          v.ks_lo = 0;
+          v.ks_n = ksp;
+          v.split = 0;
+          items2[slot] = v;
+          if (L.pool_tiles > 0) {  // (without a pool there is no table either, and nothing looks it up)
+            split_of[gj] = -1;
+            if (tall) split_of[gj + L.ND2] = -1;
+          }
+        } else {
+          const int q = slot - first_split;  // q-th split item: its extra ranges use pool tiles q*(nsplit-1) ..
+          for (int sp = 0; sp < nsplit; ++sp) {
+            v.ks_lo = k_lo[e < E_res ? 0 : 1][sp];
+            v.ks_n = k_lo[e < E_res ? 0 : 1][sp + 1] - v.ks_lo;
+            v.split = sp == 0 ? 0 : 1 + q * (nsplit - 1) + (sp - 1);
+            items2[first_split + q * nsplit + sp] = v;
+          }
+          split_of[gj] = q * (nsplit - 1);
+          if (tall) split_of[gj + L.ND2] = q * (nsplit - 1) | kSplitRowsOffset;  // rows of the short tile: BM further down the pool tiles
         }
-      } else {
-        const int q = slot - first_split;  // q-th split item: its extra ranges use pool tiles q*(nsplit-1) ..
-        atomicMin(&first_split_tile, g);
-        for (int sp = 0; sp < nsplit; ++sp) {
-          v.ks_lo = ksp * sp / nsplit;  // (at most a few thousand stages times 8)
-          v.ks_n = ksp * (sp + 1) / nsplit - v.ks_lo;
-          v.split = sp == 0 ? 0 : 1 + q * (nsplit - 1) + (sp - 1);
-          items2[first_split + q * nsplit + sp] = v;
-        }
-        split_of[gj] = q * (nsplit - 1);
-        if (tall) split_of[gj + L.ND2] = q * (nsplit - 1) | kSplitRowsOffset;  // rows of the short tile: BM further down the pool tiles
       }
     }
-    __syncthreads();  // first_split_tile is final
     if (tid == 0) {
       counters[9] = 0;  // see take_piece
       counters[1] = first_split + (W2n - first_split) * nsplit;
       counters[2] = total_tiles - total_short;  // row tiles that have GEMM-2 items
       counters[3] = nsplit;
-      counters[4] = first_split_tile;
-      counters[5] = multi_tile[0];
-      counters[6] = multi_tile[1];
+      if (first_split == W2n) counters[4] = total_tiles;
+      counters[5] = multi_l[0];
+      counters[6] = multi_l[1];
       counters[7] = L.BN2 / 2;  // neurons of a neuron tile; an output column tile is twice as wide
     }
     return;
   }
-  // Groups in the order of the experts; the shared pseudo-expert's go first once it has several row tiles: its full tiles are the
-  // longest items of a batch with a few rows per expert, and last they started last and ended long after the others
-  // (333 tokens on 64 + 2 experts of 2048 x 1408: the layer 267 -> 252 us).
-  const int sh_first = has_sh && T > BM ? 1 : 0;
-  auto group = [&](int e, int p) { return (sh_first ? (e == E_res ? 0 : e + 1) : e) * L.P + p; };
-  // 6. per (expert, partition): rank of each active tile among the active tiles of its group
-  if (total_tiles <= kPlanTilesLds) {
-    // keep patterns in LDS: one thread per (tile, partition) counts the active tiles before its own
-    for (int gidx = tid; gidx < NG; gidx += kPlanThreads) ga[gidx] = gb[gidx] = 0;  // groups without tiles
-    __syncthreads();
-    for (int q = tid; q < total_tiles * L.P; q += kPlanThreads) {
-      const int p = q % L.P, g = q / L.P;
-      const int e = tile_expert(g);
-      int cnt = 0;
-      for (int j = ts[e]; j < g; ++j) cnt += (tbits[j] >> p) & 1;
-      const int act = ((tbits[g] >> p) & 1) && !absorbed(e, g - ts[e], p) ? 1 : 0;
-      act_rank[(size_t)g * L.P + p] = act ? cnt : -1;
-      if (g - ts[e] == tiles_of(ne[e]) - 1) {  // the expert's last tile closes the group
-        ga[group(e, p)] = cnt + act;
-        gb[group(e, p)] = (cnt + act) * (e < E_res ? L.NT1 : L.NT1_sh);
+
+  // 4. GEMM-1 items in the order (expert, partition, neuron tile, row tile): the row tiles that
+  //    share one weight tile are adjacent.
+  bool use_tall1 = L.tall_tiles == 2;
+  if (price_lists) {
+    auto rounds = [&](int n) { return (float)((n + (1 << units_log2) - 1) >> units_log2); };
+    const float t0 = est[0] > 0 ? rounds(est[0]) * (float)est[1] / (float)est[0] : 0.f;
+    const float t1 = est[2] > 0 ? rounds(est[2]) * (float)est[3] / (float)est[2] : 0.f;
+    use_tall1 = est[2] < est[0] && t1 <= t0;
+  }
+  __shared__ int total1_l;
+  Item1* items1 = (Item1*)(ws + L.o_items1);
+  const int nt1_max = max(L.NT1, has_sh ? L.NT1_sh : 0), n_q = total_tiles * P;
+  //    threads that share the neuron tiles of one (row tile, partition): a power of two, as many as would otherwise idle
+  int ls = 0;
+  while (ls < 5 && (1 << ls) < nt1_max && min(n_q, kPlanRecords) << (ls + 1) <= kPlanThreads) ++ls;
+  int total1 = 0, first_half = 0;
+  for (int q0 = 0; q0 == 0 || q0 < n_q; q0 += kPlanRecords) {
+    //  What the (row tile, partition) pairs q0 .. need, a thread each ...
+    if (wv > 0 && q0 + tid - 64 < n_q) {
+      const int q = q0 + tid - 64, g = q / P, p = q - g * P;
+      const int e = tile_expert(g), n = ne[e], i = g - ts[e], nt = tiles_of(n);
+      const bool routed = e < E_res;
+      const int last = short_rows(n);  // rows of the expert's short last tile
+      const int fill = min(n - i * BM, BM);
+      TileUse u = {p == 0 ? fill : 0, last, i, true};
+      if (routed) u = tile_use<NSB>(bin_count, e, i, bm, p);
+      int rows = u.rows, nfill = fill;
+      if (rows > 0 && last && i + 1 == nt && use_tall1 && u.full_before) rows = 0;  // computed by the tall item of the tile before
+      if (rows > 0 && last && i + 2 == nt) {
+        if (use_tall1 && rows == BM && u.next_rows > 0) {  // a tall item: the rows of the expert's short last tile follow directly
+          rows += u.next_rows;
+          nfill += last;
+        } else if ((ab[e] & 1) && u.next_rows == 0) {
+          // the tall GEMM-2 items of this tile multiply partition p over the short last tile's rows too, none
+          // of which keeps it: their part of H is zeros, written by this item
+          nfill += last;
+        }
+      }
+      rec[tid - 64] = make_int4(rows | nfill << 16, u.before, ((sh_first ? (routed ? e + 1 : 0) : e) * P + p) << 16 | p << 12 | e, g * BM);
+    }
+    //  ... and, by the first wavefront, the item bases of the groups: a run of groups per lane
+    if (wv == 0 && q0 == 0) {
+      const int per = (NG + 63) >> 6, lo = lane * per, hi = min(NG, lo + per);
+      const int sh_lo = sh_first ? 0 : E_res * P, sh_hi = has_sh ? sh_lo + P : sh_lo;  // the shared pseudo-expert's groups
+      int sum = 0;
+      for (int gi = lo; gi < hi; ++gi) {
+        const int v = ga[gi], n = (v >> 1) - (use_tall1 ? v & 1 : 0), items = n * (gi >= sh_lo && gi < sh_hi ? L.NT1_sh : L.NT1);
+        ga[gi] = n;
+        gb[gi] = sum;
+        sum += items;
+      }
+      const int incl = wave_incl_sum(sum);
+      for (int gi = lo; gi < hi; ++gi) gb[gi] += incl - sum;
+      if (lane == 63) total1_l = incl;
+    }
+    lds_barrier();
+    if (q0 == 0) {
+      //  In the weight-streaming regime (few rows per expert) every item lasts as long as its weight
+      //  tile takes to arrive, so the kernel lasts a whole number of rounds of one item per compute
+      //  unit: when the last round is at most half full, its items are cut into halves of 64
+      //  neurons, which fill it (an item of more than 128 rows, or of a last neuron tile of at most
+      //  64 neurons, stays whole).
+      total1 = first_half = total1_l;  // list positions >= first_half belong to that last round
+      if (may_halve_items1(L, T)) {
+        const int rest = total1 & (L.split_items - 1);
+        if (rest > 0 && rest * 2 <= L.split_items) first_half = total1 - rest;
       }
     }
-  } else {  // very many tiles: one thread walks the tiles of a group
-    for (int gidx = tid; gidx < NG; gidx += kPlanThreads) {
-      const int pos = gidx / L.P, p = gidx % L.P, e = sh_first ? (pos == 0 ? E_res : pos - 1) : pos;
-      int nt = tiles_of(ne[e]);
-      int cnt = 0;
-      for (int i = 0; i < nt; ++i) {
-        bool act = ((tbits[ts[e] + i] >> p) & 1) && !absorbed(e, i, p);
-        act_rank[(size_t)(ts[e] + i) * L.P + p] = act ? cnt : -1;
-        cnt += act ? 1 : 0;
+    for (int qs = tid; qs < min(n_q - q0, kPlanRecords) << ls; qs += kPlanThreads) {
+      const int4 r = rec[qs >> ls];
+      Item1 v;
+      v.nrows = r.x & 0xffff;
+      if (v.nrows == 0) continue;  // no row of the tile keeps p, or no item of its own
+      v.nfill = r.x >> 16;
+      v.e = r.z & 0xfff;
+      v.p = (r.z >> 12) & 15;
+      v.row0 = r.w;
+      const int n_act = ga[r.z >> 16], base = gb[r.z >> 16] + r.y, nt1 = v.e < E_res ? L.NT1 : L.NT1_sh, width = v.e < E_res ? L.Fp : L.F_shT;
+      v.once = n_act == 1 ? 1 : 0;
+      for (int jt = qs & ((1 << ls) - 1); jt < nt1; jt += 1 << ls) {
+        v.jt = jt;
+        // MFMA path, at most 128 rows, a last neuron tile of at most 64 neurons: the half-tile variant of
+        // the kernel takes it as a first half without a second one (half the weight bytes)
+        v.half = L.mfma && v.nrows <= kMfmaBM / 2 && width - jt * kMfmaNeur <= kMfmaNeur / 2 ? 1 : 0;
+        const int at = base + jt * n_act;
+        if (at < first_half) items1[at] = v;
+        else ((Item1*)tail)[at - first_half] = v;
       }
-      ga[gidx] = cnt;
-      gb[gidx] = cnt * (e < E_res ? L.NT1 : L.NT1_sh);
     }
-  }
-  __syncthreads();
-  int total1 = block_excl_scan(gb, NG, tmp);
-  // 7. GEMM-1 items in the order (expert, partition, neuron tile, row tile): the row tiles that
-  //    share one weight tile are adjacent.  1 to 8 threads per (row tile, partition): each looks
-  //    the tile up and writes the items of every S-th neuron tile.
-  //    In the weight-streaming regime (few rows per expert) every item lasts as long as its weight
-  //    tile takes to arrive, so the kernel lasts a whole number of rounds of one item per compute
-  //    unit: when the last round is at most half full, its items are cut into halves of 64
-  //    neurons, which fill it (an item of more than 128 rows, or of a last neuron tile of at most
-  //    64 neurons, stays whole).
-  int first_half = total1;  // list positions >= first_half belong to that last round
-  if (may_halve_items1(L, T)) {
-    const int rest = total1 % L.split_items;
-    if (rest > 0 && rest * 2 <= L.split_items) first_half = total1 - rest;
-  }
-  const int nt1_max = has_sh && L.NT1_sh > L.NT1 ? L.NT1_sh : L.NT1;
-  // threads that share the neuron tiles of one (row tile, partition): as many as would otherwise idle
-  int S = kPlanThreads / max(total_tiles * L.P, 1);
-  S = S < 1 ? 1 : S > 8 ? 8 : S;
-  S = S > nt1_max ? nt1_max : S;
-  for (int qs = tid; qs < total_tiles * L.P * S; qs += kPlanThreads) {
-    const int part = qs % S, q = qs / S;
-    const int p = q % L.P, g = q / L.P;
-    const int rk = act_rank[(size_t)g * L.P + p];
-    if (rk < 0) continue;
-    const int e = tile_expert(g);
-    const int nt1 = e < E_res ? L.NT1 : L.NT1_sh;
-    const int gi = group(e, p);
-    const int i = g - ts[e];
-    Item1 v;
-    v.row0 = rs[e] + i * BM;
-    v.nfill = min(ne[e] - i * BM, BM);
-    v.nrows = tile_rows_for(e, i, p);
-    if (absorbed(e, i + 1, p)) {  // a tall item: the rows of the expert's short last tile follow directly
-      v.nrows += tile_rows_for(e, i + 1, p);
-      v.nfill += ne[e] - (i + 1) * BM;
-    } else if (i + 2 == tiles_of(ne[e]) && short_last(e) && !((tbits[g + 1] >> p) & 1)) {
-      // the tall GEMM-2 items of this tile multiply partition p over the short last tile's rows too, none
-      // of which keeps it: their part of H is zeros, written by this item
-      v.nfill += ne[e] - (i + 1) * BM;
-    }
-    v.e = e;
-    v.p = p;
-    v.once = ga[gi] == 1 ? 1 : 0;
-    for (int jt = part; jt < nt1; jt += S) {
-      v.jt = jt;
-      // MFMA path, at most 128 rows, a last neuron tile of at most 64 neurons: the half-tile variant of
-      // the kernel takes it as a first half without a second one (half the weight bytes)
-      const int live = (e < E_res ? L.Fp : L.F_shT) - jt * kMfmaNeur;
-      v.half = L.mfma && v.nrows <= kMfmaBM / 2 && live <= kMfmaNeur / 2 ? 1 : 0;
-      items1[gb[gi] + jt * ga[gi] + rk] = v;
-    }
+    if (q0 + kPlanRecords < n_q) lds_barrier();  // the records have been read
   }
   int total_slots = total1;
   if (first_half < total1) {  // the same for every thread
-    // cut the items of the last round in two where that is possible (at most 128 rows, both halves
+    // the items of the last round are cut in two where that is possible (at most 128 rows, both halves
     // of the neuron tile exist); the list stays dense: item i moves up by the cuts before it
     __shared__ int slots_wave0, slots_all;
-    __syncthreads();  // the items above are written
-    const int rest = total1 - first_half;  // <= 128: wavefronts 0 and 1
+    lds_barrier();  // the tail is complete
+    const int rest = total1 - first_half;  // <= kHalvedMost: wavefronts 0 and 1
     Item1 mine;
     int slots = 0;
     if (tid < rest) {
-      mine = items1[first_half + tid];
+      mine = ((const Item1*)tail)[tid];
       const int live = (mine.e < E_res ? L.Fp : L.F_shT) - mine.jt * kMfmaNeur;
       slots = mine.nrows <= kMfmaBM / 2 && live > kMfmaNeur / 2 ? 2 : 1;
     }
-    int incl = slots;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o, 64);
-      if ((tid & 63) >= o) incl += up;
-    }
+    const int incl = wave_incl_sum(slots);
     if (tid == 63) slots_wave0 = incl;
-    __syncthreads();  // and every item of the tail has been read before any is moved
+    lds_barrier();
     if (tid < rest) {
       const int at = first_half + incl - slots + (tid >= 64 ? slots_wave0 : 0);
       if (slots == 2) {
@@ -980,7 +1010,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       }
       if (tid == rest - 1) slots_all = at + slots;
     }
-    __syncthreads();
+    lds_barrier();
     total_slots = slots_all;
   }
   if (tid == 0) {
@@ -990,24 +1020,53 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   }
 }
 
-template <int LANES>
-static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const RouteArgs& ra, hipStream_t s) {
-  size_t sh = plan_lds_bytes(L);
-  if (LANES != 0) sh += sizeof(int32_t) * (size_t)(T * L.K + L.E * L.P);
-  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: up to 92324 bytes (512, shared ones), above what a launch gets without asking
+template <int LANES, int NSB>
+static hipError_t launch_plan_nsb(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
+  size_t sh = sizeof(int32_t) * (size_t)plan_lds_words(L);
+  sh += sizeof(int32_t) * (size_t)(LANES != 0 ? T * L.K + L.E * L.P : kSumWords);
+  if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: above what a launch gets without asking
     static PerDeviceOnce once;
-    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES>, hipFuncAttributeMaxDynamicSharedMemorySize, 104 * 1024); });
+    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES, NSB>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024); });
     if (e != hipSuccess) return e;
   }
-  plan_kernel<LANES><<<dim3(LANES != 0 ? 3 : 2), dim3(kPlanThreads), sh, s>>>(L, T, ws, ra);
+  plan_kernel<LANES, NSB><<<dim3(2 + blocks), dim3(kPlanThreads), sh, s>>>(L, T, ws, ra, chunk);
   return hipGetLastError();
 }
-hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) { return launch_plan_kernel<0>(L, T, ws, RouteArgs{}, s); }
+template <int LANES>
+static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
+  switch (L.P) {
+    case 1: return launch_plan_nsb<LANES, 1>(L, T, ws, ra, blocks, chunk, s);
+    case 2: return launch_plan_nsb<LANES, 2>(L, T, ws, ra, blocks, chunk, s);
+    case 3: return launch_plan_nsb<LANES, 3>(L, T, ws, ra, blocks, chunk, s);
+    default: return launch_plan_nsb<LANES, kSubBits>(L, T, ws, ra, blocks, chunk, s);
+  }
+}
 
-// Routing, plan and scatter of a small batch in one launch: one workgroup routes 64 tokens at once, so each of three does it
-// for itself and they write the two work lists and the row lists side by side.  1 token on 64 experts: 18 us in three launches ->
-// 14; 64 tokens on 8 experts 24 -> 16; the 8 x 128 x 256 layer on 64 tokens 31 -> 26 us in all.
-bool small_plan(const Layout& L, int T) { return T <= kSmallPlanTokens && L.E <= 64; }
+// The plan and, in further workgroups of the same launch, the row lists.  Each of these reads all the histograms, so it does that only
+// as long as they are small (256 KiB: 16384 tokens on 64 experts in two parts); beyond, the scatter kernel follows, whose workgroups claim
+// their rows with atomics.  Plan kernel + scatter kernel, before (an LDS table and a barrier for every step, fourteen in all) -> now, us: 8192
+// tokens top-8 on 64 experts in 2 parts 17.5 + 6.2 -> 11.5, 4096 top-2 on 8 in 4 parts 23.2 + 5.2 -> 13, 16384 on 2 of 8 in 4 parts
+// 18.8 + 5.0 -> 12.5, 333 on 64 + 2 in 2 parts 11.7 + 4.8 -> 9, 777 on 64 + 2 in 8 parts 20.7 + 5.5 -> 15.5; routed here as well: 1 token top-8
+// on 64 experts 12.3 -> 9, 64 top-2 on 8 in 2 parts 9.7 -> 6.5.
+hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) {
+  const int bt = route_block_tokens(L.E, T), nblk = (T + bt - 1) / bt;
+  const int per_blk = bt * L.K;                                         // pairs of a route block
+  int chunk = (nblk + 63) / 64;                                         // up to 64 workgroups ...
+  if (chunk * per_blk < kPlanThreads) chunk = kPlanThreads / per_blk;   // ... of a pair per thread and more
+  if (T > 0 && (int64_t)nblk * L.nbins <= 65536 && (int64_t)chunk * per_blk <= kListPairs * kPlanThreads)
+    return launch_plan_kernel<0>(L, T, ws, RouteArgs{}, (nblk + chunk - 1) / chunk, chunk, s);
+  const hipError_t e = launch_plan_kernel<0>(L, T, ws, RouteArgs{}, 0, 0, s);
+  return e != hipSuccess ? e : launch_scatter(L, T, ws, s);
+}
+
+// Routing, plan and row lists of a small batch in one launch: one workgroup routes 64 tokens at once with sixteen lanes each (more than 32
+// experts), up to 1024 with a lane each, so each of three does it for itself and they write the two work lists and the row lists side by side.
+// Layer times, route + plan + scatter -> this: 100 / 1000 tokens top-2 on 8 experts of 128 x 256 in fp32 29.0 -> 21.9 us, 46.6 -> 40.9; 128 / 512
+// top-4 on 16 of 1024 x 512 45.0 -> 38.5, 62.4 -> 57.8, on 32 56.8 -> 46.1, 66.7 -> 59.4; 1024 on either (4096 pairs for one workgroup to
+// place) no gain, 80.2 -> 80.5 and 75.9 -> 76.0: those take the three steps.
+bool small_plan(const Layout& L, int T) {
+  return L.E <= 32 ? T <= kPlanThreads && T * L.K <= kLanePlanPairs : T <= kRowPlanTokens && L.E <= 64;
+}
 hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const float* tau, char* ws, hipStream_t s) {
   RouteArgs a = {};
   a.logits = logits;
@@ -1018,15 +1077,14 @@ hipError_t launch_small_plan(const Layout& L, int T, const float* logits, const 
   a.bins = 1;
   a.T = T;
   set_route_layer(L, a);
-  if (L.E <= 8) return launch_plan_kernel<8>(L, T, ws, a, s);
-  if (L.E <= 32) return launch_plan_kernel<32>(L, T, ws, a, s);
-  return launch_plan_kernel<16>(L, T, ws, a, s);
+  if (L.E <= 8) return launch_plan_kernel<8>(L, T, ws, a, 1, 0, s);
+  if (L.E <= 32) return launch_plan_kernel<32>(L, T, ws, a, 1, 0, s);
+  return launch_plan_kernel<16>(L, T, ws, a, 1, 0, s);
 }
 
 // ------------------------------------------------------------------------------------- scatter
-// Places every pair with at least one kept unit into its bin's row range.  The order inside a bin
-// is arbitrary (it is decided by atomics); the layer output does not depend on it because every
-// row is computed independently of its tile neighbours.
+// The row lists of batches whose histograms are too large for the plan kernel's workgroups to read them all (see launch_plan):
+// places every pair with at least one kept unit into its bin's row range.
 constexpr int kScatterThreads = 256;
 // PPT pairs per thread (pair u of a thread is block base + u * 256 + thread: coalesced).  A block
 // claims its rows with one global atomic per bin it fills, so larger blocks mean fewer of those
