@@ -7,7 +7,7 @@
 // short last tile along) x 64 neurons, resp. x 128 output columns: a weight image of 128 rows (see pack.hip); in large batches of
 // bf16 layers of many experts two images (full_wide).
 //
-// Matrix instructions: fp32 layers multiply with v_mfma_f32_32x32x2_f32 (the precision of an fmaf chain, 256 flop
+// Matrix instructions: fp32 layers multiply with v_mfma_f32_16x16x4_f32 (the precision of an fmaf chain, 256 flop
 // per clock and compute unit, the chip's fp32 peak of ~155 TFLOP/s; without packed fp32 the vector units reach
 // half of that).  bf16 layers multiply x with W1 / W3 by v_mfma_f32_32x32x16_bf16 (exact products); for GEMM-2 the fp32
 // activation is cut into three bf16 values h = hi + mid + lo (8 + 8 + 8 significant bits: exact from |h| = 2^-110 on, below that
@@ -23,7 +23,7 @@
 // carried by one term are less exact than fp32 (2.6e-8 -> 6.5e-8), as are products of values below 2^-110.
 //
 // A workgroup is 4 wavefronts; wavefront w owns the weight rows 32 w .. 32 w + 31 of the tile's 128 and multiplies them
-// with all pair rows, so a tile of r rows costs ceil(r/32) blocks.  The 32 weight rows of a GEMM-1 wavefront are the gate
+// with all pair rows, so a tile of r rows costs ceil(r/32) blocks (fp32: ceil(r/16) of half the size).  The 32 weight rows of a GEMM-1 wavefront are the gate
 // and the up projection of the same 16 neurons, which meet in one lane.  64 rows against 128 weight rows are 2048 matrix
 // cycles for 24 KiB of operands in fp32 (12 bytes per clock: well below what L2 and HBM deliver), so for fp32 the
 // tile does not have to be larger; with few rows the kernels stream weights.  Operands travel HBM/L2 -> LDS by 16-byte
@@ -35,6 +35,8 @@
 //   bf16, 64 + 2 shared experts of 2048 x 1408 in parts of 176, 777 tokens top-6: GEMM-1 2309 -> 208 us (4 TB/s), GEMM-2 1041 -> 224 us
 //   fp32, 8 experts of 128 x 256, 64 tokens: GEMM-1 27 -> 6 us, GEMM-2 33 -> 4 us (K split over several workgroups)
 // and with tiles of two images, the whole layer: 777 tokens of the second 431 -> 399 (GEMM-2 224 -> 160).
+#include <type_traits>
+
 #include "common.h"
 
 namespace dsmoe {
@@ -101,9 +103,14 @@ __device__ __forceinline__ bf16x8 finite_only(const bf16x8& a) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
-// One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
-// SUBS = 2: two wavefronts share 32 weight rows; each multiplies one half of every stage's K values, and the sums meet in
-// the first one (w < 2) at the end.
+// One tile product: 128 / SUBS weight rows (WE bytes per value) x NJ blocks of BR pair rows (XE bytes per value), K stages of 32.
+// fp32 weights: blocks of 16 rows (v_mfma_f32_16x16x4_f32, the rate of the 32-row instruction): an expert's few rows are
+// padded half as far (with blocks of 32: 512 tokens top-8 on 64 experts of 2048 x 1024, 48 rows an expert, 522 -> 472 us for the layer, 300 tokens 415 -> 360;
+// 144 tokens, 14 rows, where weights only stream, 310 -> 315).
+// The sums of fp32 products are kept apart for the two halves of every stage's K values and added at the end: half as long chains of roundings
+// (2048 x 1024, 2 experts of 8 per token: 1.27e-6 -> 0.88e-6 off the 64-bit result).
+// SUBS = 2: two wavefronts share 32 weight rows.  fp32: each multiplies 16 of them, so that the sums are those of a whole tile bit for bit; bf16: each
+// multiplies one half of every stage's K values, and the sums meet in the first one (w < 2) at the end.
 // NONFINITE (bf16 weights x fp32 activations): some weights are infinite or NaN, see above
 template <int WE, int XE, int NJ, int SUBS, bool NONFINITE = false>
 struct FullTile {
@@ -111,24 +118,44 @@ struct FullTile {
   static constexpr int WCH = WR / 16, XCH = XR / 16;           // 16-byte chunks of a row
   static constexpr int WROWS = 128 / SUBS;
   static constexpr int NW = WROWS * WR / 4096;                 // 4 KiB loads of the weight tile per stage
-  static constexpr int XROWS = XE == 2 ? (NJ + 1) / 2 * 64 : NJ * 32;
-  static constexpr int NX = XROWS * XR / 4096;
+  static constexpr int BR = WE == 4 ? 16 : 32;                 // pair rows of a block
+  static constexpr int XROWS_LOAD = 256 / XCH;                 // rows per load
+  static constexpr int NX = (NJ * BR + XROWS_LOAD - 1) / XROWS_LOAD;
   static constexpr int NL = NW + NX;
   static constexpr int SB = NL * 4096;                         // bytes of a stage
   static constexpr int NS = kFullLds / SB < 6 ? kFullLds / SB : 6;
-  static constexpr int XROWS_LOAD = 256 / XCH;                 // rows per load
   static_assert(NS >= 2 && (NS - 2) * NL < 64, "ring");
 
-  f32x16 acc[NJ];
+  static constexpr bool SPLIT = WE == 4 && SUBS == 2;  // two wavefronts, 16 weight rows each
+  static constexpr int NI = SPLIT ? 1 : 2;             // fp32: blocks of 16 weight rows of a wavefront
+  static constexpr int NQ = WE == 4 ? NI : 4;          // groups of four accumulators per block and lane
+  f32x4 acc4[WE == 4 ? NJ : 1][2];                     // fp32: of the first half of every stage, in the end of both (SPLIT: [1] is only used by other_rows)
+  f32x4 acc4b[WE == 4 ? NJ : 1][NI];                   // of the second half
+  f32x16 acc[WE == 4 ? 1 : NJ];
+
+  // the 32 weight rows that a wavefront works on
+  static __device__ __forceinline__ int rows32(int w) { return SPLIT ? w >> 1 : w % (4 / SUBS); }
+  // Group q of block j: four consecutive weight rows of these 32, the first of them w_row(q) (SPLIT: + 16 in odd wavefronts), times pair row x_row(j).
+  __device__ __forceinline__ f32x4 group(int j, int q) const {
+    if constexpr (WE == 4) return acc4[j][q];
+    else return f32x4{acc[j][q * 4], acc[j][q * 4 + 1], acc[j][q * 4 + 2], acc[j][q * 4 + 3]};
+  }
+  static __device__ __forceinline__ int w_row(int q, int lane) { return WE == 4 ? q * 16 + (lane >> 4) * 4 : q * 8 + (lane >> 5) * 4; }
+  static __device__ __forceinline__ int x_row(int j, int lane) { return j * BR + (lane & (BR - 1)); }
 
   // rowp[i]: where this thread's chunk of its i-th row starts (K position 0); wsrc: this thread's chunk of the first weight
   // stage; next(st): byte offset of stage st in a pair row and in the weight stages, called once per stage in order
   template <class Next>
   __device__ __forceinline__ void run(int n, const char* const (&rowp)[NX], const char* wsrc, Next&& next, const char* lds, int w, int lane) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < NJ; ++j) {
+      if constexpr (WE == 4)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        for (int i = 0; i < NI; ++i) acc4[j][i] = acc4b[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      else
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    }
     const uint32_t base = lds_byte(lds) + (uint32_t)w * 1024;
     auto issue = [&](int st) {
       int64_t xo, wo;
@@ -159,22 +186,28 @@ struct FullTile {
       asm volatile("s_barrier" ::: "memory");
       multiply(lds + (st % NS) * SB, w, lane);
     }
-    if constexpr (SUBS == 2) {
+    if constexpr (WE == 4) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) acc4[j][i] += acc4b[j][i];
+    }
+    if constexpr (SUBS == 2 && !SPLIT) {
       asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
-      f32x4* part = (f32x4*)const_cast<char*>(lds) + (w & 1) * (NJ * 256) + lane;  // [4 NJ][64 lanes]
+      f32x4* part = (f32x4*)const_cast<char*>(lds) + (w & 1) * (NJ * NQ * 64) + lane;  // [NQ NJ][64 lanes]
       if (w >= 2) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) part[(j * 4 + q) * 64] = f32x4{acc[j][q * 4], acc[j][q * 4 + 1], acc[j][q * 4 + 2], acc[j][q * 4 + 3]};
+          for (int q = 0; q < NQ; ++q) part[(j * NQ + q) * 64] = group(j, q);
       }
       __syncthreads();
       if (w < 2) {
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 o = part[(j * 4 + q) * 64];
+          for (int q = 0; q < NQ; ++q) {
+            const f32x4 o = part[(j * NQ + q) * 64];
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[j][q * 4 + c] += o[c];
           }
@@ -182,23 +215,43 @@ struct FullTile {
     }
   }
 
+  // SPLIT: the odd wavefronts' sums go to the even ones, as group 1
+  __device__ __forceinline__ void other_rows(const char* lds, int w, int lane) {
+    asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
+    f32x4* part = (f32x4*)const_cast<char*>(lds) + (w >> 1) * (NJ * 64) + lane;  // [NJ][64 lanes]
+    if (w & 1)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) part[j * 64] = acc4[j][0];
+    __syncthreads();
+    if (!(w & 1))
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc4[j][1] = part[j * 64];
+  }
+
   __device__ __forceinline__ void multiply(const char* stage, int w, int lane) {
     const int r32 = lane & 31, h = lane >> 5;
-    const int k0 = SUBS == 2 ? w >> 1 : 0;  // this wavefront's half of the stage
-    const char* wrow = stage + (w % (4 / SUBS) * 32 + r32) * WR;
+    const int k0 = SUBS == 2 ? w >> 1 : 0;  // bf16: this wavefront's half of the stage
+    const char* wrow = stage + (rows32(w) * 32 + r32) * WR;
     const char* xrow = stage + NW * 4096 + r32 * XR;
-    if constexpr (WE == 4) {  // fp32 x fp32: chunk 2s + h of a row holds K values 8s + 4h .. 8s + 4h + 3
+    if constexpr (WE == 4) {  // fp32 x fp32: chunk 4s + h of a row holds K values 16s + 4h .. 16s + 4h + 3; instruction i takes every lane's i-th
+      const int r16 = lane & 15, h16 = lane >> 4;
 #pragma unroll
-      for (int s0 = 0; s0 < 4 / SUBS; ++s0) {
-        const int s = s0 + k0 * 2;
-        const f32x4 a = *(const f32x4*)(wrow + swz_full<WCH>(r32, 2 * s + h) * 16);
-        f32x4 b[NJ];
+      for (int s = 0; s < 2; ++s) {
+        const int at = swz_full<WCH>(r16, 4 * s + h16) * 16;  // (rows 16 apart have the same rotation)
+        f32x4 a[NI], b[NJ];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) b[j] = *(const f32x4*)(xrow + j * 32 * XR + swz_full<XCH>(r32, 2 * s + h) * 16);
+        for (int i = 0; i < NI; ++i) a[i] = *(const f32x4*)(stage + (rows32(w) * 32 + (SPLIT ? (w & 1) * 16 : i * 16) + r16) * WR + at);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < NJ; ++j) b[j] = *(const f32x4*)(stage + NW * 4096 + (j * 16 + r16) * XR + at);
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j][i], acc[j], 0, 0, 0);
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+              f32x4& c = s == 0 ? acc4[j][i] : acc4b[j][i];
+              c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][k], b[j][k], c, 0, 0, 0);
+            }
       }
     } else if constexpr (XE == 2) {  // bf16 x bf16: K values 16s + 8h .. 16s + 8h + 7
 #pragma unroll
@@ -233,6 +286,17 @@ struct FullTile {
   }
 };
 
+// The pieces of a list: whole items, the last kFullHalved as two halves of their weight tile (tiles of two images: an image each).
+constexpr int kFullHalved = 256;
+struct FullPiece {
+  int item, half;  // half -1: the whole item
+};
+__device__ __forceinline__ int full_pieces(int items) { return items + min(items, kFullHalved); }
+__device__ __forceinline__ FullPiece full_piece(int items, int id) {
+  const int whole = max(items - kFullHalved, 0), cut = id - whole;
+  return cut < 0 ? FullPiece{id, -1} : FullPiece{whole + (cut >> 1), cut & 1};
+}
+
 // ------------------------------------------------------------------------------------- GEMM-1
 template <typename T, int NJ, int SUBS>
 __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it, int sub, const char* packed, const char* x, int64_t x_row, char* ws,
@@ -260,53 +324,88 @@ __device__ __forceinline__ void gemm1_full_tile(const Layout& L, const Item1& it
     wo = k * (128 * Tile::WR);
     ++k;
   }, lds, w, lane);
-  // acc[j][v]: weight row 8*(v/4) + 4*h + v%4 of the wavefront's 32 (16 gate rows, then the 16 up rows of the same
-  // neurons), pair row j*32 + lane%32
+  // the wavefront's 32 weight rows are 16 gate rows, then the 16 up rows of the same neurons
   float* H = (float*)(ws + (sh ? L.o_Hs : L.o_H)) + (size_t)(sh ? it.row0 : it.row0 - L.sh_rows) * ld + (size_t)it.p * Fpk;
-  if (SUBS == 2 && w >= 2) return;
-  const int n0 = it.jt * kFullNeur + sub * (kFullNeur / SUBS) + w * 16 + (lane >> 5) * 4;
+  if constexpr (Tile::SPLIT) t.other_rows(lds, w, lane);
+  if (Tile::SPLIT ? w & 1 : SUBS == 2 && w >= 2) return;
+  const int n_tile = it.jt * kFullNeur + sub * (kFullNeur / SUBS) + Tile::rows32(w) * 16;
+  constexpr int NG = sizeof(T) == 4 ? 1 : 2;  // groups of gate rows, and of up rows
+
   // the neurons that pad a partition to whole stages are zeros whatever came out: zero weights times an infinite x are NaN
   const int Fp = sh ? L.F_shT : L.Fp;
   float z = 0.f;  // stays zero as long as every activation is finite
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int r = j * 32 + (lane & 31);
+    const int r = Tile::x_row(j, lane);
     if (r >= it.nfill) continue;
     const bool kept = r < it.nrows && ((row_bits[r] >> it.p) & 1);
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
+    for (int q = 0; q < NG; ++q) {
+      const f32x4 gate = t.group(j, q), up = t.group(j, NG + q);
+      const int n = n_tile + Tile::w_row(q, lane);
       f32x4 o;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        o[c] = kept && n0 + g * 8 + c < Fp ? epi_value<false>(epi, t.acc[j][g * 4 + c], t.acc[j][8 + g * 4 + c]) : 0.f;
+        o[c] = kept && n + c < Fp ? epi_value<false>(epi, gate[c], up[c]) : 0.f;
         z = __builtin_fmaf(o[c], 0.f, z);
       }
-      if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = o;
+      if (n < Fpk) *(f32x4*)(H + (size_t)r * ld + n) = o;
     }
   }
   if (sizeof(T) == 2 && SUBS == 1 && L.wide && z != 0.f) ((int32_t*)(ws + L.o_counters))[kNonfiniteH] = 1;  // (true for NaN)
-  for (int r = NJ * 32 + (lane & 31); r < it.nfill; r += 32) {  // rows that keep nothing of this partition, beyond the blocks multiplied: zeros
-    for (int g = 0; g < 2; ++g)
-      if (n0 + g * 8 < Fpk) *(f32x4*)(H + (size_t)r * ld + n0 + g * 8) = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int r = Tile::x_row(NJ, lane); r < it.nfill; r += Tile::BR) {  // rows that keep nothing of this partition, beyond the blocks multiplied: zeros
+    for (int q = 0; q < NG; ++q) {
+      const int n = n_tile + Tile::w_row(q, lane);
+      if (n < Fpk) *(f32x4*)(H + (size_t)r * ld + n) = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   }
 }
 
+// f(blocks) with the number of blocks of pair rows (see FullTile) as a compile-time constant
+template <typename T, class F>
+__device__ __forceinline__ void with_blocks(int nrows, F&& f) {
+  if constexpr (sizeof(T) == 4) {
+    switch ((nrows + 15) >> 4) {
+      case 1: f(std::integral_constant<int, 1>()); break;
+      case 2: f(std::integral_constant<int, 2>()); break;
+      case 3: f(std::integral_constant<int, 3>()); break;
+      case 4: f(std::integral_constant<int, 4>()); break;
+      case 5: f(std::integral_constant<int, 5>()); break;
+      case 6: f(std::integral_constant<int, 6>()); break;
+      case 7: f(std::integral_constant<int, 7>()); break;
+      default: f(std::integral_constant<int, 8>()); break;
+    }
+  } else {
+    switch ((nrows + 31) >> 5) {
+      case 1: f(std::integral_constant<int, 1>()); break;
+      case 2: f(std::integral_constant<int, 2>()); break;
+      case 3: f(std::integral_constant<int, 3>()); break;
+      default: f(std::integral_constant<int, 4>()); break;
+    }
+  }
+}
+
+// SUBS: 2: all items in two halves; 1: none; 0: the last ones of the list (see full_parts)
+template <int SUBS>
+__device__ __forceinline__ int pieces_of(int items) { return SUBS == 2 ? items * 2 : SUBS == 0 ? full_pieces(items) : items; }
+template <int SUBS>
+__device__ __forceinline__ FullPiece piece_of(int items, int id) {
+  return SUBS == 2 ? FullPiece{id >> 1, id & 1} : SUBS == 0 ? full_piece(items, id) : FullPiece{id, -1};
+}
 template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm1_full_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int n = counters[0] * SUBS, id = take_piece<true>(n, counters + 8, lds), sub = id % SUBS;
+  const int items = counters[0], n = pieces_of<SUBS>(items), id = take_piece<true>(n, counters + 8, lds);
   if (id >= n) return;
-  const Item1 it = ((const Item1*)(ws + L.o_items1))[id / SUBS];
+  const FullPiece piece = piece_of<SUBS>(items, id);
+  const Item1 it = ((const Item1*)(ws + L.o_items1))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#define DSMOE_ROWS(N) gemm1_full_tile<T, N, SUBS>(L, it, sub, packed, x, x_row, ws, epi, lds, w, lane)
-  switch ((it.nrows + 31) >> 5) {
-    case 1: DSMOE_ROWS(1); break;
-    case 2: DSMOE_ROWS(2); break;
-    case 3: DSMOE_ROWS(3); break;
-    default: DSMOE_ROWS(4); break;
-  }
-#undef DSMOE_ROWS
+  with_blocks<T>(it.nrows, [&](auto blocks) {
+    constexpr int N = decltype(blocks)::value;
+    if (SUBS != 1 && piece.half >= 0) gemm1_full_tile<T, N, 2>(L, it, piece.half, packed, x, x_row, ws, epi, lds, w, lane);
+    else if constexpr (SUBS != 2) gemm1_full_tile<T, N, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane);
+  });
 }
 
 // ------------------------------------------------------------------------------------- GEMM-2
@@ -343,7 +442,6 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
     xo = kt * Tile::XR;
     wo = kt * (128 * Tile::WR);
   }, lds, w, lane);
-  // acc[j][v]: output column w*32 + 8*(v/4) + 4*h + v%4 of the tile, pair row j*32 + lane%32
   float* Y;
   int ldy;
   if (it.split == 0) {  // the item's rows of Yp
@@ -353,22 +451,24 @@ __device__ __forceinline__ void gemm2_full_tile(const Layout& L, const Item2& it
     Y = (float*)(ws + L.o_pool) + (size_t)(it.split - 1) * L.pool_rows * L.BN2 + (L.wide ? (it.jd & 1) * kFullBN2 : 0);
     ldy = L.BN2;
   }
-  if (SUBS == 2 && w >= 2) return;
-  const int c0 = sub * (kFullBN2 / SUBS) + w * 32 + (lane >> 5) * 4, d0 = it.jd * kFullBN2 + c0;
+  if (!Tile::SPLIT && SUBS == 2 && w >= 2) return;
+  const int c0 = sub * (kFullBN2 / SUBS) + Tile::rows32(w) * 32 + (Tile::SPLIT ? (w & 1) * 16 : 0), d0 = it.jd * kFullBN2;
   const bool vec = (L.D & 3) == 0;
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    const int r = j * 32 + (lane & 31);
+    const int r = Tile::x_row(j, lane);
     if (r >= it.nrows) continue;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float* at = Y + (size_t)r * ldy + c0 + g * 8;
+    for (int q = 0; q < Tile::NQ; ++q) {
+      const int c = c0 + Tile::w_row(q, lane);
+      const f32x4 o = t.group(j, q);
+      float* at = Y + (size_t)r * ldy + c;
       if (vec) {
-        if (d0 + g * 8 < L.D) *(f32x4*)at = f32x4{t.acc[j][g * 4], t.acc[j][g * 4 + 1], t.acc[j][g * 4 + 2], t.acc[j][g * 4 + 3]};
+        if (d0 + c < L.D) *(f32x4*)at = o;
       } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (d0 + g * 8 + c < L.D) at[c] = t.acc[j][g * 4 + c];
+        for (int i = 0; i < 4; ++i)
+          if (d0 + c + i < L.D) at[i] = o[i];
       }
     }
   }
@@ -378,23 +478,21 @@ template <typename T, int SUBS>
 __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int n = counters[1] * SUBS, id = take_piece<true>(n, counters + 9, lds), sub = id % SUBS;
+  const int items = counters[1], n = pieces_of<SUBS>(items), id = take_piece<true>(n, counters + 9, lds);
   if (id >= n) return;
-  const Item2 it = ((const Item2*)(ws + L.o_items2))[id / SUBS];
+  const FullPiece piece = piece_of<SUBS>(items, id);
+  const Item2 it = ((const Item2*)(ws + L.o_items2))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#define DSMOE_ROWS(NONFINITE)                                                                              \
-  switch ((it.nrows + 31) >> 5) {                                                                     \
-    case 1: gemm2_full_tile<T, 1, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
-    case 2: gemm2_full_tile<T, 2, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
-    case 3: gemm2_full_tile<T, 3, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;           \
-    default: gemm2_full_tile<T, 4, SUBS, NONFINITE>(L, it, sub, packed, ws, lds, w, lane); break;          \
-  }
-  if (sizeof(T) == 2 && *(const int32_t*)(packed + L.p_scale)) {
-    DSMOE_ROWS(sizeof(T) == 2)
-  } else {
-    DSMOE_ROWS(false)
-  }
-#undef DSMOE_ROWS
+  auto run = [&](auto nonfinite) {
+    with_blocks<T>(it.nrows, [&](auto blocks) {
+      constexpr int N = decltype(blocks)::value;
+      constexpr bool NONFINITE = sizeof(T) == 2 && decltype(nonfinite)::value;
+      if (SUBS != 1 && piece.half >= 0) gemm2_full_tile<T, N, 2, NONFINITE>(L, it, piece.half, packed, ws, lds, w, lane);
+      else if constexpr (SUBS != 2) gemm2_full_tile<T, N, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane);
+    });
+  };
+  if (sizeof(T) == 2 && *(const int32_t*)(packed + L.p_scale)) run(std::integral_constant<bool, sizeof(T) == 2>());
+  else run(std::false_type());
 }
 
 // ------------------------------------------------------------------------------------- two images to a tile
@@ -563,28 +661,17 @@ __device__ __forceinline__ void gemm1_wide_tile(const Layout& L, const Item1& it
   }
 }
 
-// The pieces of a list: whole items, the last kFullHalved as their two images.
-constexpr int kFullHalved = 256;
-struct WidePiece {
-  int item, image;  // image -1: both
-};
-__device__ __forceinline__ int wide_pieces(int items) { return items + min(items, kFullHalved); }
-__device__ __forceinline__ WidePiece wide_piece(int items, int id) {
-  const int whole = max(items - kFullHalved, 0), cut = id - whole;
-  return cut < 0 ? WidePiece{id, -1} : WidePiece{whole + (cut >> 1), cut & 1};
-}
-
 __global__ __launch_bounds__(256, 2) void gemm1_wide_kernel(Layout L, const char* packed, const char* x, int64_t x_row, char* ws, int epi) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int items = counters[0], n = wide_pieces(items), id = take_piece<true>(n, counters + 8, lds);
+  const int items = counters[0], n = full_pieces(items), id = take_piece<true>(n, counters + 8, lds);
   if (id >= n) return;
-  const WidePiece piece = wide_piece(items, id);
+  const FullPiece piece = full_piece(items, id);
   Item1 it = ((const Item1*)(ws + L.o_items1))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min((it.e == L.E_res ? L.NI1_sh : L.NI1) - 2 * it.jt, 2);
-  if (piece.image >= images) return;
-  if (piece.image < 0 && images == 2) {
+  if (piece.half >= images) return;
+  if (piece.half < 0 && images == 2) {
     switch (blocks) {
       case 1: gemm1_wide_tile<1>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
       case 2: gemm1_wide_tile<2>(L, it, packed, x, x_row, ws, epi, lds, w, lane); break;
@@ -593,7 +680,7 @@ __global__ __launch_bounds__(256, 2) void gemm1_wide_kernel(Layout L, const char
     }
     return;
   }
-  it.jt = 2 * it.jt + max(piece.image, 0);
+  it.jt = 2 * it.jt + max(piece.half, 0);
   switch (blocks) {
     case 1: gemm1_full_tile<uint16_t, 1, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
     case 2: gemm1_full_tile<uint16_t, 2, 1>(L, it, 0, packed, x, x_row, ws, epi, lds, w, lane); break;
@@ -675,15 +762,15 @@ __device__ __forceinline__ void gemm2_wide_tile(const Layout& L, const Item2& it
 __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char* packed, char* ws) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   int32_t* counters = (int32_t*)(ws + L.o_counters);
-  const int items = counters[1], n = wide_pieces(items), id = take_piece<true>(n, counters + 9, lds);
+  const int items = counters[1], n = full_pieces(items), id = take_piece<true>(n, counters + 9, lds);
   if (id >= n) return;
-  const WidePiece piece = wide_piece(items, id);
+  const FullPiece piece = full_piece(items, id);
   Item2 it = ((const Item2*)(ws + L.o_items2))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min(L.NI2 - 2 * it.jd, 2);
   const bool nonfinite = *(const int32_t*)(packed + L.p_scale) != 0;  // some weight of W2 is infinite or NaN
-  if (piece.image >= images) return;
-  if (piece.image < 0 && images == 2) {
+  if (piece.half >= images) return;
+  if (piece.half < 0 && images == 2) {
 #define DSMOE_ROWS(SAFE)                                                                 \
   switch (blocks) {                                                                      \
     case 1: gemm2_wide_tile<1, SAFE>(L, it, packed, ws, lds, w, lane); break;            \
@@ -699,7 +786,7 @@ __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char
 #undef DSMOE_ROWS
     return;
   }
-  it.jd = 2 * it.jd + max(piece.image, 0);
+  it.jd = 2 * it.jd + max(piece.half, 0);
 #define DSMOE_ROWS(NONFINITE)                                                                                 \
   switch (blocks) {                                                                                           \
     case 1: gemm2_full_tile<uint16_t, 1, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane); break;            \
@@ -730,6 +817,7 @@ static hipError_t set_lds_attr() {
   static PerDeviceOnce once;
   return once.run([] {
     for (const void* fn : {(const void*)gemm1_wide_kernel, (const void*)gemm2_wide_kernel,
+                           (const void*)gemm1_full_kernel<float, 0>, (const void*)gemm2_full_kernel<float, 0>,
                            (const void*)gemm1_full_kernel<float, 1>, (const void*)gemm1_full_kernel<float, 2>, (const void*)gemm1_full_kernel<uint16_t, 1>,
                            (const void*)gemm1_full_kernel<uint16_t, 2>, (const void*)gemm2_full_kernel<float, 1>, (const void*)gemm2_full_kernel<float, 2>,
                            (const void*)gemm2_full_kernel<uint16_t, 1>, (const void*)gemm2_full_kernel<uint16_t, 2>}) {
@@ -746,7 +834,13 @@ static hipError_t set_lds_attr() {
 // routing more so (127 of the fp32 ones with popularity rank^-1.2 280 -> 204).  Beyond, the rows are read twice for nothing: 300
 // tokens (37 pairs each) on the former 390 -> 414 us, 400 on the latter 335 -> 354.  An expert's share of the pairs does not
 // depend on how many experts are resident: 64 tokens on 8 of those 64 experts 82 -> 68 us, on 2 of 8 of 1024 x 2048 49 -> 40.
-static int full_parts(const Layout& L, int T) { return (int64_t)T * L.K <= (int64_t)L.E * 16 ? 2 : 1; }
+// From 32 fp32 pairs per expert on (before any drop) the kernels are bound by the matrix cores, and the last items of the list are cut:
+// 512 / 300 tokens top-8 on 64 experts of 2048 x 1024 472 -> 463 us, 360 -> 355, 400 / 1000 top-2 on 8 of 128 x 256 32.4 -> 28.4, 42.4 -> 35.9; 200 of the
+// former (25 pairs each) 324 -> 328.
+static int full_parts(const Layout& L, int T) {
+  const int64_t pairs = (int64_t)T * L.K;
+  return pairs <= (int64_t)L.E * 16 ? 2 : L.dtype == DSMOE_F32 && pairs >= (int64_t)L.E * 32 ? 0 : 1;
+}
 
 // Tiles of two images: bf16 layers, where experts have rows enough to reuse what was cut.  The line is in pairs per expert before any drop, as
 // the host knows no more.  Single images -> two, us per layer, 700 / 777 / 1500 tokens on 64 + 2 experts of 2048 x 1408 in parts of 176, top-6
@@ -785,9 +879,11 @@ hipError_t launch_gemm1_full(const Layout& L, int T, const char* packed, const v
     return hipGetLastError();
   }
   const int subs = full_parts(L, T);
-  const dim3 block(256), grid(piece_blocks(true, subs * items1_bound(L, T)));
+  const int items = items1_bound(L, T);
+  const dim3 block(256), grid(piece_blocks(true, subs == 2 ? 2 * items : items + (subs == 0 ? kFullHalved : 0)));
 #define DSMOE_LAUNCH(TYPE, SUBS) gemm1_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, xs, x_row, ws, epi)
   if (elem == 4 && subs == 2) DSMOE_LAUNCH(float, 2);
+  else if (elem == 4 && subs == 0) DSMOE_LAUNCH(float, 0);
   else if (elem == 4) DSMOE_LAUNCH(float, 1);
   else if (subs == 2) DSMOE_LAUNCH(uint16_t, 2);
   else DSMOE_LAUNCH(uint16_t, 1);
@@ -805,9 +901,11 @@ hipError_t launch_gemm2_full(const Layout& L, int T, const char* packed, char* w
     return hipGetLastError();
   }
   const int subs = full_parts(L, T);
-  const dim3 block(256), grid(piece_blocks(true, subs * items2_bound(L, T)));
+  const int items = items2_bound(L, T);
+  const dim3 block(256), grid(piece_blocks(true, subs == 2 ? 2 * items : items + (subs == 0 ? kFullHalved : 0)));
 #define DSMOE_LAUNCH(TYPE, SUBS) gemm2_full_kernel<TYPE, SUBS><<<grid, block, kFullLds, s>>>(L, packed, ws)
   if (L.dtype == DSMOE_F32 && subs == 2) DSMOE_LAUNCH(float, 2);
+  else if (subs == 0) DSMOE_LAUNCH(float, 0);
   else if (L.dtype == DSMOE_F32) DSMOE_LAUNCH(float, 1);
   else if (subs == 2) DSMOE_LAUNCH(uint16_t, 2);
   else DSMOE_LAUNCH(uint16_t, 1);
