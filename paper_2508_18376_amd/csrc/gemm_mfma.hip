@@ -31,7 +31,7 @@
 // registers in between), through a ring of 4 stages (4 x 32 KiB of the CU's 160 KiB LDS), three
 // stages in flight ahead of the one being multiplied.  Weight tiles are stored pre-swizzled by
 // moe_partition_weights, so their copy is a linear 16 KiB stream; activation rows are gathered
-// through the row list (GEMM-1) or read in place (GEMM-2) with the same chunk rotation.
+// through the row list with the same chunk rotation (GEMM-1), or are such images already (GEMM-2: H, see h_stage).
 //
 // The loads are written as inline assembly so that their completion can be awaited per stage
 // (s_waitcnt vmcnt(N)): the compiler never sees them and must not be allowed to move LDS reads
@@ -344,6 +344,17 @@ struct WaveTile {
   }
 };
 
+// The intermediate activation H (half precision) lies in HBM as GEMM-2 wants it in LDS: per row tile (256 rows) and 32
+// neurons one 16 KiB image [256 rows][32], the chunks of a row rotated as everywhere (swz_chunk); the images of a row tile follow
+// each other along the neurons.  GEMM-2 then streams whole cache lines in order, for H as for W2, and GEMM-1's write-out is linear
+// too.  As rows of F values a stage was 256 pieces of 64 bytes at the stride of a row, twice the L2 requests.  Rows -> images, GEMM-2
+// without drop, us: 8192 tokens on 64 experts of 2048 x 1024 322 -> 315, x 1280 354 -> 339, 4096 on 8 of 4096 x 14336 757 -> 744;
+// layers at 25 % drop: 8192 tokens on the first 723 -> 714, 333 and 7001 on 64 + 2 of 2048 x 1408 249 -> 246 and 837 -> 821.
+// Image of neurons 32 kt .. of the row tile of `row` (kts images to a row tile).
+__device__ __forceinline__ char* h_stage(void* H, int row, int kt, int kts) {
+  return (char*)H + ((size_t)(row / kMfmaBM) * kts + kt) * kStageBytes;
+}
+
 // ------------------------------------------------------------------------------------- GEMM-1
 struct G1Args {
   Item1 it;
@@ -469,16 +480,16 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
   }
 
   // epilogue.  acc[i][j][v]: weight row a_row0 + i*32 + 8*(v/4) + 4*(lane/32) + v%4, pair row
-  // b_row0 + j*32 + lane%32.  Swish(gate) * up is rounded to half precision and parked in LDS as a
-  // [256 rows][128 neurons] tile (320 rows in a tall tile; rows padded to 272 bytes against bank conflicts), then written
-  // out in whole 256-byte row segments: 16 lanes per row, 16 bytes per lane.
-  constexpr int kHsRow = kMfmaNeur * 2 + 16;
-  constexpr int kRowsOut = RING::BYTES >= kTallRows * kHsRow ? kTallRows : kStreamRows;  // (the streaming kernels')
+  // b_row0 + j*32 + lane%32.  Swish(gate) * up is rounded to half precision and parked in LDS as the four
+  // stage images of H (32 neurons each, see h_stage) that the tile is, and written out as the linear stream those are:
+  // 64 rows of an image per pass, 16 bytes per thread.
+  constexpr int kRowsOut = RING::BYTES > kStreamLds ? kTallRows : kStreamRows;  // (the streaming kernels')
+  constexpr int kImageOut = kRowsOut * kRowBytes;
   block_barrier();  // every wave is done reading the last stage
   // one block of 32 rows x 32 neurons: gate and up accumulators of weight blocks i and i + 1, pair row r of this lane
   auto emit = [&](const f32x16& gate, const f32x16& up, int r, bool kept, int i) {
     const int nb = (a_row0 >> 5) + ((i + arot) & 3) + 4 * half;  // weight block index; neurons of the tile: (nb/2)*32 ..
-    char* srow = lds + r * kHsRow + ((nb >> 1) * 32 + (le >> 5) * 4) * 2;
+    char* srow = lds + (nb >> 1) * kImageOut + r * kRowBytes + (le >> 5) * 8;  // neurons 8 vq + 4 (lane / 32) ..: chunk vq of the row
     // one branch per block of sixteen values, so that their chains of dependent operations interleave
     // (a select per value makes the compiler branch around every single evaluation)
     if (kept) {
@@ -495,11 +506,11 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
         uint2 pk;
         pk.x = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h[0], h[1]));
         pk.y = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(h[2], h[3]));
-        *(uint2*)(srow + vq * 16) = pk;
+        *(uint2*)(srow + swz_chunk(r, vq) * 16) = pk;
       }
     } else {
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) *(uint2*)(srow + vq * 16) = make_uint2(0, 0);
+      for (int vq = 0; vq < 4; ++vq) *(uint2*)(srow + swz_chunk(r, vq) * 16) = make_uint2(0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);  // one block of rows and 32 neurons at a time: keeps the register pressure of the epilogue low
   };
@@ -517,24 +528,27 @@ __device__ __forceinline__ void gemm1_tile(const G1Args& g, char* lds, int a_row
     if (t.bx_mode == 3) emit(t.accx[2], t.accx[3], r, kept, 2);
   }
   __syncthreads();
-  const int n_in = g.it.jt * kMfmaNeur + (tid & 15) * 8;  // first of this lane's 8 neurons, inside the partition
-  if (n_in < g.Fp && (!HALF || ((tid & 15) >> 3) == half)) {
-    // four rows at a time: their reads first, whether or not the rows exist (pinned here: inside the
-    // branch each read would wait for its own LDS round trip), then the stores
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  // The images of the tile that exist (the last neuron tile of a partition may be short; half items have two), 64 rows of
+  // each in one go: their reads first, whether or not the rows exist (pinned here: inside the branch each read would wait
+  // for its own LDS round trip), then the stores.
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int kImages = kMfmaNeur / kBK;
+  const int have = min(kImages, (g.Fp - g.it.jt * kMfmaNeur) / kBK);
+  const int kt0 = (g.it.p * g.Fp + g.it.jt * kMfmaNeur) / kBK;
 #pragma unroll 1
-    for (int c0 = 0; c0 < kRowsOut / 16; c0 += 4) {  // up to 320 rows: the tile before an expert's short last tile zero-fills that one's rows too
-      u32x4_t v[4];
+  for (int r0 = 0; r0 < kRowsOut; r0 += 64) {  // up to 320 rows: the tile before an expert's short last tile zero-fills that one's rows too
+    if (r0 >= g.it.nfill) break;
+    u32x4_t v[kImages];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) v[c] = *(const u32x4_t*)(lds + ((c0 + c) * 16 + (tid >> 4)) * kHsRow + (tid & 15) * 16);
+    for (int c = 0; c < kImages; ++c) v[c] = *(const u32x4_t*)(lds + c * kImageOut + r0 * kRowBytes + tid * 16);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(v[c]));
+    for (int c = 0; c < kImages; ++c) asm volatile("" : "+v"(v[c]));
+    const int r = r0 + (tid >> 2);
+    if (r < g.it.nfill) {  // rows [nrows, nfill) of the row tile keep nothing of this partition: zeros
+      char* dst = h_stage(g.H, g.hrow0 + r0, kt0, g.ld / kBK) + (r0 & (kMfmaBM - 1)) * kRowBytes + tid * 16;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int r = (c0 + c) * 16 + (tid >> 4);
-        if (r < g.it.nfill)  // rows [nrows, nfill) of the row tile keep nothing of this partition: zeros
-          *(u32x4_t*)(g.H + (size_t)(g.hrow0 + r) * g.ld + (size_t)g.it.p * g.Fp + n_in) = r < g.it.nrows ? v[c] : u32x4_t{0, 0, 0, 0};
-      }
+      for (int c = 0; c < kImages; ++c)
+        if (c < have && (!HALF || (c >> 1) == half)) *(u32x4_t*)(dst + c * kStageBytes) = r < g.it.nrows ? v[c] : u32x4_t{0, 0, 0, 0};
     }
   }
 }
@@ -626,7 +640,7 @@ struct G2Args {
   Item2 it;
   int np, KSp, nstages, D;
   i32x4 rsW, rsH;
-  uint32_t lds_w, h_row_bytes;
+  uint32_t lds_w, h_tile_bytes;  // h_tile_bytes: a row tile of H
   char* Y;       // where row 0, column 0 of this item's output tile goes (float, or half precision: YH)
   int ldy;       // its row stride in elements: D in Yp, 256 in a pool tile
   float yscale;  // YH: the accumulators are stored times this power of two (see kYpHalfScale)
@@ -657,8 +671,8 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
 #pragma unroll
   for (int i = 0; i < NH; ++i) {
     const int r = i * 64 + (tid >> 2);
-    const int rr = r < g.it.nrows ? r : g.it.nrows - 1;
-    hoff[i] = (uint32_t)rr * g.h_row_bytes + (uint32_t)(swz_chunk(r, tid & 3) * 16);
+    const int rr = min(r, g.it.nrows - 1);  // rows past the end re-read the last valid row
+    hoff[i] = (uint32_t)(rr / kMfmaBM) * g.h_tile_bytes + (uint32_t)((rr % kMfmaBM) * kRowBytes + (tid & 3) * 16);
   }
   // stages run over the partitions some row of this tile keeps (Sec. 4: dropped units cost nothing);
   // begin() is called with increasing st, so a running cursor maps st -> K position.
@@ -674,7 +688,7 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
       while (p_cur < g.np && !((g.it.kmask >> p_cur) & 1)) ++p_cur;
     }
     slot = (uint32_t)(st % RING::NS) * RING::SB + g.lds_w;
-    sH = (uint32_t)(kt * kRowBytes);
+    sH = (uint32_t)(kt * kStageBytes);
     sW = (uint32_t)(kt * kStageBytes + g.col0 * kRowBytes);
   };
   auto one = [&](int q) {
@@ -779,11 +793,11 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
   g.D = L.D;
   const char* wbase = sh ? packed + L.p_sw2 + (int64_t)g.it.jd * KT * kStageBytes
                          : packed + L.p_w2 + ((int64_t)g.it.e * L.ND2 + g.it.jd) * KT * kStageBytes;
-  const uint16_t* H = sh ? (const uint16_t*)(ws + L.o_Hs) : (const uint16_t*)(ws + L.o_H);
-  const int hrow0 = sh ? g.it.row0 : g.it.row0 - L.sh_rows;
-  const char* hbase = (const char*)(H + (size_t)hrow0 * ld);
+  const int hrow0 = sh ? g.it.row0 : g.it.row0 - L.sh_rows;  // row tiles start at multiples of 256
+  const char* hbase = h_stage(ws + (sh ? L.o_Hs : L.o_H), hrow0, 0, KT);
+  g.h_tile_bytes = (uint32_t)(KT * kStageBytes);
   g.rsW = make_rsrc(wbase, (uint32_t)((int64_t)KT * kStageBytes));
-  g.rsH = make_rsrc(hbase, (uint32_t)((int64_t)g.it.nrows * ld * 2));
+  g.rsH = make_rsrc(hbase, g.it.nrows > kMfmaBM ? 2 * g.h_tile_bytes : g.h_tile_bytes);
   const size_t yel = L.yp_half ? 2 : 4;
   if (g.it.split == 0) {  // the item's rows of Yp
     g.Y = ws + L.o_Yp + ((size_t)g.it.row0 * L.D + g.it.jd * kMfmaBN2) * yel;
@@ -794,7 +808,6 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
   }
   g.yscale = kYpHalfScale;
   g.col0 = 0;
-  g.h_row_bytes = (uint32_t)(ld * 2);
 
   g.lds_w = lds_offset(lds) + (uint32_t)(w * 1024);
   g.nstages = 0;
