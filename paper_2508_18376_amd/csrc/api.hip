@@ -168,7 +168,6 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
     L.p_w2 = takep(L.w2_expert_bytes * L.E_res);
     L.p_sw13 = takep((int64_t)L.NT1_sh * KS1 * kStageBytes);
     L.p_sw2 = takep(L.n_shared > 0 ? (int64_t)L.ND2 * (L.F_shT / kBK) * kStageBytes : 0);
-    L.p_scale = takep(16);
   } else {
     L.w13_expert_bytes = (int64_t)L.P * L.NT1 * (2 * kFullNeur) * L.Dk * elem;
     L.w2_expert_bytes = (int64_t)L.ND2 * kFullBN2 * L.Fh * elem;
@@ -176,11 +175,8 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
     L.p_w2 = takep(L.w2_expert_bytes * L.E_res);
     L.p_sw13 = takep((int64_t)L.NT1_sh * (2 * kFullNeur) * L.Dk * elem);
     L.p_sw2 = takep((int64_t)L.ND2 * kFullBN2 * L.Fsk * elem);
-    L.p_scale = takep(elem == 2 ? 16 : 0);
   }
-  // the permutation check borrows the start of the packed buffer for its counters
-  const int64_t need_check = ((int64_t)L.E_res * L.F + 1) * 4;
-  if (q < need_check) q = align_up(need_check, 256);
+  L.p_scale = takep(sizeof(PackRecord));
   L.packed_bytes = q;
   L.router_mfma = (c.dtype == DSMOE_BF16 && L.D % 64 == 0) ? 1 : 0;
   L.router_bytes = L.router_mfma ? (int64_t)L.D * ((L.E + 31) / 32 * 32) * 2 : (int64_t)L.D * L.E * 4;
@@ -303,21 +299,21 @@ int moe_partition_weights(dsmoe_ctx* ctx_, const void* w1, const void* w3, const
   if (L.n_shared > 0 && (!sh_w1 || !sh_w3 || !sh_w2)) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   hipError_t err;
-  if (perm) {
-    int32_t* scratch = (int32_t*)packed_out;
-    err = launch_perm_check(L, perm, scratch, s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
-    int32_t bad = 0;
-    err = hipMemcpyAsync(&bad, scratch + (size_t)L.E_res * L.F, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
-    err = hipStreamSynchronize(s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
-    if (bad != 0) return DSMOE_EPERM;
-  }
+  // what the kernels found is read once all of them are under way; a perm that is none, or a scale that does not fit, costs their time
   err = launch_pack(L, w1, w3, w2, sh_w1, sh_w3, sh_w2, perm, (char*)packed_out, ctx->cfg.n_shared, ctx->cfg.d_ff_shared, s);
+  if (err != hipSuccess) return hip_fail(ctx, err);
+  PackRecord rec;
+  err = hipMemcpyAsync(&rec, (const char*)packed_out + L.p_scale, sizeof(rec), hipMemcpyDeviceToHost, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   err = hipStreamSynchronize(s);
   if (err != hipSuccess) return hip_fail(ctx, err);
+  if (rec.bad_perm) return DSMOE_EPERM;
+  if (rec.repack) {
+    err = launch_repack_w2(L, w2, sh_w2, perm, (char*)packed_out, s);
+    if (err != hipSuccess) return hip_fail(ctx, err);
+    err = hipStreamSynchronize(s);
+    if (err != hipSuccess) return hip_fail(ctx, err);
+  }
   return DSMOE_OK;
 }
 
@@ -486,11 +482,12 @@ int moe_transform_complete(dsmoe_ctx* ctx_, const void* wg, const void* w1, cons
   hipStream_t s = (hipStream_t)stream;
   hipError_t err;
   if (perm) {
-    int32_t* scratch = (int32_t*)((char*)workspace + L.o_perm_check);
-    err = launch_perm_check(L, perm, scratch, s);
+    int32_t *inv = (int32_t*)((char*)workspace + L.o_perm_check), *bad_at = inv + (size_t)L.E_res * L.F, bad = 0;
+    err = launch_fill_i32(bad_at, 1, 0, s);
     if (err != hipSuccess) return hip_fail(ctx, err);
-    int32_t bad = 0;
-    err = hipMemcpyAsync(&bad, scratch + (size_t)L.E_res * L.F, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    err = launch_invert_perm(L, perm, inv, bad_at, s);
+    if (err != hipSuccess) return hip_fail(ctx, err);
+    err = hipMemcpyAsync(&bad, bad_at, sizeof(int32_t), hipMemcpyDeviceToHost, s);
     if (err != hipSuccess) return hip_fail(ctx, err);
     err = hipStreamSynchronize(s);
     if (err != hipSuccess) return hip_fail(ctx, err);

@@ -67,6 +67,15 @@ struct Item2 {  // one tile of GEMM-2: rows x output column tile jd, summed over
   int32_t split;        // 0: the item writes its rows of Yp; n > 0: it writes partial-output tile n-1 of the pool
 };
 
+// What packing leaves beside the weights (32 bytes at Layout::p_scale, cleared before it).
+struct PackRecord {
+  uint32_t largest;  // MFMA layout: bits of the largest |W2| that the scale was taken from; full-precision layout of bf16: 1 if W2 has an infinity or NaN
+  float scale, unscale;  // MFMA layout: 2^s that the images of W2 carry; 2^-(s + h_shift), which the combine kernel applies
+  int32_t repack;    // a weight does not fit half precision at this scale
+  int32_t bad_perm;
+  int32_t pad[3];
+};
+
 // Everything the device code needs to know about the layer and the workspace.
 struct Layout {
   // layer
@@ -103,7 +112,7 @@ struct Layout {
   int64_t o_items1, o_items2;
   int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
   // packed weights byte offsets
-  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the W2 scale record (MFMA layout); int32: W2 has an infinity or NaN (full-precision layout)
+  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the PackRecord
   int64_t w13_expert_bytes, w2_expert_bytes;  // strides between experts (mfma layout)
 };
 
@@ -202,7 +211,10 @@ hipError_t launch_perm_from_importance(const Layout& L, const float* importance,
 hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s);
-hipError_t launch_perm_check(const Layout& L, const int32_t* perm, int32_t* scratch, hipStream_t s);
+// W2 once more, with the scale of the largest |W2| of all (after a launch_pack that left PackRecord::repack)
+hipError_t launch_repack_w2(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s);
+// the inverse of perm; *bad (cleared by the caller) is set if perm is not a permutation
+hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s);
 
 // ---- device helpers ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }

@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
       else if constexpr (SUBS != 2) gemm2_full_tile<T, N, 1, NONFINITE>(L, it, 0, packed, ws, lds, w, lane);
     });
   };
-  if (sizeof(T) == 2 && *(const int32_t*)(packed + L.p_scale)) run(std::integral_constant<bool, sizeof(T) == 2>());
+  if (sizeof(T) == 2 && ((const PackRecord*)(packed + L.p_scale))->largest) run(std::integral_constant<bool, sizeof(T) == 2>());
   else run(std::false_type());
 }
 
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(256, 2) void gemm2_wide_kernel(Layout L, const char
   Item2 it = ((const Item2*)(ws + L.o_items2))[piece.item];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blocks = (it.nrows + 31) >> 5, images = min(L.NI2 - 2 * it.jd, 2);
-  const bool nonfinite = *(const int32_t*)(packed + L.p_scale) != 0;  // some weight of W2 is infinite or NaN
+  const bool nonfinite = ((const PackRecord*)(packed + L.p_scale))->largest != 0;  // some weight of W2 is infinite or NaN
   if (piece.half >= images) return;
   if (piece.half < 0 && images == 2) {
 #define DSMOE_ROWS(SAFE)                                                                 \

@@ -15,10 +15,11 @@
 //   W2   stage (e*ND2 + jd)*(F/32) + kt : 256 output columns x 32 neurons (positions kt*32..),
 //        as IEEE half precision times 2^s (GEMM-2 multiplies half-precision operands: its left
 //        operand, the intermediate activation, needs more significant bits than bf16 has).  s is
-//        chosen per layer so that the largest |W2| lands in [2^14, 2^15): every bf16 value within a
-//        factor 2^-29 of the largest is then exactly representable (smaller ones round to the
-//        subnormal grid, 2^-39 of the largest); the combine kernel multiplies by 2^-s, exactly.
-//        The scale record sits at p_scale: uint32 largest |W2| bits, float 2^s, float 2^-(s+k), int32 s.
+//        chosen per layer so that the largest |W2| of a sample lands in [2^14, 2^15) (all of a W2 of up to 32 M values;
+//        otherwise every 3rd to 31st run of 2048): every bf16 value within a factor 2^-29 of that is then exactly
+//        representable (smaller ones round to the subnormal grid, 2^-39 of it).  A layer with a larger |W2| that no longer
+//        fits half precision is packed again from the largest of all.  The combine kernel multiplies by 2^-s, exactly.
+//        The record (PackRecord) sits at p_scale.
 //   W3 carries the factor 2^k of cfg.h_scale_log2 (exact in bf16), so that the intermediate activation
 //        comes out of GEMM-1 times 2^k, in the range half precision resolves best, at no run-time cost.
 //   neurons / columns past the end are zero.
@@ -32,11 +33,11 @@ __device__ __forceinline__ uint4 load_once(const void* p) {  // non-temporal
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out.  One read of W2,
-// bound by HBM: four 16-byte loads in flight per thread, non-temporal, and one atomic per workgroup (all on one address).
-// 0.94 GB: 205 us with plain loads and an atomic per wavefront -> 160.  What is left for fewer than four loads a thread (all of a
-// tensor of up to 16.8 M values) comes 16 bytes at a time, too: loading 8 experts of 512 x 1024 62 -> 60 us.
-__global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int64_t n, uint32_t* out) {
+// largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out: of every stride-th run of 2048
+// values.  Bound by HBM: four runs in flight per workgroup, non-temporal, and one atomic per workgroup (all on one address).
+// 0.94 GB, all of it: 160 us (with plain loads and an atomic per wavefront 205); a sample of 16 M values 11 us.
+constexpr int kAbsmaxRun = 2048, kAbsmaxBlocks = 2048;
+__global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int64_t n, int stride, uint32_t* out) {
   uint32_t m = 0;
   auto one = [&](uint32_t a) { m = a < 0x7f80u && a > m ? a : m; };
   auto eight = [&](uint4 v) {
@@ -48,8 +49,8 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
     }
   };
   const bool vec = (((uintptr_t)w) & 15) == 0;
-  const int64_t step = (int64_t)gridDim.x * 256 * 8;
-  int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  const int64_t step = (int64_t)gridDim.x * stride * kAbsmaxRun;
+  int64_t i = (int64_t)blockIdx.x * stride * kAbsmaxRun + threadIdx.x * 8;
   if (vec) {
     for (; i + 3 * step + 8 <= n; i += 4 * step) {
       uint4 v[4];
@@ -71,16 +72,25 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
     if (m) atomicMax(out, m);
   }
 }
+static void launch_absmax(const void* w, int64_t n, int stride, PackRecord* rec, hipStream_t s) {
+  const int64_t runs = (n + (int64_t)stride * kAbsmaxRun - 1) / ((int64_t)stride * kAbsmaxRun);
+  const int blocks = (int)(runs < kAbsmaxBlocks ? runs : kAbsmaxBlocks);
+  absmax_bf16_kernel<<<dim3(blocks), dim3(256), 0, s>>>((const uint16_t*)w, n, stride, &rec->largest);
+}
+// The scale is needed before the first value is packed, and finding the largest of all |W2| reads W2 once more (a sixth of
+// the packing of 8 experts of 4096 x 14336, which took 1.52 ms with it and takes 1.34 without).  A sample of 16 to 32 M values tells its
+// binade as well as that binade and the next have room for: only a W2 whose largest value is more than twice (for some, four
+// times) the sample's largest is packed twice.  Odd strides: a row of a power of two of values is met in all of its columns.
+static int absmax_stride(int64_t n) {
+  const int64_t k = n >> 24;
+  return k < 2 ? 1 : k > 31 ? 31 : (int)(k | 1);
+}
 
-// rec[0] = largest |W2| bits  ->  rec[1] = 2^s, rec[2] = 2^-(s + h_shift), rec[3] = s, with largest * 2^s in
-// [2^14, 2^15).  rec[2] undoes both powers of two the packed weights carry: 2^s in W2 and 2^h_shift in W3.
-__global__ void w2_scale_kernel(uint32_t* rec, int h_shift) {
-  const int e = (int)(rec[0] >> 7);  // biased exponent of the largest value (0: zero or subnormal)
-  int s = e == 0 ? 0 : 14 - (e - 127);
-  s = s < -80 ? -80 : s > 80 ? 80 : s;
-  rec[1] = (uint32_t)(127 + s) << 23;
-  rec[2] = (uint32_t)(127 - s - h_shift) << 23;
-  rec[3] = (uint32_t)s;
+// largest |W2| bits -> s with largest * 2^s in [2^14, 2^15)
+__device__ __forceinline__ int w2_shift(uint32_t largest) {
+  const int e = (int)(largest >> 7);  // biased exponent (0: zero or subnormal)
+  const int s = e == 0 ? 0 : 14 - (e - 127);
+  return s < -80 ? -80 : s > 80 ? 80 : s;
 }
 
 // a bf16 value times 2^k (k = L.h_shift), exact unless it leaves bf16's exponent range
@@ -156,6 +166,30 @@ __device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
   return v;
 }
 
+// Some of the eight bf16 values `raw` is too large for the scale of a sample whose largest bits were `sampled`: finite, but
+// infinite as scaled half precision; or not zero where the whole sample was.  (Values beyond every scale stay infinite, as they
+// are when the scale is that of the largest.)
+__device__ __forceinline__ bool misses(uint4 raw, uint4 half, uint32_t sampled) {
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w}, h[4] = {half.x, half.y, half.z, half.w};
+  u16x2 m = {0, 0};  // largest |half|
+  uint32_t any = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, h[i] & 0x7fff7fffu));
+    any |= r[i] & 0x7fff7fffu;
+  }
+  bool miss = sampled == 0 && any != 0;
+  if (m.x >= 0x7c00u || m.y >= 0x7c00u) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t a = r[i >> 1] >> (16 * (i & 1)) & 0x7fffu, b = h[i >> 1] >> (16 * (i & 1)) & 0x7fffu;
+      miss |= a < 0x7f80u && b == 0x7c00u;
+    }
+  }
+  return miss;
+}
+
 // some of the eight bf16 values is infinite or NaN
 __device__ __forceinline__ bool not_finite(uint4 v) {
   auto one = [](uint32_t u) { return (u & 0x7f80u) == 0x7f80u || (u & 0x7f800000u) == 0x7f800000u; };
@@ -211,6 +245,7 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
       const int c = c0 + cg * PT::COLS_GET + i;
       if (c >= Fs) continue;
       const int pos = inv ? inv[(size_t)e * Fs + c] : pos0 * e + c;
+      if (inv && (uint32_t)pos >= (uint32_t)Fs) continue;  // not a permutation (reported when all is done)
       const int p = pos / Fp, nin = pos - p * Fp;
       const int row = Im::row(nin);
       char* stage = out + ((((int64_t)e * per_expert * P + p) * NT1 + nin / Im::NEUR) * KS1 + ks) * Im::STAGE;
@@ -224,26 +259,43 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
 // (source rows, in permuted order; zeros past the end of a partition) x COLS output columns: one stage image, or two
 // of 128 columns.  w2: [experts][P * Fp][D]; KSp: stages of a partition, KT: of the expert, nd: column tiles of the images.
 template <typename T, bool FULL>
-__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, float* rec, int D, int F, int Fp,
-                                                      int KSp, int KT, int nd, int vec) {
+__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, PackRecord* rec, int D, int F, int Fp,
+                                                      int KSp, int KT, int nd, int vec, int h_shift) {
   using PT = PackTile<T>;
   constexpr int BN = FULL ? kFullBN2 : kMfmaBN2, RB = kBK * sizeof(T);
   __shared__ PT t;
   const int nb = (D + PT::COLS - 1) / PT::COLS;
   const int c0 = (int)(blockIdx.x % nb) * PT::COLS, kt = blockIdx.x / nb, e = blockIdx.y, tid = threadIdx.x;
-  const float scale = FULL ? 1.f : rec[1];
+  float scale = 1.f;
+  uint32_t sampled = 0;  // largest |W2| of the sample
+  if (!FULL) {
+    sampled = rec->largest;
+    const int sh = w2_shift(sampled);
+    scale = __uint_as_float((uint32_t)(127 + sh) << 23);
+    if ((blockIdx.x | blockIdx.y | tid) == 0) {
+      rec->scale = scale;
+      rec->unscale = __uint_as_float((uint32_t)(127 - sh - h_shift) << 23);  // undoes 2^s of W2 and 2^h_shift of W3
+    }
+  }
   uint4 a[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int in = kt % KSp * kBK + u * 8 + (tid >> 5), pos = kt / KSp * Fp + in;
     const T* row = nullptr;
-    if (in < Fp) row = w2 + ((size_t)e * F + (perm ? perm[(size_t)e * F + pos] : pos)) * D;
+    if (in < Fp) {
+      const int src = perm ? perm[(size_t)e * F + pos] : pos;
+      if ((uint32_t)src < (uint32_t)F) row = w2 + ((size_t)e * F + src) * D;  // (not a permutation: reported when all is done)
+    }
     a[u] = PT::template load<false>(row, c0 + (tid & 31) * PT::V, D, vec);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    if (!FULL) a[u] = map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
-    if (FULL && sizeof(T) == 2 && not_finite(a[u])) *(int32_t*)rec = 1;
+    if constexpr (!FULL) {
+      const uint4 raw = a[u];
+      a[u] = map_halves(raw, [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
+      if (misses(raw, a[u], sampled)) rec->repack = 1;
+    }
+    if (FULL && sizeof(T) == 2 && not_finite(a[u])) rec->largest = 1;
     t.put(u * 8 + (tid >> 5), tid & 31, a[u]);
   }
   __syncthreads();
@@ -290,14 +342,41 @@ __global__ void invert_perm_kernel(const int32_t* perm, int32_t* inv, int F, int
   if (t >= n) return;
   const int64_t e = t / F;
   const int src = perm[t];
-  if (src >= 0 && src < F) inv[e * F + src] = (int32_t)(t % F);  // a bad perm is refused before this runs; stay in bounds regardless
+  if (src >= 0 && src < F) inv[e * F + src] = (int32_t)(t % F);
+}
+// *bad: some neuron is not the one that perm names at the position inv has for it, i.e. none names it (inv is whatever was
+// there before), so perm is no permutation
+__global__ void perm_check_kernel(const int32_t* perm, const int32_t* inv, int F, int64_t n, int32_t* bad) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const int64_t e = t / F;
+  const int pos = inv[t];
+  if (pos < 0 || pos >= F || perm[e * F + pos] != (int)(t % F)) *bad = 1;
+}
+hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s) {
+  const int64_t n = (int64_t)L.E_res * L.F;
+  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+  invert_perm_kernel<<<grid, block, 0, s>>>(perm, inv, L.F, n);
+  perm_check_kernel<<<grid, block, 0, s>>>(perm, inv, L.F, n, bad);
+  return hipGetLastError();
+}
+
+template <typename T, bool FULL>
+static void w2_images(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s) {
+  auto images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {
+    const int KSp = Fpk / kBK, KT = F / Fp * KSp, C = PackTile<T>::COLS;
+    const int vec = L.D % PackTile<T>::V == 0 && ((uintptr_t)w & 15) == 0;
+    pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * KT), experts), dim3(256), 0, s>>>(
+        (const T*)w, order, out, (PackRecord*)(packed + L.p_scale), L.D, F, Fp, KSp, KT, L.ND2, vec, L.h_shift);
+  };
+  images(w2, perm, packed + L.p_w2, L.E_res, L.F, L.Fp, L.Fpk);
+  if (L.n_shared > 0) images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT, L.F_shT, L.Fsk);
 }
 
 template <typename T, bool FULL>
 static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3, const void* sw2,
                               const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
   const dim3 block(256);
-  float* rec = (float*)(packed + L.p_scale);
   const int KS1 = L.Dk / kBK, C = PackTile<T>::COLS;
   // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
   // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
@@ -305,8 +384,8 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
   int32_t* inv = nullptr;
   if (perm) {
     inv = (int32_t*)(packed + L.p_w2);
-    const int64_t n = (int64_t)L.E_res * L.F;
-    invert_perm_kernel<<<dim3((unsigned)((n + 255) / 256)), block, 0, s>>>(perm, inv, L.F, n);
+    const hipError_t e = launch_invert_perm(L, perm, inv, &((PackRecord*)(packed + L.p_scale))->bad_perm, s);
+    if (e != hipSuccess) return e;
   }
   auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
   auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
@@ -319,58 +398,32 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
       pack_w13_padding_kernel<T, FULL><<<dim3((unsigned)blocks_of_256(total)), block, 0, s>>>(out, groups, Fp, NT1, KS1);
     }
   };
-  auto w2_images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {
-    const int KSp = Fpk / kBK, KT = F / Fp * KSp;
-    pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * KT), experts), block, 0, s>>>(
-        (const T*)w, order, out, rec, L.D, F, Fp, KSp, KT, L.ND2, L.D % PackTile<T>::V == 0 && aligned(w, w));
-  };
   w13(w1, w3, inv, packed + L.p_w13, L.E_res, L.F, L.Fp, L.P, L.NT1, 1);
-  w2_images(w2, perm, packed + L.p_w2, L.E_res, L.F, L.Fp, L.Fpk);
-  if (n_shared > 0) {
-    w13(sw1, sw3, nullptr, packed + L.p_sw13, n_shared, F_sh, L.F_shT, 1, L.NT1_sh, 0);
-    w2_images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT, L.F_shT, L.Fsk);
-  }
+  if (n_shared > 0) w13(sw1, sw3, nullptr, packed + L.p_sw13, n_shared, F_sh, L.F_shT, 1, L.NT1_sh, 0);
+  w2_images<T, FULL>(L, w2, sw2, perm, packed, s);
   return hipGetLastError();
 }
 
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
+  PackRecord* rec = (PackRecord*)(packed + L.p_scale);
+  const hipError_t e = launch_fill_i32((int32_t*)rec, sizeof(PackRecord) / 4, 0, s);
+  if (e != hipSuccess) return e;
   if (L.mfma) {
-    // the layer's W2 scale (see the layout comment at the top), from the largest |W2| of routed and shared experts
-    uint32_t* rec = (uint32_t*)(packed + L.p_scale);
-    hipError_t e0 = launch_fill_i32((int32_t*)rec, 4, 0, s);
-    if (e0 != hipSuccess) return e0;
-    absmax_bf16_kernel<<<dim3(2048), dim3(256), 0, s>>>((const uint16_t*)w2, (int64_t)L.E_res * L.F * L.D, rec);
-    if (n_shared > 0) absmax_bf16_kernel<<<dim3(512), dim3(256), 0, s>>>((const uint16_t*)sw2, (int64_t)L.F_shT * L.D, rec);
-    w2_scale_kernel<<<dim3(1), dim3(1), 0, s>>>(rec, L.h_shift);
+    const int64_t n = (int64_t)L.E_res * L.F * L.D, n_sh = (int64_t)L.F_shT * L.D;
+    launch_absmax(w2, n, absmax_stride(n), rec, s);
+    if (n_shared > 0) launch_absmax(sw2, n_sh, absmax_stride(n_sh), rec, s);
     return pack_images<uint16_t, false>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
   }
   if (L.dtype == DSMOE_F32) return pack_images<float, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
-  hipError_t e1 = launch_fill_i32((int32_t*)(packed + L.p_scale), 4, 0, s);
-  if (e1 != hipSuccess) return e1;
   return pack_images<uint16_t, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
 }
 
-// perm check: scratch[0 .. E_res*F) counts how often each neuron id is named (zeroed by the
-// caller), scratch[E_res*F] counts violations (out of range or named twice).
-__global__ void perm_check_kernel(Layout L, const int32_t* perm, int32_t* scratch) {
-  const int64_t n = (int64_t)L.E_res * L.F;
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= n) return;
-  const int e = (int)(q / L.F);
-  const int v = perm[q];
-  if (v < 0 || v >= L.F) {
-    atomicAdd(&scratch[n], 1);
-  } else if (atomicAdd(&scratch[(size_t)e * L.F + v], 1) != 0) {
-    atomicAdd(&scratch[n], 1);
-  }
-}
-
-hipError_t launch_perm_check(const Layout& L, const int32_t* perm, int32_t* scratch, hipStream_t s) {
-  const int64_t n = (int64_t)L.E_res * L.F;
-  hipError_t err = launch_fill_i32(scratch, n + 1, 0, s);
-  if (err != hipSuccess) return err;
-  perm_check_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(L, perm, scratch);
+hipError_t launch_repack_w2(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s) {
+  PackRecord* rec = (PackRecord*)(packed + L.p_scale);
+  launch_absmax(w2, (int64_t)L.E_res * L.F * L.D, 1, rec, s);
+  if (L.n_shared > 0) launch_absmax(sw2, (int64_t)L.F_shT * L.D, 1, rec, s);
+  w2_images<uint16_t, false>(L, w2, sw2, perm, packed, s);
   return hipGetLastError();
 }
 

@@ -1372,7 +1372,7 @@ __global__ __launch_bounds__(256) void combine_scalar_kernel(Layout L, int T, co
 
 hipError_t launch_combine(const Layout& L, int T, const char* packed, char* ws, void* y, hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  const float* w2_inv = L.mfma ? (const float*)(packed + L.p_scale) + 2 : nullptr;
+  const float* w2_inv = L.mfma ? &((const PackRecord*)(packed + L.p_scale))->unscale : nullptr;
   const int DV = L.D / (L.yp_half ? 8 : 4);
   if (L.D % 4 == 0 && (int64_t)T * DV <= kSlotThreads) {
     const int slots = L.K + (L.n_shared > 0 ? 1 : 0);

@@ -1,0 +1,91 @@
+"""The power of two that moe_partition_weights gives the packed W2 comes from a sample of it (every third run of 2048 values at this
+size): weights that only the rest of W2 has, and permutations that are none, on the matrix-core path.
+
+Bar: W2 is exact in half precision from 2^-29 of the scale's binade up, so the outputs differ from float64 by the rounding of H and of
+the partial outputs (2^-11 of the value each) and the fp32 sums: below 2e-3 of the output's RMS where many terms of like size are
+added, as for any other layer, and up to 2^-10 of the value itself where one term (an outlier weight) carries the sum.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+E, F, D, T = 2, 8192, 2048, 16  # E * F * D = 2^25: the smallest that is sampled
+RUN = 2048
+
+
+def _layer():
+    from paper_2508_18376_amd import DualSparseLayer
+    return DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=E, n_part=2, max_tokens=T, dtype="bf16", y_fp32=True)
+
+
+@pytest.mark.parametrize("kind", ["even", "within_a_binade", "outlier", "outlier_and_infinity", "sample_of_zeros", "all_zero", "last_run"])
+def test_w2_values_that_the_sample_misses(kind):
+    import torch
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda:0").mul_(0.02).bfloat16()
+
+    w1, w3, w2 = normal(E, D, F), normal(E, D, F), normal(E, F, D)
+    runs = w2.view(-1, RUN)
+    if kind == "within_a_binade":
+        runs[1, 7] = 2.0 * float(w2.abs().max())
+    elif kind in ("outlier", "outlier_and_infinity"):
+        runs[1, 7] = 40.0
+    elif kind == "sample_of_zeros":
+        runs[0::3] = 0
+    elif kind == "all_zero":
+        w2.zero_()
+    elif kind == "last_run":  # 16384 runs: the last one is in the sample, the one before is not
+        runs[-2] *= 256.0
+    if kind == "outlier_and_infinity":
+        runs[4, 9] = float("inf")
+    x = torch.randn(T, D, generator=gen, device="cuda:0").bfloat16()
+    logits = torch.randn(T, E, generator=gen, device="cuda:0")
+    layer = _layer()
+    layer.partition_weights(w1, w3, w2)
+    y = layer.forward(x, logits, torch.zeros(E, 2, device="cuda:0")).double().cpu()
+    g = torch.softmax(logits.double().cpu(), dim=1)
+    ref = torch.zeros(T, D, dtype=torch.float64)
+    xd = x.double().cpu()
+    for e in range(E):
+        a = xd @ w1[e].double().cpu()
+        h = a * torch.sigmoid(a) * (xd @ w3[e].double().cpu())
+        ref += g[:, e:e + 1] * (h @ w2[e].double().cpu())
+    good = torch.isfinite(ref)
+    if kind == "outlier_and_infinity":  # the one column of the infinite weight (half-precision partial outputs saturate)
+        good = torch.ones_like(good)
+        good[:, 9] = False
+    assert torch.isfinite(y[good]).all()
+    rms = ref[good].square().mean().sqrt()
+    assert ((y - ref).abs() <= 2e-3 * rms + 2.0 ** -10 * ref.abs())[good].all()
+    layer.close()
+
+
+@pytest.mark.parametrize("D_,F_", [(128, 256), (96, 120)])  # matrix-core and full-precision path
+@pytest.mark.parametrize("kind", ["twice", "beyond", "negative", "other_expert"])
+def test_bad_permutation_of_a_bf16_layer_is_rejected(D_, F_, kind):
+    import torch
+    from paper_2508_18376_amd import DsmoeError, DualSparseLayer
+    layer = DualSparseLayer(d_model=D_, d_ff=F_, n_experts=3, top_k=1, n_part=2, max_tokens=8, dtype="bf16")
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    w1, w3, w2 = (torch.randn(s, generator=gen, device="cuda:0").bfloat16() for s in ((3, D_, F_), (3, D_, F_), (3, F_, D_)))
+    good = torch.rand(3, F_, generator=gen, device="cuda:0").argsort(dim=1).to(torch.int32)
+    x, logits, tau = torch.randn(8, D_, generator=gen, device="cuda:0").bfloat16(), torch.randn(8, 3, generator=gen, device="cuda:0"), torch.zeros(3, 2, device="cuda:0")
+    layer.partition_weights(w1, w3, w2, perm=good)
+    y = layer.forward(x, logits, tau).clone()
+    bad = good.clone()
+    if kind == "twice":
+        bad[2, F_ - 1] = bad[2, 0]
+    elif kind == "beyond":
+        bad[0, 5] = F_
+    elif kind == "negative":
+        bad[1, 0] = -1
+    else:
+        bad[1] += F_
+    with pytest.raises(DsmoeError) as ei:
+        layer.partition_weights(w1, w3, w2, perm=bad)
+    assert ei.value.status == -2
+    layer.partition_weights(w1, w3, w2, perm=good)
+    assert torch.equal(layer.forward(x, logits, tau), y)
+    layer.close()
