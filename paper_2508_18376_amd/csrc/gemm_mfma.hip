@@ -56,6 +56,16 @@ struct Ring {
   static constexpr int NS = NS_, SB = SB_, BOFF = BOFF_, BYTES = NS_ * SB_;
 };
 using RingWhole = Ring<kStages, kStagePair, kStageBytes>;  // 16 KiB A tile + 16 KiB B tile
+// Ragged tiles: 16 KiB of weights + only the 64-row groups that exist, and as many such stages as the allocation holds (7, 6, 5, 4).
+// A unit with one short tile streams weights only as fast as it has them in flight: with four slots of 32 KiB, of which three
+// stages of 20 KiB were, 333 tokens on 64 + 2 experts of 2048 x 1408 took 247.2 us, with six of seven 243.5 (GEMM-1 143 -> 139, GEMM-2
+// 81 -> 78).
+constexpr int ragged_stage(int rows) { return kStageBytes + (rows + 63) / 64 * 64 * (kBK * 2); }
+constexpr int ragged_depth(int rows) { return kLdsBytes / ragged_stage(rows) < 8 ? kLdsBytes / ragged_stage(rows) : 8; }
+template <int ROWS>
+using RingRagged = Ring<ragged_depth(ROWS), ragged_stage(ROWS), kStageBytes>;
+template <int ROWS>
+using RingRagged2 = Ring<ragged_depth(ROWS), ragged_stage(ROWS), ragged_stage(ROWS) - kStageBytes>;  // GEMM-2: the rows first
 // half-tile items of GEMM-1 (at most 128 rows): 8 KiB of weights + 8 KiB of rows, twice as deep
 using RingHalf = Ring<8, kStageBytes, kStageBytes / 2>;
 static_assert(RingHalf::BYTES <= kLdsBytes, "same allocation");
@@ -592,7 +602,7 @@ __device__ __forceinline__ void gemm1_half_item(const G1Args& g, char* lds, int 
 // a ragged row tile.  4 x 1 wavefronts: 64 weight rows x the ceil(nrows/32) blocks of pair rows that exist
 template <bool PROFILE, bool ONCE>
 __device__ __forceinline__ void gemm1_ragged_item(const G1Args& g, char* lds, int w) {
-#define DSMOE_RAGGED(N) gemm1_tile<2, 8, N, PROFILE, 4, false, RingWhole, (N * 32 + 63) / 64, false, ONCE>(g, lds, w * 64, 0, w)
+#define DSMOE_RAGGED(N) gemm1_tile<2, 8, N, PROFILE, 4, false, RingRagged<N * 32>, (N * 32 + 63) / 64, false, ONCE>(g, lds, w * 64, 0, w)
   switch ((g.it.nrows + 31) >> 5) {
     case 1: DSMOE_RAGGED(1); break;
     case 2: DSMOE_RAGGED(2); break;
@@ -817,7 +827,7 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
 // a ragged row tile.  1 x 4 wavefronts: the ceil(nrows/32) blocks of pair rows that exist x 64 columns
 template <bool NT, bool YH, bool ONCE>
 __device__ __forceinline__ void gemm2_ragged_item(const G2Args& g, char* lds, int w) {
-#define DSMOE_RAGGED(N) gemm2_tile<8, 2, N, NT, YH, RingWhole, false, ONCE>(g, lds, 0, w * 64, w)
+#define DSMOE_RAGGED(N) gemm2_tile<8, 2, N, NT, YH, RingRagged2<N * 32>, false, ONCE>(g, lds, 0, w * 64, w)
   switch ((g.it.nrows + 31) >> 5) {
     case 1: DSMOE_RAGGED(1); break;
     case 2: DSMOE_RAGGED(2); break;
