@@ -15,8 +15,8 @@
 //   W2   stage (e*ND2 + jd)*(F/32) + kt : 256 output columns x 32 neurons (positions kt*32..),
 //        as IEEE half precision times 2^s (GEMM-2 multiplies half-precision operands: its left
 //        operand, the intermediate activation, needs more significant bits than bf16 has).  s is
-//        chosen per layer so that the largest |W2| of a sample lands in [2^14, 2^15) (all of a W2 of up to 32 M values;
-//        otherwise every 3rd to 31st run of 2048): every bf16 value within a factor 2^-29 of that is then exactly
+//        chosen per layer so that the largest |W2| of a sample lands in [2^14, 2^15) (all of a W2 of up to 16 M values;
+//        otherwise every 3rd to 63rd run of 2048): every bf16 value within a factor 2^-29 of that is then exactly
 //        representable (smaller ones round to the subnormal grid, 2^-39 of it).  A layer with a larger |W2| that no longer
 //        fits half precision is packed again from the largest of all.  The combine kernel multiplies by 2^-s, exactly.
 //        The record (PackRecord) sits at p_scale.
@@ -35,8 +35,9 @@ __device__ __forceinline__ uint4 load_once(const void* p) {  // non-temporal
 
 // largest finite |w| of a bf16 tensor, as its bit pattern (monotone in the value), into *out: of every stride-th run of 2048
 // values.  Bound by HBM: four runs in flight per workgroup, non-temporal, and one atomic per workgroup (all on one address).
-// 0.94 GB, all of it: 160 us (with plain loads and an atomic per wavefront 205); a sample of 16 M values 11 us.
-constexpr int kAbsmaxRun = 2048, kAbsmaxBlocks = 2048;
+// 0.94 GB, all of it: 160 us (with plain loads and an atomic per wavefront 205); of it a sample of 16 M values 27 us (the atomics of
+// 2048 workgroups), of 8 M values by 512 workgroups 10 us.
+constexpr int kAbsmaxRun = 2048;
 __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int64_t n, int stride, uint32_t* out) {
   uint32_t m = 0;
   auto one = [&](uint32_t a) { m = a < 0x7f80u && a > m ? a : m; };
@@ -73,17 +74,18 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
   }
 }
 static void launch_absmax(const void* w, int64_t n, int stride, PackRecord* rec, hipStream_t s) {
+  const int most = stride == 1 && n > (int64_t)1 << 26 ? 2048 : 512;
   const int64_t runs = (n + (int64_t)stride * kAbsmaxRun - 1) / ((int64_t)stride * kAbsmaxRun);
-  const int blocks = (int)(runs < kAbsmaxBlocks ? runs : kAbsmaxBlocks);
+  const int blocks = (int)(runs < most ? runs : most);
   absmax_bf16_kernel<<<dim3(blocks), dim3(256), 0, s>>>((const uint16_t*)w, n, stride, &rec->largest);
 }
-// The scale is needed before the first value is packed, and finding the largest of all |W2| reads W2 once more (a sixth of
-// the packing of 8 experts of 4096 x 14336, which took 1.52 ms with it and takes 1.34 without).  A sample of 16 to 32 M values tells its
+// The scale is needed before the first value is packed, and finding the largest of all |W2| reads W2 once more (a tenth
+// of the packing of 8 experts of 4096 x 14336, which took 1.52 ms with it and takes 1.36 without).  A sample of 8 to 16 M values tells its
 // binade as well as that binade and the next have room for: only a W2 whose largest value is more than twice (for some, four
 // times) the sample's largest is packed twice.  Odd strides: a row of a power of two of values is met in all of its columns.
 static int absmax_stride(int64_t n) {
-  const int64_t k = n >> 24;
-  return k < 2 ? 1 : k > 31 ? 31 : (int)(k | 1);
+  const int64_t k = n >> 23;
+  return k < 2 ? 1 : k > 63 ? 63 : (int)(k | 1);
 }
 
 // largest |W2| bits -> s with largest * 2^s in [2^14, 2^15)
