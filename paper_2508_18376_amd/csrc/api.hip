@@ -377,13 +377,16 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
     if (err == hipSuccess) err = (call); \
   } while (0)
   mark(0);
-  if (router_packed && err == hipSuccess) err = launch_router(L, T, router_packed, x, const_cast<float*>(logits_buf), s);
+  const bool routed = router_packed && !small_plan(L, T) && router_routes(L, T);
+  if (err == hipSuccess && routed) err = launch_router_route(L, T, router_packed, x, const_cast<float*>(logits_buf), tau, ws, s);
+  else if (err == hipSuccess && router_packed) err = launch_router(L, T, router_packed, x, const_cast<float*>(logits_buf), s);
   if (small_plan(L, T)) {
     DSMOE_STEP(1, launch_small_plan(L, T, logits, tau, ws, s));
     mark(2);
     mark(3);
   } else {
-    DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
+    if (routed) mark(1);
+    else DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
                                (int32_t*)(ws + L.o_bin_count), nullptr, s));
     DSMOE_STEP(2, launch_plan(L, T, ws, s));
     mark(3);

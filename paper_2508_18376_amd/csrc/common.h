@@ -200,6 +200,10 @@ hipError_t launch_gemm1_mfma(const Layout& L, int T, const char* packed, const v
 hipError_t launch_select_thresholds(const Layout& L, int T, const float* logits, const float* tau_max, int group_size, int row_cap, char* ws,
                                     float* tau, int32_t* pair_count, hipStream_t s);
 hipError_t launch_router_pack(const Layout& L, const void* wg, char* out, hipStream_t s);
+// the router product and the routing of its batch in one launch, where router_routes() says so
+bool router_routes(const Layout& L, int T);
+hipError_t launch_router_route(const Layout& L, int T, const char* router_packed, const void* x, float* logits, const float* tau, char* ws,
+                               hipStream_t s);
 hipError_t launch_router(const Layout& L, int T, const char* router_packed, const void* x, float* logits, hipStream_t s);
 hipError_t launch_transform_complete(const Layout& L, const void* wg, const void* w1, const void* w3, const void* w2,
                                      const int32_t* perm, void* wg_out, void* w1_out, void* w3_out, void* w2_out,

@@ -6,7 +6,7 @@
 // 1 KiB contiguous per operand.  x comes straight from memory in operand order too: with 16 x 16 blocks four lanes
 // cover 64 contiguous bytes of a token (32 x 32 blocks would touch 64 separate 16-byte pieces per load, which the
 // address units take one by one).
-#include "common.h"
+#include "route.h"
 
 namespace dsmoe {
 
@@ -47,11 +47,18 @@ __global__ void router_pack_generic_kernel(const T* __restrict__ wg, float* __re
 // Workgroup = MT * 16 tokens x (NT tiles of 16 experts); its W wavefronts take every W-th 64-step of the
 // contraction (enough loads in flight to stream x at HBM rate even for a few thousand tokens) and
 // add their partial tiles through LDS in a fixed order, so results are reproducible bit for bit.
+// ROUTE: the workgroup's logits (all E experts are in it) stay in LDS and are routed there, one histogram row per workgroup, as
+// route_row_kernel would: a launch and a round trip through memory less.
 // Measured: 1 token x 2048 x 64 experts 7.1 -> 4.2 us, 64 x 4096 x 8 16.5 -> 9, 333 x 2048 x 64 12.2 -> 7.2, 8192 x 2048 x 64 20.6 -> 18.
-template <int NT, int W, int MT>
+template <int NT, int W, int MT, bool ROUTE>
 __global__ __launch_bounds__(W * 64) void router_mfma_kernel(const uint16_t* __restrict__ x, const uint4* __restrict__ wgp,
-                                                             float* __restrict__ logits, int T, int D, int E, int NT_all) {
+                                                             float* __restrict__ logits, int T, int D, int E, int NT_all, RouteArgs ra) {
   extern __shared__ float part[];  // [W][MT][NT][4][64]: wavefront, 16 tokens, tile, accumulator register, lane
+  float* rows = part + W * MT * NT * 256;                    // ROUTE: [16][E] logits,
+  int32_t* hist = (int32_t*)(rows + 16 * NT * 16);           // the histogram
+  float* tau_l = (float*)(hist + ra.nhist);                  // and the threshold table
+  static_assert(!ROUTE || (MT == 1 && MT * 16 == kWaveBlockTokens), "one histogram row for 16 tokens");
+  if (ROUTE) route_row_setup(ra, hist, tau_l, W * 64);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int t0 = blockIdx.x * (MT * 16);
   const int nt0 = blockIdx.y * NT;
@@ -114,7 +121,16 @@ __global__ __launch_bounds__(W * 64) void router_mfma_kernel(const uint16_t* __r
     for (int ww = 0; ww < W; ++ww) sum += part[(((ww * MT + i) * NT + j) * 4 + v) * 64 + l];
     const int e = (nt0 + j) * 16 + (l & 15);
     const int t = t0 + 16 * i + 4 * (l >> 4) + v;
-    if (nt0 + j < NT_all && e < E && t < T) logits[(size_t)t * E + e] = sum;
+    if (nt0 + j < NT_all && e < E && t < T) {
+      logits[(size_t)t * E + e] = sum;
+      if (ROUTE) rows[(t - t0) * E + e] = sum;
+    }
+  }
+  if constexpr (ROUTE) {
+    __syncthreads();
+    route_row_tokens<(NT + 3) / 4, 1, W, kRoute>(ra, rows, t0, min(T, t0 + 16), hist, tau_l, nullptr);
+    __syncthreads();
+    flush_hist(ra, hist, W * 64);
   }
 }
 
@@ -161,20 +177,43 @@ hipError_t launch_router_pack(const Layout& L, const void* wg, char* out, hipStr
   return hipGetLastError();
 }
 
-template <int NT, int W, int MT>
-static hipError_t launch_router_tokens(const Layout& L, int T, const uint4* wgp, const void* x, float* logits, int NT_all, hipStream_t s) {
-  constexpr int lds = W * MT * NT * 4 * 64 * 4;
+template <int NT, int W, int MT, bool ROUTE>
+static hipError_t launch_router_tokens(const Layout& L, int T, const uint4* wgp, const void* x, float* logits, int NT_all, const RouteArgs& ra, hipStream_t s) {
+  constexpr int lds = W * MT * NT * 4 * 64 * 4, most = lds + (ROUTE ? 16 * NT * 16 * 4 + NT * 16 * ((1 << kSubBits) + kMaxPart) * 4 : 0);
   static PerDeviceOnce once;  // one per instantiation
-  hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)router_mfma_kernel<NT, W, MT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); });
+  hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)router_mfma_kernel<NT, W, MT, ROUTE>, hipFuncAttributeMaxDynamicSharedMemorySize, most); });
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)((T + MT * 16 - 1) / (MT * 16)), (unsigned)((NT_all + NT - 1) / NT));
-  router_mfma_kernel<NT, W, MT><<<grid, dim3(W * 64), lds, s>>>((const uint16_t*)x, wgp, logits, T, L.D, L.E, NT_all);
+  router_mfma_kernel<NT, W, MT, ROUTE><<<grid, dim3(W * 64), most, s>>>((const uint16_t*)x, wgp, logits, T, L.D, L.E, NT_all, ra);
   return hipGetLastError();
 }
 template <int NT, int W>
 static hipError_t launch_router_mfma(const Layout& L, int T, const uint4* wgp, const void* x, float* logits, int NT_all, hipStream_t s) {
-  if (T <= kRouterFewTokens) return launch_router_tokens<NT, W, 1>(L, T, wgp, x, logits, NT_all, s);
-  return launch_router_tokens<NT, W, 2>(L, T, wgp, x, logits, NT_all, s);
+  if (T <= kRouterFewTokens) return launch_router_tokens<NT, W, 1, false>(L, T, wgp, x, logits, NT_all, RouteArgs{}, s);
+  return launch_router_tokens<NT, W, 2, false>(L, T, wgp, x, logits, NT_all, RouteArgs{}, s);
+}
+
+// Batches whose routing goes with the router product: those that route_row_kernel routes in blocks of the 16 tokens that a
+// router workgroup has, if that workgroup sees all experts.  (Up to 32 experts routing takes a lane per token instead; beyond 128 an
+// expert group each has its own workgroup; larger batches count 64 tokens to a histogram row, so that the plan has fewer rows to add.)
+// 333 tokens on 64 + 2 experts of 2048 x 1408: 242.7 us in two launches, 238.9 in one.
+bool router_routes(const Layout& L, int T) { return L.router_mfma && L.E > 32 && L.E <= 128 && T <= kWaveSmallBatch; }
+
+hipError_t launch_router_route(const Layout& L, int T, const char* router_packed, const void* x, float* logits, const float* tau, char* ws,
+                               hipStream_t s) {
+  if (T <= 0) return hipSuccess;
+  RouteArgs a = {};
+  a.tau = tau;
+  a.idx = (int32_t*)(ws + L.o_idx);
+  a.w = (float*)(ws + L.o_w);
+  a.keep = (uint8_t*)(ws + L.o_keep);
+  a.bin_count = (int32_t*)(ws + L.o_bin_count);
+  a.T = T;
+  set_route_layer(L, a);
+  const uint4* wgp = (const uint4*)router_packed;
+  const int NT = (L.E + 31) / 32 * 2;
+  if (NT == 4) return launch_router_tokens<4, 16, 1, true>(L, T, wgp, x, logits, NT, a, s);
+  return launch_router_tokens<8, 8, 1, true>(L, T, wgp, x, logits, NT, a, s);
 }
 
 hipError_t launch_router(const Layout& L, int T, const char* router_packed, const void* x, float* logits, hipStream_t s) {
