@@ -169,8 +169,8 @@ __device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
 }
 
 // Some of the eight bf16 values `raw` is too large for the scale of a sample whose largest bits were `sampled`: finite, but
-// infinite as scaled half precision; or not zero where the whole sample was.  (Values beyond every scale stay infinite, as they
-// are when the scale is that of the largest.)
+// infinite as scaled half precision; or normal where the whole sample was zero or subnormal, which says nothing about the scale.  (Values
+// beyond every scale stay infinite, as they are when the scale is that of the largest.)
 __device__ __forceinline__ bool misses(uint4 raw, uint4 half, uint32_t sampled) {
   typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
   const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w}, h[4] = {half.x, half.y, half.z, half.w};
@@ -179,9 +179,9 @@ __device__ __forceinline__ bool misses(uint4 raw, uint4 half, uint32_t sampled) 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, h[i] & 0x7fff7fffu));
-    any |= r[i] & 0x7fff7fffu;
+    any |= r[i] & 0x7f807f80u;  // exponents
   }
-  bool miss = sampled == 0 && any != 0;
+  bool miss = sampled < 0x80u && any != 0;
   if (m.x >= 0x7c00u || m.y >= 0x7c00u) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {

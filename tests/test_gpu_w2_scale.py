@@ -18,7 +18,7 @@ def _layer():
     return DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=E, n_part=2, max_tokens=T, dtype="bf16", y_fp32=True)
 
 
-@pytest.mark.parametrize("kind", ["even", "within_a_binade", "outlier", "outlier_and_infinity", "sample_of_zeros", "all_zero", "last_run"])
+@pytest.mark.parametrize("kind", ["even", "within_a_binade", "outlier", "outlier_and_infinity", "sample_of_zeros", "all_zero", "last_run", "sample_of_subnormals"])
 def test_w2_values_that_the_sample_misses(kind):
     import torch
     gen = torch.Generator(device="cuda:0").manual_seed(5)
@@ -34,6 +34,9 @@ def test_w2_values_that_the_sample_misses(kind):
         runs[1, 7] = 40.0
     elif kind == "sample_of_zeros":
         runs[0::5] = 0
+    elif kind == "sample_of_subnormals":
+        w2.mul_(5e-5)  # the rest: 1e-6
+        runs[0::5] = 1e-39
     elif kind == "all_zero":
         w2.zero_()
     elif kind == "last_run":  # 16384 runs: the last one is not in the sample
