@@ -20,8 +20,9 @@ constexpr int kPoolRows = 256 + kTallExtra;  // rows of a partial-output tile of
 constexpr int kSplitRowsOffset = 1 << 30;    // flag in the (row tile, column tile) -> pool tile table: the tile's rows sit kMfmaBM rows down
 constexpr int kMaxTailSplit = 8;  // most K ranges an item of the last, partly filled round of items is split into
 constexpr int kPoolTiles = 768;   // partial-output tiles (256 x 256) the extra K ranges can need at most
-// Half-precision partial outputs hold the GEMM-2 accumulators times 2^-10.  The accumulators are sums
-// over the kept neurons of (activation x 2^k) x (W2 x 2^s) with the largest |W2 x 2^s| in [2^14, 2^15):
+// Half-precision partial outputs hold the sums of GEMM-2 times 2^-10.  These are sums
+// over the kept neurons of (activation x 2^k) x (W2 x 2^S) with the largest |W2 x 2^S| in [2^14, 2^15) (the images of W2 may
+// carry another power of two, see PackRecord):
 // for activations of order one they are of order sqrt(neurons) x 5000, i.e. 1e2 .. 1e3 after the
 // scaling, with a factor 60 and more up to half precision's largest value and seven decades down to its
 // smallest normal one, whatever the scale of the weights (and, through cfg.h_scale_log2, of the activations).
@@ -69,11 +70,13 @@ struct Item2 {  // one tile of GEMM-2: rows x output column tile jd, summed over
 
 // What packing leaves beside the weights (32 bytes at Layout::p_scale, cleared before it).
 struct PackRecord {
-  uint32_t largest;  // MFMA layout: bits of the largest |W2| that the scale was taken from; full-precision layout of bf16: 1 if W2 has an infinity or NaN
-  float scale, unscale;  // MFMA layout: 2^s that the images of W2 carry; 2^-(s + h_shift), which the combine kernel applies
+  uint32_t largest;  // MFMA layout: bits of the largest |W2| that the scale 2^s of the images was taken from; full-precision layout of bf16: 1 if W2 has an infinity or NaN
+  int32_t beyond;    // MFMA layout: (biased) exponent of the largest |W2| of all, if that is of a higher binade; else 0
+  float yscale;      // MFMA layout: 2^(S - s), S being the scale that the largest |W2| of all gives: GEMM-2's partial outputs carry 2^S, so that their range does not hang on s
+  float unscale;     // MFMA layout: 2^-(S + h_shift), which the combine kernel applies
   int32_t repack;    // a weight does not fit half precision at this scale
   int32_t bad_perm;
-  int32_t pad[3];
+  int32_t pad[2];
 };
 
 // Everything the device code needs to know about the layer and the workspace.

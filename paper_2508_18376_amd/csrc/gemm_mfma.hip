@@ -653,7 +653,7 @@ struct G2Args {
   uint32_t lds_w, h_tile_bytes;  // h_tile_bytes: a row tile of H
   char* Y;       // where row 0, column 0 of this item's output tile goes (float, or half precision: YH)
   int ldy;       // its row stride in elements: D in Yp, 256 in a pool tile
-  float yscale;  // YH: the accumulators are stored times this power of two (see kYpHalfScale)
+  float yscale;  // the accumulators are stored times this power of two (see PackRecord) and, YH, kYpHalfScale
   int col0;      // first column of this workgroup's part of the item's column tile
   bool once;     // the expert has one row tile: nobody else reads this part of W2
 };
@@ -706,6 +706,7 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
     else dma16(g.rsH, slot + (q - NW) * 4096, hoff[q - NW], sH);
   };
   t.mainloop(g.nstages, begin, one, lds);
+  const float yscale = YH ? g.yscale * kYpHalfScale : g.yscale;
   tid = fresh_tid(w);  // see gemm1_tile: the epilogue's addresses are worked out after the main loop
   const int le = tid & 63;
 
@@ -732,10 +733,10 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
 #pragma unroll
       for (int vq = 0; vq < 4; ++vq) {
         char* at = mine + (le & 31) * kYsRow + (jc * 32 + vq * 8 + (le >> 5) * 4) * kEl;
-        if constexpr (YH) {  // times 2^-10, saturating, round to nearest even
+        if constexpr (YH) {  // saturating, round to nearest even
           float v[4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_fmed3f(A[j][vq * 4 + c] * g.yscale, -kHalfMax, kHalfMax);
+          for (int c = 0; c < 4; ++c) v[c] = __builtin_amdgcn_fmed3f(A[j][vq * 4 + c] * yscale, -kHalfMax, kHalfMax);
           f16x2 lo, hi;
           lo[0] = (_Float16)v[0], lo[1] = (_Float16)v[1], hi[0] = (_Float16)v[2], hi[1] = (_Float16)v[3];
           uint2 pk;
@@ -744,10 +745,10 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
           *(uint2*)at = pk;
         } else {
           f32x4_t o;
-          o.x = A[j][vq * 4 + 0];
-          o.y = A[j][vq * 4 + 1];
-          o.z = A[j][vq * 4 + 2];
-          o.w = A[j][vq * 4 + 3];
+          o.x = A[j][vq * 4 + 0] * yscale;
+          o.y = A[j][vq * 4 + 1] * yscale;
+          o.z = A[j][vq * 4 + 2] * yscale;
+          o.w = A[j][vq * 4 + 3] * yscale;
           *(f32x4_t*)at = o;
         }
       }
@@ -816,12 +817,13 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
     g.Y = ws + L.o_pool + (size_t)(g.it.split - 1) * kPoolRows * kMfmaBN2 * yel;
     g.ldy = kMfmaBN2;
   }
-  g.yscale = kYpHalfScale;
+  g.yscale = ((const __attribute__((address_space(4))) PackRecord*)(uintptr_t)(packed + L.p_scale))->yscale;  // (constant memory: a scalar load)
   g.col0 = 0;
 
   g.lds_w = lds_offset(lds) + (uint32_t)(w * 1024);
   g.nstages = 0;
   for (int p = 0; p < g.np; ++p) g.nstages += ((g.it.kmask >> p) & 1) ? g.it.ks_n : 0;
+  asm volatile("" : "+s"(g.yscale));  // arrives here, with the other scalars: a scalar load still under way in the main loop would be waited for with its LDS reads
 }
 
 // a ragged row tile.  1 x 4 wavefronts: the ceil(nrows/32) blocks of pair rows that exist x 64 columns

@@ -168,29 +168,26 @@ __device__ __forceinline__ uint4 map_halves(uint4 v, Op op) {
   return v;
 }
 
-// Some of the eight bf16 values `raw` is too large for the scale of a sample whose largest bits were `sampled`: finite, but
-// infinite as scaled half precision; or normal where the whole sample was zero or subnormal, which says nothing about the scale.  (Values
-// beyond every scale stay infinite, as they are when the scale is that of the largest.)
-__device__ __forceinline__ bool misses(uint4 raw, uint4 half, uint32_t sampled) {
+// The largest finite one of eight bf16 values, as its bits, if it is of a higher binade than `sampled`, the largest of the sample (or normal
+// where all of the sample is zero or subnormal); else 0.
+__device__ __forceinline__ uint32_t beyond_sample(uint4 raw, uint32_t sampled) {
   typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-  const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w}, h[4] = {half.x, half.y, half.z, half.w};
-  u16x2 m = {0, 0};  // largest |half|
-  uint32_t any = 0;
+  const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w}, binade = sampled | 0x7fu;
+  u16x2 m = {0, 0};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, h[i] & 0x7fff7fffu));
-    any |= r[i] & 0x7f807f80u;  // exponents
-  }
-  bool miss = sampled < 0x80u && any != 0;
-  if (m.x >= 0x7c00u || m.y >= 0x7c00u) {
+  for (int i = 0; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, r[i] & 0x7fff7fffu));
+  uint32_t most = 0;
+  if (m.x > binade || m.y > binade) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const uint32_t a = r[i >> 1] >> (16 * (i & 1)) & 0x7fffu, b = h[i >> 1] >> (16 * (i & 1)) & 0x7fffu;
-      miss |= a < 0x7f80u && b == 0x7c00u;
+      const uint32_t a = r[i >> 1] >> (16 * (i & 1)) & 0x7fffu;
+      if (a > binade && a < 0x7f80u) most = max(most, a);
     }
   }
-  return miss;
+  return most;
 }
+// the largest exponent that fits half precision at the scale of the sample; 0: a sample that is zero or subnormal sets no scale
+__device__ __forceinline__ int w2_room(uint32_t sampled) { return sampled < 0x80u ? 0 : 142 - w2_shift(sampled); }
 
 // some of the eight bf16 values is infinite or NaN
 __device__ __forceinline__ bool not_finite(uint4 v) {
@@ -262,7 +259,7 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
 // of 128 columns.  w2: [experts][P * Fp][D]; KSp: stages of a partition, KT: of the expert, nd: column tiles of the images.
 template <typename T, bool FULL>
 __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, PackRecord* rec, int D, int F, int Fp,
-                                                      int KSp, int KT, int nd, int vec, int h_shift) {
+                                                      int KSp, int KT, int nd, int vec) {
   using PT = PackTile<T>;
   constexpr int BN = FULL ? kFullBN2 : kMfmaBN2, RB = kBK * sizeof(T);
   __shared__ PT t;
@@ -272,12 +269,7 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
   uint32_t sampled = 0;  // largest |W2| of the sample
   if (!FULL) {
     sampled = rec->largest;
-    const int sh = w2_shift(sampled);
-    scale = __uint_as_float((uint32_t)(127 + sh) << 23);
-    if ((blockIdx.x | blockIdx.y | tid) == 0) {
-      rec->scale = scale;
-      rec->unscale = __uint_as_float((uint32_t)(127 - sh - h_shift) << 23);  // undoes 2^s of W2 and 2^h_shift of W3
-    }
+    scale = __uint_as_float((uint32_t)(127 + w2_shift(sampled)) << 23);
   }
   uint4 a[4];
 #pragma unroll
@@ -293,9 +285,11 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     if constexpr (!FULL) {
-      const uint4 raw = a[u];
-      a[u] = map_halves(raw, [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
-      if (misses(raw, a[u], sampled)) rec->repack = 1;
+      if (const uint32_t most = beyond_sample(a[u], sampled)) {
+        atomicMax(&rec->beyond, (int)(most >> 7));
+        if ((int)(most >> 7) > w2_room(sampled)) rec->repack = 1;
+      }
+      a[u] = map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
     }
     if (FULL && sizeof(T) == 2 && not_finite(a[u])) rec->largest = 1;
     t.put(u * 8 + (tid >> 5), tid & 31, a[u]);
@@ -363,16 +357,24 @@ hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv
   return hipGetLastError();
 }
 
+// the powers of two that GEMM-2 and the combine kernel apply, once all of W2 has been looked at
+__global__ void w2_record_kernel(PackRecord* rec, int h_shift) {
+  const int packed = w2_shift(rec->largest), all = rec->beyond ? w2_shift((uint32_t)rec->beyond << 7) : packed;
+  rec->yscale = ldexpf(1.f, all - packed);
+  rec->unscale = ldexpf(1.f, -all - h_shift);
+}
+
 template <typename T, bool FULL>
 static void w2_images(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s) {
   auto images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {
     const int KSp = Fpk / kBK, KT = F / Fp * KSp, C = PackTile<T>::COLS;
     const int vec = L.D % PackTile<T>::V == 0 && ((uintptr_t)w & 15) == 0;
     pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * KT), experts), dim3(256), 0, s>>>(
-        (const T*)w, order, out, (PackRecord*)(packed + L.p_scale), L.D, F, Fp, KSp, KT, L.ND2, vec, L.h_shift);
+        (const T*)w, order, out, (PackRecord*)(packed + L.p_scale), L.D, F, Fp, KSp, KT, L.ND2, vec);
   };
   images(w2, perm, packed + L.p_w2, L.E_res, L.F, L.Fp, L.Fpk);
   if (L.n_shared > 0) images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT, L.F_shT, L.Fsk);
+  if (!FULL) w2_record_kernel<<<dim3(1), dim3(1), 0, s>>>((PackRecord*)(packed + L.p_scale), L.h_shift);
 }
 
 template <typename T, bool FULL>

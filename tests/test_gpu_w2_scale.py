@@ -5,6 +5,8 @@ Bar: W2 is exact in half precision from 2^-29 of the scale's binade up, so the o
 the partial outputs (2^-11 of the value each) and the fp32 sums: below 2e-3 of the output's RMS where many terms of like size are
 added, as for any other layer, and up to 2^-10 of the value itself where one term (an outlier weight) carries the sum.
 """
+import math
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -91,4 +93,29 @@ def test_bad_permutation_of_a_bf16_layer_is_rejected(D_, F_, kind):
     assert ei.value.status == -2
     layer.partition_weights(w1, w3, w2, perm=good)
     assert torch.equal(layer.forward(x, logits, tau), y)
+    layer.close()
+
+
+def test_headroom_of_partial_outputs_when_the_sample_misses_the_top_binade():
+    # One weight of the next binade, which the sample does not meet.  Partial outputs are scaled by the largest weight of all: sums that
+    # reach 47800 of half precision's 65504 so, and would saturate at twice that by the sample's.
+    import torch
+    layer = _layer()
+    gen = torch.Generator(device="cuda:0").manual_seed(7)
+    x, logits, tau = torch.ones(T, D, device="cuda:0").bfloat16(), torch.randn(T, E, generator=gen, device="cuda:0"), torch.zeros(E, 2, device="cuda:0")
+    w1 = torch.full((E, D, F), 1 / 256, device="cuda:0").bfloat16()
+    w2 = torch.full((E, F, D), 255 / 128, device="cuda:0").bfloat16()
+    w2.view(-1, RUN)[1, 7] = 2.0
+    ranges = 1
+    for _ in range(2):  # how many K ranges a sum is in is the plan's affair: known after a call
+        gate, up = D / 256, 3000.0 * ranges / F / 8.0
+        w3 = torch.full((E, D, F), up / D, device="cuda:0").bfloat16()
+        layer.partition_weights(w1, w3, w2)
+        y = layer.forward(x, logits, tau).double().cpu()
+        ranges = int(layer.plan(T)["counters"][3])
+    h = gate / (1 + math.exp(-gate)) * D * float(w3[0, 0, 0])
+    ref = h * w2.double().sum(1).cpu()  # [E][D]
+    ref = torch.softmax(logits.double().cpu(), dim=1) @ ref
+    assert 2.9e3 < h * F / ranges < 3.1e3
+    assert ((y - ref).abs() <= 2e-3 * ref).all()
     layer.close()
