@@ -176,7 +176,7 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
     L.p_sw13 = takep((int64_t)L.NT1_sh * (2 * kFullNeur) * L.Dk * elem);
     L.p_sw2 = takep((int64_t)L.ND2 * kFullBN2 * L.Fsk * elem);
   }
-  L.p_scale = takep(sizeof(PackRecord));
+  L.p_scale = takep((int64_t)sizeof(PackRecord) + (L.mfma ? w2_tiles(L) : 0));
   L.packed_bytes = q;
   L.router_mfma = (c.dtype == DSMOE_BF16 && L.D % 64 == 0) ? 1 : 0;
   L.router_bytes = L.router_mfma ? (int64_t)L.D * ((L.E + 31) / 32 * 32) * 2 : (int64_t)L.D * L.E * 4;
@@ -299,7 +299,7 @@ int moe_partition_weights(dsmoe_ctx* ctx_, const void* w1, const void* w3, const
   if (L.n_shared > 0 && (!sh_w1 || !sh_w3 || !sh_w2)) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   hipError_t err;
-  // what the kernels found is read once all of them are under way; a perm that is none, or a scale that does not fit, costs their time
+  // what the kernels found is read once all of them are under way; a perm that is none costs their time
   err = launch_pack(L, w1, w3, w2, sh_w1, sh_w3, sh_w2, perm, (char*)packed_out, ctx->cfg.n_shared, ctx->cfg.d_ff_shared, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   PackRecord rec;
@@ -308,12 +308,6 @@ int moe_partition_weights(dsmoe_ctx* ctx_, const void* w1, const void* w3, const
   err = hipStreamSynchronize(s);
   if (err != hipSuccess) return hip_fail(ctx, err);
   if (rec.bad_perm) return DSMOE_EPERM;
-  if (rec.repack) {
-    err = launch_repack_w2(L, w2, sh_w2, perm, (char*)packed_out, s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
-    err = hipStreamSynchronize(s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
-  }
   return DSMOE_OK;
 }
 

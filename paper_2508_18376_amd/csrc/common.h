@@ -68,16 +68,28 @@ struct Item2 {  // one tile of GEMM-2: rows x output column tile jd, summed over
   int32_t split;        // 0: the item writes its rows of Yp; n > 0: it writes partial-output tile n-1 of the pool
 };
 
-// What packing leaves beside the weights (32 bytes at Layout::p_scale, cleared before it).
+// What packing leaves beside the weights (at Layout::p_scale, cleared before it).  MFMA layout: the images of W2 carry a power of two, which is
+// the sample's (pack.hip) except in the column tiles (256 columns of an expert, the unit of a GEMM-2 item) with a weight that does not fit half
+// precision so.  A byte for each of them follows the record, the shared pseudo-expert's last: the (biased) exponent of its largest |W2|
+// if that is of a higher binade than the sample's, else 0.
 struct PackRecord {
-  uint32_t largest;  // MFMA layout: bits of the largest |W2| that the scale 2^s of the images was taken from; full-precision layout of bf16: 1 if W2 has an infinity or NaN
-  int32_t beyond;    // MFMA layout: (biased) exponent of the largest |W2| of all, if that is of a higher binade; else 0
-  float yscale;      // MFMA layout: 2^(S - s), S being the scale that the largest |W2| of all gives: GEMM-2's partial outputs carry 2^S, so that their range does not hang on s
-  float unscale;     // MFMA layout: 2^-(S + h_shift), which the combine kernel applies
-  int32_t repack;    // a weight does not fit half precision at this scale
+  uint32_t largest;  // MFMA layout: bits of the sample's largest |W2|; full-precision layout of bf16: 1 if W2 has an infinity or NaN
+  int32_t room;      // MFMA layout: the largest exponent that fits at the sample's scale (0: a sample that is zero or subnormal sets no scale)
+  int32_t shift0;    // ... 2^shift0 is the scale of the column tiles without a larger one
+  int32_t shift;     // ... 2^shift is the scale that the largest |W2| of all gives: GEMM-2's partial outputs carry it, so that their range
+                     // does not hang on the sample and they all add up
+  float unscale;     // ... 2^-(shift + h_shift), which the combine kernel applies
+  int32_t beyond;    // ... some column tile's byte is set
   int32_t bad_perm;
-  int32_t pad[2];
+  int32_t pad;
 };
+// the power of two that takes |W2| of (biased) exponent e to [2^14, 2^15)
+__device__ __forceinline__ int w2_shift(int e) {
+  const int s = e == 0 ? 0 : 14 - (e - 127);  // (0: zero or subnormal)
+  return s < -80 ? -80 : s > 80 ? 80 : s;
+}
+// ... and that of a column tile
+__device__ __forceinline__ int w2_tile_shift(int room, int shift0, int beyond) { return beyond > room ? w2_shift(beyond) : shift0; }
 
 // Everything the device code needs to know about the layer and the workspace.
 struct Layout {
@@ -115,7 +127,7 @@ struct Layout {
   int64_t o_items1, o_items2;
   int64_t o_row_token, o_row_bits, o_H, o_Hs, o_Yp, o_sel, o_logits, o_perm_check, o_pool, o_split_of, ws_bytes;
   // packed weights byte offsets
-  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the PackRecord
+  int64_t p_w13, p_w2, p_sw13, p_sw2, p_scale, packed_bytes, router_bytes;  // p_scale: the PackRecord and what follows it
   int64_t w13_expert_bytes, w2_expert_bytes;  // strides between experts (mfma layout)
 };
 
@@ -170,6 +182,8 @@ __host__ __device__ inline bool may_halve_items1(const Layout& L, int T) {
 inline int items1_bound(const Layout& L, int T) {
   return items1_whole_bound(L, T) + (may_halve_items1(L, T) ? L.split_items / 2 : 0);
 }
+// column tiles of W2, the shared pseudo-expert's among them
+inline int w2_tiles(const Layout& L) { return (L.E_res + (L.n_shared > 0 ? 1 : 0)) * L.ND2; }
 inline int items2_bound(const Layout& L, int T) {
   const int whole = (routed_tiles_bound(L, T) + shared_tiles(L, T)) * L.ND2;
   return whole + L.pool_tiles;  // every extra K range of a split item is one more item
@@ -218,8 +232,6 @@ hipError_t launch_perm_from_importance(const Layout& L, const float* importance,
 hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s);
-// W2 once more, with the scale of the largest |W2| of all (after a launch_pack that left PackRecord::repack)
-hipError_t launch_repack_w2(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s);
 // the inverse of perm; *bad (cleared by the caller) is set if perm is not a permutation
 hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s);
 

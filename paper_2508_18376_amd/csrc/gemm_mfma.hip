@@ -817,7 +817,14 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
     g.Y = ws + L.o_pool + (size_t)(g.it.split - 1) * kPoolRows * kMfmaBN2 * yel;
     g.ldy = kMfmaBN2;
   }
-  g.yscale = ((const __attribute__((address_space(4))) PackRecord*)(uintptr_t)(packed + L.p_scale))->yscale;  // (constant memory: a scalar load)
+  const auto* rec = (const __attribute__((address_space(4))) PackRecord*)(uintptr_t)(packed + L.p_scale);  // (as constant memory: scalar loads)
+  g.yscale = 1.f;
+  if (rec->beyond) {
+    const int tile = __builtin_amdgcn_readfirstlane(g.it.e * L.ND2 + g.it.jd);
+    const int beyond = ((const __attribute__((address_space(4))) uint32_t*)(rec + 1))[tile >> 2] >> (8 * (tile & 3)) & 255;
+    const int n = rec->shift - w2_tile_shift(rec->room, rec->shift0, beyond);  // -160 .. 0
+    g.yscale = __int_as_float(__builtin_amdgcn_readfirstlane(n >= -126 ? (127 + n) << 23 : 1 << max(149 + n, 0)));  // (no zero: an infinity stays one)
+  }
   g.col0 = 0;
 
   g.lds_w = lds_offset(lds) + (uint32_t)(w * 1024);

@@ -17,9 +17,9 @@
 //        operand, the intermediate activation, needs more significant bits than bf16 has).  s is
 //        chosen per layer so that the largest |W2| of a sample lands in [2^14, 2^15) (all of a W2 of up to 16 M values;
 //        otherwise every 3rd to 63rd run of 2048): every bf16 value within a factor 2^-29 of that is then exactly
-//        representable (smaller ones round to the subnormal grid, 2^-39 of it).  A layer with a larger |W2| that no longer
-//        fits half precision is packed again from the largest of all.  The combine kernel multiplies by 2^-s, exactly.
-//        The record (PackRecord) sits at p_scale.
+//        representable (smaller ones round to the subnormal grid, 2^-39 of it).  Column tiles of an expert with a larger
+//        |W2| that no longer fits half precision are packed again with an s of their own.  GEMM-2 and the combine
+//        kernel take the powers of two out again, exactly.  The record (PackRecord) sits at p_scale.
 //   W3 carries the factor 2^k of cfg.h_scale_log2 (exact in bf16), so that the intermediate activation
 //        comes out of GEMM-1 times 2^k, in the range half precision resolves best, at no run-time cost.
 //   neurons / columns past the end are zero.
@@ -74,25 +74,16 @@ __global__ __launch_bounds__(256) void absmax_bf16_kernel(const uint16_t* w, int
   }
 }
 static void launch_absmax(const void* w, int64_t n, int stride, PackRecord* rec, hipStream_t s) {
-  const int most = stride == 1 && n > (int64_t)1 << 26 ? 2048 : 512;
   const int64_t runs = (n + (int64_t)stride * kAbsmaxRun - 1) / ((int64_t)stride * kAbsmaxRun);
-  const int blocks = (int)(runs < most ? runs : most);
-  absmax_bf16_kernel<<<dim3(blocks), dim3(256), 0, s>>>((const uint16_t*)w, n, stride, &rec->largest);
+  absmax_bf16_kernel<<<dim3((unsigned)(runs < 512 ? runs : 512)), dim3(256), 0, s>>>((const uint16_t*)w, n, stride, &rec->largest);
 }
 // The scale is needed before the first value is packed, and finding the largest of all |W2| reads W2 once more (a tenth
 // of the packing of 8 experts of 4096 x 14336, which took 1.52 ms with it and takes 1.36 without).  A sample of 8 to 16 M values tells its
-// binade as well as that binade and the next have room for: only a W2 whose largest value is more than twice (for some, four
-// times) the sample's largest is packed twice.  Odd strides: a row of a power of two of values is met in all of its columns.
+// binade as well as that binade and the next have room for (see repack_w2_kernel): only column tiles whose largest value is more than twice (for some, four
+// times) the sample's largest are packed twice.  Odd strides: a row of a power of two of values is met in all of its columns.
 static int absmax_stride(int64_t n) {
   const int64_t k = n >> 23;
   return k < 2 ? 1 : k > 63 ? 63 : (int)(k | 1);
-}
-
-// largest |W2| bits -> s with largest * 2^s in [2^14, 2^15)
-__device__ __forceinline__ int w2_shift(uint32_t largest) {
-  const int e = (int)(largest >> 7);  // biased exponent (0: zero or subnormal)
-  const int s = e == 0 ? 0 : 14 - (e - 127);
-  return s < -80 ? -80 : s > 80 ? 80 : s;
 }
 
 // a bf16 value times 2^k (k = L.h_shift), exact unless it leaves bf16's exponent range
@@ -186,14 +177,27 @@ __device__ __forceinline__ uint32_t beyond_sample(uint4 raw, uint32_t sampled) {
   }
   return most;
 }
-// the largest exponent that fits half precision at the scale of the sample; 0: a sample that is zero or subnormal sets no scale
-__device__ __forceinline__ int w2_room(uint32_t sampled) { return sampled < 0x80u ? 0 : 142 - w2_shift(sampled); }
+// byte i becomes at least v (rarely called: for weights beyond the sample)
+__device__ __forceinline__ void raise_byte(uint32_t* words, int i, uint32_t v) {
+  uint32_t* at = words + (i >> 2);
+  const int sh = 8 * (i & 3);
+  uint32_t old = *(volatile uint32_t*)at;
+  while ((old >> sh & 255) < v) {
+    const uint32_t seen = atomicCAS(at, old, (old & ~(255u << sh)) | v << sh);
+    if (seen == old) break;
+    old = seen;
+  }
+}
 
 // some of the eight bf16 values is infinite or NaN
 __device__ __forceinline__ bool not_finite(uint4 v) {
   auto one = [](uint32_t u) { return (u & 0x7f80u) == 0x7f80u || (u & 0x7f800000u) == 0x7f800000u; };
   return one(v.x) || one(v.y) || one(v.z) || one(v.w);
 }
+
+// Neuron c of an expert is not the one that perm names at the position inv has for it, i.e. none names it (inv is whatever was
+// there before): perm is no permutation.
+__device__ __forceinline__ bool not_inverse(const int32_t* perm, int pos, int c, int F) { return (uint32_t)pos >= (uint32_t)F || perm[pos] != c; }
 
 // Where neuron nin of a partition sits in its W13 images: neuron tile, image row of its gate projection; the up row is UP
 // rows further down.  FULL: the full-precision layout.
@@ -209,9 +213,11 @@ struct W13Image {
 // rows d) of both matrices and writes each neuron's gate and up image rows at the place the inverse permutation
 // names (inv == nullptr: identity order).  w1, w3: [experts][D][Fs]; column c of expert e is neuron pos0 * e + c of
 // image expert e * per_expert (the shared experts are consecutive neurons of one image expert: per_expert 0).
+// The workgroups of the first K stage also check perm against inv, see not_inverse (a launch of its own for that is the seventh in front of
+// the host's read of the outcome, and with seven that takes 27 us longer than with six).
 // What is left to the 5.3 TB/s of a large copy are the 64-byte runs that a random order scatters.
 template <typename T, bool FULL>
-__global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3, const int32_t* inv, char* out, int D, int KS1,
+__global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3, const int32_t* perm, const int32_t* inv, int32_t* bad, char* out, int D, int KS1,
                                                        int Fs, int Fp, int P, int NT1, int pos0, int per_expert, int h_shift, int vec) {
   using PT = PackTile<T>;
   using Im = W13Image<T, FULL>;
@@ -244,6 +250,7 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
       const int c = c0 + cg * PT::COLS_GET + i;
       if (c >= Fs) continue;
       const int pos = inv ? inv[(size_t)e * Fs + c] : pos0 * e + c;
+      if (inv && (ks | lc) == 0 && not_inverse(perm + (size_t)e * Fs, pos, c, Fs)) *bad = 1;
       if (inv && (uint32_t)pos >= (uint32_t)Fs) continue;  // not a permutation (reported when all is done)
       const int p = pos / Fp, nin = pos - p * Fp;
       const int row = Im::row(nin);
@@ -254,46 +261,35 @@ __global__ __launch_bounds__(256) void pack_w13_kernel(const T* w1, const T* w3,
   }
 }
 
-// W2 -> W2 images (matrix-core path: half precision times the layer's power of two).  A workgroup takes 32 neuron positions
-// (source rows, in permuted order; zeros past the end of a partition) x COLS output columns: one stage image, or two
-// of 128 columns.  w2: [experts][P * Fp][D]; KSp: stages of a partition, KT: of the expert, nd: column tiles of the images.
-template <typename T, bool FULL>
-__global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t* perm, char* out, PackRecord* rec, int D, int F, int Fp,
-                                                      int KSp, int KT, int nd, int vec) {
+// W2 of the routed experts, or of the shared ones, and its images.  w2: [experts][F][D]; neurons of a partition; stages of a
+// partition and of the expert; 16-byte loads are aligned.
+template <typename T>
+struct W2Tensor {
+  const T* w2;
+  const int32_t* perm;
+  char* out;
+  int F, Fp, KSp, KT, vec;
+};
+// One K stage of PackTile::COLS output columns from c0 on: 32 neuron positions (source rows, in permuted order; zeros past the end of a
+// partition), one stage image, or two of 128 columns; nd: column tiles of the images.  op(v): eight (four) values as the images hold them.
+template <typename T, bool FULL, class Op>
+__device__ __forceinline__ void pack_w2_stage(PackTile<T>& t, const W2Tensor<T>& w, int D, int nd, int e, int kt, int c0, Op&& op) {
   using PT = PackTile<T>;
   constexpr int BN = FULL ? kFullBN2 : kMfmaBN2, RB = kBK * sizeof(T);
-  __shared__ PT t;
-  const int nb = (D + PT::COLS - 1) / PT::COLS;
-  const int c0 = (int)(blockIdx.x % nb) * PT::COLS, kt = blockIdx.x / nb, e = blockIdx.y, tid = threadIdx.x;
-  float scale = 1.f;
-  uint32_t sampled = 0;  // largest |W2| of the sample
-  if (!FULL) {
-    sampled = rec->largest;
-    scale = __uint_as_float((uint32_t)(127 + w2_shift(sampled)) << 23);
-  }
+  const int tid = threadIdx.x;
   uint4 a[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int in = kt % KSp * kBK + u * 8 + (tid >> 5), pos = kt / KSp * Fp + in;
+    const int in = kt % w.KSp * kBK + u * 8 + (tid >> 5), pos = kt / w.KSp * w.Fp + in;
     const T* row = nullptr;
-    if (in < Fp) {
-      const int src = perm ? perm[(size_t)e * F + pos] : pos;
-      if ((uint32_t)src < (uint32_t)F) row = w2 + ((size_t)e * F + src) * D;  // (not a permutation: reported when all is done)
+    if (in < w.Fp) {
+      const int src = w.perm ? w.perm[(size_t)e * w.F + pos] : pos;
+      if ((uint32_t)src < (uint32_t)w.F) row = w.w2 + ((size_t)e * w.F + src) * D;  // (not a permutation: reported when all is done)
     }
-    a[u] = PT::template load<false>(row, c0 + (tid & 31) * PT::V, D, vec);
+    a[u] = PT::template load<false>(row, c0 + (tid & 31) * PT::V, D, w.vec);
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if constexpr (!FULL) {
-      if (const uint32_t most = beyond_sample(a[u], sampled)) {
-        atomicMax(&rec->beyond, (int)(most >> 7));
-        if ((int)(most >> 7) > w2_room(sampled)) rec->repack = 1;
-      }
-      a[u] = map_halves(a[u], [&](uint16_t v) { return (uint32_t)bf16_to_scaled_half(v, scale); });
-    }
-    if (FULL && sizeof(T) == 2 && not_finite(a[u])) rec->largest = 1;
-    t.put(u * 8 + (tid >> 5), tid & 31, a[u]);
-  }
+  for (int u = 0; u < 4; ++u) t.put(u * 8 + (tid >> 5), tid & 31, op(a[u]));
   __syncthreads();
 #pragma unroll
   for (int pass = 0; pass < PT::PASSES; ++pass) {
@@ -304,9 +300,79 @@ __global__ __launch_bounds__(256) void pack_w2_kernel(const T* w2, const int32_t
     for (int i = 0; i < PT::COLS_GET; ++i) {
       const int c = c0 + cg * PT::COLS_GET + i, jd = c / BN, row = c % BN;
       if (jd >= nd) continue;
-      char* stage = out + (((int64_t)e * nd + jd) * KT + kt) * (BN * RB);
+      char* stage = w.out + (((int64_t)e * nd + jd) * w.KT + kt) * (BN * RB);
       *(uint4*)(stage + row * RB + swz_full<RB / 16>(row, lc) * 16) = o[i];
     }
+  }
+}
+__device__ __forceinline__ uint4 scaled_halves(uint4 v, int shift) {
+  const float scale = __uint_as_float((uint32_t)(127 + shift) << 23);
+  return map_halves(v, [&](uint16_t b) { return (uint32_t)bf16_to_scaled_half(b, scale); });
+}
+
+// W2 -> W2 images (matrix-core path: half precision times the sample's power of two).  A workgroup takes one stage, see above.
+// beyond: matrix-core path, the bytes of these experts' column tiles, see PackRecord
+template <typename T, bool FULL>
+__global__ __launch_bounds__(256) void pack_w2_kernel(W2Tensor<T> w, PackRecord* rec, int beyond0, int D, int nd) {
+  using PT = PackTile<T>;
+  static_assert(FULL || PT::COLS == kMfmaBN2, "one column tile");
+  __shared__ PT t;
+  const int nb = (D + PT::COLS - 1) / PT::COLS, jd = blockIdx.x % nb, e = blockIdx.y;
+  const uint32_t sampled = FULL ? 0 : rec->largest;
+  pack_w2_stage<T, FULL>(t, w, D, nd, e, blockIdx.x / nb, jd * PT::COLS, [&](uint4 v) {
+    if constexpr (FULL) {
+      if (sizeof(T) == 2 && not_finite(v)) rec->largest = 1;
+      return v;
+    } else {
+      if (const uint32_t most = beyond_sample(v, sampled)) raise_byte((uint32_t*)(rec + 1), beyond0 + e * nd + jd, most >> 7);
+      return scaled_halves(v, w2_shift(sampled >> 7));
+    }
+  });
+}
+
+// Once all of W2 has been looked at: the powers of two of the record, and the column tiles whose largest weight does not fit at the
+// sample's scale once more with their own.  Outliers are few, and so are those tiles: loading 8 experts of 4096 x 14336 (128 column
+// tiles) takes 1.36 ms, with a weight far beyond the others in 1 / 4 / 16 / 64 places that the sample misses 1.37 / 1.38 / 1.41 / 1.51
+// (all of W2 again from its largest, which the host asked for when it had seen the record: 1.92 for any of them; the largest of all
+// found first: 1.53 always); 64 experts of 2048 x 1024 0.39, with 1 or 4 of them 0.40 (0.57; 0.47).
+// n: words of four column tiles.  (Every workgroup has an order of its own in todo: its stages of a tile do not follow from it.)
+constexpr int kRepackBlocks = 1024;
+__global__ __launch_bounds__(256) void repack_w2_kernel(W2Tensor<uint16_t> routed, W2Tensor<uint16_t> shared, PackRecord* rec, int n, int E_res, int D, int nd,
+                                                        int h_shift) {
+  __shared__ PackTile<uint16_t> t;
+  __shared__ uint32_t todo[1024];  // column tile << 8 | exponent
+  __shared__ int count, top;
+  const int blocks = gridDim.x, tid = threadIdx.x;
+  const bool usable = rec->largest >= 0x80u;
+  const int sampled = w2_shift(rec->largest >> 7), room = usable ? 142 - sampled : 0;
+  if (tid == 0) top = 0;
+  for (int base = 0; base < n; base += 256) {
+    if (tid == 0) count = 0;
+    __syncthreads();
+    const uint32_t word = base + tid < n ? ((const uint32_t*)(rec + 1))[base + tid] : 0;
+    for (int i = 0; i < 4; ++i) {
+      const int b = word >> (8 * i) & 255;
+      if (b) atomicMax(&top, b);
+      if (b > room) todo[atomicAdd(&count, 1)] = (uint32_t)((base + tid) * 4 + i) << 8 | b;
+    }
+    __syncthreads();
+    for (int i = 0; i < count; ++i) {
+      const int tile = todo[i] >> 8, shift = w2_shift(todo[i] & 255), e = tile / nd;
+      const W2Tensor<uint16_t>& w = e < E_res ? routed : shared;
+      for (int kt = (blockIdx.x + tile * 97) % blocks; kt < w.KT; kt += blocks) {
+        __syncthreads();
+        pack_w2_stage<uint16_t, false>(t, w, D, nd, e < E_res ? e : 0, kt, tile % nd * kMfmaBN2, [&](uint4 v) { return scaled_halves(v, shift); });
+      }
+    }
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && tid == 0) {
+    const int shift = top ? w2_shift(top) : sampled;
+    rec->room = room;
+    rec->shift0 = usable ? sampled : shift;  // (column tiles of zeros and subnormals alone: zeros at any scale)
+    rec->shift = shift;
+    rec->beyond = top;
+    rec->unscale = ldexpf(1.f, -shift - h_shift);  // undoes 2^shift of the partial outputs and 2^h_shift of W3
   }
 }
 
@@ -340,41 +406,39 @@ __global__ void invert_perm_kernel(const int32_t* perm, int32_t* inv, int F, int
   const int src = perm[t];
   if (src >= 0 && src < F) inv[e * F + src] = (int32_t)(t % F);
 }
-// *bad: some neuron is not the one that perm names at the position inv has for it, i.e. none names it (inv is whatever was
-// there before), so perm is no permutation
 __global__ void perm_check_kernel(const int32_t* perm, const int32_t* inv, int F, int64_t n, int32_t* bad) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
   const int64_t e = t / F;
   const int pos = inv[t];
-  if (pos < 0 || pos >= F || perm[e * F + pos] != (int)(t % F)) *bad = 1;
+  if (not_inverse(perm + e * F, pos, (int)(t % F), F)) *bad = 1;
 }
+static dim3 perm_grid(const Layout& L) { return dim3((unsigned)(((int64_t)L.E_res * L.F + 255) / 256)); }
 hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s) {
   const int64_t n = (int64_t)L.E_res * L.F;
-  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-  invert_perm_kernel<<<grid, block, 0, s>>>(perm, inv, L.F, n);
-  perm_check_kernel<<<grid, block, 0, s>>>(perm, inv, L.F, n, bad);
+  invert_perm_kernel<<<perm_grid(L), dim3(256), 0, s>>>(perm, inv, L.F, n);
+  perm_check_kernel<<<perm_grid(L), dim3(256), 0, s>>>(perm, inv, L.F, n, bad);
   return hipGetLastError();
-}
-
-// the powers of two that GEMM-2 and the combine kernel apply, once all of W2 has been looked at
-__global__ void w2_record_kernel(PackRecord* rec, int h_shift) {
-  const int packed = w2_shift(rec->largest), all = rec->beyond ? w2_shift((uint32_t)rec->beyond << 7) : packed;
-  rec->yscale = ldexpf(1.f, all - packed);
-  rec->unscale = ldexpf(1.f, -all - h_shift);
 }
 
 template <typename T, bool FULL>
 static void w2_images(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s) {
-  auto images = [&](const void* w, const int32_t* order, char* out, int experts, int F, int Fp, int Fpk) {
-    const int KSp = Fpk / kBK, KT = F / Fp * KSp, C = PackTile<T>::COLS;
-    const int vec = L.D % PackTile<T>::V == 0 && ((uintptr_t)w & 15) == 0;
-    pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * KT), experts), dim3(256), 0, s>>>(
-        (const T*)w, order, out, (PackRecord*)(packed + L.p_scale), L.D, F, Fp, KSp, KT, L.ND2, vec);
+  PackRecord* rec = (PackRecord*)(packed + L.p_scale);
+  auto tensor = [&](const void* w, const int32_t* order, int64_t out, int F, int Fp, int Fpk) {
+    const int KSp = Fpk / kBK;
+    return W2Tensor<T>{(const T*)w, order, packed + out, F, Fp, KSp, Fp ? F / Fp * KSp : 0, L.D % PackTile<T>::V == 0 && ((uintptr_t)w & 15) == 0};
   };
-  images(w2, perm, packed + L.p_w2, L.E_res, L.F, L.Fp, L.Fpk);
-  if (L.n_shared > 0) images(sw2, nullptr, packed + L.p_sw2, 1, L.F_shT, L.F_shT, L.Fsk);
-  if (!FULL) w2_record_kernel<<<dim3(1), dim3(1), 0, s>>>((PackRecord*)(packed + L.p_scale), L.h_shift);
+  const W2Tensor<T> routed = tensor(w2, perm, L.p_w2, L.F, L.Fp, L.Fpk), shared = tensor(sw2, nullptr, L.p_sw2, L.F_shT, L.F_shT, L.Fsk);
+  auto images = [&](const W2Tensor<T>& w, int experts, int beyond0) {
+    const int C = PackTile<T>::COLS;
+    pack_w2_kernel<T, FULL><<<dim3((unsigned)((L.D + C - 1) / C * w.KT), experts), dim3(256), 0, s>>>(w, rec, beyond0, L.D, L.ND2);
+  };
+  images(routed, L.E_res, 0);
+  if (L.n_shared > 0) images(shared, 1, L.E_res * L.ND2);
+  if constexpr (!FULL) {
+    const int words = (w2_tiles(L) + 3) / 4;
+    repack_w2_kernel<<<dim3(kRepackBlocks), dim3(256), 0, s>>>(routed, shared, rec, words, L.E_res, L.D, L.ND2, L.h_shift);
+  }
 }
 
 template <typename T, bool FULL>
@@ -388,14 +452,13 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
   int32_t* inv = nullptr;
   if (perm) {
     inv = (int32_t*)(packed + L.p_w2);
-    const hipError_t e = launch_invert_perm(L, perm, inv, &((PackRecord*)(packed + L.p_scale))->bad_perm, s);
-    if (e != hipSuccess) return e;
+    invert_perm_kernel<<<perm_grid(L), block, 0, s>>>(perm, inv, L.F, (int64_t)L.E_res * L.F);
   }
   auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
   auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
     const int vec = Fs % PackTile<T>::V == 0 && aligned(a, b);
     pack_w13_kernel<T, FULL><<<dim3((unsigned)((Fs + C - 1) / C * KS1), experts), block, 0, s>>>(
-        (const T*)a, (const T*)b, order, out, L.D, KS1, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
+        (const T*)a, (const T*)b, perm, order, &((PackRecord*)(packed + L.p_scale))->bad_perm, out, L.D, KS1, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
     const int pad = NT1 * W13Image<T, FULL>::NEUR - Fp, groups = (per_expert ? experts : 1) * P;
     if (pad > 0) {
       const int64_t total = (int64_t)groups * KS1 * pad * 2 * PackTile<T>::CH;
@@ -411,7 +474,7 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s) {
   PackRecord* rec = (PackRecord*)(packed + L.p_scale);
-  const hipError_t e = launch_fill_i32((int32_t*)rec, sizeof(PackRecord) / 4, 0, s);
+  const hipError_t e = launch_fill_i32((int32_t*)rec, sizeof(PackRecord) / 4 + (L.mfma ? (w2_tiles(L) + 3) / 4 : 0), 0, s);
   if (e != hipSuccess) return e;
   if (L.mfma) {
     const int64_t n = (int64_t)L.E_res * L.F * L.D, n_sh = (int64_t)L.F_shT * L.D;
@@ -421,14 +484,6 @@ hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const vo
   }
   if (L.dtype == DSMOE_F32) return pack_images<float, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
   return pack_images<uint16_t, true>(L, w1, w3, w2, sw1, sw3, sw2, perm, packed, n_shared, F_sh, s);
-}
-
-hipError_t launch_repack_w2(const Layout& L, const void* w2, const void* sw2, const int32_t* perm, char* packed, hipStream_t s) {
-  PackRecord* rec = (PackRecord*)(packed + L.p_scale);
-  launch_absmax(w2, (int64_t)L.E_res * L.F * L.D, 1, rec, s);
-  if (L.n_shared > 0) launch_absmax(sw2, (int64_t)L.F_shT * L.D, 1, rec, s);
-  w2_images<uint16_t, false>(L, w2, sw2, perm, packed, s);
-  return hipGetLastError();
 }
 
 }  // namespace dsmoe

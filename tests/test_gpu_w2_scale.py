@@ -20,6 +20,17 @@ def _layer():
     return DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=E, n_part=2, max_tokens=T, dtype="bf16", y_fp32=True)
 
 
+def _reference(x, g, w):
+    """Sum over the experts of g[:, e] f_e(x), in 64 bits."""
+    import torch
+    y = torch.zeros(x.shape[0], w[2].shape[2], dtype=torch.float64)
+    xd = x.double().cpu()
+    for e in range(w[0].shape[0]):
+        a = xd @ w[0][e].double().cpu()
+        y += g[:, e:e + 1] * ((a * torch.sigmoid(a) * (xd @ w[1][e].double().cpu())) @ w[2][e].double().cpu())
+    return y
+
+
 @pytest.mark.parametrize("kind", ["even", "within_a_binade", "outlier", "outlier_and_infinity", "sample_of_zeros", "all_zero", "last_run", "sample_of_subnormals"])
 def test_w2_values_that_the_sample_misses(kind):
     import torch
@@ -50,13 +61,7 @@ def test_w2_values_that_the_sample_misses(kind):
     layer = _layer()
     layer.partition_weights(w1, w3, w2)
     y = layer.forward(x, logits, torch.zeros(E, 2, device="cuda:0")).double().cpu()
-    g = torch.softmax(logits.double().cpu(), dim=1)
-    ref = torch.zeros(T, D, dtype=torch.float64)
-    xd = x.double().cpu()
-    for e in range(E):
-        a = xd @ w1[e].double().cpu()
-        h = a * torch.sigmoid(a) * (xd @ w3[e].double().cpu())
-        ref += g[:, e:e + 1] * (h @ w2[e].double().cpu())
+    ref = _reference(x, torch.softmax(logits.double().cpu(), dim=1), (w1, w3, w2))
     good = torch.isfinite(ref)
     if kind == "outlier_and_infinity":  # the one column of the infinite weight (half-precision partial outputs saturate)
         good = torch.ones_like(good)
@@ -119,3 +124,35 @@ def test_headroom_of_partial_outputs_when_the_sample_misses_the_top_binade():
     assert 2.9e3 < h * F / ranges < 3.1e3
     assert ((y - ref).abs() <= 2e-3 * ref).all()
     layer.close()
+
+
+@pytest.mark.parametrize("where,h_scale", [("routed", 0), ("routed", 6), ("shared", -4)])
+def test_a_weight_beyond_the_sample_rescales_its_column_tile_alone(where, h_scale):
+    # Weights 2^-41 of the outlier's size, in another column tile: nothing is left of them at the outlier's scale (half precision reaches
+    # down to 2^-39 of the largest), and they are exact at the sample's.  Partial outputs in fp32: those in half precision share one scale.
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda:0").mul_(0.02).bfloat16()
+
+    sh = dict(n_shared=1, d_ff_shared=F) if where == "shared" else {}
+    layer = DualSparseLayer(d_model=D, d_ff=F, n_experts=E, top_k=E, n_part=2, max_tokens=T, dtype="bf16", y_fp32=True, partial_fp32=True,
+                            h_scale_log2=h_scale, **sh)
+    w = [normal(E, D, F), normal(E, D, F), normal(E, F, D)]
+    shared = [normal(1, D, F), normal(1, D, F), normal(1, F, D)] if sh else None
+    for m in (w, shared):
+        if m:
+            m[2][:, :, 512:768] *= 2.0 ** -20
+    perm = torch.rand(E, F, generator=gen, device="cuda:0").argsort(dim=1).to(torch.int32)
+    (shared or w)[2].view(-1, RUN)[1, 7] = 3e4  # neuron 1 of the first expert, column 7
+    x, logits = torch.randn(T, D, generator=gen, device="cuda:0").bfloat16(), torch.randn(T, E, generator=gen, device="cuda:0")
+    layer.partition_weights(*w, perm=perm, **(dict(zip(("sh_w1", "sh_w3", "sh_w2"), shared)) if shared else {}))
+    y = layer.forward(x, logits, torch.zeros(E, 2, device="cuda:0")).double().cpu()
+    layer.close()
+    g = torch.softmax(logits.double().cpu(), dim=1)
+    ref = _reference(x, g, w) + (_reference(x, torch.ones(T, 1, dtype=torch.float64), shared) if shared else 0.0)
+    for cols in (slice(0, 256), slice(256, 512), slice(512, 768), slice(768, D)):
+        r = ref[:, cols]
+        assert ((y[:, cols] - r).abs() <= 2e-3 * r.square().mean().sqrt() + 2.0 ** -10 * r.abs()).all(), cols
