@@ -22,8 +22,8 @@
  *     kernels have run.  "stream" is a hipStream_t passed as void* (NULL = the default stream).
  *   - All calls return 0 (DSMOE_OK) or a negative dsmoe_status; they never throw.
  *   - moe_route_and_mask and moe_dualsparse_forward only enqueue kernels: no host
- *     synchronisation, no allocation.  moe_partition_weights synchronises the stream once,
- *     when all its kernels are under way (it reads back the permutation check).
+ *     synchronisation, no allocation.  moe_partition_weights with a perm synchronises the stream
+ *     once, when all its kernels are under way (it reads back the permutation check); without one it only enqueues.
  *   - NaN router logits give unspecified routing (not an error): a NaN logit ranks last, every token
  *     still gets K distinct expert ids in range, and no later step leaves its buffers.
  *   - A context keeps a little host-side state per call (profiling events, the last plan's row

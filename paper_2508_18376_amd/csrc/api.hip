@@ -299,9 +299,10 @@ int moe_partition_weights(dsmoe_ctx* ctx_, const void* w1, const void* w3, const
   if (L.n_shared > 0 && (!sh_w1 || !sh_w3 || !sh_w2)) return DSMOE_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   hipError_t err;
-  // what the kernels found is read once all of them are under way; a perm that is none costs their time
   err = launch_pack(L, w1, w3, w2, sh_w1, sh_w3, sh_w2, perm, (char*)packed_out, ctx->cfg.n_shared, ctx->cfg.d_ff_shared, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
+  if (!perm) return DSMOE_OK;  // nothing to wait for: the call can be captured
+  // what the kernels found is read once all of them are under way; a perm that is none costs their time
   PackRecord rec;
   err = hipMemcpyAsync(&rec, (const char*)packed_out + L.p_scale, sizeof(rec), hipMemcpyDeviceToHost, s);
   if (err != hipSuccess) return hip_fail(ctx, err);
