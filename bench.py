@@ -189,9 +189,9 @@ class Workload:
         g1_flops = 4.0 * spec.D * self.Fp * units + 4.0 * spec.D * spec.F_sh * spec.n_shared * spec.T
         g2_flops = 2.0 * spec.D * self.Fp * units + 2.0 * spec.D * spec.F_sh * spec.n_shared * spec.T
         kernels = {k: {"ms": v} for k, v in kms.items()}
-        kernels["route_mask"]["GBps"] = bytes_route / (kms["route_mask"] * 1e-3) / 1e9
-        kernels["scatter"]["GBps"] = bytes_scatter / (kms["scatter"] * 1e-3) / 1e9
-        kernels["combine"]["GBps"] = bytes_combine / (kms["combine"] * 1e-3) / 1e9
+        for name, nbytes in (("route_mask", bytes_route), ("scatter", bytes_scatter), ("combine", bytes_combine)):
+            if kms[name] > 0.0:  # (0: a step that another kernel does)
+                kernels[name]["GBps"] = nbytes / (kms[name] * 1e-3) / 1e9
         kernels["gemm1"]["tflops"] = g1_flops / (kms["gemm1"] * 1e-3) / 1e12
         kernels["gemm2"]["tflops"] = g2_flops / (kms["gemm2"] * 1e-3) / 1e12
         return kernels, g1_flops

@@ -304,8 +304,9 @@ int dsmoe_plan_layout(const dsmoe_ctx* ctx, int64_t* out);
 /*
  * Per-kernel timing of the next moe_dualsparse_forward calls on this context, for benchmarks.
  * The steps of the layer (Eq. 1-4 with the drops of Sec. 4) run as up to seven kernels: router
- * (only in moe_dualsparse_forward_routed; otherwise its slot reads 0), route+mask, plan, scatter,
- * GEMM-1, GEMM-2, combine.  begin creates HIP events (host objects, no
+ * (only in moe_dualsparse_forward_routed), route+mask, plan, scatter, GEMM-1, GEMM-2, combine.  The slot of a step without a kernel of
+ * its own reads 0: plan does route+mask in small batches, and writes the row lists instead of scatter unless a batch has very many
+ * histograms; router does route+mask in batches of up to 2048 tokens on 33 to 128 experts.  begin creates HIP events (host objects, no
  * device memory); while profiling, forward records them on its stream between the kernels
  * (level 2) or only around GEMM-1 (level 1) and stays asynchronous; calls beyond max_calls are not
  * recorded.  end waits for the recorded events, writes the mean duration in milliseconds of each

@@ -366,34 +366,33 @@ static int forward_impl(Ctx* ctx, const Layout& base, const void* packed, const 
     else if (boundary == 4) err = hipEventRecord(ev[0], s);
     else if (boundary == 5) err = hipEventRecord(ev[1], s);
   };
-#define DSMOE_STEP(b, call) \
-  do {                      \
-    mark(b);                \
-    if (err == hipSuccess) err = (call); \
+  // step b with a kernel of its own, or (unless `own`) an empty interval: another step's kernel does its work, or there is none to do
+  unsigned ran = 0;
+#define DSMOE_STEP_IF(b, own, call)               \
+  do {                                            \
+    mark(b);                                      \
+    if (own) {                                    \
+      ran |= 1u << (b);                           \
+      if (err == hipSuccess) err = (call);        \
+    }                                             \
   } while (0)
-  mark(0);
-  const bool routed = router_packed && !small_plan(L, T) && router_routes(L, T);
-  if (err == hipSuccess && routed) err = launch_router_route(L, T, router_packed, x, const_cast<float*>(logits_buf), tau, ws, s);
-  else if (err == hipSuccess && router_packed) err = launch_router(L, T, router_packed, x, const_cast<float*>(logits_buf), s);
-  if (small_plan(L, T)) {
-    DSMOE_STEP(1, launch_small_plan(L, T, logits, tau, ws, s));
-    mark(2);
-    mark(3);
-  } else {
-    if (routed) mark(1);
-    else DSMOE_STEP(1, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
-                               (int32_t*)(ws + L.o_bin_count), nullptr, s));
-    DSMOE_STEP(2, launch_plan(L, T, ws, s));
-    mark(3);
-  }
+#define DSMOE_STEP(b, call) DSMOE_STEP_IF(b, true, call)
+  const bool small = small_plan(L, T), routed = router_packed && !small && router_routes(L, T);
+  DSMOE_STEP_IF(0, router_packed, routed ? launch_router_route(L, T, router_packed, x, const_cast<float*>(logits_buf), tau, ws, s)
+                                         : launch_router(L, T, router_packed, x, const_cast<float*>(logits_buf), s));
+  DSMOE_STEP_IF(1, !small && !routed, launch_route(L, logits, T, tau, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w), (uint8_t*)(ws + L.o_keep),
+                                                   (int32_t*)(ws + L.o_bin_count), nullptr, s));
+  DSMOE_STEP(2, small ? launch_small_plan(L, T, logits, tau, ws, s) : launch_plan(L, T, ws, s));
+  DSMOE_STEP_IF(3, !small && !plan_writes_rows(L, T), launch_scatter(L, T, ws, s));
   DSMOE_STEP(4, L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 0, s)
                        : launch_gemm1_full(L, T, (const char*)packed, x, ws, 0, s));
   DSMOE_STEP(5, L.mfma ? launch_gemm2_mfma(L, T, (const char*)packed, ws, s) : launch_gemm2_full(L, T, (const char*)packed, ws, s));
   DSMOE_STEP(6, launch_combine(L, T, (const char*)packed, ws, y, s));
   mark(kNumKernels);
 #undef DSMOE_STEP
+#undef DSMOE_STEP_IF
   if (err != hipSuccess) return hip_fail(ctx, err);
-  if (rec) pf.calls += 1;
+  if (rec) pf.ran[pf.calls++] = (uint8_t)ran;
   return DSMOE_OK;
 }
 
@@ -504,13 +503,21 @@ int dsmoe_profile_begin(dsmoe_ctx* ctx_, int level, int max_calls) {
   const int per_call = level == 2 ? kNumKernels + 1 : 2;
   const size_t n = (size_t)per_call * max_calls;
   pf.ev = (hipEvent_t*)calloc(n, sizeof(hipEvent_t));
-  if (!pf.ev) return DSMOE_EINVAL;
+  pf.ran = (uint8_t*)calloc(max_calls, 1);
+  auto drop = [&] {
+    free(pf.ev);
+    free(pf.ran);
+    pf = Profile();
+  };
+  if (!pf.ev || !pf.ran) {
+    drop();
+    return DSMOE_EINVAL;
+  }
   for (size_t i = 0; i < n; ++i) {
     hipError_t e = hipEventCreate(&pf.ev[i]);
     if (e != hipSuccess) {
       for (size_t j = 0; j < i; ++j) (void)hipEventDestroy(pf.ev[j]);
-      free(pf.ev);
-      pf.ev = nullptr;
+      drop();
       return hip_fail(ctx, e);
     }
   }
@@ -537,6 +544,7 @@ int dsmoe_profile_end(dsmoe_ctx* ctx_, float* ms, int* calls) {
     }
     if (pf.level == 2) {
       for (int k = 0; k < kNumKernels; ++k) {
+        if (!(pf.ran[c] >> k & 1)) continue;
         float t = 0.f;
         e = hipEventElapsedTime(&t, ev[k], ev[k + 1]);
         if (e != hipSuccess) {
@@ -557,6 +565,7 @@ int dsmoe_profile_end(dsmoe_ctx* ctx_, float* ms, int* calls) {
   const size_t n = (size_t)per_call * pf.max_calls;
   for (size_t i = 0; i < n; ++i) (void)hipEventDestroy(pf.ev[i]);
   free(pf.ev);
+  free(pf.ran);
   pf = Profile();
   return rc;
 }
@@ -583,6 +592,7 @@ int moe_profile_importance(dsmoe_ctx* ctx_, const void* packed, const void* x, c
     err = launch_route(L, logits, T, nullptr, (int32_t*)(ws + L.o_idx), (float*)(ws + L.o_w),
                        (uint8_t*)(ws + L.o_keep), (int32_t*)(ws + L.o_bin_count), nullptr, s);
   if (err == hipSuccess) err = launch_plan(L, T, ws, s);
+  if (err == hipSuccess && !plan_writes_rows(L, T)) err = launch_scatter(L, T, ws, s);
   if (err == hipSuccess)
     err = L.mfma ? launch_gemm1_mfma(L, T, (const char*)packed, x, ws, 1 + metric, s)
                  : launch_gemm1_full(L, T, (const char*)packed, x, ws, 1 + metric, s);

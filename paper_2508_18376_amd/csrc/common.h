@@ -151,13 +151,14 @@ struct PerDeviceOnce {
   }
 };
 
-constexpr int kNumKernels = 7;  // router (if any), route, plan, scatter, gemm1, gemm2, combine
+constexpr int kNumKernels = 7;  // router, route, plan, scatter, gemm1, gemm2, combine (the first and the fourth where there are any)
 
 struct Profile {
   int level = 0;       // 0 off, 1 GEMM-1 only, 2 every kernel
   int max_calls = 0;
   int calls = 0;
   hipEvent_t* ev = nullptr;  // level 1: 2 per call; level 2: kNumKernels + 1 per call
+  uint8_t* ran = nullptr;    // per call, bit k: kernel k was launched (steps that another one's launch includes are not)
 };
 
 struct Ctx {
@@ -201,7 +202,8 @@ hipError_t launch_route(const Layout& L, const float* logits, int T, const float
 // The normalised scores instead of routing results: their histograms per expert of the whole router (sel: rows of kSelRow,
 // cleared by the caller), or the scores themselves (n [T][K], -1 where the expert is not resident; sel == nullptr).
 hipError_t launch_route_scores(const Layout& L, const float* logits, int T, int32_t* sel, float* n, hipStream_t s);
-// plan and row lists
+// plan and, where plan_writes_rows says so, row lists; else launch_scatter has to follow
+bool plan_writes_rows(const Layout& L, int T);
 hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s);
 // small batches: routing, plan and row lists in one launch
 bool small_plan(const Layout& L, int T);

@@ -815,15 +815,20 @@ static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const Rou
 // tokens top-8 on 64 experts in 2 parts 17.5 + 6.2 -> 11.5, 4096 top-2 on 8 in 4 parts 23.2 + 5.2 -> 13, 16384 on 2 of 8 in 4 parts
 // 18.8 + 5.0 -> 12.5, 333 on 64 + 2 in 2 parts 11.7 + 4.8 -> 9, 777 on 64 + 2 in 8 parts 20.7 + 5.5 -> 15.5; routed here as well: 1 token top-8
 // on 64 experts 12.3 -> 9, 64 top-2 on 8 in 2 parts 9.7 -> 6.5.
-hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) {
-  const int bt = route_block_tokens(L.E, T), nblk = (T + bt - 1) / bt;
-  const int per_blk = bt * L.K;                                         // pairs of a route block
+static int route_blocks(const Layout& L, int T) {
+  const int bt = route_block_tokens(L.E, T);
+  return (T + bt - 1) / bt;
+}
+static int list_chunk(const Layout& L, int T) {  // route blocks to a workgroup of the row lists; 0: no such workgroups
+  const int nblk = route_blocks(L, T), per_blk = route_block_tokens(L.E, T) * L.K;  // pairs of a route block
   int chunk = (nblk + 63) / 64;                                         // up to 64 workgroups ...
   if (chunk * per_blk < kPlanThreads) chunk = kPlanThreads / per_blk;   // ... of a pair per thread and more
-  if (T > 0 && (int64_t)nblk * L.nbins <= 65536 && (int64_t)chunk * per_blk <= kListPairs * kPlanThreads)
-    return launch_plan_kernel<0>(L, T, ws, RouteArgs{}, (nblk + chunk - 1) / chunk, chunk, s);
-  const hipError_t e = launch_plan_kernel<0>(L, T, ws, RouteArgs{}, 0, 0, s);
-  return e != hipSuccess ? e : launch_scatter(L, T, ws, s);
+  return T > 0 && (int64_t)nblk * L.nbins <= 65536 && (int64_t)chunk * per_blk <= kListPairs * kPlanThreads ? chunk : 0;
+}
+bool plan_writes_rows(const Layout& L, int T) { return list_chunk(L, T) > 0; }
+hipError_t launch_plan(const Layout& L, int T, char* ws, hipStream_t s) {
+  const int chunk = list_chunk(L, T);
+  return launch_plan_kernel<0>(L, T, ws, RouteArgs{}, chunk ? (route_blocks(L, T) + chunk - 1) / chunk : 0, chunk, s);
 }
 
 // Routing, plan and row lists of a small batch in one launch: one workgroup routes 64 tokens at once with sixteen lanes each (more than 32
