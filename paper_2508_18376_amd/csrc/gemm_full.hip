@@ -68,6 +68,8 @@ template <int N>
 __device__ __forceinline__ void wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// Barrier behind which a stage may be overwritten: this wavefront's LDS reads have arrived.
+__device__ __forceinline__ void read_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 __device__ __forceinline__ uint32_t lds_byte(const char* p) {
   return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const char*)p);
 }
@@ -172,7 +174,7 @@ struct FullTile {
     int st = 0;
     for (; st + NS - 1 < n; ++st) {
       wait_loads<(NS - 2) * NL>();  // stage st has landed (for this wavefront; the barrier makes it so for all)
-      asm volatile("s_barrier" ::: "memory");
+      read_barrier();
       issue(st + NS - 1);           // into the slot of stage st - 1, which every wavefront has finished reading
       multiply(lds + (st % NS) * SB, w, lane);
     }
@@ -183,7 +185,7 @@ struct FullTile {
       else if (NS > 4 && left == NS - 4) wait_loads<(NS > 4 ? NS - 4 : 0) * NL>();
       else if (NS > 5 && left == NS - 5) wait_loads<(NS > 5 ? NS - 5 : 0) * NL>();
       else wait_loads<0>();
-      asm volatile("s_barrier" ::: "memory");
+      read_barrier();
       multiply(lds + (st % NS) * SB, w, lane);
     }
     if constexpr (WE == 4) {
@@ -193,7 +195,7 @@ struct FullTile {
         for (int i = 0; i < NI; ++i) acc4[j][i] += acc4b[j][i];
     }
     if constexpr (SUBS == 2 && !SPLIT) {
-      asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
+      read_barrier();  // every wavefront is done reading the last stage
       f32x4* part = (f32x4*)const_cast<char*>(lds) + (w & 1) * (NJ * NQ * 64) + lane;  // [NQ NJ][64 lanes]
       if (w >= 2) {
 #pragma unroll
@@ -217,7 +219,7 @@ struct FullTile {
 
   // SPLIT: the odd wavefronts' sums go to the even ones, as group 1
   __device__ __forceinline__ void other_rows(const char* lds, int w, int lane) {
-    asm volatile("s_barrier" ::: "memory");  // every wavefront is done reading the last stage
+    read_barrier();  // every wavefront is done reading the last stage
     f32x4* part = (f32x4*)const_cast<char*>(lds) + (w >> 1) * (NJ * 64) + lane;  // [NJ][64 lanes]
     if (w & 1)
 #pragma unroll
@@ -496,9 +498,6 @@ __global__ __launch_bounds__(256, 2) void gemm2_full_kernel(Layout L, const char
 }
 
 // ------------------------------------------------------------------------------------- two images to a tile
-// Barrier behind which a stage may be overwritten: this wavefront's LDS reads have arrived.
-__device__ __forceinline__ void read_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // The product of both images of a tile (2 x 128 weight rows, bf16) with NJ blocks of 32 pair rows (XE bytes per value), K stages of 32.
 template <int XE, int NJ>
 struct WideTile {
