@@ -86,9 +86,11 @@ bool build_layout(const dsmoe_config& c, Layout& L, Room room = Room::kContext) 
   L.g2_rows_inner = !L.mfma || (int64_t)L.F * kMfmaBN2 * 2 >= (1 << 20) ? 1 : 0;
   // tall items need whole neuron tiles (the variant for a half-full last neuron tile has no tall form)
   auto whole_tiles = [](int n) { const int m = n % kMfmaNeur; return m == 0 || m > kMfmaNeur / 2; };
+  // ... and the two row tiles of H that an item of GEMM-2 then reads through one descriptor of 32-bit offsets (up to 4 M neurons)
+  auto two_tiles = [](int64_t neurons) { return 2 * (neurons / kBK) * kStageBytes < (int64_t)1 << 32; };
   // (full-precision path: an item's time follows its rows and each one saved is a weight tile not fetched again: always)
   L.tall_tiles = !L.mfma ? 2
-                 : c.tall_items >= 0 && whole_tiles(L.Fp) && (L.n_shared == 0 || whole_tiles(L.F_shT)) ? 1 + c.tall_items : 0;
+                 : c.tall_items >= 0 && whole_tiles(L.Fp) && two_tiles(L.F) && (L.n_shared == 0 || (whole_tiles(L.F_shT) && two_tiles(L.F_shT))) ? 1 + c.tall_items : 0;
   const int nsub_bits = L.P < kSubBits ? L.P : kSubBits;
   L.nsub = 1 << nsub_bits;
   L.nbins = L.E_res * L.nsub;

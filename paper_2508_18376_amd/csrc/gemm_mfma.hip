@@ -698,8 +698,8 @@ __device__ __forceinline__ void gemm2_tile(const G2Args& g, char* lds, int a_row
       while (p_cur < g.np && !((g.it.kmask >> p_cur) & 1)) ++p_cur;
     }
     slot = (uint32_t)(st % RING::NS) * RING::SB + g.lds_w;
-    sH = (uint32_t)(kt * kStageBytes);
-    sW = (uint32_t)(kt * kStageBytes + g.col0 * kRowBytes);
+    sH = (uint32_t)kt * kStageBytes;
+    sW = (uint32_t)kt * kStageBytes + (uint32_t)(g.col0 * kRowBytes);
   };
   auto one = [&](int q) {
     if (q < NW) dma16<ONCE>(g.rsW, slot + RING::BOFF + q * 4096, woff, sW + q * 4096);
