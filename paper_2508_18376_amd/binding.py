@@ -103,8 +103,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+def _raw_stream_accessor():
+    """f(device index) -> raw handle of its current stream.  The direct accessor is not part of torch's public interface."""
+    return getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
+_raw_stream = _raw_stream_accessor()
+
+
 def _stream(stream) -> int:
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    return _raw_stream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 def dsmoe_strerror(status: int) -> str:
