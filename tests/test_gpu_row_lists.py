@@ -18,6 +18,8 @@ CASES = [
     (256, 8, 8, 3, 0, None, "ragged"), (257, 8, 8, 3, 1, None, "ragged"), (128, 32, 16, 1, 0, None, "rate0.25"), (129, 20, 16, 5, 0, (3, 20), "ragged"),
     (1024, 64, 2, 4, 1, None, "ragged"), (1025, 64, 2, 4, 0, None, "ragged"), (65, 40, 3, 1, 0, None, "rate0.25"), (2049, 33, 16, 2, 0, (0, 1), "ragged"),
     (4500, 3, 2, 8, 1, None, "ragged"), (2300, 512, 1, 1, 0, None, "rate0.25"),
+    # histograms summed a bin per thread: 8192 bins (7 rows), 66 bins (no multiple of four)
+    (100, 512, 16, 8, 1, None, "ragged"), (1100, 33, 3, 1, 0, None, "rate0.25"),
 ]
 
 

@@ -156,3 +156,34 @@ def test_a_weight_beyond_the_sample_rescales_its_column_tile_alone(where, h_scal
     for cols in (slice(0, 256), slice(256, 512), slice(512, 768), slice(768, D)):
         r = ref[:, cols]
         assert ((y[:, cols] - r).abs() <= 2e-3 * r.square().mean().sqrt() + 2.0 ** -10 * r.abs()).all(), cols
+
+
+@pytest.mark.parametrize("tokens", [16, 300])  # streaming kernels; full, tall and ragged row tiles
+@pytest.mark.parametrize("partial_fp32", [False, True])
+def test_column_tiles_of_several_scales(tokens, partial_fp32):
+    # outliers of several binades in some column tiles of routed and shared experts, one in the last tile of 32 columns and two in one tile,
+    # where each decides its own scale; the outputs of all tiles add up
+    import torch
+    from paper_2508_18376_amd import DualSparseLayer
+    D_, F_ = 2080, 4096
+    gen = torch.Generator(device="cuda:0").manual_seed(8)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=gen, device="cuda:0").mul_(0.02).bfloat16()
+
+    layer = DualSparseLayer(d_model=D_, d_ff=F_, n_experts=3, top_k=3, n_part=2, n_shared=2, d_ff_shared=1024, max_tokens=tokens, dtype="bf16",
+                            y_fp32=True, partial_fp32=partial_fp32)
+    w = [normal(3, D_, F_), normal(3, D_, F_), normal(3, F_, D_)]
+    shared = [normal(2, D_, 1024), normal(2, D_, 1024), normal(2, 1024, D_)]
+    for e, neuron, col, v in ((0, 1, 5, 0.6), (0, 2, 300, 1.5), (0, 4093, 301, -5.0), (2, 3, 2079, 3.0)):
+        assert ((e * F_ + neuron) * D_ + col) // RUN % 3  # (every third run is sampled)
+        w[2][e, neuron, col] = v
+    perm = torch.rand(3, F_, generator=gen, device="cuda:0").argsort(dim=1).to(torch.int32)
+    x, logits = torch.randn(tokens, D_, generator=gen, device="cuda:0").bfloat16(), torch.randn(tokens, 3, generator=gen, device="cuda:0")
+    for sh_outlier in (0.02, -6.0):  # (the shared experts' W2 is sampled whole: with the second nothing is beyond the sample)
+        shared[2][1, 7, 2050] = sh_outlier
+        layer.partition_weights(*w, perm=perm, sh_w1=shared[0], sh_w3=shared[1], sh_w2=shared[2])
+        y = layer.forward(x, logits, torch.zeros(3, 2, device="cuda:0")).double().cpu()
+        ref = _reference(x, torch.softmax(logits.double().cpu(), dim=1), w) + _reference(x, torch.ones(tokens, 2, dtype=torch.float64), shared)
+        assert ((y - ref).abs() <= 2e-3 * ref.square().mean().sqrt() + 2.0 ** -10 * ref.abs()).all()
+    layer.close()
