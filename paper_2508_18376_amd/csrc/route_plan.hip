@@ -170,6 +170,8 @@ __host__ __device__ inline int plan_lds_words(const Layout& L) {
   const int groups = 2 * NG > L.nbins ? 2 * NG : L.nbins;  // (the workgroups with the row lists keep the next row of every bin there)
   return ((L.nbins + 3) & ~3) + ((3 * E_tot + 3) & ~3) + ((groups + 3) & ~3) + kPlanTilesLds / 2 + kPlanRecords * 4 + kHalvedMost * (int)(sizeof(Item1) / 4);
 }
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 constexpr int kSumWords = 8192;  // partial column sums of the histograms (LANES == 0), behind the tables
 
 // inclusive sum over the lanes of a wavefront, in registers
@@ -260,7 +262,9 @@ __device__ __forceinline__ TileUse tile_use(const int32_t* bin_count, int e, int
 // LANES: 0: the batch has been routed (its histograms are in the workspace).  Else every workgroup routes it, see
 // launch_small_plan: 8 or 32: a lane per token and at most that many experts; 16: sixteen lanes per token, at most 64 experts.
 // chunk: LANES == 0: route blocks whose pairs a workgroup of the row lists takes (0: no such workgroups, launch_scatter follows).
-template <int LANES, int NSB>
+// MANY: more than 64 experts, or bins that are no multiple of four (in a kernel of their own: what these need slows the others down, as a
+// launch fetches its instructions from memory: 333 tokens on 64 + 2 experts 9.5 us, with it 10.6)
+template <int LANES, int NSB, bool MANY>
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, char* ws, RouteArgs ra, int chunk) {
   extern __shared__ __attribute__((aligned(16))) int32_t sm[];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -325,29 +329,43 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         pr_e[u] = idx[pr];
       }
     }
-    // Four columns to a thread, up to sixteen threads to a column, up to sixteen rows in flight each; the partial sums meet in LDS.
+    // Four columns to a thread (two where an odd number of experts has two bins each), up to sixteen threads to a column, up to sixteen rows
+    // in flight each; where a column has several threads the partial sums meet in LDS.  (One load after the other for the bins that are no
+    // multiple of four, or more than 4096: 16384 tokens on 512 experts in 8 parts 603 us instead of 121, on 257 in one 85 instead of 26.)
     const int nb = L.nbins;
-    if ((nb & 3) == 0 && nb <= kSumWords / 2) {
-      const int cols = nb >> 2, G = min(16, kPlanThreads / cols);
-      const int g = tid / cols, c4 = tid - g * cols;
-      int4 sum = make_int4(0, 0, 0, 0), before = sum;
-      if (g < G) {
+    auto sums = [&](auto zero) {
+      using V = decltype(zero);
+      constexpr int N = sizeof(V) / 4;
+      const int cols = nb / N, G = max(min(16, kPlanThreads / cols), MANY ? 1 : 0);
+      const bool direct = MANY && G == 1;  // the sums need no others
+      auto column = [&](int at) {
+        const int g = at / cols, c = at - g * cols;
+        if (g >= G) return;
+        V sum = zero, before = zero;
         for (int r = 0; r < nblk; r += 16 * G) {
-          int4 v[16];
+          V v[16];
 #pragma unroll
           for (int u = 0; u < 16; ++u)
-            if (r + u * G < nblk) v[u] = *(const int4*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c4 * 4);
+            if (r + u * G < nblk) v[u] = *(const V*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c * N);
 #pragma unroll
           for (int u = 0; u < 16; ++u)
             if (r + u * G < nblk) {
               const int row = r + u * G + g, in = row < nblk ? -1 : 0, pre = row < blk0 ? -1 : 0;
-              sum.x += v[u].x & in, sum.y += v[u].y & in, sum.z += v[u].z & in, sum.w += v[u].w & in;
-              before.x += v[u].x & pre, before.y += v[u].y & pre, before.z += v[u].z & pre, before.w += v[u].w & pre;
+              sum += v[u] & in;
+              before += v[u] & pre;
             }
         }
-        *(int4*)(pairs + g * nb + c4 * 4) = sum;
-        if (rows_list) *(int4*)(pairs + kSumWords / 2 + g * nb + c4 * 4) = before;
-      }
+        *(V*)(direct ? bin_count + c * N : pairs + g * nb + c * N) = sum;
+        if (!rows_list) return;
+        if (!direct) *(V*)(pairs + kSumWords / 2 + g * nb + c * N) = before;
+        else
+          for (int i = 0; i < N; ++i) next[c * N + i] = before[i];  // (not at a multiple of 16 bytes)
+      };
+      if constexpr (MANY)
+        for (int at = tid; at < cols * G; at += kPlanThreads) column(at);  // (more than once only for G == 1)
+      else
+        column(tid);
+      if (direct) return;
       lds_barrier();
       for (int c = tid; c < nb; c += kPlanThreads) {
         int n = 0, m = 0;
@@ -358,17 +376,12 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         bin_count[c] = n;
         if (rows_list) next[c] = m;
       }
+    };
+    if constexpr (MANY && NSB == 1) {
+      if (nb & 3) sums(i32x2{0, 0});
+      else sums(i32x4{0, 0, 0, 0});
     } else {
-      for (int c = tid; c < nb; c += kPlanThreads) {
-        int n = 0, m = 0;
-        for (int r = 0; r < nblk; ++r) {
-          const int v = blk_hist[(size_t)r * nb + c];
-          n += v;
-          m += r < blk0 ? v : 0;
-        }
-        bin_count[c] = n;
-        if (rows_list) next[c] = m;
-      }
+      sums(i32x4{0, 0, 0, 0});
     }
   }
   lds_barrier();
@@ -378,6 +391,21 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   // tall and compute its rows too.  Only if the short tile keeps no partition that the tile before it drops: the tall items run over
   // the partitions of the full tile, and where the short tile lacks one of them its rows of H are zeros (written by the
   // GEMM-1 item of the full tile, see step 4).
+  // Beyond 64 experts it takes several turns, and what an expert's bins need goes over all threads: 512 experts in 4 parts (16 bins), one
+  // token 29 -> 17 us.
+  const bool makes_starts = rows_list || (lists2 && LANES == 0 && chunk == 0);
+  auto starts = [&](int e, int off) {  // first row of every bin of expert e, whose first row is off
+    int32_t* cursor = (int32_t*)(ws + L.o_cursor);  // where the scatter kernel starts
+    for (int bin = e * Bins<NSB>::N; bin < (e + 1) * Bins<NSB>::N; ++bin) {
+      if (!rows_list) cursor[bin] = off;
+      else next[bin] = (LANES == 0 ? next[bin] : 0) + off;  // (behind the rows of the blocks before this workgroup's)
+      off += bin_count[bin];
+    }
+  };
+  if constexpr (MANY) {
+    for (int e = tid; e < E_res; e += kPlanThreads) ne[e] = Bins<NSB>::rows(bin_count, e);
+    lds_barrier();
+  }
   if (wv == 0) {
     int tiles = 0, shorts = 0;
     uint64_t multi = 0;  // bit e & 63: some expert e has more than one row tile
@@ -390,7 +418,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     }
     for (int e0 = 0; e0 < E_res; e0 += 64) {
       const int e = e0 + lane;
-      const int n = e < E_res ? Bins<NSB>::rows(bin_count, e) : 0, nt = tiles_of(n);
+      const int n = e >= E_res ? 0 : MANY ? ne[e] : Bins<NSB>::rows(bin_count, e), nt = tiles_of(n);
       int s = 0;
       if (!rows_list && L.tall_tiles && short_rows(n)) {
         const int2 bits = Bins<NSB>::kept(bin_count, e, (nt - 2) * BM, (nt - 1) * BM, n, P);
@@ -403,15 +431,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         ne[e] = n;
         ts[e] = t0;
         ab[e] = 2 * (shorts + __popcll(short_m & ((1ull << lane) - 1))) + s;
-        if (rows_list || (lists2 && LANES == 0 && chunk == 0)) {
-          int32_t* cursor = (int32_t*)(ws + L.o_cursor);  // where the scatter kernel starts
-          int off = t0 * BM;
-          for (int bin = e * Bins<NSB>::N; bin < (e + 1) * Bins<NSB>::N; ++bin) {
-            if (!rows_list) cursor[bin] = off;
-            else next[bin] = (LANES == 0 ? next[bin] : 0) + off;  // (behind the rows of the blocks before this workgroup's)
-            off += bin_count[bin];
-          }
-        }
+        if (!MANY && makes_starts) starts(e, t0 * BM);
         if (!rows_list)
           for (int i = t0; i < min(t0 + nt, kPlanTilesLds); ++i) texp[i] = (uint16_t)e;
         if (lists2) {
@@ -427,6 +447,10 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       total_short_l = shorts;
       multi_l[0] = (int)(uint32_t)multi, multi_l[1] = (int)(uint32_t)(multi >> 32);
     }
+  }
+  if (MANY && makes_starts) {
+    lds_barrier();
+    for (int e = tid; e < E_res; e += kPlanThreads) starts(e, ts[e] * BM);
   }
 
   // 2. The row lists.  The order inside a bin is arbitrary (it is decided by atomics); the layer output does not depend on it because
@@ -480,13 +504,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
       const int pos = gi / P, p = gi - pos * P, e = sh_first ? (pos == 0 ? E_res : pos - 1) : pos;
       int n_e = p == 0 ? T : 0, rows = n_e, tiles = tiles_of(n_e), merged = short_rows(n_e) > 0;
       if (e < E_res) {
-        n_e = Bins<NSB>::rows(bin_count, e);
-        const int nt = tiles_of(n_e);
         rows = 0;
-        Bins<NSB>::each(bin_count, e, [&](int sb, int, int end) { rows = Bins<NSB>::keeps(sb, p) ? end : rows; });
-        const TileUse u = tile_use<NSB>(bin_count, e, nt - 1, bm, p);
-        tiles = u.before + (u.rows > 0);
-        merged = short_rows(n_e) && u.rows > 0 && u.full_before;
+        n_e = Bins<NSB>::each(bin_count, e, [&](int sb, int, int end) { rows = Bins<NSB>::keeps(sb, p) ? end : rows; });
+        const int nt = tiles_of(n_e);
+        tiles = rows > 0, merged = 0;  // (as long as there is one tile)
+        if (nt > 1) {
+          const TileUse u = tile_use<NSB>(bin_count, e, nt - 1, bm, p);
+          tiles = u.before + (u.rows > 0);
+          merged = short_rows(n_e) && u.rows > 0 && u.full_before;
+        }
       }
       ga[gi] = 2 * tiles + merged;  // the tiles that have an item, and whether the last one's goes into a tall one
       if (price_lists && rows > 0) {
@@ -669,12 +695,15 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   __shared__ int total1_l;
   Item1* items1 = (Item1*)(ws + L.o_items1);
   const int nt1_max = max(L.NT1, has_sh ? L.NT1_sh : 0), n_q = total_tiles * P;
-  //    threads that share the neuron tiles of one (row tile, partition): a power of two, as many as would otherwise idle
+  //    Up to kPlanRecords (row tile, partition) pairs leave what their items need in LDS, and a power of two of threads, as many as would
+  //    otherwise idle, share the neuron tiles of each; the threads of more pairs write the items of one after the other themselves.
+  const bool direct = n_q > kPlanRecords;
   int ls = 0;
-  while (ls < 5 && (1 << ls) < nt1_max && min(n_q, kPlanRecords) << (ls + 1) <= kPlanThreads) ++ls;
+  while (!direct && ls < 5 && (1 << ls) < nt1_max && n_q << (ls + 1) <= kPlanThreads) ++ls;
   int total1 = 0, first_half = 0;
   for (int q0 = 0; q0 == 0 || q0 < n_q; q0 += kPlanRecords) {
-    //  What the (row tile, partition) pairs q0 .. need, a thread each ...
+    //  What this thread's pair needs ...
+    int4 mine = make_int4(0, 0, 0, 0);
     if (wv > 0 && q0 + tid - 64 < n_q) {
       const int q = q0 + tid - 64, g = q / P, p = q - g * P;
       const int e = tile_expert(g), n = ne[e], i = g - ts[e], nt = tiles_of(n);
@@ -695,25 +724,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
           nfill += last;
         }
       }
-      rec[tid - 64] = make_int4(rows | nfill << 16, u.before, ((sh_first ? (routed ? e + 1 : 0) : e) * P + p) << 16 | p << 12 | e, g * BM);
+      mine = make_int4(rows | nfill << 16, u.before, ((sh_first ? (routed ? e + 1 : 0) : e) * P + p) << 16 | p << 12 | e, g * BM);
+      if (!direct) rec[tid - 64] = mine;
     }
-    //  ... and, by the first wavefront, the item bases of the groups: a run of groups per lane
-    if (wv == 0 && q0 == 0) {
-      const int per = (NG + 63) >> 6, lo = lane * per, hi = min(NG, lo + per);
-      const int sh_lo = sh_first ? 0 : E_res * P, sh_hi = has_sh ? sh_lo + P : sh_lo;  // the shared pseudo-expert's groups
-      int sum = 0;
-      for (int gi = lo; gi < hi; ++gi) {
-        const int v = ga[gi], n = (v >> 1) - (use_tall1 ? v & 1 : 0), items = n * (gi >= sh_lo && gi < sh_hi ? L.NT1_sh : L.NT1);
-        ga[gi] = n;
-        gb[gi] = sum;
-        sum += items;
-      }
-      const int incl = wave_incl_sum(sum);
-      for (int gi = lo; gi < hi; ++gi) gb[gi] += incl - sum;
-      if (lane == 63) total1_l = incl;
-    }
-    lds_barrier();
     if (q0 == 0) {
+      //  ... and, by the first wavefront, the item bases of the groups
+      if (wv == 0) {
+        const int sh_lo = sh_first ? 0 : E_res * P, sh_hi = has_sh ? sh_lo + P : sh_lo;  // the shared pseudo-expert's groups
+        int sum = 0;
+#pragma unroll 4
+        for (int g0 = 0; g0 < NG; g0 += 64) {
+          const int gi = g0 + lane, v = gi < NG ? ga[gi] : 0, n = (v >> 1) - (use_tall1 ? v & 1 : 0);
+          const int items = n * (gi >= sh_lo && gi < sh_hi ? L.NT1_sh : L.NT1), incl = wave_incl_sum(items);
+          if (gi < NG) ga[gi] = n, gb[gi] = sum + incl - items;
+          sum += __builtin_amdgcn_readlane(incl, 63);
+        }
+        if (lane == 0) total1_l = sum;
+      }
+      lds_barrier();
       //  In the weight-streaming regime (few rows per expert) every item lasts as long as its weight
       //  tile takes to arrive, so the kernel lasts a whole number of rounds of one item per compute
       //  unit: when the last round is at most half full, its items are cut into halves of 64
@@ -725,8 +753,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         if (rest > 0 && rest * 2 <= L.split_items) first_half = total1 - rest;
       }
     }
-    for (int qs = tid; qs < min(n_q - q0, kPlanRecords) << ls; qs += kPlanThreads) {
-      const int4 r = rec[qs >> ls];
+    for (int qs = direct ? 0 : tid; qs < (direct ? 1 : n_q << ls); qs += kPlanThreads) {
+      const int4 r = direct ? mine : rec[qs >> ls];
       Item1 v;
       v.nrows = r.x & 0xffff;
       if (v.nrows == 0) continue;  // no row of the tile keeps p, or no item of its own
@@ -746,7 +774,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         else ((Item1*)tail)[at - first_half] = v;
       }
     }
-    if (q0 + kPlanRecords < n_q) lds_barrier();  // the records have been read
   }
   int total_slots = total1;
   if (first_half < total1) {  // the same for every thread
@@ -787,17 +814,23 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
   }
 }
 
-template <int LANES, int NSB>
-static hipError_t launch_plan_nsb(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
+template <int LANES, int NSB, bool MANY>
+static hipError_t launch_plan_many(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
   size_t sh = sizeof(int32_t) * (size_t)plan_lds_words(L);
   sh += sizeof(int32_t) * (size_t)(LANES != 0 ? T * L.K + L.E * L.P : kSumWords);
   if (sh > 48 * 1024) {  // hundreds of experts x 8 parts: above what a launch gets without asking
     static PerDeviceOnce once;
-    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES, NSB>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024); });
+    hipError_t e = once.run([] { return hipFuncSetAttribute((const void*)plan_kernel<LANES, NSB, MANY>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024); });
     if (e != hipSuccess) return e;
   }
-  plan_kernel<LANES, NSB><<<dim3(2 + blocks), dim3(kPlanThreads), sh, s>>>(L, T, ws, ra, chunk);
+  plan_kernel<LANES, NSB, MANY><<<dim3(2 + blocks), dim3(kPlanThreads), sh, s>>>(L, T, ws, ra, chunk);
   return hipGetLastError();
+}
+template <int LANES, int NSB>
+static hipError_t launch_plan_nsb(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
+  if constexpr (LANES == 0)
+    if (L.E_res > 64 || (L.nbins & 3)) return launch_plan_many<LANES, NSB, true>(L, T, ws, ra, blocks, chunk, s);
+  return launch_plan_many<LANES, NSB, false>(L, T, ws, ra, blocks, chunk, s);
 }
 template <int LANES>
 static hipError_t launch_plan_kernel(const Layout& L, int T, char* ws, const RouteArgs& ra, int blocks, int chunk, hipStream_t s) {
