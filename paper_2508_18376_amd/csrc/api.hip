@@ -482,8 +482,6 @@ int moe_transform_complete(dsmoe_ctx* ctx_, const void* wg, const void* w1, cons
   hipError_t err;
   if (perm) {
     int32_t *inv = (int32_t*)((char*)workspace + L.o_perm_check), *bad_at = inv + (size_t)L.E_res * L.F, bad = 0;
-    err = launch_fill_i32(bad_at, 1, 0, s);
-    if (err != hipSuccess) return hip_fail(ctx, err);
     err = launch_invert_perm(L, perm, inv, bad_at, s);
     if (err != hipSuccess) return hip_fail(ctx, err);
     err = hipMemcpyAsync(&bad, bad_at, sizeof(int32_t), hipMemcpyDeviceToHost, s);

@@ -234,7 +234,7 @@ hipError_t launch_perm_from_importance(const Layout& L, const float* importance,
 hipError_t launch_gemm2_mfma(const Layout& L, int T, const char* packed, char* ws, hipStream_t s);
 hipError_t launch_pack(const Layout& L, const void* w1, const void* w3, const void* w2, const void* sw1, const void* sw3,
                        const void* sw2, const int32_t* perm, char* packed, int n_shared, int F_sh, hipStream_t s);
-// the inverse of perm; *bad (cleared by the caller) is set if perm is not a permutation
+// the inverse of perm; *bad: perm is not a permutation
 hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s);
 
 // ---- device helpers ---------------------------------------------------------------------------

@@ -398,10 +398,11 @@ __global__ __launch_bounds__(256) void pack_w13_padding_kernel(char* out, int gr
   }
 }
 
-// inv[e][perm[e][pos]] = pos
-__global__ void invert_perm_kernel(const int32_t* perm, int32_t* inv, int F, int64_t n) {
+// inv[e][perm[e][pos]] = pos; *bad, which what follows may set, is cleared
+__global__ void invert_perm_kernel(const int32_t* perm, int32_t* inv, int F, int64_t n, int32_t* bad) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
+  if (t == 0) *bad = 0;
   const int64_t e = t / F;
   const int src = perm[t];
   if (src >= 0 && src < F) inv[e * F + src] = (int32_t)(t % F);
@@ -416,7 +417,7 @@ __global__ void perm_check_kernel(const int32_t* perm, const int32_t* inv, int F
 static dim3 perm_grid(const Layout& L) { return dim3((unsigned)(((int64_t)L.E_res * L.F + 255) / 256)); }
 hipError_t launch_invert_perm(const Layout& L, const int32_t* perm, int32_t* inv, int32_t* bad, hipStream_t s) {
   const int64_t n = (int64_t)L.E_res * L.F;
-  invert_perm_kernel<<<perm_grid(L), dim3(256), 0, s>>>(perm, inv, L.F, n);
+  invert_perm_kernel<<<perm_grid(L), dim3(256), 0, s>>>(perm, inv, L.F, n, bad);
   perm_check_kernel<<<perm_grid(L), dim3(256), 0, s>>>(perm, inv, L.F, n, bad);
   return hipGetLastError();
 }
@@ -449,16 +450,16 @@ static hipError_t pack_images(const Layout& L, const void* w1, const void* w3, c
   // The W1 / W3 stages are written from source columns (see pack_w13_kernel), which needs the inverse
   // permutation: it is parked in the W2 region of the packed buffer, which the W2 kernel overwrites.
   // (That region has at least E_res * F * 32 * sizeof(T) bytes, the table E_res * F * 4.)
-  int32_t* inv = nullptr;
+  int32_t *inv = nullptr, *bad = &((PackRecord*)(packed + L.p_scale))->bad_perm;
   if (perm) {
     inv = (int32_t*)(packed + L.p_w2);
-    invert_perm_kernel<<<perm_grid(L), block, 0, s>>>(perm, inv, L.F, (int64_t)L.E_res * L.F);
+    invert_perm_kernel<<<perm_grid(L), block, 0, s>>>(perm, inv, L.F, (int64_t)L.E_res * L.F, bad);
   }
   auto aligned = [](const void* a, const void* b) { return (((uintptr_t)a | (uintptr_t)b) & 15) == 0; };
   auto w13 = [&](const void* a, const void* b, const int32_t* order, char* out, int experts, int Fs, int Fp, int P, int NT1, int per_expert) {
     const int vec = Fs % PackTile<T>::V == 0 && aligned(a, b);
     pack_w13_kernel<T, FULL><<<dim3((unsigned)((Fs + C - 1) / C * KS1), experts), block, 0, s>>>(
-        (const T*)a, (const T*)b, perm, order, &((PackRecord*)(packed + L.p_scale))->bad_perm, out, L.D, KS1, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
+        (const T*)a, (const T*)b, perm, order, bad, out, L.D, KS1, Fs, Fp, P, NT1, per_expert ? 0 : Fs, per_expert, L.h_shift, vec);
     const int pad = NT1 * W13Image<T, FULL>::NEUR - Fp, groups = (per_expert ? experts : 1) * P;
     if (pad > 0) {
       const int64_t total = (int64_t)groups * KS1 * pad * 2 * PackTile<T>::CH;
