@@ -333,39 +333,27 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
     // in flight each; where a column has several threads the partial sums meet in LDS.  (One load after the other for the bins that are no
     // multiple of four, or more than 4096: 16384 tokens on 512 experts in 8 parts 603 us instead of 121, on 257 in one 85 instead of 26.)
     const int nb = L.nbins;
-    auto sums = [&](auto zero) {
-      using V = decltype(zero);
-      constexpr int N = sizeof(V) / 4;
-      const int cols = nb / N, G = max(min(16, kPlanThreads / cols), MANY ? 1 : 0);
-      const bool direct = MANY && G == 1;  // the sums need no others
-      auto column = [&](int at) {
-        const int g = at / cols, c = at - g * cols;
-        if (g >= G) return;
-        V sum = zero, before = zero;
+    if constexpr (!MANY) {
+      const int cols = nb >> 2, G = min(16, kPlanThreads / cols);
+      const int g = tid / cols, c4 = tid - g * cols;
+      int4 sum = make_int4(0, 0, 0, 0), before = sum;
+      if (g < G) {
         for (int r = 0; r < nblk; r += 16 * G) {
-          V v[16];
+          int4 v[16];
 #pragma unroll
           for (int u = 0; u < 16; ++u)
-            if (r + u * G < nblk) v[u] = *(const V*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c * N);
+            if (r + u * G < nblk) v[u] = *(const int4*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c4 * 4);
 #pragma unroll
           for (int u = 0; u < 16; ++u)
             if (r + u * G < nblk) {
               const int row = r + u * G + g, in = row < nblk ? -1 : 0, pre = row < blk0 ? -1 : 0;
-              sum += v[u] & in;
-              before += v[u] & pre;
+              sum.x += v[u].x & in, sum.y += v[u].y & in, sum.z += v[u].z & in, sum.w += v[u].w & in;
+              before.x += v[u].x & pre, before.y += v[u].y & pre, before.z += v[u].z & pre, before.w += v[u].w & pre;
             }
         }
-        *(V*)(direct ? bin_count + c * N : pairs + g * nb + c * N) = sum;
-        if (!rows_list) return;
-        if (!direct) *(V*)(pairs + kSumWords / 2 + g * nb + c * N) = before;
-        else
-          for (int i = 0; i < N; ++i) next[c * N + i] = before[i];  // (not at a multiple of 16 bytes)
-      };
-      if constexpr (MANY)
-        for (int at = tid; at < cols * G; at += kPlanThreads) column(at);  // (more than once only for G == 1)
-      else
-        column(tid);
-      if (direct) return;
+        *(int4*)(pairs + g * nb + c4 * 4) = sum;
+        if (rows_list) *(int4*)(pairs + kSumWords / 2 + g * nb + c4 * 4) = before;
+      }
       lds_barrier();
       for (int c = tid; c < nb; c += kPlanThreads) {
         int n = 0, m = 0;
@@ -376,12 +364,52 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(Layout L, int T, cha
         bin_count[c] = n;
         if (rows_list) next[c] = m;
       }
-    };
-    if constexpr (MANY && NSB == 1) {
-      if (nb & 3) sums(i32x2{0, 0});
-      else sums(i32x4{0, 0, 0, 0});
     } else {
-      sums(i32x4{0, 0, 0, 0});
+      auto sums = [&](auto zero) {
+        using V = decltype(zero);
+        constexpr int N = sizeof(V) / 4;
+        const int cols = nb / N, G = max(min(16, kPlanThreads / cols), 1);
+        const bool direct = G == 1;  // the sums need no others
+        for (int at = tid; at < cols * G; at += kPlanThreads) {  // (more than once only for G == 1)
+          const int g = at / cols, c = at - g * cols;
+          V sum = zero, before = zero;
+          for (int r = 0; r < nblk; r += 16 * G) {
+            V v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+              if (r + u * G < nblk) v[u] = *(const V*)(blk_hist + (size_t)min(r + u * G + g, nblk - 1) * nb + c * N);
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+              if (r + u * G < nblk) {
+                const int row = r + u * G + g, in = row < nblk ? -1 : 0, pre = row < blk0 ? -1 : 0;
+                sum += v[u] & in;
+                before += v[u] & pre;
+              }
+          }
+          *(V*)(direct ? bin_count + c * N : pairs + g * nb + c * N) = sum;
+          if (!rows_list) continue;
+          if (!direct) *(V*)(pairs + kSumWords / 2 + g * nb + c * N) = before;
+          else
+            for (int i = 0; i < N; ++i) next[c * N + i] = before[i];  // (not at a multiple of 16 bytes)
+        }
+        if (direct) return;
+        lds_barrier();
+        for (int c = tid; c < nb; c += kPlanThreads) {
+          int n = 0, m = 0;
+          for (int q = 0; q < G; ++q) {
+            n += pairs[q * nb + c];
+            if (rows_list) m += pairs[kSumWords / 2 + q * nb + c];
+          }
+          bin_count[c] = n;
+          if (rows_list) next[c] = m;
+        }
+      };
+      if constexpr (NSB == 1) {
+        if (nb & 3) sums(i32x2{0, 0});
+        else sums(i32x4{0, 0, 0, 0});
+      } else {
+        sums(i32x4{0, 0, 0, 0});
+      }
     }
   }
   lds_barrier();
