@@ -147,7 +147,8 @@ int moe_route_and_mask(dsmoe_ctx* ctx, const float* logits, int32_t T, const flo
  *           preserved between calls; two calls that overlap in time need two workspaces
  * bf16 layers accumulate in fp32 and round the output once.  On the matrix-core path the
  * intermediate activation Swish(x W1) * (x W3) is stored in IEEE half precision (values beyond
- * +-65504 saturate) and multiplied with W2 held as half precision times a per-layer power of two,
+ * +-65504 saturate) and multiplied with W2 held as half precision times a power of two (the layer's, or that of the
+ * 256 columns of an expert where these hold much larger weights than the rest),
  * which represents every bf16 weight within 2^-29 of the largest exactly, and the per-pair partial
  * outputs are stored in half precision unless cfg.partial_fp32 is set; bf16 layers on the full-precision
  * path (see dsmoe_uses_mfma) keep both in fp32.

@@ -28,8 +28,8 @@
 // two by moe_partition_weights.  |H| beyond 65504 saturates.
 //
 // Operand tiles [256][32] bf16 travel HBM/L2 -> LDS by buffer loads that write LDS directly (no
-// registers in between), through a ring of 4 stages (4 x 32 KiB of the CU's 160 KiB LDS), three
-// stages in flight ahead of the one being multiplied.  Weight tiles are stored pre-swizzled by
+// registers in between), through a ring of 4 stages (4 x 32 KiB of the CU's 160 KiB LDS; ragged tiles: up to 7
+// smaller ones), three stages (six) in flight ahead of the one being multiplied.  Weight tiles are stored pre-swizzled by
 // moe_partition_weights, so their copy is a linear 16 KiB stream; activation rows are gathered
 // through the row list with the same chunk rotation (GEMM-1), or are such images already (GEMM-2: H, see h_stage).
 //
@@ -357,7 +357,8 @@ struct WaveTile {
 // The intermediate activation H (half precision) lies in HBM as GEMM-2 wants it in LDS: per row tile (256 rows) and 32
 // neurons one 16 KiB image [256 rows][32], the chunks of a row rotated as everywhere (swz_chunk); the images of a row tile follow
 // each other along the neurons.  GEMM-2 then streams whole cache lines in order, for H as for W2, and GEMM-1's write-out is linear
-// too.  As rows of F values a stage was 256 pieces of 64 bytes at the stride of a row, twice the L2 requests.  Rows -> images, GEMM-2
+// too.  As rows of F values a stage was 256 pieces of 64 bytes at the stride of a row; GEMM-2's L2 requests fell from 89 to 60 million a
+// launch (4096 tokens on 8 of 4096 x 14336, nothing dropped) and from 24 to 18 (8192 on 64 of 2048 x 1024).  Rows -> images, GEMM-2
 // without drop, us: 8192 tokens on 64 experts of 2048 x 1024 322 -> 315, x 1280 354 -> 339, 4096 on 8 of 4096 x 14336 757 -> 744;
 // layers at 25 % drop: 8192 tokens on the first 723 -> 714, 333 and 7001 on 64 + 2 of 2048 x 1408 249 -> 246 and 837 -> 821.
 // Image of neurons 32 kt .. of the row tile of `row` (kts images to a row tile).
@@ -819,7 +820,7 @@ __device__ __forceinline__ void gemm2_setup(G2Args& g, int item_id, const Layout
   }
   const auto* rec = (const __attribute__((address_space(4))) PackRecord*)(uintptr_t)(packed + L.p_scale);  // (as constant memory: scalar loads)
   g.yscale = 1.f;
-  if (rec->beyond) {
+  if (rec->beyond) {  // some column tile has a scale of its own, or one that is not the common one of the partial outputs
     const int tile = __builtin_amdgcn_readfirstlane(g.it.e * L.ND2 + g.it.jd);
     const int beyond = ((const __attribute__((address_space(4))) uint32_t*)(rec + 1))[tile >> 2] >> (8 * (tile & 3)) & 255;
     const int n = rec->shift - w2_tile_shift(rec->room, rec->shift0, beyond);  // -160 .. 0

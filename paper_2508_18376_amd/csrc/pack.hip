@@ -78,7 +78,7 @@ static void launch_absmax(const void* w, int64_t n, int stride, PackRecord* rec,
   absmax_bf16_kernel<<<dim3((unsigned)(runs < 512 ? runs : 512)), dim3(256), 0, s>>>((const uint16_t*)w, n, stride, &rec->largest);
 }
 // The scale is needed before the first value is packed, and finding the largest of all |W2| reads W2 once more (a tenth
-// of the packing of 8 experts of 4096 x 14336, which took 1.52 ms with it and takes 1.36 without).  A sample of 8 to 16 M values tells its
+// of the packing of 8 experts of 4096 x 14336, which takes 1.53 ms with it and 1.36 without).  A sample of 8 to 16 M values tells its
 // binade as well as that binade and the next have room for (see repack_w2_kernel): only column tiles whose largest value is more than twice (for some, four
 // times) the sample's largest are packed twice.  Odd strides: a row of a power of two of values is met in all of its columns.
 static int absmax_stride(int64_t n) {
