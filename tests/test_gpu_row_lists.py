@@ -20,6 +20,8 @@ CASES = [
     (4500, 3, 2, 8, 1, None, "ragged"), (2300, 512, 1, 1, 0, None, "rate0.25"),
     # histograms summed a bin per thread: 8192 bins (7 rows), 66 bins (no multiple of four)
     (100, 512, 16, 8, 1, None, "ragged"), (1100, 33, 3, 1, 0, None, "rate0.25"),
+    # more (row tile, partition) pairs than are kept in LDS, experts of several tiles: up to 64 experts, more, and an odd number with two bins each
+    (4500, 64, 8, 8, 1, None, "ragged"), (4500, 70, 8, 8, 1, (3, 70), "ragged"), (3001, 65, 4, 1, 1, None, "rate0.25"), (1000, 512, 8, 8, 0, (0, 511), "rate0.25"),
 ]
 
 
